@@ -4,21 +4,27 @@
 // form, Eq. TDKSMatVecStandard), organised for the register file of CDNA4:
 // each thread owns one column and an n x n plane of a cell's values.
 //
-//   A  (plane at fixed y node j):  gather u(i,k); x: B u, D u; z: B on both
+//   A  (plane at fixed y node j):  gather u(i,k); z: B u; x: B and S B on it
 //   -- LDS transpose of the two arrays -->
-//   B  (plane at fixed x point a): y: B on both -> u_q, d_x u_q; then in
-//      registers d_y u_q, d_z u_q by the Gauss collocation derivative,
-//      the box fluxes (diagonal metric), the potential term, the y and z
-//      transposed derivatives and the transposed y interpolation of the two
-//      results (s, s_x)
-//   -- LDS transpose of the two arrays -->
-//   C  (plane at fixed y node j):  x: B^T s + D^T s_x; z: B^T; scatter-add.
+//   B  (plane at fixed x point a): y: B on both -> u_q and the x stiffness term;
+//      in registers the y and z stiffness terms S u_q, the potential term, all
+//      weighted and summed, and the transposed y interpolation of the sum
+//   -- LDS transpose of the one array -->
+//   C  (plane at fixed y node j):  x: B^T; z: B^T; scatter-add.
 //
-// Only the y direction crosses threads, so the cell data make four LDS
-// round trips (two arrays each way) instead of fifteen.  Every 1D contraction
-// uses the reflection symmetry of the GLL nodes and Gauss points
-// (B[n-1-a][n-1-i] = B[a][i], D and Dg antisymmetric): even/odd folding halves
-// the multiply-adds.  The folded tables are evaluated at compile time for the
+// The metric of a box cell is one diagonal per cell, so a direction's
+// derivative, flux and transposed derivative are one contraction with the 1D
+// stiffness S of the Gauss-point basis (make_gauss_stiff): ten 1D contractions
+// per cell and three arrays through LDS, where separate derivatives took
+// fifteen and four.  What bounds the kernel is instruction issue and latency,
+// so the shorter chain shows directly: FP32, 13 x 17 x 11 cells, p = 4, 5
+// orbitals 48.0 -> 31.6 us (the lane-pair kernel, FP64, 16^3 cells, p = 5, 8
+// orbitals: 139 -> 112 us).
+//
+// Only the y direction crosses threads.  Every 1D contraction uses the
+// reflection symmetry of the GLL nodes and Gauss points
+// (B[n-1-a][n-1-i] = B[a][i], S and S B likewise): even/odd folding halves the
+// multiply-adds.  The folded tables are evaluated at compile time for the
 // kernel's order (make_foldset), so each coefficient is an instruction
 // constant: no table loads, and no scalar-memory waits that would also wait
 // for the LDS transposes.
@@ -54,25 +60,15 @@ constexpr int plane_wpe() {
   return sizeof(T) == 4 ? (N == 5 || N == 6 ? 3 : 2) : (N >= 6 ? 1 : 2);
 }
 
-// hold both transposed arrays in LDS at once (fewer barriers) instead of
-// passing them through one buffer in turn; measured slower on both precisions
-// at n = 6 (more live registers), kept selectable
-template <typename T, int N>
-constexpr bool plane_two_buffers() {
-  return false;
-}
-
 template <typename T, int N, int CB, int CPB>
 __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_eu(plane_wpe<T, N>())))
     plane_kernel(PlaneParams<T> P) {
   constexpr int VOL = N * N * N;
   constexpr int THREADS = CPB * N * CB;
-  constexpr bool TWO = plane_two_buffers<T, N>();
   // 1D tables of order N, folded, as compile-time constants
-  constexpr FoldSet<N> FS = make_foldset<N>();
+  constexpr BoxFoldSet<N> FS = make_box_foldset<N>();
   auto wprod = [&](int b, int c) { return (T)(FS.wq[b] * FS.wq[c]); };
   __shared__ T sX[CPB * VOL * CB];
-  __shared__ T sY[TWO ? CPB * VOL * CB : 1];
   __shared__ T sV[CPB * VOL];  // weighted potential of the block's cells
   __shared__ double sRed[THREADS];
   if (P.done && *P.done) return;
@@ -141,11 +137,10 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
   const int NxI = P.Nx - 2, NyI = P.Ny - 2;
 
   // ---------------- A: plane j = pl, values (i, k) -------------------------------------
-  T tu[N][N], tx[N][N];  // [x][z]
+  T u[N][N];  // [i][k] gathered, then [i][c], then S B u at [x point][z point]
   {
     const int j = pl;
     const int J = cy * P.p + j;
-    T u[N][N];  // [i][k]
     // node (I, J, K) -> element offset; all loads are issued unconditionally
     // from a valid address (masked entries read element 0 and are zeroed)
     const bool jok = P.fullgrid ? true : (J > 0 && J < P.Ny - 1);
@@ -207,73 +202,46 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
 #pragma unroll
         for (int i = 0; i < N; ++i) u[i][k] *= my;
     }
-    // x: interpolation and nodal derivative at the Gauss points, per z line
+    // z: interpolation, per x node
 #pragma unroll
-    for (int k = 0; k < N; ++k) {
+    for (int i = 0; i < N; ++i) {
+      T o[N];
+      eo<T, N, 1>(FS.B, u[i], o);
+#pragma unroll
+      for (int c = 0; c < N; ++c) u[i][c] = o[c];
+    }
+    // x, per z point: interpolation into the transpose buffer, S B kept
+#pragma unroll
+    for (int c = 0; c < N; ++c) {
       T line[N], o1[N], o2[N];
 #pragma unroll
-      for (int i = 0; i < N; ++i) line[i] = u[i][k];
-      eo2<T, N, 1, -1>(FS.B, FS.D, line, o1, o2);
+      for (int i = 0; i < N; ++i) line[i] = u[i][c];
+      eo2<T, N, 1, 1>(FS.B, FS.SB, line, o1, o2);
 #pragma unroll
       for (int a = 0; a < N; ++a) {
-        tu[a][k] = o1[a];
-        tx[a][k] = o2[a];
-      }
-    }
-    // z: interpolation of both, per x point
-#pragma unroll
-    for (int a = 0; a < N; ++a) {
-      T o1[N], o2[N];
-      eo<T, N, 1>(FS.B, tu[a], o1);
-      eo<T, N, 1>(FS.B, tx[a], o2);
-#pragma unroll
-      for (int c = 0; c < N; ++c) {
-        tu[a][c] = o1[c];
-        tx[a][c] = o2[c];
+        sX[sidx(pl, a, c)] = o1[a];
+        u[a][c] = o2[a];
       }
     }
   }
-  // ---------------- transpose: (j; a, c) -> (a; j, c) ------------------------------------
-  T v[N][N], w[N][N];  // [y][z] at x point a = pl
-  if constexpr (TWO) {
+  __syncthreads();
+  // ---------------- transposes (j; a, c) -> (a; j, c), y interpolation of u ----------------
+  T uq[N][N];  // [b][c] at x point a = pl
 #pragma unroll
-    for (int a = 0; a < N; ++a)
+  for (int c = 0; c < N; ++c) {
+    T l[N], o[N];
 #pragma unroll
-      for (int c = 0; c < N; ++c) {
-        sX[sidx(pl, a, c)] = tu[a][c];
-        sY[sidx(pl, a, c)] = tx[a][c];
-      }
-    __syncthreads();
+    for (int j = 0; j < N; ++j) l[j] = sX[sidx(j, pl, c)];
+    eo<T, N, 1>(FS.B, l, o);
 #pragma unroll
-    for (int j = 0; j < N; ++j)
-#pragma unroll
-      for (int c = 0; c < N; ++c) {
-        v[j][c] = sX[sidx(j, pl, c)];
-        w[j][c] = sY[sidx(j, pl, c)];
-      }
-    __syncthreads();
-  } else {
-#pragma unroll
-    for (int a = 0; a < N; ++a)
-#pragma unroll
-      for (int c = 0; c < N; ++c) sX[sidx(pl, a, c)] = tu[a][c];
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < N; ++j)
-#pragma unroll
-      for (int c = 0; c < N; ++c) v[j][c] = sX[sidx(j, pl, c)];
-    __syncthreads();
-#pragma unroll
-    for (int a = 0; a < N; ++a)
-#pragma unroll
-      for (int c = 0; c < N; ++c) sX[sidx(pl, a, c)] = tx[a][c];
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < N; ++j)
-#pragma unroll
-      for (int c = 0; c < N; ++c) w[j][c] = sX[sidx(j, pl, c)];
-    __syncthreads();
+    for (int b = 0; b < N; ++b) uq[b][c] = o[b];
   }
+  __syncthreads();
+#pragma unroll
+  for (int a = 0; a < N; ++a)
+#pragma unroll
+    for (int c = 0; c < N; ++c) sX[sidx(pl, a, c)] = u[a][c];
+  __syncthreads();
 
   // ---------------- B: plane a = pl, quadrature values (b, c) --------------------------------
   double energy = 0.0;
@@ -285,121 +253,61 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
     T wa = (T)FS.wq[0];
 #pragma unroll
     for (int q = 1; q < N; ++q) wa = pl == q ? (T)FS.wq[q] : wa;
-    gx = (T)(P.kin * sFc[3 * N + 0]) * wa;
+    gx = (T)(P.kin * sFc[3 * N + 0]);  // S B carries the x weights
     gy = (T)(P.kin * sFc[3 * N + 1]) * wa;
     gz = (T)(P.kin * sFc[3 * N + 2]) * wa;
   }
-  // B1: x flux from w, transposed y interpolation, straight into the transpose
-  // buffer (free: every thread has finished reading w)
+  // x stiffness term and the potential, per z point
+  T acc[N][N];
 #pragma unroll
   for (int c = 0; c < N; ++c) {
     T l[N], o[N];
 #pragma unroll
-    for (int j = 0; j < N; ++j) l[j] = w[j][c];
-    eo<T, N, 1>(FS.B, l, o);  // u_x at (pl, b, c)
-    T le = 0;
+    for (int j = 0; j < N; ++j) l[j] = sX[sidx(j, pl, c)];
+    eo<T, N, 1>(FS.B, l, o);
 #pragma unroll
     for (int b = 0; b < N; ++b) {
       const T f = gx * wprod(b, c) * o[b];
-      acc_energy<T>(energy, le, f * o[b]);
-      o[b] = f;
+      acc[b][c] = havev ? sV[slot * VOL + pl + N * (b + N * c)] * uq[b][c] + f : f;
     }
-    flush_energy<T>(energy, le);
-    eo<T, N, 1>(FS.Bt, o, l);
-#pragma unroll
-    for (int j = 0; j < N; ++j) sX[sidx(j, pl, c)] = l[j];
+    // keep the potential reads of later lines from being hoisted here
     __builtin_amdgcn_sched_barrier(0);
   }
-  // B2: u_q, potential, y and z fluxes, transposed y interpolation
-  T s[N][N];  // [j][c]
-  {
-    T uq[N][N], acc[N][N];
+  __syncthreads();
+  // z stiffness term, per y point
 #pragma unroll
-    for (int c = 0; c < N; ++c) {
-      T l[N], o[N];
+  for (int b = 0; b < N; ++b) {
+    T d[N];
+    eo<T, N, 1>(FS.S, uq[b], d);
+    const T g = gz * (T)FS.wq[b];
 #pragma unroll
-      for (int j = 0; j < N; ++j) l[j] = v[j][c];
-      eo<T, N, 1>(FS.B, l, o);
-      T le = 0;
+    for (int c = 0; c < N; ++c) acc[b][c] += g * d[c];
+  }
+  // y stiffness term, the quadratic form u_q . (sum) and the transposed y
+  // interpolation into the transpose buffer, per z point
 #pragma unroll
-      for (int b = 0; b < N; ++b) {
-        uq[b][c] = o[b];
-        const T pot = havev ? sV[slot * VOL + pl + N * (b + N * c)] * o[b] : (T)0;
-        acc_energy<T>(energy, le, pot * o[b]);
-        acc[b][c] = pot;
-      }
-      flush_energy<T>(energy, le);
-      // keep the potential reads of later lines from being hoisted here
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    // z flux, per y line
+  for (int c = 0; c < N; ++c) {
+    T l[N], d[N];
+#pragma unroll
+    for (int b = 0; b < N; ++b) l[b] = uq[b][c];
+    eo<T, N, 1>(FS.S, l, d);
+    const T g = gy * (T)FS.wq[c];
+    T le = 0;
 #pragma unroll
     for (int b = 0; b < N; ++b) {
-      T d[N], r[N];
-      eo<T, N, -1>(FS.G, uq[b], d);
-      T le = 0;
-#pragma unroll
-      for (int c = 0; c < N; ++c) {
-        const T f = gz * wprod(b, c) * d[c];
-        acc_energy<T>(energy, le, f * d[c]);
-        d[c] = f;
-      }
-      flush_energy<T>(energy, le);
-      eo<T, N, -1>(FS.Gt, d, r);
-#pragma unroll
-      for (int c = 0; c < N; ++c) acc[b][c] += r[c];
+      d[b] = g * d[b] + acc[b][c];
+      acc_energy<T>(energy, le, d[b] * l[b]);
     }
-    // y flux and transposed y interpolation, per z line
+    flush_energy<T>(energy, le);
+    eo<T, N, 1>(FS.Bt, d, l);
 #pragma unroll
-    for (int c = 0; c < N; ++c) {
-      T l[N], d[N], r[N];
-#pragma unroll
-      for (int b = 0; b < N; ++b) l[b] = uq[b][c];
-      eo<T, N, -1>(FS.G, l, d);
-      T le = 0;
-#pragma unroll
-      for (int b = 0; b < N; ++b) {
-        const T f = gy * wprod(b, c) * d[b];
-        acc_energy<T>(energy, le, f * d[b]);
-        d[b] = f;
-      }
-      flush_energy<T>(energy, le);
-      eo<T, N, -1>(FS.Gt, d, r);
-#pragma unroll
-      for (int b = 0; b < N; ++b) r[b] += acc[b][c];
-      eo<T, N, 1>(FS.Bt, r, l);
-      if constexpr (TWO) {
-#pragma unroll
-        for (int j = 0; j < N; ++j) sY[sidx(j, pl, c)] = l[j];
-      } else {
-#pragma unroll
-        for (int j = 0; j < N; ++j) s[j][c] = l[j];
-      }
-    }
+    for (int j = 0; j < N; ++j) sX[sidx(j, pl, c)] = l[j];
   }
-  // ---------------- transposes: (a; j, c) -> (j; a, c) ----------------------------------------
   // the quadratic form is parked in LDS here, unconditionally: otherwise the
   // compiler sinks its whole accumulation chain into the final reduction and
   // keeps every partial product alive across phase C
   sRed[t] = act ? energy : 0.0;
-  T s2[N][N], sx2[N][N];  // [x point a][z point c] at node plane j = pl (one-buffer blocks)
   __syncthreads();
-  if constexpr (!TWO) {
-#pragma unroll
-    for (int a = 0; a < N; ++a)
-#pragma unroll
-      for (int c = 0; c < N; ++c) sx2[a][c] = sX[sidx(pl, a, c)];
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < N; ++j)
-#pragma unroll
-      for (int c = 0; c < N; ++c) sX[sidx(j, pl, c)] = s[j][c];
-    __syncthreads();
-#pragma unroll
-    for (int a = 0; a < N; ++a)
-#pragma unroll
-      for (int c = 0; c < N; ++c) s2[a][c] = sX[sidx(pl, a, c)];
-  }
 
   // ---------------- C: plane j = pl: x then z transposed, scatter ------------------------------
   {
@@ -407,21 +315,12 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
     T h[N][N];  // [i][c]
 #pragma unroll
     for (int c = 0; c < N; ++c) {
-      T l1[N], l2[N], o1[N], o2[N];
+      T l[N], o[N];
 #pragma unroll
-      for (int a = 0; a < N; ++a) {
-        if constexpr (TWO) {
-          l1[a] = sY[sidx(pl, a, c)];
-          l2[a] = sX[sidx(pl, a, c)];
-        } else {
-          l1[a] = s2[a][c];
-          l2[a] = sx2[a][c];
-        }
-      }
-      eo<T, N, 1>(FS.Bt, l1, o1);
-      eo<T, N, -1>(FS.Dt, l2, o2);
+      for (int a = 0; a < N; ++a) l[a] = sX[sidx(pl, a, c)];
+      eo<T, N, 1>(FS.Bt, l, o);
 #pragma unroll
-      for (int i = 0; i < N; ++i) h[i][c] = o1[i] + o2[i];
+      for (int i = 0; i < N; ++i) h[i][c] = o[i];
     }
     const int J = cy * P.p + j;
     const bool jok = P.fullgrid ? true : (J > 0 && J < P.Ny - 1);
@@ -486,7 +385,7 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
 template <typename T, int N, int CB>
 constexpr int plane_lds(int cpb) {
   constexpr int VOL = N * N * N;
-  return cpb * VOL * CB * (int)sizeof(T) * (plane_two_buffers<T, N>() ? 2 : 1) + cpb * VOL * (int)sizeof(T) +
+  return cpb * VOL * CB * (int)sizeof(T) + cpb * VOL * (int)sizeof(T) +
          cpb * N * CB * 8 + cpb * (3 * N + 3) * 8;
 }
 

@@ -9,11 +9,10 @@
 // z forms, in each lane, the partial sums over its own inputs for its own
 // outputs and for the partner's, and swaps the latter with the partner by a DPP
 // quad permutation.  The mirror symmetry of the 1D tables
-// (A[n-1-c][n-1-k] = S A[c][k], S = +1 for B, -1 for D and Dg) makes the two
-// lanes run identical code with identical coefficients: lane 1 only multiplies
-// its inputs by S.  All tables are compile-time constants (make_pairset).  A
-// lane then keeps half the registers of a plane-owning thread, which lets FP64
-// run two waves per SIMD.
+// (A[n-1-c][n-1-k] = A[c][k] for B, S and S B, see the plane kernel) makes the
+// two lanes run identical code with identical coefficients.  All tables are
+// compile-time constants (make_pairset).  A lane then keeps half the registers
+// of a plane-owning thread, which lets FP64 run two waves per SIMD.
 #include "tdfe_fold.h"
 
 namespace {
@@ -57,8 +56,8 @@ struct PairParams {
 
 // the kernel's tables for order N, evaluated at compile time
 struct PairSet {
-  FoldE<double> fB, fBt, fD, fDt, fG, fGt;  // B, B^T, D, D^T, Dg, Dg^T (x and y directions)
-  SplitT<double> zB, zBt, zG, zGt;          // B, B^T, Dg, Dg^T along z
+  FoldE<double> fB, fBt, fS, fSB;  // B, B^T, S, S B (x and y directions)
+  SplitT<double> zB, zBt, zS;      // B, B^T, S along z
   double wq[TDFE_MAXN];
 };
 
@@ -85,23 +84,21 @@ constexpr void split_tab(const double* A, int N, bool transpose, SplitT<double>&
 template <int N>
 constexpr PairSet make_pairset() {
   const tdfe1d::Rule R = tdfe1d::make_rule(N - 1);
+  const GaussStiff K = make_gauss_stiff(R);
   PairSet F{};
   fold_even(R.B, N, false, F.fB);
   fold_even(R.B, N, true, F.fBt);
-  fold_even(R.D, N, false, F.fD);
-  fold_even(R.D, N, true, F.fDt);
-  fold_even(R.Dg, N, false, F.fG);
-  fold_even(R.Dg, N, true, F.fGt);
+  fold_even(K.S, N, false, F.fS);
+  fold_even(K.SB, N, false, F.fSB);
   split_tab(R.B, N, false, F.zB);
   split_tab(R.B, N, true, F.zBt);
-  split_tab(R.Dg, N, false, F.zG);
-  split_tab(R.Dg, N, true, F.zGt);
+  split_tab(K.S, N, false, F.zS);
   for (int i = 0; i < TDFE_MAXN; ++i) F.wq[i] = R.wq[i];
   return F;
 }
 
-// out[a] = sum_i A[a][i] in[i], A folded with symmetry S (even N)
-template <typename T, int N, int S>
+// out[a] = sum_i A[a][i] in[i], A folded with A[n-1-a][n-1-i] = A[a][i] (even N)
+template <typename T, int N>
 __device__ __forceinline__ void eoe(const FoldE<double>& F, const T* in, T* out) {
   constexpr int H = N / 2;
   T e[H], o[H];
@@ -119,7 +116,7 @@ __device__ __forceinline__ void eoe(const FoldE<double>& F, const T* in, T* out)
       Qv += (T)F.O[a * PH + i] * o[i];
     }
     out[a] = Pv + Qv;
-    out[N - 1 - a] = S > 0 ? Pv - Qv : Qv - Pv;
+    out[N - 1 - a] = Pv - Qv;
   }
 }
 
@@ -136,13 +133,11 @@ __device__ __forceinline__ T pair_swap(T v) {
 }
 
 // contraction along the paired direction: in/out hold this lane's H local
-// entries; sg = S on lane 1, 1 on lane 0
+// entries
 template <typename T, int N>
-__device__ __forceinline__ void zsplit(const SplitT<double>& F, const T* in, T* out, T sg) {
+__device__ __forceinline__ void zsplit(const SplitT<double>& F, const T* x, T* out) {
   constexpr int H = N / 2;
-  T x[H], own[H], oth[H];
-#pragma unroll
-  for (int k = 0; k < H; ++k) x[k] = sg * in[k];
+  T own[H], oth[H];
 #pragma unroll
   for (int c = 0; c < H; ++c) {
     T a = 0, b = 0;
@@ -189,7 +184,6 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
   const bool cell_ok = cell < P.n_cell;
   const int colg = chunk * CB + col;
   const bool act = cell_ok && colg < P.cols;
-  const T sgn = h ? (T)-1 : (T)1;  // S = -1 tables on lane 1
   // global z index of local entry q
   auto zg = [&](int q) { return h ? N - 1 - q : q; };
 
@@ -290,11 +284,10 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
   };
 
   // ---------------- A: plane j = pl, values (i, local k) ---------------------------------
-  T tu[N][H], tx[N][H];  // [x point][local z]
+  T u[N][H];  // [i][local k] gathered, then [i][c], then S B u at [x point][local z point]
   {
     PlaneNodes Q;
     plane_nodes(Q, false);
-    T u[N][H];
 #pragma unroll
     for (int k = 0; k < H; ++k)
 #pragma unroll
@@ -320,52 +313,46 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
     for (int k = 0; k < H; ++k)
 #pragma unroll
       for (int i = 0; i < N; ++i) u[i][k] *= Q.fx[i] * Q.fz[k] * (Q.my * cs);
+    // z: interpolation (paired), per x node
 #pragma unroll
-    for (int k = 0; k < H; ++k) {
+    for (int i = 0; i < N; ++i) {
+      T o[H];
+      zsplit<T, N>(FS.zB, u[i], o);
+#pragma unroll
+      for (int c = 0; c < H; ++c) u[i][c] = o[c];
+    }
+    // x, per local z point: interpolation into the transpose buffer, S B kept
+#pragma unroll
+    for (int c = 0; c < H; ++c) {
       T line[N], o1[N], o2[N];
 #pragma unroll
-      for (int i = 0; i < N; ++i) line[i] = u[i][k];
-      eoe<T, N, 1>(FS.fB, line, o1);
-      eoe<T, N, -1>(FS.fD, line, o2);
+      for (int i = 0; i < N; ++i) line[i] = u[i][c];
+      eoe<T, N>(FS.fB, line, o1);
+      eoe<T, N>(FS.fSB, line, o2);
 #pragma unroll
       for (int a = 0; a < N; ++a) {
-        tu[a][k] = o1[a];
-        tx[a][k] = o2[a];
-      }
-    }
-#pragma unroll
-    for (int a = 0; a < N; ++a) {
-      T o1[H], o2[H];
-      zsplit<T, N>(FS.zB, tu[a], o1, (T)1);
-      zsplit<T, N>(FS.zB, tx[a], o2, (T)1);
-#pragma unroll
-      for (int c = 0; c < H; ++c) {
-        tu[a][c] = o1[c];
-        tx[a][c] = o2[c];
+        sX[sidx(pl, a, zg(c))] = o1[a];
+        u[a][c] = o2[a];
       }
     }
   }
-  // ---------------- transpose: (j; a, c) -> (a; j, c) ---------------------------------------
-  T v[N][H], w[N][H];  // [y node][local z] at x point a = pl
+  __syncthreads();
+  // ---------------- transposes (j; a, c) -> (a; j, c), y interpolation of u ----------------
+  T uq[N][H];  // [b][local c] at x point a = pl
+#pragma unroll
+  for (int c = 0; c < H; ++c) {
+    T l[N], o[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) l[j] = sX[sidx(j, pl, zg(c))];
+    eoe<T, N>(FS.fB, l, o);
+#pragma unroll
+    for (int b = 0; b < N; ++b) uq[b][c] = o[b];
+  }
+  __syncthreads();
 #pragma unroll
   for (int a = 0; a < N; ++a)
 #pragma unroll
-    for (int c = 0; c < H; ++c) sX[sidx(pl, a, zg(c))] = tu[a][c];
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < N; ++j)
-#pragma unroll
-    for (int c = 0; c < H; ++c) v[j][c] = sX[sidx(j, pl, zg(c))];
-  __syncthreads();
-#pragma unroll
-  for (int a = 0; a < N; ++a)
-#pragma unroll
-    for (int c = 0; c < H; ++c) sX[sidx(pl, a, zg(c))] = tx[a][c];
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < N; ++j)
-#pragma unroll
-    for (int c = 0; c < H; ++c) w[j][c] = sX[sidx(j, pl, zg(c))];
+    for (int c = 0; c < H; ++c) sX[sidx(pl, a, zg(c))] = u[a][c];
   __syncthreads();
 
   // ---------------- B: plane a = pl, Gauss points (b, local c) ---------------------------------
@@ -375,7 +362,7 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
     T wa = (T)FS.wq[0];  // selected from the constants: no per-lane memory load
 #pragma unroll
     for (int q = 1; q < N; ++q) wa = pl == q ? (T)FS.wq[q] : wa;
-    gx = (T)(P.kin * sFc[3 * N + 0]) * wa;
+    gx = (T)(P.kin * sFc[3 * N + 0]);  // S B carries the x weights
     gy = (T)(P.kin * sFc[3 * N + 1]) * wa;
     gz = (T)(P.kin * sFc[3 * N + 2]) * wa;
   }
@@ -384,128 +371,72 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
   T wc[H];
 #pragma unroll
   for (int c = 0; c < H; ++c) wc[c] = (T)FS.wq[c];
-  // B1: x flux from w, transposed y interpolation, into the transpose buffer
+  // x stiffness term and the potential, per local z point
+  T acc[N][H];
 #pragma unroll
   for (int c = 0; c < H; ++c) {
     T l[N], o[N];
 #pragma unroll
-    for (int j = 0; j < N; ++j) l[j] = w[j][c];
-    eoe<T, N, 1>(FS.fB, l, o);
-    T le = 0;
+    for (int j = 0; j < N; ++j) l[j] = sX[sidx(j, pl, zg(c))];
+    eoe<T, N>(FS.fB, l, o);
 #pragma unroll
     for (int b = 0; b < N; ++b) {
       const T f = gx * ((T)FS.wq[b] * wc[c]) * o[b];
-      acc_energy<T>(energy, le, f * o[b]);
-      o[b] = f;
+      acc[b][c] = P.vw ? sV[slot * VOL + pl + N * (b + N * zg(c))] * uq[b][c] + f : f;
     }
-    flush_energy<T>(energy, le);
-    eoe<T, N, 1>(FS.fBt, o, l);
-#pragma unroll
-    for (int j = 0; j < N; ++j) sX[sidx(j, pl, zg(c))] = l[j];
     __builtin_amdgcn_sched_barrier(0);
   }
-  // B2: u_q, potential, z and y fluxes, transposed y interpolation
-  T s[N][H];  // [y node][local z]
-  {
-    T uq[N][H], acc[N][H];
+  __syncthreads();
+  // z stiffness term, per y point (paired contraction)
 #pragma unroll
-    for (int c = 0; c < H; ++c) {
-      T l[N], o[N];
+  for (int b = 0; b < N; ++b) {
+    T d[H];
+    zsplit<T, N>(FS.zS, uq[b], d);
+    const T g = gz * (T)FS.wq[b];
 #pragma unroll
-      for (int j = 0; j < N; ++j) l[j] = v[j][c];
-      eoe<T, N, 1>(FS.fB, l, o);
-      T le = 0;
+    for (int c = 0; c < H; ++c) acc[b][c] += g * d[c];
+  }
+  // y stiffness term, the quadratic form u_q . (sum) and the transposed y
+  // interpolation into the transpose buffer, per local z point
 #pragma unroll
-      for (int b = 0; b < N; ++b) {
-        uq[b][c] = o[b];
-        const T pot = P.vw ? sV[slot * VOL + pl + N * (b + N * zg(c))] * o[b] : (T)0;
-        acc_energy<T>(energy, le, pot * o[b]);
-        acc[b][c] = pot;
-      }
-      flush_energy<T>(energy, le);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    // z flux, per y point (paired contractions)
+  for (int c = 0; c < H; ++c) {
+    T l[N], d[N];
+#pragma unroll
+    for (int b = 0; b < N; ++b) l[b] = uq[b][c];
+    eoe<T, N>(FS.fS, l, d);
+    const T g = gy * wc[c];
+    T le = 0;
 #pragma unroll
     for (int b = 0; b < N; ++b) {
-      T d[H], rr[H];
-      zsplit<T, N>(FS.zG, uq[b], d, sgn);
-      T le = 0;
-#pragma unroll
-      for (int c = 0; c < H; ++c) {
-        const T f = gz * ((T)FS.wq[b] * wc[c]) * d[c];
-        acc_energy<T>(energy, le, f * d[c]);
-        d[c] = f;
-      }
-      flush_energy<T>(energy, le);
-      zsplit<T, N>(FS.zGt, d, rr, sgn);
-#pragma unroll
-      for (int c = 0; c < H; ++c) acc[b][c] += rr[c];
+      d[b] = g * d[b] + acc[b][c];
+      acc_energy<T>(energy, le, d[b] * l[b]);
     }
-    // y flux and transposed y interpolation, per local z point
+    flush_energy<T>(energy, le);
+    eoe<T, N>(FS.fBt, d, l);
 #pragma unroll
-    for (int c = 0; c < H; ++c) {
-      T l[N], d[N], rr[N];
-#pragma unroll
-      for (int b = 0; b < N; ++b) l[b] = uq[b][c];
-      eoe<T, N, -1>(FS.fG, l, d);
-      T le = 0;
-#pragma unroll
-      for (int b = 0; b < N; ++b) {
-        const T f = gy * ((T)FS.wq[b] * wc[c]) * d[b];
-        acc_energy<T>(energy, le, f * d[b]);
-        d[b] = f;
-      }
-      flush_energy<T>(energy, le);
-      eoe<T, N, -1>(FS.fGt, d, rr);
-#pragma unroll
-      for (int b = 0; b < N; ++b) rr[b] += acc[b][c];
-      eoe<T, N, 1>(FS.fBt, rr, l);
-#pragma unroll
-      for (int j = 0; j < N; ++j) s[j][c] = l[j];
-    }
+    for (int j = 0; j < N; ++j) sX[sidx(j, pl, zg(c))] = l[j];
   }
-  // ---------------- transposes: (a; j, c) -> (j; a, c) ---------------------------------------
   sRed[t] = act ? energy : 0.0;
-  T s2[N][H], sx2[N][H];  // [x point][local z] at node plane j = pl
   __syncthreads();
-#pragma unroll
-  for (int a = 0; a < N; ++a)
-#pragma unroll
-    for (int c = 0; c < H; ++c) sx2[a][c] = sX[sidx(pl, a, zg(c))];
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < N; ++j)
-#pragma unroll
-    for (int c = 0; c < H; ++c) sX[sidx(j, pl, zg(c))] = s[j][c];
-  __syncthreads();
-#pragma unroll
-  for (int a = 0; a < N; ++a)
-#pragma unroll
-    for (int c = 0; c < H; ++c) s2[a][c] = sX[sidx(pl, a, zg(c))];
 
   // ---------------- C: plane j = pl: x transposed, z transposed (paired), scatter -------------------
   {
     T hh[N][H];  // [x node][local z point]
 #pragma unroll
     for (int c = 0; c < H; ++c) {
-      T l1[N], l2[N], o1[N], o2[N];
+      T l[N], o[N];
 #pragma unroll
-      for (int a = 0; a < N; ++a) {
-        l1[a] = s2[a][c];
-        l2[a] = sx2[a][c];
-      }
-      eoe<T, N, 1>(FS.fBt, l1, o1);
-      eoe<T, N, -1>(FS.fDt, l2, o2);
+      for (int a = 0; a < N; ++a) l[a] = sX[sidx(pl, a, zg(c))];
+      eoe<T, N>(FS.fBt, l, o);
 #pragma unroll
-      for (int i = 0; i < N; ++i) hh[i][c] = o1[i] + o2[i];
+      for (int i = 0; i < N; ++i) hh[i][c] = o[i];
     }
     PlaneNodes Q;
     plane_nodes(Q, true);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       T o[H];
-      zsplit<T, N>(FS.zBt, hh[i], o, (T)1);
+      zsplit<T, N>(FS.zBt, hh[i], o);
 #pragma unroll
       for (int k = 0; k < H; ++k) {
         if (((Q.imask >> i) & (Q.kmask >> k) & 1u) != 0)

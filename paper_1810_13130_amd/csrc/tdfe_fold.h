@@ -31,6 +31,33 @@ struct FoldSet {
   double wq[TDFE_MAXN];
 };
 
+// The 1D stiffness of the Gauss-point Lagrange basis, S = Dg^T diag(w) Dg, and
+// S B (nodes to points).  On box cells, whose metric is one diagonal per
+// cell, a direction's derivative, flux and transposed derivative are S along
+// it times the other two directions' weights: one contraction instead of two.
+// S is symmetric under reflection of both indices, so it folds as B does.
+struct GaussStiff {
+  double S[TDFE_MAXN * TDFE_MAXN];
+  double SB[TDFE_MAXN * TDFE_MAXN];
+};
+constexpr GaussStiff make_gauss_stiff(const tdfe1d::Rule& R) {
+  GaussStiff G{};
+  const int n = R.n;
+  for (int a = 0; a < n; ++a)
+    for (int b = 0; b < n; ++b) {
+      double v = 0.0;
+      for (int q = 0; q < n; ++q) v += R.wq[q] * R.Dg[q * TDFE_MAXN + a] * R.Dg[q * TDFE_MAXN + b];
+      G.S[a * TDFE_MAXN + b] = v;
+    }
+  for (int a = 0; a < n; ++a)
+    for (int i = 0; i < n; ++i) {
+      double v = 0.0;
+      for (int q = 0; q < n; ++q) v += G.S[a * TDFE_MAXN + q] * R.B[q * TDFE_MAXN + i];
+      G.SB[a * TDFE_MAXN + i] = v;
+    }
+  return G;
+}
+
 constexpr void fold_c(const double* A, int N, int S, bool transpose, Folded<double>& F) {
   const int H = N / 2;
   for (int a = 0; a < H; ++a)
@@ -57,6 +84,25 @@ constexpr FoldSet<N> make_foldset() {
   fold_c(R.D, N, -1, true, F.Dt);
   fold_c(R.Dg, N, -1, false, F.G);
   fold_c(R.Dg, N, -1, true, F.Gt);
+  for (int i = 0; i < TDFE_MAXN; ++i) F.wq[i] = R.wq[i];
+  return F;
+}
+
+// the folded tables of the box kernels: B, B^T, S and S B
+template <int N>
+struct BoxFoldSet {
+  Folded<double> B, Bt, S, SB;
+  double wq[TDFE_MAXN];
+};
+template <int N>
+constexpr BoxFoldSet<N> make_box_foldset() {
+  const tdfe1d::Rule R = tdfe1d::make_rule(N - 1);
+  const GaussStiff K = make_gauss_stiff(R);
+  BoxFoldSet<N> F{};
+  fold_c(R.B, N, 1, false, F.B);
+  fold_c(R.B, N, 1, true, F.Bt);
+  fold_c(K.S, N, 1, false, F.S);
+  fold_c(K.SB, N, 1, false, F.SB);
   for (int i = 0; i < TDFE_MAXN; ++i) F.wq[i] = R.wq[i];
   return F;
 }
