@@ -97,7 +97,9 @@ typedef struct {
  * orbitals; TDFE_BASIS_CHUNK_ORB=n caps only the basis memory at n orbitals
  * (soft-capped chunks may still be wider), as on a device with less memory;
  * TDFE_APPLY_VARIANT=line|pair|plane forces one operator kernel family
- * where it applies (the default picks per mesh, order and precision).
+ * where it applies (the default picks per mesh, order and precision);
+ * TDFE_CELL_BUFFER_BYTES=n caps the buffer of per-cell operator results (at
+ * most 256 MB; launches that do not fit add to the output directly).
  * hip_stream: hipStream_t (may be 0).  *out receives a new context. */
 tdfe_status tdfe_fe_mesh_setup(const tdfe_mesh_desc* d, void* hip_stream, tdfe_ctx** out);
 

@@ -16,7 +16,7 @@
 // form (Eq. TDKSMatVecStandard).  The quadratic form u^T H u of every
 // column is accumulated from the quadrature-point fluxes and reduced per
 // workgroup; it equals Re<x, Hbar x> and feeds the Lanczos alpha.
-#include "tdfe_internal.h"
+#include "tdfe_cells.h"
 #include "tdfe_rule1d.h"
 
 namespace {
@@ -611,6 +611,33 @@ tdfe_status launch_p(tdfe_ctx* c, KParams& P, bool geom) {
   return tdfe_fail(c, TDFE_EINVAL, "unsupported order p=%d", c->p);
 }
 
+// y (+)= the sums of the per-cell results: one block per row of DoFs (fixed y
+// and z), a lane per node and W columns (16 bytes where the columns allow it)
+template <typename T, int W, bool ADD>
+__global__ void __launch_bounds__(256)
+    assemble_kernel(const T* __restrict__ e, T* __restrict__ y, CellMap M, int cols, int ld, const int* done) {
+  if (done && *done) return;
+  const int C2 = cols / W;
+  const int Op = C2 <= 4 ? 4 : (C2 <= 8 ? 8 : (C2 <= 16 ? 16 : 32));
+  const int XL = 256 / Op;
+  const CellRow R = cell_row(M, 1 + (int)(blockIdx.x % (unsigned)M.NyI), 1 + (int)(blockIdx.x / (unsigned)M.NyI));
+  T* const yr = y + (int64_t)blockIdx.x * M.NxI * ld;
+  for (int o = (int)threadIdx.x % Op; o < C2; o += Op)
+    for (int I = (int)threadIdx.x / Op; I < M.NxI; I += XL) {
+      CellLane<T, W> L;
+      L.at(M, I);
+      T* const d = yr + (int64_t)I * ld + W * o;
+      T h[W], y0[W];
+      if constexpr (ADD) {
+#pragma unroll
+        for (int q = 0; q < W; ++q) y0[q] = d[q];
+      }
+      L.sum(e, R, cols, o, h);
+#pragma unroll
+      for (int q = 0; q < W; ++q) d[q] = ADD ? y0[q] + h[q] : h[q];
+    }
+}
+
 }  // namespace
 
 int64_t tdfe_blocks_apply(const tdfe_ctx* c, int cols) {
@@ -619,27 +646,110 @@ int64_t tdfe_blocks_apply(const tdfe_ctx* c, int cols) {
   return c->n_cell;
 }
 
+// Launches of the plane and lane-pair kernels: Loewdin DoF vectors,
+// p <= 7; two or more columns on trilinear cells (one column leaves n threads
+// per cell with the metric staged for the whole cell: the line kernel is
+// faster there, 0.64 ms against 2.2 ms for the Hartree solve's one-column
+// products on the graded mesh)
+static bool block_kernels_ok(const tdfe_ctx* c, const ApplyArgs& a) {
+  return c->variant != TDFE_VARIANT_LINE && a.lowdin && !a.fullgrid &&
+         (c->box ? tdfe_box_kernel_ok(c) : tdfe_curved_kernel_ok(c, a.cols, a.fp32));
+}
+
+static tdfe_status launch_blocks(tdfe_ctx* c, const ApplyArgs& a) {
+  // default policy, from measurements on the benchmark and graded workloads:
+  // box cells: the
+  // lane-pair kernel for FP64 at even n (two waves per SIMD), the plane kernel
+  // otherwise; trilinear cells: see tdfe_launch_apply_curved
+  if (!c->box) return tdfe_launch_apply_curved(c, a);
+  const bool pair = c->variant == TDFE_VARIANT_PAIR || (c->variant == 0 && !a.fp32);
+  if (pair && tdfe_pair_kernel_ok(c)) return tdfe_launch_apply_pair(c, a);
+  return tdfe_launch_apply_box(c, a);
+}
+
+// Columns of a launch whose per-cell results fit the cell buffer (0: none).
+// Per-cell results take plain stores where the scatter takes atomics (1.3 TB/s
+// of values), and leave n^3 / p^3 vectors for the consumer to read where the
+// scatter leaves one, so they pay while they stay in the memory-side cache.
+// Operator + update per Krylov step: 16^3 box cells, p = 5, 8 orbitals, FP64
+// (113 MB) 112 + 36 us scattered, 63 + 48 us per cell; FP32 (57 MB) 56 + 24 and
+// 38 + 28; 24^3 trilinear cells, p = 6 (607 MB) 545 + 228 us scattered, 537 +
+// 314 us per cell.
+static int cells_fit(const tdfe_ctx* c, const ApplyArgs& a) {
+  if (!c->eloc || c->mfma || a.cols % 2 || !block_kernels_ok(c, a)) return 0;
+  const size_t col = (size_t)c->n_cell * c->n * c->n * c->n * (a.fp32 ? 4 : 8);
+  const int cap = (int)std::min<size_t>(c->eloc_bytes / col, 1 << 20);
+  return a.cols <= cap ? a.cols : cap / 16 * 16;
+}
+
+bool tdfe_cells_ok(const tdfe_ctx* c, int cols, bool fp32) {
+  ApplyArgs a{};
+  a.cols = a.ld = cols;
+  a.lowdin = true;
+  a.fp32 = fp32;
+  return cells_fit(c, a) == cols;
+}
+
+tdfe_status tdfe_launch_apply_cells(tdfe_ctx* c, const ApplyArgs& a0) {
+  ApplyArgs a = a0;
+  if (cells_fit(c, a) != a.cols) return tdfe_fail(c, TDFE_EINVAL, "apply: no per-cell results for this launch");
+  if (a.fp32 && !tdfe_fp32(c)) return tdfe_fail(c, TDFE_EINVAL, "apply: FP32 launch in an FP64 context");
+  a.y = c->eloc;
+  a.eld = a.cols;
+  a.cells = true;
+  return launch_blocks(c, a);
+}
+
+// y (+)= H x through the cell buffer, `step` columns at a time
+static tdfe_status launch_cells_sum(tdfe_ctx* c, const ApplyArgs& a0, int step) {
+  const size_t eb = a0.fp32 ? 4 : 8;
+  const CellMap M{c->ncx, c->ncy, c->ncz, c->p, c->Nx - 2, c->Ny - 2, c->Nz - 2};
+  const dim3 grid((unsigned)(M.NyI * M.NzI));
+  for (int col0 = 0; col0 < a0.cols; col0 += step) {
+    ApplyArgs a = a0;
+    a.cols = std::min(step, a0.cols - col0);
+    a.eld = a.cols;
+    a.cells = true;
+    a.x = (const char*)a0.x + col0 * eb;
+    a.y = c->eloc;
+    if (a0.colscale) a.colscale = a0.colscale + col0 / 2;
+    TDFE_TRY(launch_blocks(c, a));
+    void* const y = (char*)a0.y + col0 * eb;
+    auto assemble = [&](auto kernel, auto* e, auto* out) {
+      hipLaunchKernelGGL(kernel, grid, dim3(256), 0, c->stream, e, out, M, a.cols, a.ld, a.done_flag);
+    };
+    auto* const e64 = (const double*)c->eloc;
+    auto* const e32 = (const float*)c->eloc;
+    if (!a.fp32 && a.overwrite) assemble(assemble_kernel<double, 2, false>, e64, (double*)y);
+    if (!a.fp32 && !a.overwrite) assemble(assemble_kernel<double, 2, true>, e64, (double*)y);
+    if (a.fp32 && a.cols % 4 == 0) assemble(assemble_kernel<float, 4, true>, e32, (float*)y);
+    if (a.fp32 && a.cols % 4 != 0) assemble(assemble_kernel<float, 2, true>, e32, (float*)y);
+    TDFE_HIP(c, hipGetLastError());
+  }
+  return TDFE_OK;
+}
+
+bool tdfe_can_overwrite(const tdfe_ctx* c, const ApplyArgs& a) {
+  return !c->octree && !a.fp32 && !a.energy && cells_fit(c, a) > 0;
+}
+
 static tdfe_status launch_local(tdfe_ctx* c, const ApplyArgs& a) {
   if (c->octree) return tdfe_launch_apply_octree(c, a);
   // the FP32 copy of the potential exists in mixed contexts only
   if (a.fp32 && !tdfe_fp32(c)) return tdfe_fail(c, TDFE_EINVAL, "apply: FP32 launch in an FP64 context");
-  // default policy, from measurements on the benchmark and graded workloads:
-  // box cells: the lane-pair kernel for FP64 at even n (two waves per SIMD;
-  // 130 us against 170 us for the plane kernel at 16^3 cells, p = 5, 8
-  // orbitals), the plane kernel otherwise; trilinear cells, two or more
-  // columns at p <= 7: the lane-pair kernel for FP64 and for FP32 at p = 7,
-  // the plane kernel for FP32 below p = 7; the line kernel for one column and
-  // at p = 8
+  if (a.cols < 1) return tdfe_fail(c, TDFE_EINVAL, "apply: cols < 1");
+  // M^-1/2 exists on the interior DoFs only
+  if (a.lowdin && a.fullgrid) return tdfe_fail(c, TDFE_EINVAL, "apply: Loewdin scaling on the full node grid");
   if (c->mfma && tdfe_mfma_kernel_ok(c, a)) return tdfe_launch_apply_mfma(c, a);
-  if (c->variant != TDFE_VARIANT_LINE) {
-    if (c->box) {
-      const bool pair = c->variant == TDFE_VARIANT_PAIR || (c->variant == 0 && !a.fp32);
-      if (pair && tdfe_pair_kernel_ok(c)) return tdfe_launch_apply_pair(c, a);
-      if (tdfe_box_kernel_ok(c)) return tdfe_launch_apply_box(c, a);
-    } else if (tdfe_curved_kernel_ok(c, a.cols, a.fp32)) {
-      return tdfe_launch_apply_curved(c, a);
-    }
+  const int step = cells_fit(c, a);
+  if (step == a.cols || (step > 0 && !a.energy)) return launch_cells_sum(c, a, step);
+  if (block_kernels_ok(c, a)) {
+    ApplyArgs b = a;
+    b.eld = a.cols;
+    return launch_blocks(c, b);
   }
+  // full-grid and one-column curved launches, p = 8: the line kernel, which
+  // scatters by atomics
   KParams P{};
   P.x = a.x;
   P.y = a.y;
@@ -665,7 +775,6 @@ static tdfe_status launch_local(tdfe_ctx* c, const ApplyArgs& a) {
   P.lowdin = a.lowdin;
   P.fullgrid = a.fullgrid;
   P.groups_out = a.n_blocks_out;
-  if (a.cols < 1) return tdfe_fail(c, TDFE_EINVAL, "apply: cols < 1");
   const bool geom = !c->box;
   if (a.fp32) return launch_p<float>(c, P, geom);
   return launch_p<double>(c, P, geom);

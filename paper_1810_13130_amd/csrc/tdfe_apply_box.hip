@@ -10,7 +10,7 @@
 //      in registers the y and z stiffness terms S u_q, the potential term, all
 //      weighted and summed, and the transposed y interpolation of the sum
 //   -- LDS transpose of the one array -->
-//   C  (plane at fixed y node j):  x: B^T; z: B^T; scatter-add.
+//   C  (plane at fixed y node j):  x: B^T; z: B^T; results x M^-1/2 (CellOut).
 //
 // The metric of a box cell is one diagonal per cell, so a direction's
 // derivative, flux and transposed derivative are one contraction with the 1D
@@ -35,8 +35,8 @@ namespace {
 template <typename T>
 struct PlaneParams {
   const void* x;
-  void* y;
-  int ld, cols, nchunks;
+  void* y;  // CELLS: per-cell results [n_cell][n^3][cols]; else the DoF vector, added to
+  int ld, cols, nchunks, eld;
   const double* colscale;
   double kin;
   const void* vw;
@@ -49,7 +49,7 @@ struct PlaneParams {
   const int* done;
   int ncx, ncy, ncz, p, Nx, Ny, Nz;
   int64_t n_cell;
-  int lowdin, fullgrid;
+  bool cells;
   double wq[TDFE_MAXN];  // Gauss weights (indexed by the thread's plane)
 };
 
@@ -60,7 +60,7 @@ constexpr int plane_wpe() {
   return sizeof(T) == 4 ? (N == 5 || N == 6 ? 3 : 2) : (N >= 6 ? 1 : 2);
 }
 
-template <typename T, int N, int CB, int CPB>
+template <typename T, int N, int CB, int CPB, bool CELLS>
 __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_eu(plane_wpe<T, N>())))
     plane_kernel(PlaneParams<T> P) {
   constexpr int VOL = N * N * N;
@@ -143,24 +143,19 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
     const int J = cy * P.p + j;
     // node (I, J, K) -> element offset; all loads are issued unconditionally
     // from a valid address (masked entries read element 0 and are zeroed)
-    const bool jok = P.fullgrid ? true : (J > 0 && J < P.Ny - 1);
+    const bool jok = J > 0 && J < P.Ny - 1;
     unsigned imask = 0, kmask = 0;
 #pragma unroll
     for (int q = 0; q < N; ++q) {
       const int I = cx * P.p + q, K = cz * P.p + q;
-      if (P.fullgrid || (I > 0 && I < P.Nx - 1)) imask |= 1u << q;
-      if (P.fullgrid || (K > 0 && K < P.Nz - 1)) kmask |= 1u << q;
+      if (I > 0 && I < P.Nx - 1) imask |= 1u << q;
+      if (K > 0 && K < P.Nz - 1) kmask |= 1u << q;
     }
     if (!act || !jok) imask = 0;
     // element index of (i, k): e0 + i * ld + k * kstride
-    int64_t e0, kstride;
-    if (P.fullgrid) {
-      e0 = ((int64_t)cx * P.p + (int64_t)P.Nx * ((int64_t)J + (int64_t)P.Ny * cz * P.p)) * P.ld + colg;
-      kstride = (int64_t)P.Nx * P.Ny * P.ld;
-    } else {
-      e0 = ((int64_t)(cx * P.p - 1) + (int64_t)NxI * ((int64_t)(J - 1) + (int64_t)NyI * (cz * P.p - 1))) * P.ld + colg;
-      kstride = (int64_t)NxI * NyI * P.ld;
-    }
+    const int64_t e0 =
+        ((int64_t)(cx * P.p - 1) + (int64_t)NxI * ((int64_t)(J - 1) + (int64_t)NyI * (cz * P.p - 1))) * P.ld + colg;
+    const int64_t kstride = (int64_t)NxI * NyI * P.ld;
 #pragma unroll
     for (int k = 0; k < N; ++k) {
 #pragma unroll
@@ -182,26 +177,17 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
       if (f < CPB * NFC) sF[f] = fr[k];
     }
     __syncthreads();
-    T my = (T)1;
-    if (P.lowdin && imask) my = (T)sFc[N + j] * cs;
-    else my = cs;
-    if (P.lowdin) {
-      T fx[N], fz[N];
+    const T my = (T)sFc[N + j] * cs;
+    T fx[N], fz[N];
 #pragma unroll
-      for (int q = 0; q < N; ++q) {
-        fx[q] = ((imask >> q) & 1u) ? (T)sFc[q] : (T)0;
-        fz[q] = ((kmask >> q) & 1u) ? (T)sFc[2 * N + q] : (T)0;
-      }
-#pragma unroll
-      for (int k = 0; k < N; ++k)
-#pragma unroll
-        for (int i = 0; i < N; ++i) u[i][k] *= fx[i] * fz[k] * my;
-    } else {
-#pragma unroll
-      for (int k = 0; k < N; ++k)
-#pragma unroll
-        for (int i = 0; i < N; ++i) u[i][k] *= my;
+    for (int q = 0; q < N; ++q) {
+      fx[q] = ((imask >> q) & 1u) ? (T)sFc[q] : (T)0;
+      fz[q] = ((kmask >> q) & 1u) ? (T)sFc[2 * N + q] : (T)0;
     }
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+#pragma unroll
+      for (int i = 0; i < N; ++i) u[i][k] *= fx[i] * fz[k] * my;
     // z: interpolation, per x node
 #pragma unroll
     for (int i = 0; i < N; ++i) {
@@ -322,47 +308,23 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
 #pragma unroll
       for (int i = 0; i < N; ++i) h[i][c] = o[i];
     }
-    const int J = cy * P.p + j;
-    const bool jok = P.fullgrid ? true : (J > 0 && J < P.Ny - 1);
-    unsigned imask = 0, kmask = 0;
-#pragma unroll
-    for (int q = 0; q < N; ++q) {
-      const int I = cx * P.p + q, K = cz * P.p + q;
-      if (P.fullgrid || (I > 0 && I < P.Nx - 1)) imask |= 1u << q;
-      if (P.fullgrid || (K > 0 && K < P.Nz - 1)) kmask |= 1u << q;
-    }
-    if (!act || !jok) imask = 0;
-    int64_t e0, kstride;
-    if (P.fullgrid) {
-      e0 = ((int64_t)cx * P.p + (int64_t)P.Nx * ((int64_t)J + (int64_t)P.Ny * cz * P.p)) * P.ld + colg;
-      kstride = (int64_t)P.Nx * P.Ny * P.ld;
-    } else {
-      e0 = ((int64_t)(cx * P.p - 1) + (int64_t)NxI * ((int64_t)(J - 1) + (int64_t)NyI * (cz * P.p - 1))) * P.ld + colg;
-      kstride = (int64_t)NxI * NyI * P.ld;
-    }
     T fx[N], fz[N];
-    T my = (T)1;
+    const T my = (T)sFc[N + j];
 #pragma unroll
     for (int q = 0; q < N; ++q) {
-      fx[q] = (T)1;
-      fz[q] = (T)1;
+      fx[q] = (T)sFc[q];
+      fz[q] = (T)sFc[2 * N + q];
     }
-    if (P.lowdin && imask) {
-      my = (T)sFc[N + j];
-#pragma unroll
-      for (int q = 0; q < N; ++q) {
-        if ((imask >> q) & 1u) fx[q] = (T)sFc[q];
-        if ((kmask >> q) & 1u) fz[q] = (T)sFc[2 * N + q];
-      }
-    }
+    const CellOut<T, N, CELLS> E(Y, P, cell, cx, cy, cz, j, colg, act);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       T o[N];
       eo<T, N, 1>(FS.Bt, h[i], o);
+      if (E.jok && E.xok(i)) {
+        T* const row = E.e + i * E.sx;
 #pragma unroll
-      for (int k = 0; k < N; ++k) {
-        if (((imask >> i) & (kmask >> k) & 1u) != 0)
-          unsafeAtomicAdd(Y + (e0 + (int64_t)i * P.ld + (int64_t)k * kstride), o[k] * fx[i] * fz[k] * my);
+        for (int k = 0; k < N; ++k)
+          if (E.zok(k)) E.put(row + k * E.sz, o[k] * fx[i] * fz[k] * my);
       }
     }
   }
@@ -372,7 +334,7 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
     if (t < CB) {
       double acc = 0.0;
       for (int u = t; u < THREADS; u += CB) acc += sRed[u];
-      if (chunk * CB + t < P.cols) P.energy[(int64_t)group * P.cols + chunk * CB + t] = acc;
+      if (chunk * CB + t < P.cols) P.energy[(int64_t)group * P.eld + chunk * CB + t] = acc;
     }
   }
 }
@@ -406,8 +368,11 @@ tdfe_status launch_plane(tdfe_ctx* c, PlaneParams<T>& P, int64_t* groups_out) {
   const int64_t groups = (c->n_cell + CPB - 1) / CPB;
   P.nchunks = (P.cols + CB - 1) / CB;
   if (groups_out) *groups_out = groups;
-  hipLaunchKernelGGL((plane_kernel<T, N, CB, CPB>), dim3((unsigned)(groups * P.nchunks)), dim3(CPB * N * CB), 0,
-                     c->stream, P);
+  const dim3 grid((unsigned)(groups * P.nchunks)), block(CPB * N * CB);
+  if (P.cells)
+    hipLaunchKernelGGL((plane_kernel<T, N, CB, CPB, true>), grid, block, 0, c->stream, P);
+  else
+    hipLaunchKernelGGL((plane_kernel<T, N, CB, CPB, false>), grid, block, 0, c->stream, P);
   TDFE_HIP(c, hipGetLastError());
   return TDFE_OK;
 }
@@ -462,8 +427,8 @@ tdfe_status launch_box(tdfe_ctx* c, const ApplyArgs& a) {
   P.Ny = c->Ny;
   P.Nz = c->Nz;
   P.n_cell = c->n_cell;
-  P.lowdin = a.lowdin;
-  P.fullgrid = a.fullgrid;
+  P.eld = a.eld;
+  P.cells = a.cells;
   const int N = c->n;
   for (int i = 0; i < N; ++i) P.wq[i] = c->wq[i];
   return launch_plane_p<T>(c, P, a.n_blocks_out);

@@ -11,7 +11,7 @@
 //      transposed derivatives; transposed y interpolation of (V u_q + ...) and of
 //      the x flux
 //   -- LDS transpose of the two arrays -->
-//   C  (plane at node y = j): x: B^T s + D^T s_x; z: B^T; scatter-add (x M^-1/2).
+//   C  (plane at node y = j): x: B^T s + D^T s_x; z: B^T; results x M^-1/2 (CellOut).
 // The x derivative is taken on the nodes (D = Dg B along x) so that x never
 // crosses threads; only y does.  Contractions use the even/odd folded tables.
 #include "tdfe_fold.h"
@@ -21,8 +21,8 @@ namespace {
 template <typename T>
 struct CurvedParams {
   const void* x;
-  void* y;
-  int ld, cols, nchunks;
+  void* y;  // CELLS: per-cell results [n_cell][n^3][cols]; else the DoF vector, added to
+  int ld, cols, nchunks, eld;
   const double* colscale;
   double kin;
   const void* vw;
@@ -33,7 +33,7 @@ struct CurvedParams {
   const int* done;
   int ncx, ncy, ncz, p, Nx, Ny, Nz;
   int64_t n_cell;
-  int lowdin, fullgrid;
+  bool cells;
   double eta[TDFE_MAXN];  // Gauss points on [-1, 1]
   double wq[TDFE_MAXN];   // Gauss weights
 };
@@ -43,7 +43,7 @@ constexpr int cplane_wpe() {
   return sizeof(T) == 4 ? 2 : 1;
 }
 
-template <typename T, int N, int CB, int CPB>
+template <typename T, int N, int CB, int CPB, bool CELLS>
 __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_eu(cplane_wpe<T, N>())))
     cplane_kernel(CurvedParams<T> P) {
   constexpr int VOL = N * N * N;
@@ -112,8 +112,7 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
   }
   const int64_t c0 = (int64_t)group * CPB;
   // per-node scale of the block's cells, staged once per block (the column
-  // lanes of a plane share it): M^-1/2 on DoFs (1 without the Loewdin
-  // scaling) and 0 on Dirichlet nodes and past the last cell, which zeroes
+  // lanes of a plane share it): M^-1/2 on DoFs and 0 on Dirichlet nodes and past the last cell, which zeroes
   // their gathered values and their scattered contributions
   constexpr int NM = NV;
   T mr[NM];
@@ -127,13 +126,11 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
     if (in) {
       const int ex = (int)(ce % P.ncx), ey = (int)((ce / P.ncx) % P.ncy), ez = (int)(ce / ((int64_t)P.ncx * P.ncy));
       const int I = ex * P.p + r % N, Jn = ey * P.p + (r / N) % N, K = ez * P.p + r / (N * N);
-      if (!P.fullgrid) {
-        in = I > 0 && I < P.Nx - 1 && Jn > 0 && Jn < P.Ny - 1 && K > 0 && K < P.Nz - 1;
-        idx = (int64_t)(I - 1) + (int64_t)(P.Nx - 2) * ((int64_t)(Jn - 1) + (int64_t)(P.Ny - 2) * (K - 1));
-      }
+      in = I > 0 && I < P.Nx - 1 && Jn > 0 && Jn < P.Ny - 1 && K > 0 && K < P.Nz - 1;
+      idx = (int64_t)(I - 1) + (int64_t)(P.Nx - 2) * ((int64_t)(Jn - 1) + (int64_t)(P.Ny - 2) * (K - 1));
     }
-    const T mval = MV[(in && P.lowdin) ? idx : 0];
-    mr[k] = in ? (P.lowdin ? mval : (T)1) : (T)0;
+    const T mval = MV[in ? idx : 0];
+    mr[k] = in ? mval : (T)0;
   }
   T vr[NV];
 #pragma unroll
@@ -157,23 +154,9 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
 
   // node (i, j, k) of this cell -> element offset and inside flag
   const int J = cy * P.p + pl;
-  const bool jok = P.fullgrid ? true : (J > 0 && J < P.Ny - 1);
-  unsigned imask = 0, kmask = 0;
-#pragma unroll
-  for (int q = 0; q < N; ++q) {
-    const int I = cx * P.p + q, K = cz * P.p + q;
-    if (P.fullgrid || (I > 0 && I < P.Nx - 1)) imask |= 1u << q;
-    if (P.fullgrid || (K > 0 && K < P.Nz - 1)) kmask |= 1u << q;
-  }
-  if (!act || !jok) imask = 0;
-  int64_t n0, nk;  // node index of (0, j, 0) and the node stride along z
-  if (P.fullgrid) {
-    n0 = (int64_t)cx * P.p + (int64_t)P.Nx * ((int64_t)J + (int64_t)P.Ny * cz * P.p);
-    nk = (int64_t)P.Nx * P.Ny;
-  } else {
-    n0 = (int64_t)(cx * P.p - 1) + (int64_t)NxI * ((int64_t)(J - 1) + (int64_t)NyI * (cz * P.p - 1));
-    nk = (int64_t)NxI * NyI;
-  }
+  // node index of (0, j, 0) and the node stride along z
+  const int64_t n0 = (int64_t)(cx * P.p - 1) + (int64_t)NxI * ((int64_t)(J - 1) + (int64_t)NyI * (cz * P.p - 1));
+  const int64_t nk = (int64_t)NxI * NyI;
 
   // metric of the block's Gauss points from the LDS corners (read in phase B,
   // after the transposes' barriers); Gauss points and weights from LDS
@@ -261,12 +244,10 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
     {
       // the resource is built from the block's first cell (the lowest rows
       // any of its cells touches) and made explicitly wave-uniform
-      const int64_t rows = P.fullgrid ? (int64_t)P.Nx * P.Ny * P.Nz : (int64_t)NxI * NyI * (P.Nz - 2);
+      const int64_t rows = (int64_t)NxI * NyI * (P.Nz - 2);
       const int bx = (int)(c0 % P.ncx), by = (int)((c0 / P.ncx) % P.ncy), bz = (int)(c0 / ((int64_t)P.ncx * P.ncy));
-      const int64_t first = P.fullgrid ? (int64_t)bx * P.p + (int64_t)P.Nx * ((int64_t)by * P.p +
-                                                                              (int64_t)P.Ny * bz * P.p)
-                                       : (int64_t)(bx * P.p - 1) + (int64_t)NxI * ((int64_t)(by * P.p - 1) +
-                                                                                 (int64_t)NyI * (bz * P.p - 1));
+      const int64_t first = (int64_t)(bx * P.p - 1) + (int64_t)NxI * ((int64_t)(by * P.p - 1) +
+                            (int64_t)NyI * (bz * P.p - 1));
       const int64_t base = first > 0 ? first : 0;
       const int64_t bytes = (rows - base) * P.ld * (int64_t)sizeof(T);
       const uint64_t addr = (uint64_t)(uintptr_t)(X + base * P.ld);
@@ -475,6 +456,7 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
 #pragma unroll
       for (int i = 0; i < N; ++i) h[i][c] = o1[i] + o2[i];
     }
+    const CellOut<T, N, CELLS> E(Y, P, cell, cx, cy, cz, pl, colg, act);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       // the line's M^-1/2 values are loaded before its contraction, so that
@@ -484,14 +466,12 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
       for (int k = 0; k < N; ++k) ml[k] = sM[slot * VOL + i + N * (pl + N * k)];
       T o[N];
       eo<T, N, 1>(FS.Bt, h[i], o);
-      // imask / kmask depend on the cell only, so these branches are uniform
-      // whenever a wave holds one cell; act and the plane's own row test are
-      // folded into imask
-      if ((imask >> i) & 1u) {
-        T* yrow = Y + ((n0 + i) * P.ld + colg);
+      // (the node tests depend on the cell only: uniform whenever a wave holds one cell)
+      if (E.jok && E.xok(i)) {
+        T* const row = E.e + i * E.sx;
 #pragma unroll
         for (int k = 0; k < N; ++k)
-          if ((kmask >> k) & 1u) unsafeAtomicAdd(yrow + (int64_t)k * nk * P.ld, o[k] * ml[k]);
+          if (E.zok(k)) E.put(row + k * E.sz, o[k] * ml[k]);
       }
     }
   }
@@ -501,7 +481,7 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
     if (t < CB) {
       double acc = 0.0;
       for (int u = t; u < THREADS; u += CB) acc += sRed[u];
-      if (chunk * CB + t < P.cols) P.energy[(int64_t)group * P.cols + chunk * CB + t] = acc;
+      if (chunk * CB + t < P.cols) P.energy[(int64_t)group * P.eld + chunk * CB + t] = acc;
     }
   }
 }
@@ -532,8 +512,11 @@ tdfe_status launch_cplane(tdfe_ctx* c, CurvedParams<T>& P, int64_t* groups_out) 
   const int64_t groups = (c->n_cell + CPB - 1) / CPB;
   P.nchunks = (P.cols + CB - 1) / CB;
   if (groups_out) *groups_out = groups;
-  hipLaunchKernelGGL((cplane_kernel<T, N, CB, CPB>), dim3((unsigned)(groups * P.nchunks)), dim3(CPB * N * CB), 0,
-                     c->stream, P);
+  const dim3 grid((unsigned)(groups * P.nchunks)), block(CPB * N * CB);
+  if (P.cells)
+    hipLaunchKernelGGL((cplane_kernel<T, N, CB, CPB, true>), grid, block, 0, c->stream, P);
+  else
+    hipLaunchKernelGGL((cplane_kernel<T, N, CB, CPB, false>), grid, block, 0, c->stream, P);
   TDFE_HIP(c, hipGetLastError());
   return TDFE_OK;
 }
@@ -710,7 +693,7 @@ constexpr int cpair_wpe() {
   return 2;
 }
 
-template <typename T, int N, int CB, int CPB>
+template <typename T, int N, int CB, int CPB, bool CELLS>
 __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_per_eu(cpair_wpe<T, N>())))
     cpair_kernel(CurvedParams<T> P) {
   constexpr int H = N / 2;
@@ -790,13 +773,11 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
     if (in) {
       const int ex = (int)(ce % P.ncx), ey = (int)((ce / P.ncx) % P.ncy), ez = (int)(ce / ((int64_t)P.ncx * P.ncy));
       const int I = ex * P.p + rr % N, Jn = ey * P.p + (rr / N) % N, K = ez * P.p + rr / (N * N);
-      if (!P.fullgrid) {
-        in = I > 0 && I < P.Nx - 1 && Jn > 0 && Jn < P.Ny - 1 && K > 0 && K < P.Nz - 1;
-        idx = (int64_t)(I - 1) + (int64_t)(P.Nx - 2) * ((int64_t)(Jn - 1) + (int64_t)(P.Ny - 2) * (K - 1));
-      }
+      in = I > 0 && I < P.Nx - 1 && Jn > 0 && Jn < P.Ny - 1 && K > 0 && K < P.Nz - 1;
+      idx = (int64_t)(I - 1) + (int64_t)(P.Nx - 2) * ((int64_t)(Jn - 1) + (int64_t)(P.Ny - 2) * (K - 1));
     }
-    const T mval = MV[(in && P.lowdin) ? idx : 0];
-    mr[k] = in ? (P.lowdin ? mval : (T)1) : (T)0;
+    const T mval = MV[in ? idx : 0];
+    mr[k] = in ? mval : (T)0;
   }
   T vr[NV];
 #pragma unroll
@@ -817,31 +798,10 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
   auto sidx = [&](int y, int x, int z) { return (((slot * N + y) * N + x) * N + z) * CB + col; };
   const int NxI = P.Nx - 2, NyI = P.Ny - 2;
 
-  // scatter masks: node rows i of the plane and this lane's local z entries
-  // that are DoFs; the shared middle entry is scattered by lane 0 only
   const int J = cy * P.p + pl;
-  const bool jok = P.fullgrid ? true : (J > 0 && J < P.Ny - 1);
-  unsigned imask = 0, kmask = 0;
-#pragma unroll
-  for (int q = 0; q < N; ++q) {
-    const int I = cx * P.p + q;
-    if (P.fullgrid || (I > 0 && I < P.Nx - 1)) imask |= 1u << q;
-  }
-#pragma unroll
-  for (int q = 0; q < HZ; ++q) {
-    const int K = cz * P.p + zg(q);
-    if (P.fullgrid || (K > 0 && K < P.Nz - 1)) kmask |= 1u << q;
-  }
-  if (ODD && h) kmask &= ~(1u << H);
-  if (!act || !jok) imask = 0;
-  int64_t n0, nk;  // node index of (0, j, 0) and the node stride along z
-  if (P.fullgrid) {
-    n0 = (int64_t)cx * P.p + (int64_t)P.Nx * ((int64_t)J + (int64_t)P.Ny * cz * P.p);
-    nk = (int64_t)P.Nx * P.Ny;
-  } else {
-    n0 = (int64_t)(cx * P.p - 1) + (int64_t)NxI * ((int64_t)(J - 1) + (int64_t)NyI * (cz * P.p - 1));
-    nk = (int64_t)NxI * NyI;
-  }
+  // node index of (0, j, 0) and the node stride along z
+  const int64_t n0 = (int64_t)(cx * P.p - 1) + (int64_t)NxI * ((int64_t)(J - 1) + (int64_t)NyI * (cz * P.p - 1));
+  const int64_t nk = (int64_t)NxI * NyI;
 
   // ---------------- A: plane j = pl, values (i, local k) -----------------------------------------
   T tu[N][HZ], tx[N][HZ];  // [x point][local z]
@@ -851,12 +811,10 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
       // buffer resource from the block's first cell, wave-uniform (see the
       // plane kernel): out-of-range nodes read 0, Dirichlet nodes inside the
       // range read a value that the zero in sM cancels
-      const int64_t rows = P.fullgrid ? (int64_t)P.Nx * P.Ny * P.Nz : (int64_t)NxI * NyI * (P.Nz - 2);
+      const int64_t rows = (int64_t)NxI * NyI * (P.Nz - 2);
       const int bx = (int)(c0 % P.ncx), by = (int)((c0 / P.ncx) % P.ncy), bz = (int)(c0 / ((int64_t)P.ncx * P.ncy));
-      const int64_t first = P.fullgrid ? (int64_t)bx * P.p + (int64_t)P.Nx * ((int64_t)by * P.p +
-                                                                              (int64_t)P.Ny * bz * P.p)
-                                       : (int64_t)(bx * P.p - 1) + (int64_t)NxI * ((int64_t)(by * P.p - 1) +
-                                                                                 (int64_t)NyI * (bz * P.p - 1));
+      const int64_t first = (int64_t)(bx * P.p - 1) + (int64_t)NxI * ((int64_t)(by * P.p - 1) +
+                            (int64_t)NyI * (bz * P.p - 1));
       const int64_t base = first > 0 ? first : 0;
       const int64_t bytes = (rows - base) * P.ld * (int64_t)sizeof(T);
       const uint64_t addr = (uint64_t)(uintptr_t)((const T*)P.x + base * P.ld);
@@ -1061,6 +1019,11 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
 #pragma unroll
       for (int i = 0; i < N; ++i) hh[i][c] = o1[i] + o2[i];
     }
+    const CellOut<T, N, CELLS> E(Y, P, cell, cx, cy, cz, pl, colg, act);
+    // this lane's z entries run up from node 0 or down from node n-1
+    T* const e0 = E.e + (h ? (N - 1) * E.sz : 0);
+    const int64_t sz = h ? -E.sz : E.sz;
+    const bool z0 = h ? E.hiz : E.loz;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       T ml[HZ];
@@ -1068,11 +1031,11 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
       for (int k = 0; k < HZ; ++k) ml[k] = sM[slot * VOL + i + N * (pl + N * zg(k))];
       T o[HZ];
       zpair<T, N>(ZS.Bt, hh[i], o, (T)1);
-      if ((imask >> i) & 1u) {
-        T* yrow = Y + ((n0 + i) * P.ld + colg);
+      if (E.jok && E.xok(i)) {
+        T* const row = e0 + i * E.sx;
 #pragma unroll
         for (int k = 0; k < HZ; ++k)
-          if ((kmask >> k) & 1u) unsafeAtomicAdd(yrow + (int64_t)zg(k) * nk * P.ld, o[k] * ml[k]);
+          if ((k > 0 || z0) && !(ODD && k == H && h)) E.put(row + k * sz, o[k] * ml[k]);
       }
     }
   }
@@ -1082,7 +1045,7 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
     if (t < CB) {
       double acc = 0.0;
       for (int u = 2 * t; u < THREADS; u += 2 * CB) acc += sRed[u] + sRed[u + 1];
-      if (chunk * CB + t < P.cols) P.energy[(int64_t)group * P.cols + chunk * CB + t] = acc;
+      if (chunk * CB + t < P.cols) P.energy[(int64_t)group * P.eld + chunk * CB + t] = acc;
     }
   }
 }
@@ -1111,8 +1074,11 @@ tdfe_status launch_cpair(tdfe_ctx* c, CurvedParams<T>& P, int64_t* groups_out) {
   const int64_t groups = (c->n_cell + CPB - 1) / CPB;
   P.nchunks = (P.cols + CB - 1) / CB;
   if (groups_out) *groups_out = groups;
-  hipLaunchKernelGGL((cpair_kernel<T, N, CB, CPB>), dim3((unsigned)(groups * P.nchunks)), dim3(2 * CPB * N * CB), 0,
-                     c->stream, P);
+  const dim3 grid((unsigned)(groups * P.nchunks)), block(2 * CPB * N * CB);
+  if (P.cells)
+    hipLaunchKernelGGL((cpair_kernel<T, N, CB, CPB, true>), grid, block, 0, c->stream, P);
+  else
+    hipLaunchKernelGGL((cpair_kernel<T, N, CB, CPB, false>), grid, block, 0, c->stream, P);
   TDFE_HIP(c, hipGetLastError());
   return TDFE_OK;
 }
@@ -1150,19 +1116,20 @@ tdfe_status launch_curved(tdfe_ctx* c, const ApplyArgs& a) {
   P.Ny = c->Ny;
   P.Nz = c->Nz;
   P.n_cell = c->n_cell;
-  P.lowdin = a.lowdin;
-  P.fullgrid = a.fullgrid;
+  P.eld = a.eld;
+  P.cells = a.cells;
   const int N = c->n;
   for (int i = 0; i < N; ++i) {
     P.eta[i] = c->eta[i];
     P.wq[i] = c->wq[i];
   }
-  // lane pairs for FP64 (two waves per SIMD instead of one) and for FP32 at
-  // n = 8 (162 VGPRs against the plane kernel's 256: 1.75 against 1.98 ms per
-  // 2-orbital launch of the all-electron workload); plane ownership for FP32
-  // otherwise (at n = 7 both run two waves per SIMD and the pairs' duplicated
-  // z work loses: 2.24 against 1.50 ms per 16-orbital graded launch)
-  const bool pair = c->variant == TDFE_VARIANT_PAIR || (c->variant == 0 && (sizeof(T) == 8 || N == 8));
+  // lane pairs for FP64 above n = 5 (two waves per SIMD instead of one; at n =
+  // 5 a plane fits: 295 against 385 us per 8-orbital launch on 24^3 cells) and
+  // for FP32 at n = 8 (162 VGPRs against the plane kernel's 256: 1.75 against
+  // 1.98 ms per 2-orbital launch of the all-electron workload); plane ownership
+  // for FP32 otherwise (at n = 7 both run two waves per SIMD and the pairs'
+  // duplicated z work loses: 2.24 against 1.50 ms per 16-orbital graded launch)
+  const bool pair = c->variant == TDFE_VARIANT_PAIR || (c->variant == 0 && (sizeof(T) == 8 ? N > 5 : N == 8));
   if (pair) {
     switch (N) {
       case 2: return launch_cpair_n<T, 2>(c, P, a.n_blocks_out);
@@ -1202,7 +1169,5 @@ bool tdfe_curved_kernel_ok(const tdfe_ctx* c, int cols, bool fp32) {
 tdfe_status tdfe_launch_apply_curved(tdfe_ctx* c, const ApplyArgs& a) {
   if (a.cols < 1) return tdfe_fail(c, TDFE_EINVAL, "apply: cols < 1");
   if (!tdfe_curved_kernel_ok(c, a.cols, a.fp32)) return tdfe_fail(c, TDFE_EINVAL, "curved operator: unsupported mesh or order");
-  // M^-1/2 exists on the interior DoFs only
-  if (a.lowdin && a.fullgrid) return tdfe_fail(c, TDFE_EINVAL, "apply: Loewdin scaling on the full node grid");
   return a.fp32 ? launch_curved<float>(c, a) : launch_curved<double>(c, a);
 }

@@ -37,8 +37,8 @@ struct SplitT {
 template <typename T>
 struct PairParams {
   const void* x;
-  void* y;
-  int ld, cols, nchunks;
+  void* y;  // CELLS: per-cell results [n_cell][n^3][cols]; else the DoF vector, added to
+  int ld, cols, nchunks, eld;
   const double* colscale;
   double kin;
   const void* vw;
@@ -50,7 +50,7 @@ struct PairParams {
   const int* done;
   int ncx, ncy, ncz, p, Nx, Ny, Nz;
   int64_t n_cell;
-  int lowdin, fullgrid;
+  bool cells;
   double wq[TDFE_MAXN];
 };
 
@@ -158,7 +158,7 @@ constexpr int pair_wpe() {
   return sizeof(T) == 8 ? 2 : 3;
 }
 
-template <typename T, int N, int CB, int CPB>
+template <typename T, int N, int CB, int CPB, bool CELLS>
 __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_per_eu(pair_wpe<T, N>())))
     pair_kernel(PairParams<T> P) {
   static_assert(N % 2 == 0 && N / 2 <= PH, "even n <= 8");
@@ -235,65 +235,44 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
   auto sidx = [&](int y, int x, int z) { return (((slot * N + y) * N + x) * N + z) * CB + col; };
   const int NxI = P.Nx - 2, NyI = P.Ny - 2;
 
-  // node masks, element offsets and Loewdin factors of node plane j = pl
-  // (phases A and C; recomputed in C rather than held through B): fx, fz
-  // and my are the x, z and y factors of M^-1/2
-  struct PlaneNodes {
-    unsigned imask, kmask;  // kmask over local z entries
-    int64_t e0, kstride;
+  // Loewdin factors of node plane j = pl (phases A and C; read again in C
+  // rather than held through B)
+  struct PlaneFactors {
     T fx[N], fz[H], my;
   };
-  auto plane_nodes = [&](PlaneNodes& Q, bool factors) {
-    const int J = cy * P.p + pl;
-    const bool jok = P.fullgrid ? true : (J > 0 && J < P.Ny - 1);
-    Q.imask = 0;
-    Q.kmask = 0;
+  auto plane_factors = [&](PlaneFactors& Q) {
+    Q.my = (T)sFc[N + pl];
 #pragma unroll
-    for (int q = 0; q < N; ++q) {
-      const int I = cx * P.p + q;
-      if (P.fullgrid || (I > 0 && I < P.Nx - 1)) Q.imask |= 1u << q;
-    }
+    for (int q = 0; q < N; ++q) Q.fx[q] = (T)sFc[q];
 #pragma unroll
-    for (int q = 0; q < H; ++q) {
-      const int K = cz * P.p + zg(q);
-      if (P.fullgrid || (K > 0 && K < P.Nz - 1)) Q.kmask |= 1u << q;
-    }
-    if (!act || !jok) Q.imask = 0;
-    if (P.fullgrid) {
-      Q.e0 = ((int64_t)cx * P.p + (int64_t)P.Nx * ((int64_t)J + (int64_t)P.Ny * cz * P.p)) * P.ld + colg;
-      Q.kstride = (int64_t)P.Nx * P.Ny * P.ld;
-    } else {
-      Q.e0 = ((int64_t)(cx * P.p - 1) + (int64_t)NxI * ((int64_t)(J - 1) + (int64_t)NyI * (cz * P.p - 1))) * P.ld +
-             colg;
-      Q.kstride = (int64_t)NxI * NyI * P.ld;
-    }
-    Q.my = (T)1;
-#pragma unroll
-    for (int q = 0; q < N; ++q) Q.fx[q] = (T)1;
-#pragma unroll
-    for (int q = 0; q < H; ++q) Q.fz[q] = (T)1;
-    if (factors && P.lowdin && Q.imask) {
-      Q.my = (T)sFc[N + pl];
-#pragma unroll
-      for (int q = 0; q < N; ++q)
-        if ((Q.imask >> q) & 1u) Q.fx[q] = (T)sFc[q];
-#pragma unroll
-      for (int q = 0; q < H; ++q)
-        if ((Q.kmask >> q) & 1u) Q.fz[q] = (T)sFc[2 * N + zg(q)];
-    }
+    for (int q = 0; q < H; ++q) Q.fz[q] = (T)sFc[2 * N + zg(q)];
   };
 
   // ---------------- A: plane j = pl, values (i, local k) ---------------------------------
   T u[N][H];  // [i][local k] gathered, then [i][c], then S B u at [x point][local z point]
   {
-    PlaneNodes Q;
-    plane_nodes(Q, false);
+    const int J = cy * P.p + pl;
+    unsigned imask = 0, kmask = 0;  // DoFs among the x nodes and the local z entries
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+      const int I = cx * P.p + q;
+      if (I > 0 && I < P.Nx - 1) imask |= 1u << q;
+    }
+#pragma unroll
+    for (int q = 0; q < H; ++q) {
+      const int K = cz * P.p + zg(q);
+      if (K > 0 && K < P.Nz - 1) kmask |= 1u << q;
+    }
+    if (!act || J <= 0 || J >= P.Ny - 1) imask = 0;
+    const int64_t e0 =
+        ((int64_t)(cx * P.p - 1) + (int64_t)NxI * ((int64_t)(J - 1) + (int64_t)NyI * (cz * P.p - 1))) * P.ld + colg;
+    const int64_t kstride = (int64_t)NxI * NyI * P.ld;
 #pragma unroll
     for (int k = 0; k < H; ++k)
 #pragma unroll
       for (int i = 0; i < N; ++i) {
-        const bool ok = ((Q.imask >> i) & (Q.kmask >> k) & 1u) != 0;
-        const int64_t e = ok ? Q.e0 + (int64_t)i * P.ld + (int64_t)zg(k) * Q.kstride : 0;
+        const bool ok = ((imask >> i) & (kmask >> k) & 1u) != 0;
+        const int64_t e = ok ? e0 + (int64_t)i * P.ld + (int64_t)zg(k) * kstride : 0;
         const T val = X[e];
         u[i][k] = ok ? val : (T)0;
       }
@@ -308,7 +287,8 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
       if (f < CPB * NFC) sF[f] = fr[k];
     }
     __syncthreads();
-    plane_nodes(Q, true);
+    PlaneFactors Q;
+    plane_factors(Q);
 #pragma unroll
     for (int k = 0; k < H; ++k)
 #pragma unroll
@@ -431,16 +411,22 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
 #pragma unroll
       for (int i = 0; i < N; ++i) hh[i][c] = o[i];
     }
-    PlaneNodes Q;
-    plane_nodes(Q, true);
+    PlaneFactors Q;
+    plane_factors(Q);
+    const CellOut<T, N, CELLS> E(Y, P, cell, cx, cy, cz, pl, colg, act);
+    // this lane's z entries run up from node 0 or down from node n-1
+    T* const e0 = E.e + (h ? (N - 1) * E.sz : 0);
+    const int64_t sz = h ? -E.sz : E.sz;
+    const bool z0 = h ? E.hiz : E.loz;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       T o[H];
       zsplit<T, N>(FS.zBt, hh[i], o);
+      if (E.jok && E.xok(i)) {
+        T* const row = e0 + i * E.sx;
 #pragma unroll
-      for (int k = 0; k < H; ++k) {
-        if (((Q.imask >> i) & (Q.kmask >> k) & 1u) != 0)
-          unsafeAtomicAdd(Y + (Q.e0 + (int64_t)i * P.ld + (int64_t)zg(k) * Q.kstride), o[k] * (Q.fx[i] * Q.fz[k] * Q.my));
+        for (int k = 0; k < H; ++k)
+          if (k > 0 || z0) E.put(row + k * sz, o[k] * (Q.fx[i] * Q.fz[k] * Q.my));
       }
     }
   }
@@ -450,7 +436,7 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
     if (t < CB) {
       double acc = 0.0;
       for (int u = 2 * t; u < THREADS; u += 2 * CB) acc += sRed[u] + sRed[u + 1];
-      if (chunk * CB + t < P.cols) P.energy[(int64_t)group * P.cols + chunk * CB + t] = acc;
+      if (chunk * CB + t < P.cols) P.energy[(int64_t)group * P.eld + chunk * CB + t] = acc;
     }
   }
 }
@@ -482,8 +468,11 @@ tdfe_status launch_pair(tdfe_ctx* c, PairParams<T>& P, int64_t* groups_out) {
   const int64_t groups = (c->n_cell + CPB - 1) / CPB;
   P.nchunks = (P.cols + CB - 1) / CB;
   if (groups_out) *groups_out = groups;
-  hipLaunchKernelGGL((pair_kernel<T, N, CB, CPB>), dim3((unsigned)(groups * P.nchunks)), dim3(2 * CPB * N * CB), 0,
-                     c->stream, P);
+  const dim3 grid((unsigned)(groups * P.nchunks)), block(2 * CPB * N * CB);
+  if (P.cells)
+    hipLaunchKernelGGL((pair_kernel<T, N, CB, CPB, true>), grid, block, 0, c->stream, P);
+  else
+    hipLaunchKernelGGL((pair_kernel<T, N, CB, CPB, false>), grid, block, 0, c->stream, P);
   TDFE_HIP(c, hipGetLastError());
   return TDFE_OK;
 }
@@ -522,8 +511,8 @@ tdfe_status launch_pair_box(tdfe_ctx* c, const ApplyArgs& a) {
   P.Ny = c->Ny;
   P.Nz = c->Nz;
   P.n_cell = c->n_cell;
-  P.lowdin = a.lowdin;
-  P.fullgrid = a.fullgrid;
+  P.eld = a.eld;
+  P.cells = a.cells;
   const int N = c->n;
   for (int i = 0; i < N; ++i) P.wq[i] = c->wq[i];
   switch (N) {

@@ -131,6 +131,46 @@ __device__ __forceinline__ int remap_block(int p, int G) {
   return x * q + min(x, r) + (p >> 3);
 }
 
+// Where a cell's results go.  CELLS: to the cell's own n^3 rows of y, every node
+// (plain stores; the consumer sums the cells, tdfe_cells.h).  Otherwise added
+// to the DoF vector y by hardware atomics, DoF nodes only.  Atomics on this
+// chip are performed beyond the per-XCD L2s at about 1.3 TB/s of values, plain
+// stores run at 5.5; see cells_fit for when the cell rows pay.
+template <typename T, int N, bool CELLS>
+struct CellOut {
+  T* e;  // node (0, j, 0) of the cell, this lane's column
+  int64_t sx, sz;
+  bool lox, hix, loz, hiz, jok;
+  template <typename Params>
+  __device__ __forceinline__ CellOut(T* Y, const Params& P, int64_t cell, int cx, int cy, int cz, int j, int colg,
+                                     bool act) {
+    lox = CELLS || cx > 0;
+    hix = CELLS || cx < P.ncx - 1;
+    loz = CELLS || cz > 0;
+    hiz = CELLS || cz < P.ncz - 1;
+    jok = act && (CELLS || ((j > 0 || cy > 0) && (j < N - 1 || cy < P.ncy - 1)));
+    if constexpr (CELLS) {
+      sx = P.cols;
+      sz = (int64_t)(N * N) * P.cols;
+      e = Y + (cell * (N * N * N) + N * j) * P.cols + colg;
+    } else {
+      const int64_t NxI = P.Nx - 2, NyI = P.Ny - 2;
+      sx = P.ld;
+      sz = NxI * NyI * P.ld;
+      e = Y + ((int64_t)(cx * P.p - 1) + NxI * ((int64_t)(cy * P.p + j - 1) + NyI * (cz * P.p - 1))) * P.ld + colg;
+    }
+  }
+  // x node i, z node k are written (i, k compile-time constants after unrolling)
+  __device__ __forceinline__ bool xok(int i) const { return (i > 0 || lox) && (i < N - 1 || hix); }
+  __device__ __forceinline__ bool zok(int k) const { return (k > 0 || loz) && (k < N - 1 || hiz); }
+  __device__ __forceinline__ void put(T* d, T v) const {
+    if constexpr (CELLS)
+      *d = v;
+    else
+      unsafeAtomicAdd(d, v);
+  }
+};
+
 // out[a] = sum_i A[a][i] in[i] by even/odd folding; A given folded (in any
 // precision, converted to T), symmetry S
 template <typename T, int N, int S, typename FT>

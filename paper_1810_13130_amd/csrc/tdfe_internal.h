@@ -13,6 +13,9 @@
 
 // one Krylov chunk holds at most this many real columns (2 per orbital)
 #define TDFE_MAX_COLS 64
+// largest buffer of per-cell operator results: the chip's memory-side cache
+// (256 MB) holds what the operator writes until its consumer reads it
+#define TDFE_CELL_BYTES ((size_t)256 << 20)
 // a soft-capped chunk runs only with a cap of at least this many vectors and
 // at least twice the largest Krylov dimension seen
 #define TDFE_SOFT_CAP_MIN 32
@@ -95,6 +98,10 @@ struct tdfe_ctx {
   double* pcgs = nullptr;     // [16] CG scalars (rz, rr, bb, alpha, beta, pAp)
   void* krylov = nullptr;     // (k_max+1) x [n_dof][2 chunk_orb]
   void* hq = nullptr;         // [n_dof][2 max(chunk_orb, wide_orb)] apply output
+  // per-cell results of the operator, [n_cell][n^3][columns], and their size
+  // (at most TDFE_CELL_BYTES; 0: octree meshes and p = 8)
+  void* eloc = nullptr;
+  size_t eloc_bytes = 0, cell_cap = TDFE_CELL_BYTES;
   void* half = nullptr;       // [n_dof][2 n_orb_max] predictor state (complex128)
   double* partial = nullptr;  // reduction partials
   double* partial2 = nullptr; // [128][TDFE_MAX_COLS] first level of the two-level alpha reduction
@@ -214,6 +221,9 @@ struct ApplyArgs {
   int64_t* n_blocks_out;
   const int* done_flag; // early-exit flag (device) or NULL
   bool fp32;            // x, y stored as float
+  bool overwrite;       // y = result instead of y += result (where tdfe_can_overwrite)
+  int eld;              // columns of a row of `energy` (set by the launchers)
+  bool cells;           // y holds per-cell results (set by the launchers)
   bool nonlocal;        // Hbar launches: add the Kleinman-Bylander term when projectors are set
 };
 tdfe_status tdfe_launch_apply(tdfe_ctx* c, const ApplyArgs& a);
@@ -223,6 +233,14 @@ tdfe_status tdfe_launch_apply_box(tdfe_ctx* c, const ApplyArgs& a);
 // lane-pair variant for box cells of even n (tdfe_apply_pair.hip)
 bool tdfe_pair_kernel_ok(const tdfe_ctx* c);
 tdfe_status tdfe_launch_apply_pair(tdfe_ctx* c, const ApplyArgs& a);
+// where the cell buffer c->eloc holds a launch, the plane and lane-pair
+// kernels write each cell's results there; tdfe_launch_apply sums
+// them into a.y (or stores the sums there, with a.overwrite),
+// tdfe_launch_apply_cells leaves them to the caller, who sums them where they
+// are used (tdfe_cells.h)
+bool tdfe_cells_ok(const tdfe_ctx* c, int cols, bool fp32);
+tdfe_status tdfe_launch_apply_cells(tdfe_ctx* c, const ApplyArgs& a);
+bool tdfe_can_overwrite(const tdfe_ctx* c, const ApplyArgs& a);
 // trilinear-cell variant in the same layout (tdfe_apply_curved.hip)
 bool tdfe_curved_kernel_ok(const tdfe_ctx* c, int cols, bool fp32);
 #define TDFE_VARIANT_LINE 1

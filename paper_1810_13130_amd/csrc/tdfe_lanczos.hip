@@ -34,6 +34,7 @@
 #include <chrono>
 #include <cmath>
 
+#include "tdfe_cells.h"
 #include "tdfe_cheb.h"
 #include "tdfe_internal.h"
 
@@ -262,6 +263,82 @@ __global__ void __launch_bounds__(RED_THREADS)
   block_col_sum(acc, Cp, sred, sred);
   __syncthreads();
   if (threadIdx.x < C) partial[(int64_t)bid * C + threadIdx.x] = sred[threadIdx.x];
+}
+
+// The three-term step after the four-lane operator, whose output is per cell:
+// one pass sums a DoF's contributions and takes the step,
+//   w_{j+1} = m_j (sum of the cells' s_j^2 Hbar w_j) - alpha_j s_j w_j
+//             - m_j s_{j-1} w_{j-1},      m_j = beta_{j-1} (1 and no last term for j = 0).
+// Blocks work row by row of DoFs (see tdfe_cells.h), a lane moves 16
+// bytes of a row (one FP64 or two FP32 orbitals).  Reads the cell results once (n^3 / p^3 vectors), w_j and
+// w_{j-1}, writes w_{j+1}; no operator output vector is kept, seeded or cleared.
+constexpr int CELL_BLOCKS = 2048;
+template <typename T, int W>
+__global__ void __launch_bounds__(RED_THREADS)
+    update_cells_kernel(const T* __restrict__ e, const T* __restrict__ wa, const T* __restrict__ wp,
+                        T* __restrict__ wn, int C, CellMap M, const double* alpha_j, const double* s_j,
+                        const double* m_j, const double* s_p, const int* status, double* __restrict__ partial,
+                        const int* done, SmallExp se) {
+  typedef typename CellLane<T, W>::V V;
+  constexpr int NO = W / 2;  // orbitals per lane
+  __shared__ double sred[RED_THREADS];
+  __shared__ double sorb[2 * RED_THREADS / 4];
+  if (*done) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) post_progress(se.progress, se.gen, se.k - 1);
+  if ((int)blockIdx.x < se.nblk) {
+    small_exp_block(se);
+    return;
+  }
+  const int bid = (int)blockIdx.x - se.nblk;
+  const int C2 = C / W;
+  const int Op = C2 <= 4 ? 4 : (C2 <= 8 ? 8 : (C2 <= 16 ? 16 : 32));
+  const int XL = RED_THREADS / Op;
+  const int o = (int)threadIdx.x % Op;
+  const int xl = (int)threadIdx.x / Op;
+  double acc[NO];
+#pragma unroll
+  for (int q = 0; q < NO; ++q) acc[q] = 0.0;
+  if (o < C2) {
+    double ca[NO], cm[NO], cb[NO];
+#pragma unroll
+    for (int q = 0; q < NO; ++q) {
+      const int oo = o * NO + q;
+      const bool live = status[oo] == 0;
+      ca[q] = live ? alpha_j[oo] * s_j[oo] : 0.0;
+      cm[q] = live ? (m_j ? m_j[oo] : 1.0) : 0.0;
+      cb[q] = live && wp ? m_j[oo] * s_p[oo] : 0.0;
+    }
+    const int nrows = M.NyI * M.NzI;
+    for (int r = bid; r < nrows; r += CELL_BLOCKS) {
+      const CellRow R = cell_row(M, 1 + r % M.NyI, 1 + r / M.NyI);
+      for (int I = xl; I < M.NxI; I += XL) {
+        CellLane<T, W> L;
+        L.at(M, I);
+        const int64_t d = ((int64_t)r * M.NxI + I) * C2 + o;
+        const V a = __builtin_nontemporal_load((const V*)wa + d);
+        V b = (V)0;
+        if (wp) b = __builtin_nontemporal_load((const V*)wp + d);
+        double h[W];
+        L.sum(e, R, C, o, h);
+        V w;
+#pragma unroll
+        for (int q = 0; q < W; ++q) {
+          w[q] = (T)(cm[q / 2] * h[q] - ca[q / 2] * (double)a[q] - cb[q / 2] * (double)b[q]);
+          acc[q / 2] += (double)w[q] * (double)w[q];
+        }
+        __builtin_nontemporal_store(w, (V*)wn + d);
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < NO; ++q) {
+    block_col_sum(acc[q], Op, sred, sred);
+    __syncthreads();
+    if (threadIdx.x < C2) sorb[threadIdx.x * NO + q] = sred[threadIdx.x];
+    __syncthreads();
+  }
+  // the consumers sum column pairs: the orbital's sum in its even column
+  if (threadIdx.x < C) partial[(int64_t)bid * C + threadIdx.x] = (threadIdx.x & 1) ? 0.0 : sorb[threadIdx.x >> 1];
 }
 
 // out[o] = f( sum_b partial[b][2o] + partial[b][2o+1] ), one block per orbital, fixed order.
@@ -590,8 +667,13 @@ tdfe_status run_chunk(tdfe_ctx* c, const void* vw, const double* in, double* out
   // estimate below a small multiple of that (times ||psibar||) buys nothing
   const double tol_rel = sizeof(T) == 4 ? TDFE_MIXED_TOL_FLOOR : 0.0;
 
+  // per-cell operator output summed by the update itself (the nonlocal term
+  // adds to an assembled vector)
+  const bool cells = c->n_proj == 0 && tdfe_cells_ok(c, C, sizeof(T) == 4);
+  const int red_blocks = cells ? CELL_BLOCKS : RED_BLOCKS;  // rows of the update's norm partials
+  const CellMap map{c->ncx, c->ncy, c->ncz, c->p, c->Nx - 2, c->Ny - 2, c->Nz - 2};
   hipLaunchKernelGGL(init_scal_kernel, dim3(1), dim3(64), 0, c->stream, S, Nc);
-  TDFE_TRY(tdfe_zero(c, Hq, (size_t)vstride * sizeof(T)));
+  if (!cells) TDFE_TRY(tdfe_zero(c, Hq, (size_t)vstride * sizeof(T)));
   TDFE_TRY(tdfe_zero(c, err_flag, sizeof(int)));
   hipLaunchKernelGGL((copy_in_kernel<T>), dim3(RED_BLOCKS), dim3(RED_THREADS), 0, c->stream, in, ld, 2 * o0, W, C, nd,
                      c->partial);
@@ -636,7 +718,7 @@ tdfe_status run_chunk(tdfe_ctx* c, const void* vw, const double* in, double* out
     a.n_blocks_out = &groups;
     a.done_flag = S.done;
     a.fp32 = sizeof(T) == 4;
-    TDFE_TRY(tdfe_launch_apply(c, a));
+    TDFE_TRY(cells ? tdfe_launch_apply_cells(c, a) : tdfe_launch_apply(c, a));
     // m = beta_{k-2} for k >= 2 (the operator input was scaled by s^2, not s), 1 for k = 1
     const double* m = k >= 2 ? S.beta + (size_t)(k - 2) * Nc : (const double*)nullptr;
     if (groups > 64 * ALPHA_SLICES) {
@@ -653,17 +735,34 @@ tdfe_status run_chunk(tdfe_ctx* c, const void* vw, const double* in, double* out
                          S.alpha + (size_t)(k - 1) * Nc, 0, (double*)nullptr, (double*)nullptr, m, (const int*)S.done);
     }
     SmallExp se{S, Nc, k, K, k <= CHK_THREADS ? Nc : 0, tau, c->jtab, dprog, gen};
-    hipLaunchKernelGGL((update_kernel<T>), dim3(RED_BLOCKS + se.nblk), dim3(RED_THREADS), 0, c->stream, Hq,
+    if (cells) {
+      auto update = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(CELL_BLOCKS + se.nblk), dim3(RED_THREADS), 0, c->stream, (const T*)c->eloc,
+                           (const T*)wk, k >= 2 ? (const T*)(wk - vstride) : (const T*)nullptr,
+                           W + (int64_t)k * vstride, C, map, (const double*)(S.alpha + (size_t)(k - 1) * Nc),
+                           (const double*)(S.scale + (size_t)(k - 1) * Nc), m,
+                           (const double*)(S.scale + (size_t)(k >= 2 ? k - 2 : 0) * Nc), (const int*)S.status,
+                           c->partial, (const int*)S.done, se);
+      };
+      // 16 bytes per lane where the columns allow it
+      constexpr int WIDE = sizeof(T) == 4 ? 4 : 2;
+      if (C % WIDE == 0)
+        update(update_cells_kernel<T, WIDE>);
+      else
+        update(update_cells_kernel<T, 2>);
+    } else {
+        hipLaunchKernelGGL((update_kernel<T>), dim3(RED_BLOCKS + se.nblk), dim3(RED_THREADS), 0, c->stream, Hq,
                        (const T*)wk, W + (int64_t)k * vstride, C, nd, (const double*)(S.alpha + (size_t)(k - 1) * Nc),
                        (const double*)(S.scale + (size_t)(k - 1) * Nc), m, (const int*)S.status, c->partial,
                        (const int*)S.done, se);
+    }
     // beta_k, the scale 1/beta_k of the next basis vector and the stop test
     if (k <= CHK_THREADS) {
       hipLaunchKernelGGL(beta_check_kernel, dim3(Nc), dim3(RED_THREADS), 0, c->stream, (const double*)c->partial,
-                         (int64_t)RED_BLOCKS, C, S, Nc, k, K, Kc, tau, tol, tol_rel, err_flag, dflag, gen);
+                         (int64_t)red_blocks, C, S, Nc, k, K, Kc, tau, tol, tol_rel, err_flag, dflag, gen);
     } else {
       hipLaunchKernelGGL(finalize_pairs_kernel, dim3(Nc), dim3(RED_THREADS), 0, c->stream, c->partial,
-                         (int64_t)RED_BLOCKS, C, S.beta + (size_t)(k - 1) * Nc, 3, S.scale + (size_t)k * Nc,
+                         (int64_t)red_blocks, C, S.beta + (size_t)(k - 1) * Nc, 3, S.scale + (size_t)k * Nc,
                          S.cs + (size_t)k * Nc, (const double*)nullptr, (const int*)S.done);
       hipLaunchKernelGGL(check_kernel, dim3(Nc), dim3(CHK_THREADS), 0, c->stream, S, Nc, k, K, Kc, tau, tol, tol_rel,
                          err_flag, dflag, gen, c->jtab);
@@ -1046,7 +1145,6 @@ static tdfe_status apply_checked(tdfe_ctx* c, const void* dev_psibar, void* dev_
   if (!c->bound) return tdfe_fail(c, TDFE_ESTATE, "apply_H before bind_workspace");
   if (!c->have_potential) return tdfe_fail(c, TDFE_ESTATE, "apply_H before set_potential");
   const int cols = 2 * n_orb;
-  if (zero) TDFE_TRY(tdfe_zero(c, dev_out, (size_t)c->n_dof * cols * sizeof(double)));
   ApplyArgs a{};
   a.x = dev_psibar;
   a.y = dev_out;
@@ -1057,6 +1155,8 @@ static tdfe_status apply_checked(tdfe_ctx* c, const void* dev_psibar, void* dev_
   a.lowdin = true;
   a.nonlocal = true;
   a.fp32 = false;
+  a.overwrite = zero && tdfe_can_overwrite(c, a);
+  if (zero && !a.overwrite) TDFE_TRY(tdfe_zero(c, dev_out, (size_t)c->n_dof * cols * sizeof(double)));
   return tdfe_launch_apply(c, a);
 }
 

@@ -212,6 +212,11 @@ void carve(tdfe_ctx* c, char* base) {
   const int cols = 2 * std::max(c->chunk_orb, c->wide_orb);  // widest chunk's columns
   c->krylov = k.take<char>((size_t)(c->k_max + 1) * nd * 2 * c->chunk_orb * elem_bytes(c));
   c->hq = k.take<char>((size_t)nd * cols * elem_bytes(c));
+  const size_t evol = (size_t)ne * c->n * c->n * c->n;
+  c->eloc_bytes = c->octree || c->n > 8
+                      ? 0
+                      : std::min(evol * 2 * std::max(c->n_orb_max, c->wide_orb) * sizeof(double), c->cell_cap);
+  c->eloc = c->eloc_bytes ? (void*)k.take<char>(c->eloc_bytes) : nullptr;
   c->half = k.take<double>((size_t)nd * 2 * c->n_orb_max);
   // block partials of the operator kernels, plus rows appended after them (the nonlocal term's)
   c->n_partial = (std::max<int64_t>(ne, 4096) + 8) * std::max(cols, 8);
@@ -266,6 +271,9 @@ void init_variant(tdfe_ctx* c) {
   if (v && std::strcmp(v, "line") == 0) c->variant = TDFE_VARIANT_LINE;
   if (v && std::strcmp(v, "pair") == 0) c->variant = TDFE_VARIANT_PAIR;
   if (v && std::strcmp(v, "plane") == 0) c->variant = TDFE_VARIANT_PLANE;
+  // a smaller cell buffer (tests: column slices, or 0 for the scatter)
+  const char* b = std::getenv("TDFE_CELL_BUFFER_BYTES");
+  if (b) c->cell_cap = (size_t)std::min<unsigned long long>(std::strtoull(b, nullptr, 10), TDFE_CELL_BYTES);
 }
 
 // Krylov chunk: as many orbitals as fit in 60% of the device memory free at

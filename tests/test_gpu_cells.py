@@ -1,0 +1,83 @@
+"""The operator's two output forms against the oracle.
+
+Per-cell results (summed by their consumer) and the atomic scatter are the
+same operator: TDFE_CELL_BUFFER_BYTES = 0 forces the scatter, a small value
+makes a launch go through the cell buffer in slices of 16 columns.  Column
+counts sit at and around the 16-column passes of the four-lane kernel (p = 6
+FP64, p = 7) and below the 9 columns it starts at.  Bars: 1e-12 (FP64) and
+2e-6 (FP32) relative, as for every operator kernel here; 1e-10 for the
+exponential.
+"""
+import numpy as np
+import pytest
+
+import workloads as W
+from gpu_util import gpu_context, oracle_mesh, rel
+from oracle import lanczos, operators as op
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+MESH = {"box": 2, "graded": 3}
+
+
+def _cfg(mesh, p, n_orb, nc=(3, 2, 3)):
+    return W.scaled(W.CONFIGS[MESH[mesh]], ncell=nc, p=p, n_orb=n_orb)
+
+
+def _cap(monkeypatch, cfg, cap):
+    """None: as shipped; "scatter": no buffer; "slices": 16 FP64 columns fit."""
+    if cap == "scatter":
+        monkeypatch.setenv("TDFE_CELL_BUFFER_BYTES", "0")
+    elif cap == "slices":
+        monkeypatch.setenv("TDFE_CELL_BUFFER_BYTES", str(int(np.prod(cfg.ncell)) * (cfg.p + 1) ** 3 * 16 * 8))
+
+
+@pytest.mark.parametrize("cap", [None, "scatter", "slices"])
+@pytest.mark.parametrize("mesh,p,n_orb", [("box", 6, 5), ("box", 7, 8), ("graded", 6, 8), ("graded", 6, 9),
+                                          ("graded", 7, 17), ("box", 5, 19), ("graded", 4, 3), ("box", 1, 1)])
+def test_operator_output_forms(mesh, p, n_orb, cap, monkeypatch):
+    cfg = _cfg(mesh, p, n_orb)
+    _cap(monkeypatch, cfg, cap)
+    ctx = gpu_context(cfg, n_orb=n_orb, k_max=4)
+    m, vq = oracle_mesh(cfg)
+    x = W.random_block(m.n_dof, n_orb, 60 + p)
+    ref = op.apply_Hbar(m, vq, x)
+    xd = torch.from_numpy(x).cuda()
+    assert rel(ctx.apply_H(xd).cpu().numpy(), ref) < 1e-12
+    y0 = W.random_block(m.n_dof, n_orb, 61)
+    y = torch.from_numpy(y0).cuda()
+    ctx.apply_H_add(xd, y)
+    assert np.abs(y.cpu().numpy() - y0 - ref).max() < 1e-12 * max(np.abs(ref).max(), np.abs(y0).max())
+    ctx.close()
+
+
+@pytest.mark.parametrize("cap", [None, "scatter"])
+@pytest.mark.parametrize("mesh,p,n_orb", [("box", 7, 7), ("graded", 7, 9), ("graded", 6, 6), ("box", 5, 3)])
+def test_fp32_operator_output_forms(mesh, p, n_orb, cap, monkeypatch):
+    cfg = _cfg(mesh, p, n_orb)
+    _cap(monkeypatch, cfg, cap)
+    ctx = gpu_context(cfg, n_orb=n_orb, k_max=4, precision=1)
+    m, vq = oracle_mesh(cfg)
+    x = W.random_block(m.n_dof, n_orb, 70 + p)
+    y = torch.zeros((m.n_dof, n_orb), dtype=torch.complex64, device="cuda")
+    ctx.apply_H_add_f32(torch.from_numpy(x.astype(np.complex64)).cuda(), y)
+    assert rel(y.cpu().numpy(), op.apply_Hbar(m, vq, x)) < 2e-6
+    ctx.close()
+
+
+@pytest.mark.parametrize("cap", [None, "scatter"])
+@pytest.mark.parametrize("mesh,p,n_orb", [("box", 3, 1), ("box", 6, 6), ("graded", 6, 8), ("graded", 7, 5)])
+def test_exponential_with_both_output_forms(mesh, p, n_orb, cap, monkeypatch):
+    cfg = _cfg(mesh, p, n_orb, nc=(3, 3, 2))
+    _cap(monkeypatch, cfg, cap)
+    ctx = gpu_context(cfg, n_orb=n_orb, k_max=96)
+    m, vq = oracle_mesh(cfg)
+    x = W.random_block(m.n_dof, n_orb, 80 + p)
+    x /= np.linalg.norm(x, axis=0)
+    psi = torch.from_numpy(x).cuda()
+    ctx.lanczos_expm(psi, 0.02, 1e-12)
+    ref = lanczos.lanczos_expm(lambda z: op.apply_Hbar(m, vq, z), x, 0.02, 1e-12, 96)
+    ref = ref[0] if isinstance(ref, tuple) else ref
+    assert np.abs(psi.cpu().numpy() - ref).max() < 1e-10
+    ctx.close()
