@@ -646,7 +646,7 @@ int64_t tdfe_blocks_apply(const tdfe_ctx* c, int cols) {
   return c->n_cell;
 }
 
-// Launches of the plane and lane-pair kernels: Loewdin DoF vectors,
+// Launches of the plane, lane-pair and four-lane kernels: Loewdin DoF vectors,
 // p <= 7; two or more columns on trilinear cells (one column leaves n threads
 // per cell with the metric staged for the whole cell: the line kernel is
 // faster there, 0.64 ms against 2.2 ms for the Hartree solve's one-column
@@ -658,9 +658,10 @@ static bool block_kernels_ok(const tdfe_ctx* c, const ApplyArgs& a) {
 
 static tdfe_status launch_blocks(tdfe_ctx* c, const ApplyArgs& a) {
   // default policy, from measurements on the benchmark and graded workloads:
-  // box cells: the
+  // the four-lane kernel where tdfe_quad_kernel_ok says; box cells: the
   // lane-pair kernel for FP64 at even n (two waves per SIMD), the plane kernel
   // otherwise; trilinear cells: see tdfe_launch_apply_curved
+  if (tdfe_quad_kernel_ok(c, a)) return tdfe_launch_apply_quad(c, a);
   if (!c->box) return tdfe_launch_apply_curved(c, a);
   const bool pair = c->variant == TDFE_VARIANT_PAIR || (c->variant == 0 && !a.fp32);
   if (pair && tdfe_pair_kernel_ok(c)) return tdfe_launch_apply_pair(c, a);

@@ -233,8 +233,12 @@ tdfe_status tdfe_launch_apply_box(tdfe_ctx* c, const ApplyArgs& a);
 // lane-pair variant for box cells of even n (tdfe_apply_pair.hip)
 bool tdfe_pair_kernel_ok(const tdfe_ctx* c);
 tdfe_status tdfe_launch_apply_pair(tdfe_ctx* c, const ApplyArgs& a);
-// where the cell buffer c->eloc holds a launch, the plane and lane-pair
-// kernels write each cell's results there; tdfe_launch_apply sums
+// four-lane variant for box and trilinear cells, blocks of more than 8 columns
+// (tdfe_apply_quad.hip)
+bool tdfe_quad_kernel_ok(const tdfe_ctx* c, const ApplyArgs& a);
+tdfe_status tdfe_launch_apply_quad(tdfe_ctx* c, const ApplyArgs& a);
+// where the cell buffer c->eloc holds a launch, the plane, lane-pair and
+// four-lane kernels write each cell's results there; tdfe_launch_apply sums
 // them into a.y (or stores the sums there, with a.overwrite),
 // tdfe_launch_apply_cells leaves them to the caller, who sums them where they
 // are used (tdfe_cells.h)

@@ -1,4 +1,4 @@
-"""The operator's two output forms against the oracle.
+"""The operator's two output forms and the four-lane kernel against the oracle.
 
 Per-cell results (summed by their consumer) and the atomic scatter are the
 same operator: TDFE_CELL_BUFFER_BYTES = 0 forces the scatter, a small value
