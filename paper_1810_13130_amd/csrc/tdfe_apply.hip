@@ -13,27 +13,21 @@
 // from the 8 cell corners and couple the three gradient components.
 // The element results are added into the output with FP64/FP32 atomics
 // (hardware global_atomic_add), after the M^-1/2 scaling of the Loewdin
-// form (Eq. TDKSMatVecStandard).  The quadratic form u^T H u of every
+// form (Eq. TDKSMatVecStandard).  What bounds the one-column launches (the
+// Hartree solve's): FP64 issue, of which the metric was two thirds, and the
+// atomics' 64-byte segments.  24^3 trilinear cells, p = 6: 215 -> 96 us per
+// product with the metric formed per line, folded tables and z as the last
+// contraction.  The quadratic form u^T H u of every
 // column is accumulated from the quadrature-point fluxes and reduced per
 // workgroup; it equals Re<x, Hbar x> and feeds the Lanczos alpha.
 #include "tdfe_cells.h"
-#include "tdfe_rule1d.h"
+#include "tdfe_fold.h"
 
 namespace {
 
 template <typename T>
 __device__ __forceinline__ void atomic_add(T* p, T v) {
   unsafeAtomicAdd(p, v);
-}
-
-// logical block of physical block p in a grid of G: the dispatcher hands
-// blocks to the 8 XCDs round robin (block p to XCD p mod 8), and XCD x takes
-// the contiguous logical range starting at x q + min(x, r) (q = G / 8,
-// r = G mod 8; q + 1 blocks for x < r), so that neighbouring cells, which
-// share nodes, run under one L2
-__device__ __forceinline__ int remap_block(int p, int G) {
-  const int q = G >> 3, r = G & 7, x = p & 7;
-  return x * q + min(x, r) + (p >> 3);
 }
 
 template <int N, int CB, int CPB, int GEOM>
@@ -110,6 +104,56 @@ __device__ __forceinline__ void metric_at(const double* C, double xa, double xb,
   g[5] = s * (A[2][0] * A[2][0] + A[2][1] * A[2][1] + A[2][2] * A[2][2]);
 }
 
+// The Jacobian along an x line of a trilinear cell: its xi column is constant
+// there, the eta and zeta columns are linear in xi.  A thread that owns the
+// line forms these five vectors once and each point's columns by six
+// multiply-adds (metric_at from the corners takes about 130 operations more).
+struct LineJac {
+  double x[3], y0[3], y1[3], z0[3], z1[3];
+};
+__device__ __forceinline__ LineJac line_jacobian(const double* C, double xb, double xc) {
+  const double fy[2] = {0.5 * (1 - xb), 0.5 * (1 + xb)}, fz[2] = {0.5 * (1 - xc), 0.5 * (1 + xc)};
+  LineJac L;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    auto X = [&](int vx, int vy, int vz) { return C[((vz * 2 + vy) * 2 + vx) * 3 + d]; };
+    double sx = 0.0, ey[2], ez[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      sx += fz[u] * (fy[0] * (X(1, 0, u) - X(0, 0, u)) + fy[1] * (X(1, 1, u) - X(0, 1, u)));
+      ey[u] = 0.5 * (fz[0] * (X(u, 1, 0) - X(u, 0, 0)) + fz[1] * (X(u, 1, 1) - X(u, 0, 1)));
+      ez[u] = 0.5 * (fy[0] * (X(u, 0, 1) - X(u, 0, 0)) + fy[1] * (X(u, 1, 1) - X(u, 1, 0)));
+    }
+    L.x[d] = 0.5 * sx;
+    L.y0[d] = 0.5 * (ey[0] + ey[1]);
+    L.y1[d] = 0.5 * (ey[1] - ey[0]);
+    L.z0[d] = 0.5 * (ez[0] + ez[1]);
+    L.z1[d] = 0.5 * (ez[1] - ez[0]);
+  }
+  return L;
+}
+// w detJ J^-1 J^-T at xi = xa of the line
+__device__ __forceinline__ void line_metric(const LineJac& L, double xa, double w, double g[6]) {
+  double y[3], z[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    y[d] = L.y0[d] + xa * L.y1[d];
+    z[d] = L.z0[d] + xa * L.z1[d];
+  }
+  const double* x = L.x;
+  // rows of the adjugate: cross products of the columns
+  const double a0[3] = {y[1] * z[2] - y[2] * z[1], y[2] * z[0] - y[0] * z[2], y[0] * z[1] - y[1] * z[0]};
+  const double a1[3] = {z[1] * x[2] - z[2] * x[1], z[2] * x[0] - z[0] * x[2], z[0] * x[1] - z[1] * x[0]};
+  const double a2[3] = {x[1] * y[2] - x[2] * y[1], x[2] * y[0] - x[0] * y[2], x[0] * y[1] - x[1] * y[0]};
+  const double s = w / (x[0] * a0[0] + x[1] * a0[1] + x[2] * a0[2]);
+  g[0] = s * (a0[0] * a0[0] + a0[1] * a0[1] + a0[2] * a0[2]);
+  g[1] = s * (a0[0] * a1[0] + a0[1] * a1[1] + a0[2] * a1[2]);
+  g[2] = s * (a0[0] * a2[0] + a0[1] * a2[1] + a0[2] * a2[2]);
+  g[3] = s * (a1[0] * a1[0] + a1[1] * a1[1] + a1[2] * a1[2]);
+  g[4] = s * (a1[0] * a2[0] + a1[1] * a2[1] + a1[2] * a2[2]);
+  g[5] = s * (a2[0] * a2[0] + a2[1] * a2[1] + a2[2] * a2[2]);
+}
+
 template <typename T, int N, int CB, int CPB, int GEOM>
 __global__ void __launch_bounds__(CPB * N * N * CB)
     apply_kernel(KParams P) {
@@ -131,6 +175,7 @@ __global__ void __launch_bounds__(CPB * N * N * CB)
   // 1D tables as compile-time constants (the weights and Gauss points, read
   // with per-thread indices, stay in LDS)
   constexpr tdfe1d::Rule R = tdfe1d::make_rule(N - 1);
+  constexpr FoldSet<N> FS = make_foldset<N>();
   __shared__ double sRed[S::THREADS];
 
   if (P.done && *P.done) return;
@@ -238,13 +283,9 @@ __global__ void __launch_bounds__(CPB * N * N * CB)
 #pragma unroll
     for (int k = 0; k < N; ++k)
       r1[k] = ((gmask >> k) & 1u) ? gx1[k] * (P.lowdin ? gm1[k] * cs : cs) : (T)0;
+    eo<T, N, 1>(FS.B, r1, r2);
 #pragma unroll
-    for (int c = 0; c < N; ++c) {
-      T s = 0;
-#pragma unroll
-      for (int k = 0; k < N; ++k) s += (T)R.B[c * tdfe1d::MAXN + k] * r1[k];
-      sU[lidx<N, CB>(slot, c, j, i, col)] = s;
-    }
+    for (int c = 0; c < N; ++c) sU[lidx<N, CB>(slot, c, j, i, col)] = r2[c];
   }
   __syncthreads();
   // ---- F2: interpolate in y -------------------------------------------------------
@@ -252,13 +293,9 @@ __global__ void __launch_bounds__(CPB * N * N * CB)
     const int i = line % N, c = line / N;
 #pragma unroll
     for (int j = 0; j < N; ++j) r1[j] = sU[lidx<N, CB>(slot, c, j, i, col)];
+    eo<T, N, 1>(FS.B, r1, r2);
 #pragma unroll
-    for (int b = 0; b < N; ++b) {
-      T s = 0;
-#pragma unroll
-      for (int j = 0; j < N; ++j) s += (T)R.B[b * tdfe1d::MAXN + j] * r1[j];
-      sU[lidx<N, CB>(slot, c, b, i, col)] = s;
-    }
+    for (int b = 0; b < N; ++b) sU[lidx<N, CB>(slot, c, b, i, col)] = r2[b];
   }
   __syncthreads();
   // ---- F3: interpolate in x; x-direction flux (box) or x-derivative (curved) -------------
@@ -275,22 +312,9 @@ __global__ void __launch_bounds__(CPB * N * N * CB)
     const int b = line % N, c = line / N;
 #pragma unroll
     for (int i = 0; i < N; ++i) r1[i] = sU[lidx<N, CB>(slot, c, b, i, col)];
-    T uq[N];
-#pragma unroll
-    for (int a = 0; a < N; ++a) {
-      T s = 0;
-#pragma unroll
-      for (int i = 0; i < N; ++i) s += (T)R.B[a * tdfe1d::MAXN + i] * r1[i];
-      uq[a] = s;
-    }
-    T du[N];
-#pragma unroll
-    for (int a = 0; a < N; ++a) {
-      T s = 0;
-#pragma unroll
-      for (int q = 0; q < N; ++q) s += (T)R.Dg[a * tdfe1d::MAXN + q] * uq[q];
-      du[a] = s;
-    }
+    T uq[N], du[N];
+    eo<T, N, 1>(FS.B, r1, uq);
+    eo<T, N, -1>(FS.G, uq, du);
     if constexpr (!GEOM) {
       T pot[N], f[N];
 #pragma unroll
@@ -300,13 +324,11 @@ __global__ void __launch_bounds__(CPB * N * N * CB)
         f[a] = (T)gx * sW3[q] * du[a];
         energy += (double)f[a] * (double)du[a] + (double)pot[a] * (double)uq[a];
       }
+      eo<T, N, -1>(FS.Gt, f, r2);
 #pragma unroll
       for (int a = 0; a < N; ++a) {
-        T s = pot[a];
-#pragma unroll
-        for (int q = 0; q < N; ++q) s += (T)R.Dg[q * tdfe1d::MAXN + a] * f[q];
         sU[lidx<N, CB>(slot, c, b, a, col)] = uq[a];
-        sR[lidx<N, CB>(slot, c, b, a, col)] = s;
+        sR[lidx<N, CB>(slot, c, b, a, col)] = pot[a] + r2[a];
       }
     } else {
 #pragma unroll
@@ -319,33 +341,7 @@ __global__ void __launch_bounds__(CPB * N * N * CB)
   __syncthreads();
 
   if constexpr (!GEOM) {
-    // ---- F4: y-direction flux -----------------------------------------------------
-    {
-      const int a = line % N, c = line / N;
-#pragma unroll
-      for (int b = 0; b < N; ++b) {
-        r1[b] = sU[lidx<N, CB>(slot, c, b, a, col)];
-        r2[b] = sR[lidx<N, CB>(slot, c, b, a, col)];
-      }
-      T f[N];
-#pragma unroll
-      for (int b = 0; b < N; ++b) {
-        T s = 0;
-#pragma unroll
-        for (int q = 0; q < N; ++q) s += (T)R.Dg[b * tdfe1d::MAXN + q] * r1[q];
-        f[b] = (T)gy * sW3[a + N * (b + N * c)] * s;
-        energy += (double)f[b] * (double)s;
-      }
-#pragma unroll
-      for (int b = 0; b < N; ++b) {
-        T s = r2[b];
-#pragma unroll
-        for (int q = 0; q < N; ++q) s += (T)R.Dg[q * tdfe1d::MAXN + b] * f[q];
-        sR[lidx<N, CB>(slot, c, b, a, col)] = s;
-      }
-    }
-    __syncthreads();
-    // ---- F5: z-direction flux, then B^T in z ------------------------------------------
+    // ---- F4: z-direction flux -----------------------------------------------------
     {
       const int a = line % N, b = line / N;
 #pragma unroll
@@ -353,29 +349,39 @@ __global__ void __launch_bounds__(CPB * N * N * CB)
         r1[c] = sU[lidx<N, CB>(slot, c, b, a, col)];
         r2[c] = sR[lidx<N, CB>(slot, c, b, a, col)];
       }
-      T f[N];
+      T f[N], d[N];
+      eo<T, N, -1>(FS.G, r1, d);
 #pragma unroll
       for (int c = 0; c < N; ++c) {
-        T s = 0;
-#pragma unroll
-        for (int q = 0; q < N; ++q) s += (T)R.Dg[c * tdfe1d::MAXN + q] * r1[q];
-        f[c] = (T)gz * sW3[a + N * (b + N * c)] * s;
-        energy += (double)f[c] * (double)s;
+        f[c] = (T)gz * sW3[a + N * (b + N * c)] * d[c];
+        energy += (double)f[c] * (double)d[c];
       }
+      eo<T, N, -1>(FS.Gt, f, d);
 #pragma unroll
-      for (int c = 0; c < N; ++c) {
-        T s = r2[c];
+      for (int c = 0; c < N; ++c) sR[lidx<N, CB>(slot, c, b, a, col)] = r2[c] + d[c];
+    }
+    __syncthreads();
+    // ---- F5: y-direction flux, then B^T in y ------------------------------------------
+    {
+      const int a = line % N, c = line / N;
 #pragma unroll
-        for (int q = 0; q < N; ++q) s += (T)R.Dg[q * tdfe1d::MAXN + c] * f[q];
-        r1[c] = s;
+      for (int b = 0; b < N; ++b) {
+        r1[b] = sU[lidx<N, CB>(slot, c, b, a, col)];
+        r2[b] = sR[lidx<N, CB>(slot, c, b, a, col)];
       }
+      T f[N], d[N];
+      eo<T, N, -1>(FS.G, r1, d);
 #pragma unroll
-      for (int k = 0; k < N; ++k) {
-        T s = 0;
-#pragma unroll
-        for (int c = 0; c < N; ++c) s += (T)R.B[c * tdfe1d::MAXN + k] * r1[c];
-        sR[lidx<N, CB>(slot, k, b, a, col)] = s;
+      for (int b = 0; b < N; ++b) {
+        f[b] = (T)gy * sW3[a + N * (b + N * c)] * d[b];
+        energy += (double)f[b] * (double)d[b];
       }
+      eo<T, N, -1>(FS.Gt, f, d);
+#pragma unroll
+      for (int b = 0; b < N; ++b) r1[b] = r2[b] + d[b];
+      eo<T, N, 1>(FS.Bt, r1, r2);
+#pragma unroll
+      for (int j = 0; j < N; ++j) sR[lidx<N, CB>(slot, c, j, a, col)] = r2[j];
     }
     __syncthreads();
   } else {
@@ -384,31 +390,25 @@ __global__ void __launch_bounds__(CPB * N * N * CB)
       const int a = line % N, c = line / N;
 #pragma unroll
       for (int b = 0; b < N; ++b) r1[b] = sU[lidx<N, CB>(slot, c, b, a, col)];
+      eo<T, N, -1>(FS.G, r1, r2);
 #pragma unroll
-      for (int b = 0; b < N; ++b) {
-        T s = 0;
-#pragma unroll
-        for (int q = 0; q < N; ++q) s += (T)R.Dg[b * tdfe1d::MAXN + q] * r1[q];
-        sGY[lidx<N, CB>(slot, c, b, a, col)] = s;
-      }
+      for (int b = 0; b < N; ++b) sGY[lidx<N, CB>(slot, c, b, a, col)] = r2[b];
     }
     {
       const int a = line % N, b = line / N;
 #pragma unroll
       for (int c = 0; c < N; ++c) r1[c] = sU[lidx<N, CB>(slot, c, b, a, col)];
+      eo<T, N, -1>(FS.G, r1, r2);
 #pragma unroll
-      for (int c = 0; c < N; ++c) {
-        T s = 0;
-#pragma unroll
-        for (int q = 0; q < N; ++q) s += (T)R.Dg[c * tdfe1d::MAXN + q] * r1[q];
-        sGZ[lidx<N, CB>(slot, c, b, a, col)] = s;
-      }
+      for (int c = 0; c < N; ++c) sGZ[lidx<N, CB>(slot, c, b, a, col)] = r2[c];
     }
     __syncthreads();
     // ---- P: pointwise fluxes, x-part of the transposed derivative --------------------
     {
       const int b = line % N, c = line / N;
       T fx[N], pot[N];
+      LineJac J;
+      if constexpr (GREG) J = line_jacobian(sCor + slot * 24, sEta[b], sEta[c]);
 #pragma unroll
       for (int a = 0; a < N; ++a) {
         const int q = a + N * (b + N * c);
@@ -418,7 +418,7 @@ __global__ void __launch_bounds__(CPB * N * N * CB)
         const T* g = gr;
         if constexpr (GREG) {
           double gd[6] = {0, 0, 0, 0, 0, 0};
-          if (cell_ok) metric_at(sCor + slot * 24, sEta[a], sEta[b], sEta[c], (double)sW3[q], gd);
+          if (cell_ok) line_metric(J, R.eta[a], (double)sW3[q], gd);
 #pragma unroll
           for (int w6 = 0; w6 < 6; ++w6) gr[w6] = (T)gd[w6];
         } else {
@@ -434,88 +434,67 @@ __global__ void __launch_bounds__(CPB * N * N * CB)
         sGY[li] = ffy;
         sGZ[li] = ffz;
       }
+      eo<T, N, -1>(FS.Gt, fx, r1);
 #pragma unroll
-      for (int a = 0; a < N; ++a) {
-        T s = pot[a];
-#pragma unroll
-        for (int q = 0; q < N; ++q) s += (T)R.Dg[q * tdfe1d::MAXN + a] * fx[q];
-        sU[lidx<N, CB>(slot, c, b, a, col)] = s;
-      }
+      for (int a = 0; a < N; ++a) sU[lidx<N, CB>(slot, c, b, a, col)] = pot[a] + r1[a];
     }
     __syncthreads();
-    // ---- B1: y-part of the transposed derivative -----------------------------------
-    {
-      const int a = line % N, c = line / N;
-#pragma unroll
-      for (int b = 0; b < N; ++b) {
-        r1[b] = sU[lidx<N, CB>(slot, c, b, a, col)];
-        r2[b] = sGY[lidx<N, CB>(slot, c, b, a, col)];
-      }
-#pragma unroll
-      for (int b = 0; b < N; ++b) {
-        T s = r1[b];
-#pragma unroll
-        for (int q = 0; q < N; ++q) s += (T)R.Dg[q * tdfe1d::MAXN + b] * r2[q];
-        sU[lidx<N, CB>(slot, c, b, a, col)] = s;
-      }
-    }
-    __syncthreads();
-    // ---- B2: z-part of the transposed derivative, then B^T in z --------------------------
+    // ---- B1: z-part of the transposed derivative -----------------------------------
     {
       const int a = line % N, b = line / N;
+      T d[N];
 #pragma unroll
       for (int c = 0; c < N; ++c) {
         r1[c] = sU[lidx<N, CB>(slot, c, b, a, col)];
         r2[c] = sGZ[lidx<N, CB>(slot, c, b, a, col)];
       }
+      eo<T, N, -1>(FS.Gt, r2, d);
 #pragma unroll
-      for (int c = 0; c < N; ++c) {
-        T s = r1[c];
+      for (int c = 0; c < N; ++c) sU[lidx<N, CB>(slot, c, b, a, col)] = r1[c] + d[c];
+    }
+    __syncthreads();
+    // ---- B2: y-part of the transposed derivative, then B^T in y --------------------------
+    {
+      const int a = line % N, c = line / N;
+      T d[N];
 #pragma unroll
-        for (int q = 0; q < N; ++q) s += (T)R.Dg[q * tdfe1d::MAXN + c] * r2[q];
-        r1[c] = s;  // reads only r1[c] itself and r2
+      for (int b = 0; b < N; ++b) {
+        r1[b] = sU[lidx<N, CB>(slot, c, b, a, col)];
+        r2[b] = sGY[lidx<N, CB>(slot, c, b, a, col)];
       }
+      eo<T, N, -1>(FS.Gt, r2, d);
 #pragma unroll
-      for (int k = 0; k < N; ++k) {
-        T s = 0;
+      for (int b = 0; b < N; ++b) r1[b] += d[b];
+      eo<T, N, 1>(FS.Bt, r1, r2);
 #pragma unroll
-        for (int c = 0; c < N; ++c) s += (T)R.B[c * tdfe1d::MAXN + k] * r1[c];
-        sR[lidx<N, CB>(slot, k, b, a, col)] = s;
-      }
+      for (int j = 0; j < N; ++j) sR[lidx<N, CB>(slot, c, j, a, col)] = r2[j];
     }
     __syncthreads();
   }
-  // ---- B4: B^T in y ------------------------------------------------------------------------
+  // ---- B4: B^T in x ------------------------------------------------------------------------
   {
-    const int a = line % N, k = line / N;
+    const int j = line % N, c = line / N;
 #pragma unroll
-    for (int b = 0; b < N; ++b) r1[b] = sR[lidx<N, CB>(slot, k, b, a, col)];
+    for (int a = 0; a < N; ++a) r1[a] = sR[lidx<N, CB>(slot, c, j, a, col)];
+    eo<T, N, 1>(FS.Bt, r1, r2);
 #pragma unroll
-    for (int j = 0; j < N; ++j) {
-      T s = 0;
-#pragma unroll
-      for (int b = 0; b < N; ++b) s += (T)R.B[b * tdfe1d::MAXN + j] * r1[b];
-      sR[lidx<N, CB>(slot, k, j, a, col)] = s;
-    }
+    for (int i = 0; i < N; ++i) sR[lidx<N, CB>(slot, c, j, i, col)] = r2[i];
   }
   __syncthreads();
-  // ---- B5: B^T in x and scatter-add -------------------------------------------------------
+  // ---- B5: B^T in z and scatter-add: z last, so that neighbouring lanes write
+  // neighbouring x nodes (an atomic costs per 64-byte segment, whatever it
+  // carries: with x last a one-column launch was 343 segments per p = 6 cell) ----
   {
-    const int j = line % N, k = line / N;
+    const int i = line % N, j = line / N;
 #pragma unroll
-    for (int a = 0; a < N; ++a) r1[a] = sR[lidx<N, CB>(slot, k, j, a, col)];
+    for (int c = 0; c < N; ++c) r1[c] = sR[lidx<N, CB>(slot, c, j, i, col)];
+    eo<T, N, 1>(FS.Bt, r1, r2);
+    if (act) {
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      T s = 0;
-#pragma unroll
-      for (int a = 0; a < N; ++a) s += (T)R.B[a * tdfe1d::MAXN + i] * r1[a];
-      if (act) {
+      for (int k = 0; k < N; ++k) {
         bool inside;
         const int64_t id = node_index(i, j, k, inside);
-        if (inside) {
-          if (P.lowdin) s *= (T)P.minv[id];
-          atomic_add(Y + id * P.ld + colg, s);
-        }
+        if (inside) atomic_add(Y + id * P.ld + colg, P.lowdin ? r2[k] * (T)P.minv[id] : r2[k]);
       }
     }
   }

@@ -81,3 +81,21 @@ def test_exponential_with_both_output_forms(mesh, p, n_orb, cap, monkeypatch):
     ref = ref[0] if isinstance(ref, tuple) else ref
     assert np.abs(psi.cpu().numpy() - ref).max() < 1e-10
     ctx.close()
+
+
+@pytest.mark.parametrize("p", [1, 2, 4, 5, 7, 8])
+def test_one_column_stiffness_on_curved_cells(p):
+    """The Hartree solve's stiffness products (one column, full grid) at each
+    order: CG to a relative residual of 1e-13 against the oracle's; the bar
+    allows for a condition number of 1e3."""
+    from oracle import scf
+    cfg = _cfg("graded", p, 1)
+    ctx = gpu_context(cfg, n_orb=1, k_max=4)
+    Z, R = W.atoms(cfg)
+    ctx.set_scf(hartree=True, Z=Z, R=R, n_orb=1, pcg_tol=1e-13)
+    m, _ = oracle_mesh(cfg)
+    x = W.random_block(m.n_dof, 1, 90 + p) * 1e-2
+    phi, _ = ctx.scf_fields(torch.from_numpy(x).cuda(), w=False)
+    ref, _ = scf.Hartree(m, Z, R, tol=1e-13).solve(scf.density(m, x))
+    assert rel(phi.cpu().numpy(), ref) < 1e-10
+    ctx.close()
