@@ -631,6 +631,10 @@ int64_t tdfe_blocks_apply(const tdfe_ctx* c, int cols) {
 // faster there, 0.64 ms against 2.2 ms for the Hartree solve's one-column
 // products on the graded mesh)
 static bool block_kernels_ok(const tdfe_ctx* c, const ApplyArgs& a) {
+  // 32-bit byte offsets within a block's cells, which may wrap to the next row
+  // or layer of cells (the line kernel has no such limit)
+  const int64_t plane = (int64_t)c->Nx * c->Ny, row = (int64_t)a.ld * (a.fp32 ? 4 : 8);
+  if (3 * c->n * plane * row >= (int64_t)1 << 31 || c->n_cell >= (int64_t)1 << 30) return false;
   return c->variant != TDFE_VARIANT_LINE && a.lowdin && !a.fullgrid &&
          (c->box ? tdfe_box_kernel_ok(c) : tdfe_curved_kernel_ok(c, a.cols, a.fp32));
 }

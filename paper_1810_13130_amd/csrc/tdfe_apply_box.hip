@@ -79,19 +79,15 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
   const int group = L / P.nchunks;
   const int col = t % CB;
   const int pl = (t / CB) % N;
-  const int slot = t / (CB * N);
+  const int slot = CPB == 1 ? 0 : t / (CB * N);
   const int64_t cell = (int64_t)group * CPB + slot;
   const bool cell_ok = cell < P.n_cell;
   const int colg = chunk * CB + col;
   const bool act = cell_ok && colg < P.cols;
 
-  int cx = 0, cy = 0, cz = 0;
-  if (cell_ok) {
-    cx = (int)(cell % P.ncx);
-    cy = (int)((cell / P.ncx) % P.ncy);
-    cz = (int)(cell / ((int64_t)P.ncx * P.ncy));
-  }
-  const T* __restrict__ X = (const T*)P.x;
+  const int64_t c0 = (int64_t)group * CPB;
+  const CellPos B0 = cell_pos(P, (int)c0);
+  const CellPos cp = CPB == 1 ? B0 : cell_next(P, B0, cell_ok ? slot : 0);
   T* __restrict__ Y = (T*)P.y;
   T cs = (T)1;
   if (P.colscale && act) cs = (T)P.colscale[colg >> 1];
@@ -104,7 +100,6 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
   constexpr int NV = (CPB * VOL + THREADS - 1) / THREADS;
   constexpr int NF = (CPB * NFC + THREADS - 1) / THREADS;
   __shared__ double sF[CPB * NFC];
-  const int64_t c0 = (int64_t)group * CPB;
   T vr[NV];
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
@@ -118,15 +113,14 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
   for (int k = 0; k < NF; ++k) {
     const int f = t + k * THREADS;
     const int r = f % NFC;
-    const int64_t ce = c0 + f / NFC;
-    const bool ok = f < CPB * NFC && ce < P.n_cell;
-    const int64_t cv = ok ? ce : 0;
-    const int ex = (int)(cv % P.ncx), ey = (int)((cv / P.ncx) % P.ncy);
-    const int ez = (int)(cv / ((int64_t)P.ncx * P.ncy));
+    const int sl = f / NFC;
+    const bool ok = f < CPB * NFC && c0 + sl < P.n_cell;
+    const CellPos e = CPB == 1 ? B0 : cell_next(P, B0, ok ? sl : 0);
+    const int64_t cv = c0 + (ok ? sl : 0);
     // one load from a selected (always valid) address: no branches
-    const double* src = r < N ? P.m1x + (ex * P.p + r)
-                        : r < 2 * N ? P.m1y + (ey * P.p + r - N)
-                        : r < 3 * N ? P.m1z + (ez * P.p + r - 2 * N)
+    const double* src = r < N ? P.m1x + (e.x * P.p + r)
+                        : r < 2 * N ? P.m1y + (e.y * P.p + r - N)
+                        : r < 3 * N ? P.m1z + (e.z * P.p + r - 2 * N)
                                     : P.cellgeo + (cv * 4 + r - 3 * N);
     const double val = *src;
     fr[k] = ok ? val : 0.0;
@@ -140,30 +134,21 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
   T u[N][N];  // [i][k] gathered, then [i][c], then S B u at [x point][z point]
   {
     const int j = pl;
-    const int J = cy * P.p + j;
-    // node (I, J, K) -> element offset; all loads are issued unconditionally
-    // from a valid address (masked entries read element 0 and are zeroed)
-    const bool jok = J > 0 && J < P.Ny - 1;
-    unsigned imask = 0, kmask = 0;
-#pragma unroll
-    for (int q = 0; q < N; ++q) {
-      const int I = cx * P.p + q, K = cz * P.p + q;
-      if (I > 0 && I < P.Nx - 1) imask |= 1u << q;
-      if (K > 0 && K < P.Nz - 1) kmask |= 1u << q;
-    }
-    if (!act || !jok) imask = 0;
-    // element index of (i, k): e0 + i * ld + k * kstride
-    const int64_t e0 =
-        ((int64_t)(cx * P.p - 1) + (int64_t)NxI * ((int64_t)(J - 1) + (int64_t)NyI * (cz * P.p - 1))) * P.ld + colg;
-    const int64_t kstride = (int64_t)NxI * NyI * P.ld;
+    const __amdgpu_buffer_rsrc_t rx = cell_rsrc<T>(P, B0);
+    const uint32_t ldb = (uint32_t)P.ld * (uint32_t)sizeof(T), kst = (uint32_t)(NxI * NyI) * ldb;
+    uint32_t o0 = (uint32_t)(cp.row(P) - B0.row(P) + NxI * j) * ldb + (uint32_t)colg * (uint32_t)sizeof(T);
+    if (!act || (j == 0 && cp.y == 0) || (j == N - 1 && cp.y == P.ncy - 1)) o0 = CELL_NO_READ;
 #pragma unroll
     for (int k = 0; k < N; ++k) {
+      uint32_t ok = o0 + k * kst;
+      if (k == 0 && cp.z == 0) ok = CELL_NO_READ;
+      if (k == N - 1 && cp.z == P.ncz - 1) ok = CELL_NO_READ;
 #pragma unroll
       for (int i = 0; i < N; ++i) {
-        const bool ok = ((imask >> i) & (kmask >> k) & 1u) != 0;
-        const int64_t e = ok ? e0 + (int64_t)i * P.ld + (int64_t)k * kstride : 0;
-        const T val = X[e];
-        u[i][k] = ok ? val : (T)0;
+        uint32_t o = ok + i * ldb;
+        if (i == 0 && cp.x == 0) o = CELL_NO_READ;
+        if (i == N - 1 && cp.x == P.ncx - 1) o = CELL_NO_READ;
+        u[i][k] = cell_load<T>(rx, o);
       }
     }
 #pragma unroll
@@ -181,8 +166,8 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
     T fx[N], fz[N];
 #pragma unroll
     for (int q = 0; q < N; ++q) {
-      fx[q] = ((imask >> q) & 1u) ? (T)sFc[q] : (T)0;
-      fz[q] = ((kmask >> q) & 1u) ? (T)sFc[2 * N + q] : (T)0;
+      fx[q] = (T)sFc[q];
+      fz[q] = (T)sFc[2 * N + q];
     }
 #pragma unroll
     for (int k = 0; k < N; ++k)
@@ -232,7 +217,6 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
   // ---------------- B: plane a = pl, quadrature values (b, c) --------------------------------
   double energy = 0.0;
   T gx = 0, gy = 0, gz = 0;
-  const bool havev = P.vw != nullptr;
   if (cell_ok) {
     // Gauss weight of this thread's x point, selected from the constants (an
     // array indexed per lane would be a memory load and a wait)
@@ -254,7 +238,7 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
 #pragma unroll
     for (int b = 0; b < N; ++b) {
       const T f = gx * wprod(b, c) * o[b];
-      acc[b][c] = havev ? sV[slot * VOL + pl + N * (b + N * c)] * uq[b][c] + f : f;
+      acc[b][c] = sV[slot * VOL + pl + N * (b + N * c)] * uq[b][c] + f;  // (0 without a potential)
     }
     // keep the potential reads of later lines from being hoisted here
     __builtin_amdgcn_sched_barrier(0);
@@ -315,16 +299,15 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
       fx[q] = (T)sFc[q];
       fz[q] = (T)sFc[2 * N + q];
     }
-    const CellOut<T, N, CELLS> E(Y, P, cell, cx, cy, cz, j, colg, act);
+    const CellOut<T, N, CELLS> E(Y, P, B0, cp, c0, slot, j, colg, act);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       T o[N];
       eo<T, N, 1>(FS.Bt, h[i], o);
       if (E.jok && E.xok(i)) {
-        T* const row = E.e + i * E.sx;
 #pragma unroll
         for (int k = 0; k < N; ++k)
-          if (E.zok(k)) E.put(row + k * E.sz, o[k] * fx[i] * fz[k] * my);
+          if (E.zok(k)) E.put(i, k, E.off, o[k] * fx[i] * fz[k] * my);
       }
     }
   }

@@ -63,18 +63,15 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
   const int group = L / P.nchunks;
   const int col = t % CB;
   const int pl = (t / CB) % N;
-  const int slot = t / (CB * N);
+  const int slot = CPB == 1 ? 0 : t / (CB * N);
   const int64_t cell = (int64_t)group * CPB + slot;
   const bool cell_ok = cell < P.n_cell;
   const int colg = chunk * CB + col;
   const bool act = cell_ok && colg < P.cols;
 
-  int cx = 0, cy = 0, cz = 0;
-  if (cell_ok) {
-    cx = (int)(cell % P.ncx);
-    cy = (int)((cell / P.ncx) % P.ncy);
-    cz = (int)(cell / ((int64_t)P.ncx * P.ncy));
-  }
+  const CellPos B0 = cell_pos(P, group * CPB);
+  const CellPos cp = CPB == 1 ? B0 : cell_next(P, B0, cell_ok ? slot : 0);
+  const int cx = cp.x, cy = cp.y, cz = cp.z;
   const T* __restrict__ X = (const T*)P.x;
   T* __restrict__ Y = (T*)P.y;
   // M^-1/2 in the kernel's precision (a conversion right after each load
@@ -124,7 +121,8 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
     bool in = q < CPB * VOL && ce < P.n_cell;
     int64_t idx = 0;
     if (in) {
-      const int ex = (int)(ce % P.ncx), ey = (int)((ce / P.ncx) % P.ncy), ez = (int)(ce / ((int64_t)P.ncx * P.ncy));
+      const CellPos e = CPB == 1 ? B0 : cell_next(P, B0, q / VOL);
+      const int ex = e.x, ey = e.y, ez = e.z;
       const int I = ex * P.p + r % N, Jn = ey * P.p + (r / N) % N, K = ez * P.p + r / (N * N);
       in = I > 0 && I < P.Nx - 1 && Jn > 0 && Jn < P.Ny - 1 && K > 0 && K < P.Nz - 1;
       idx = (int64_t)(I - 1) + (int64_t)(P.Nx - 2) * ((int64_t)(Jn - 1) + (int64_t)(P.Ny - 2) * (K - 1));
@@ -245,7 +243,7 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
       // the resource is built from the block's first cell (the lowest rows
       // any of its cells touches) and made explicitly wave-uniform
       const int64_t rows = (int64_t)NxI * NyI * (P.Nz - 2);
-      const int bx = (int)(c0 % P.ncx), by = (int)((c0 / P.ncx) % P.ncy), bz = (int)(c0 / ((int64_t)P.ncx * P.ncy));
+      const int bx = B0.x, by = B0.y, bz = B0.z;
       const int64_t first = (int64_t)(bx * P.p - 1) + (int64_t)NxI * ((int64_t)(by * P.p - 1) +
                             (int64_t)NyI * (bz * P.p - 1));
       const int64_t base = first > 0 ? first : 0;
@@ -456,7 +454,7 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
 #pragma unroll
       for (int i = 0; i < N; ++i) h[i][c] = o1[i] + o2[i];
     }
-    const CellOut<T, N, CELLS> E(Y, P, cell, cx, cy, cz, pl, colg, act);
+    const CellOut<T, N, CELLS> E(Y, P, B0, cp, c0, slot, pl, colg, act);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       // the line's M^-1/2 values are loaded before its contraction, so that
@@ -468,10 +466,9 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
       eo<T, N, 1>(FS.Bt, h[i], o);
       // (the node tests depend on the cell only: uniform whenever a wave holds one cell)
       if (E.jok && E.xok(i)) {
-        T* const row = E.e + i * E.sx;
 #pragma unroll
         for (int k = 0; k < N; ++k)
-          if (E.zok(k)) E.put(row + k * E.sz, o[k] * ml[k]);
+          if (E.zok(k)) E.put(i, k, E.off, o[k] * ml[k]);
       }
     }
   }
@@ -720,7 +717,7 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
   const int group = L / P.nchunks;
   const int col = r % CB;
   const int pl = (r / CB) % N;
-  const int slot = r / (CB * N);
+  const int slot = CPB == 1 ? 0 : r / (CB * N);
   const int64_t cell = (int64_t)group * CPB + slot;
   const bool cell_ok = cell < P.n_cell;
   const int colg = chunk * CB + col;
@@ -729,12 +726,9 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
   // global z index of local entry q
   auto zg = [&](int q) { return q == H ? H : (h ? N - 1 - q : q); };
 
-  int cx = 0, cy = 0, cz = 0;
-  if (cell_ok) {
-    cx = (int)(cell % P.ncx);
-    cy = (int)((cell / P.ncx) % P.ncy);
-    cz = (int)(cell / ((int64_t)P.ncx * P.ncy));
-  }
+  const CellPos B0 = cell_pos(P, group * CPB);
+  const CellPos cp = CPB == 1 ? B0 : cell_next(P, B0, cell_ok ? slot : 0);
+  const int cx = cp.x, cy = cp.y, cz = cp.z;
   T* __restrict__ Y = (T*)P.y;
   const T* __restrict__ MV;
   if constexpr (sizeof(T) == 8)
@@ -771,7 +765,8 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
     bool in = q < CPB * VOL && ce < P.n_cell;
     int64_t idx = 0;
     if (in) {
-      const int ex = (int)(ce % P.ncx), ey = (int)((ce / P.ncx) % P.ncy), ez = (int)(ce / ((int64_t)P.ncx * P.ncy));
+      const CellPos e = CPB == 1 ? B0 : cell_next(P, B0, q / VOL);
+      const int ex = e.x, ey = e.y, ez = e.z;
       const int I = ex * P.p + rr % N, Jn = ey * P.p + (rr / N) % N, K = ez * P.p + rr / (N * N);
       in = I > 0 && I < P.Nx - 1 && Jn > 0 && Jn < P.Ny - 1 && K > 0 && K < P.Nz - 1;
       idx = (int64_t)(I - 1) + (int64_t)(P.Nx - 2) * ((int64_t)(Jn - 1) + (int64_t)(P.Ny - 2) * (K - 1));
@@ -812,7 +807,7 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
       // plane kernel): out-of-range nodes read 0, Dirichlet nodes inside the
       // range read a value that the zero in sM cancels
       const int64_t rows = (int64_t)NxI * NyI * (P.Nz - 2);
-      const int bx = (int)(c0 % P.ncx), by = (int)((c0 / P.ncx) % P.ncy), bz = (int)(c0 / ((int64_t)P.ncx * P.ncy));
+      const int bx = B0.x, by = B0.y, bz = B0.z;
       const int64_t first = (int64_t)(bx * P.p - 1) + (int64_t)NxI * ((int64_t)(by * P.p - 1) +
                             (int64_t)NyI * (bz * P.p - 1));
       const int64_t base = first > 0 ? first : 0;
@@ -1019,10 +1014,10 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
 #pragma unroll
       for (int i = 0; i < N; ++i) hh[i][c] = o1[i] + o2[i];
     }
-    const CellOut<T, N, CELLS> E(Y, P, cell, cx, cy, cz, pl, colg, act);
-    // this lane's z entries run up from node 0 or down from node n-1
-    T* const e0 = E.e + (h ? (N - 1) * E.sz : 0);
-    const int64_t sz = h ? -E.sz : E.sz;
+    const CellOut<T, N, CELLS> E(Y, P, B0, cp, c0, slot, pl, colg, act);
+    uint32_t oz[HZ];  // this lane's z entries
+#pragma unroll
+    for (int k = 0; k < HZ; ++k) oz[k] = E.off + (uint32_t)zg(k) * (uint32_t)E.sz;
     const bool z0 = h ? E.hiz : E.loz;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
@@ -1032,10 +1027,9 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
       T o[HZ];
       zpair<T, N>(ZS.Bt, hh[i], o, (T)1);
       if (E.jok && E.xok(i)) {
-        T* const row = e0 + i * E.sx;
 #pragma unroll
         for (int k = 0; k < HZ; ++k)
-          if ((k > 0 || z0) && !(ODD && k == H && h)) E.put(row + k * sz, o[k] * ml[k]);
+          if ((k > 0 || z0) && !(ODD && k == H && h)) E.put(i, 0, oz[k], o[k] * ml[k]);
       }
     }
   }

@@ -179,7 +179,7 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
   const int group = L / P.nchunks;
   const int col = r % CB;
   const int pl = (r / CB) % N;
-  const int slot = r / (CB * N);
+  const int slot = CPB == 1 ? 0 : r / (CB * N);
   const int64_t cell = (int64_t)group * CPB + slot;
   const bool cell_ok = cell < P.n_cell;
   const int colg = chunk * CB + col;
@@ -187,13 +187,9 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
   // global z index of local entry q
   auto zg = [&](int q) { return h ? N - 1 - q : q; };
 
-  int cx = 0, cy = 0, cz = 0;
-  if (cell_ok) {
-    cx = (int)(cell % P.ncx);
-    cy = (int)((cell / P.ncx) % P.ncy);
-    cz = (int)(cell / ((int64_t)P.ncx * P.ncy));
-  }
-  const T* __restrict__ X = (const T*)P.x;
+  const int64_t c0 = (int64_t)group * CPB;
+  const CellPos B0 = cell_pos(P, (int)c0);
+  const CellPos cp = CPB == 1 ? B0 : cell_next(P, B0, cell_ok ? slot : 0);
   T* __restrict__ Y = (T*)P.y;
   T cs = (T)1;
   if (P.colscale && act) cs = (T)P.colscale[colg >> 1];
@@ -205,7 +201,6 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
   constexpr int NV = (CPB * VOL + THREADS - 1) / THREADS;
   constexpr int NF = (CPB * NFC + THREADS - 1) / THREADS;
   __shared__ double sF[CPB * NFC];
-  const int64_t c0 = (int64_t)group * CPB;
   T vr[NV];
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
@@ -219,14 +214,13 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
   for (int k = 0; k < NF; ++k) {
     const int f = t + k * THREADS;
     const int r = f % NFC;
-    const int64_t ce = c0 + f / NFC;
-    const bool ok = f < CPB * NFC && ce < P.n_cell;
-    const int64_t cv = ok ? ce : 0;
-    const int ex = (int)(cv % P.ncx), ey = (int)((cv / P.ncx) % P.ncy);
-    const int ez = (int)(cv / ((int64_t)P.ncx * P.ncy));
-    const double* src = r < N ? P.m1x + (ex * P.p + r)
-                        : r < 2 * N ? P.m1y + (ey * P.p + r - N)
-                        : r < 3 * N ? P.m1z + (ez * P.p + r - 2 * N)
+    const int sl = f / NFC;
+    const bool ok = f < CPB * NFC && c0 + sl < P.n_cell;
+    const CellPos e = CPB == 1 ? B0 : cell_next(P, B0, ok ? sl : 0);
+    const int64_t cv = c0 + (ok ? sl : 0);
+    const double* src = r < N ? P.m1x + (e.x * P.p + r)
+                        : r < 2 * N ? P.m1y + (e.y * P.p + r - N)
+                        : r < 3 * N ? P.m1z + (e.z * P.p + r - 2 * N)
                                     : P.cellgeo + (cv * 4 + r - 3 * N);
     const double val = *src;
     fr[k] = ok ? val : 0.0;
@@ -251,31 +245,22 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
   // ---------------- A: plane j = pl, values (i, local k) ---------------------------------
   T u[N][H];  // [i][local k] gathered, then [i][c], then S B u at [x point][local z point]
   {
-    const int J = cy * P.p + pl;
-    unsigned imask = 0, kmask = 0;  // DoFs among the x nodes and the local z entries
+    const __amdgpu_buffer_rsrc_t rx = cell_rsrc<T>(P, B0);
+    const uint32_t ldb = (uint32_t)P.ld * (uint32_t)sizeof(T), kst = (uint32_t)(NxI * NyI) * ldb;
+    uint32_t o0 = (uint32_t)(cp.row(P) - B0.row(P) + NxI * pl) * ldb + (uint32_t)colg * (uint32_t)sizeof(T);
+    if (!act || (pl == 0 && cp.y == 0) || (pl == N - 1 && cp.y == P.ncy - 1)) o0 = CELL_NO_READ;
 #pragma unroll
-    for (int q = 0; q < N; ++q) {
-      const int I = cx * P.p + q;
-      if (I > 0 && I < P.Nx - 1) imask |= 1u << q;
-    }
-#pragma unroll
-    for (int q = 0; q < H; ++q) {
-      const int K = cz * P.p + zg(q);
-      if (K > 0 && K < P.Nz - 1) kmask |= 1u << q;
-    }
-    if (!act || J <= 0 || J >= P.Ny - 1) imask = 0;
-    const int64_t e0 =
-        ((int64_t)(cx * P.p - 1) + (int64_t)NxI * ((int64_t)(J - 1) + (int64_t)NyI * (cz * P.p - 1))) * P.ld + colg;
-    const int64_t kstride = (int64_t)NxI * NyI * P.ld;
-#pragma unroll
-    for (int k = 0; k < H; ++k)
+    for (int k = 0; k < H; ++k) {
+      uint32_t ok = o0 + (uint32_t)zg(k) * kst;
+      if (k == 0 && (h ? cp.z == P.ncz - 1 : cp.z == 0)) ok = CELL_NO_READ;
 #pragma unroll
       for (int i = 0; i < N; ++i) {
-        const bool ok = ((imask >> i) & (kmask >> k) & 1u) != 0;
-        const int64_t e = ok ? e0 + (int64_t)i * P.ld + (int64_t)zg(k) * kstride : 0;
-        const T val = X[e];
-        u[i][k] = ok ? val : (T)0;
+        uint32_t o = ok + i * ldb;
+        if (i == 0 && cp.x == 0) o = CELL_NO_READ;
+        if (i == N - 1 && cp.x == P.ncx - 1) o = CELL_NO_READ;
+        u[i][k] = cell_load<T>(rx, o);
       }
+    }
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
       const int q = t + k * THREADS;
@@ -362,7 +347,7 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
 #pragma unroll
     for (int b = 0; b < N; ++b) {
       const T f = gx * ((T)FS.wq[b] * wc[c]) * o[b];
-      acc[b][c] = P.vw ? sV[slot * VOL + pl + N * (b + N * zg(c))] * uq[b][c] + f : f;
+      acc[b][c] = sV[slot * VOL + pl + N * (b + N * zg(c))] * uq[b][c] + f;  // (0 without a potential)
     }
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -413,20 +398,19 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
     }
     PlaneFactors Q;
     plane_factors(Q);
-    const CellOut<T, N, CELLS> E(Y, P, cell, cx, cy, cz, pl, colg, act);
-    // this lane's z entries run up from node 0 or down from node n-1
-    T* const e0 = E.e + (h ? (N - 1) * E.sz : 0);
-    const int64_t sz = h ? -E.sz : E.sz;
+    const CellOut<T, N, CELLS> E(Y, P, B0, cp, c0, slot, pl, colg, act);
+    uint32_t oz[H];  // this lane's z entries
+#pragma unroll
+    for (int k = 0; k < H; ++k) oz[k] = E.off + (uint32_t)zg(k) * (uint32_t)E.sz;
     const bool z0 = h ? E.hiz : E.loz;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       T o[H];
       zsplit<T, N>(FS.zBt, hh[i], o);
       if (E.jok && E.xok(i)) {
-        T* const row = e0 + i * E.sx;
 #pragma unroll
         for (int k = 0; k < H; ++k)
-          if (k > 0 || z0) E.put(row + k * sz, o[k] * (Q.fx[i] * Q.fz[k] * Q.my));
+          if (k > 0 || z0) E.put(i, 0, oz[k], o[k] * (Q.fx[i] * Q.fz[k] * Q.my));
       }
     }
   }

@@ -131,45 +131,105 @@ __device__ __forceinline__ int remap_block(int p, int G) {
   return x * q + min(x, r) + (p >> 3);
 }
 
+// position of a cell on the grid of cells
+struct CellPos {
+  int x, y, z;
+  // DoF row of its node (0, 0, 0) (before the first DoF on the domain's faces)
+  template <typename Params>
+  __device__ __forceinline__ int64_t row(const Params& P) const {
+    return (int64_t)(x * P.p - 1) + (int64_t)(P.Nx - 2) * ((int64_t)(y * P.p - 1) + (int64_t)(P.Ny - 2) * (z * P.p - 1));
+  }
+};
+// of the block's first cell (uniform: scalar arithmetic), and of the cell
+// `slot` cells further on
+template <typename Params>
+__device__ __forceinline__ CellPos cell_pos(const Params& P, int c0) {
+  const int yz = c0 / P.ncx;
+  return {c0 % P.ncx, yz % P.ncy, yz / P.ncy};
+}
+template <typename Params>
+__device__ __forceinline__ CellPos cell_next(const Params& P, CellPos c, int slot) {
+  c.x += slot;
+  while (c.x >= P.ncx) {
+    c.x -= P.ncx;
+    if (++c.y == P.ncy) {
+      c.y = 0;
+      ++c.z;
+    }
+  }
+  return c;
+}
+
 // Where a cell's results go.  CELLS: to the cell's own n^3 rows of y, every node
 // (plain stores; the consumer sums the cells, tdfe_cells.h).  Otherwise added
 // to the DoF vector y by hardware atomics, DoF nodes only.  Atomics on this
 // chip are performed beyond the per-XCD L2s at about 1.3 TB/s of values, plain
 // stores run at 5.5; see cells_fit for when the cell rows pay.
+//
+// Addresses are a block-uniform 64-bit base per node row (scalar arithmetic)
+// plus a 32-bit byte offset per lane (block_offsets_ok).
 template <typename T, int N, bool CELLS>
 struct CellOut {
-  T* e;  // node (0, j, 0) of the cell, this lane's column
-  int64_t sx, sz;
+  char* base;        // the block's first cell, node (0, 0, 0)
+  uint32_t off;      // this lane's cell, node (0, j, 0) and column from there
+  int64_t sx, sz;    // bytes
   bool lox, hix, loz, hiz, jok;
   template <typename Params>
-  __device__ __forceinline__ CellOut(T* Y, const Params& P, int64_t cell, int cx, int cy, int cz, int j, int colg,
-                                     bool act) {
-    lox = CELLS || cx > 0;
-    hix = CELLS || cx < P.ncx - 1;
-    loz = CELLS || cz > 0;
-    hiz = CELLS || cz < P.ncz - 1;
-    jok = act && (CELLS || ((j > 0 || cy > 0) && (j < N - 1 || cy < P.ncy - 1)));
+  __device__ __forceinline__ CellOut(T* Y, const Params& P, const CellPos& B, const CellPos& c, int64_t c0, int slot,
+                                     int j, int colg, bool act) {
+    lox = CELLS || c.x > 0;
+    hix = CELLS || c.x < P.ncx - 1;
+    loz = CELLS || c.z > 0;
+    hiz = CELLS || c.z < P.ncz - 1;
+    jok = act && (CELLS || ((j > 0 || c.y > 0) && (j < N - 1 || c.y < P.ncy - 1)));
     if constexpr (CELLS) {
-      sx = P.cols;
-      sz = (int64_t)(N * N) * P.cols;
-      e = Y + (cell * (N * N * N) + N * j) * P.cols + colg;
+      sx = (int64_t)P.cols * (int)sizeof(T);
+      sz = N * N * sx;
+      base = (char*)Y + c0 * N * sz;
+      off = (uint32_t)((slot * (N * N * N) + N * j) * P.cols + colg) * (uint32_t)sizeof(T);
     } else {
       const int64_t NxI = P.Nx - 2, NyI = P.Ny - 2;
-      sx = P.ld;
-      sz = NxI * NyI * P.ld;
-      e = Y + ((int64_t)(cx * P.p - 1) + NxI * ((int64_t)(cy * P.p + j - 1) + NyI * (cz * P.p - 1))) * P.ld + colg;
+      sx = (int64_t)P.ld * (int)sizeof(T);
+      sz = NxI * NyI * sx;
+      base = (char*)Y + B.row(P) * sx;
+      off = (uint32_t)(c.row(P) - B.row(P) + NxI * j) * (uint32_t)sx + (uint32_t)colg * (uint32_t)sizeof(T);
     }
   }
   // x node i, z node k are written (i, k compile-time constants after unrolling)
   __device__ __forceinline__ bool xok(int i) const { return (i > 0 || lox) && (i < N - 1 || hix); }
   __device__ __forceinline__ bool zok(int k) const { return (k > 0 || loz) && (k < N - 1 || hiz); }
-  __device__ __forceinline__ void put(T* d, T v) const {
+  // node (i, j, k) with k uniform, or i uniform and the z offset part of o
+  __device__ __forceinline__ void put(int i, int k, uint32_t o, T v) const {
+    T* const d = (T*)(base + (i * sx + k * sz) + o);
     if constexpr (CELLS)
       *d = v;
     else
       unsafeAtomicAdd(d, v);
   }
 };
+
+// the gather of a cell's plane: a buffer resource over the DoF vector from the
+// block's first row on, byte offsets per lane; entries that are not read (the
+// Dirichlet planes, columns past the last) carry offsets past its end and
+// give 0
+constexpr uint32_t CELL_NO_READ = 0x80000000u;
+template <typename T, typename Params>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t cell_rsrc(const Params& P, const CellPos& B) {
+  const int64_t first = B.row(P), rows = (int64_t)(P.Nx - 2) * (P.Ny - 2) * (P.Nz - 2);
+  const int64_t bytes = (rows - first) * P.ld * (int)sizeof(T);
+  const uint64_t ad = (uint64_t)(uintptr_t)P.x + (uint64_t)(first * P.ld * (int)sizeof(T));
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)ad);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(ad >> 32));
+  const int nrec = __builtin_amdgcn_readfirstlane((int)(bytes < 0x7fffffff ? bytes : 0x7fffffff));
+  return __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)(((uint64_t)hi << 32) | lo), 0, nrec, 0x00020000);
+}
+template <typename T>
+__device__ __forceinline__ T cell_load(__amdgpu_buffer_rsrc_t r, uint32_t o) {
+  if constexpr (sizeof(T) == 8)
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)o, 0, 0));
+  else
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)o, 0, 0));
+}
 
 // out[a] = sum_i A[a][i] in[i] by even/odd folding; A given folded (in any
 // precision, converted to T), symmetry S
