@@ -23,7 +23,7 @@
 //    (Jacobi-Anger coefficients 2 (-i)^m J_m(tau r), Bessel values by
 //    Miller's backward recurrence), one wavefront per orbital, rows across
 //    lanes.  It gives the same y as an eigendecomposition of T_k to ~1e-15.
-//    For k <= 64 it runs in leading blocks of the same iteration's update
+//    For k <= 256 it runs in leading blocks of the same iteration's update
 //    kernel (T_k is complete once alpha_k is known), so the stop test after
 //    the update is only a reduction and a comparison;
 //  * the host enqueues iterations ahead, paced by a progress word the update
@@ -33,6 +33,7 @@
 //    exit at their first instruction.
 #include <chrono>
 #include <cmath>
+#include <type_traits>
 
 #include "tdfe_cells.h"
 #include "tdfe_cheb.h"
@@ -140,10 +141,9 @@ __device__ __forceinline__ void post_progress(unsigned* progress, int gen, int k
                        __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// The small exponential of iteration k (k <= one wavefront) rides on the
-// update kernel of the same iteration: T_k needs alpha_1..alpha_k and
-// beta_1..beta_{k-1}, all known when the update starts, and only the stop
-// test waits for beta_k.  The first nblk blocks of the update grid each take
+// The small exponential of iteration k rides on the update kernel of the same
+// iteration: T_k needs alpha_1..alpha_k and beta_1..beta_{k-1}, all known when
+// the update starts, and only the stop test waits for beta_k.  The first nblk blocks of the update grid each take
 // one active orbital: y = exp(-i tau T_k) e_1 into its result slot (kept
 // there when the orbital stops), and max |alpha| and the term count into ext.
 struct SmallExp {
@@ -158,20 +158,42 @@ struct SmallExp {
   int gen;
 };
 
-__device__ void small_exp_block(const SmallExp& e) {
+//
+// Up to SMALL_ROWS rows of T_k per lane, that is k <= 256 (chosen per launch
+// as 1, 2 or 4, so that the common k <= 64 leaves the streaming blocks their
+// registers).  In a kernel of its own after the update (as still beyond 256,
+// where 8 or 16 rows take over 200 registers) the series cost 75 us of every
+// iteration past 64 of a 1.26M-DoF FP64 exponential: 102.7 -> 100.0 ms over
+// its 115 iterations.
+constexpr int SMALL_ROWS = 4;
+// R rows of T_k per lane; every load is issued before the first is waited for
+template <int R>
+__device__ void small_exp_block(const SmallExp& e, const int* done) {
   const int o = blockIdx.x;
   const int t = threadIdx.x;
-  if (t >= CHK_THREADS || e.S.status[o] != 0) return;
+  if (t >= CHK_THREADS) return;
   const int k = e.k, Nc = e.Nc;
-  const bool row = t < k;
-  const double a = row ? e.S.alpha[(size_t)t * Nc + o] : 0.0;
-  const double bl = (row && t > 0) ? e.S.beta[(size_t)(t - 1) * Nc + o] : 0.0;
-  const double br = (row && t < k - 1) ? e.S.beta[(size_t)t * Nc + o] : 0.0;
-  double yr = 0.0, yi = 0.0, amax = 0.0;
-  const int M = cheb_expm_e1_wave_gtab(k, a, bl, br, e.tau, e.jtab + (size_t)o * TDFE_JTAB_STRIDE, yr, yi, &amax);
-  if (row) {
-    e.S.y[((size_t)o * e.k_max + t) * 2 + 0] = yr;
-    e.S.y[((size_t)o * e.k_max + t) * 2 + 1] = yi;
+  const int dn = *done, st = e.S.status[o];
+  double a[R], bl[R], br[R], yr[R], yi[R], amax = 0.0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int j = R * t + r;
+    const bool row = j < k;
+    a[r] = row ? e.S.alpha[(size_t)j * Nc + o] : 0.0;
+    bl[r] = (row && j > 0) ? e.S.beta[(size_t)(j - 1) * Nc + o] : 0.0;
+    br[r] = (row && j < k - 1) ? e.S.beta[(size_t)j * Nc + o] : 0.0;
+  }
+  if (dn) return;
+  if (o == 0 && t == 0) post_progress(e.progress, e.gen, k - 1);
+  if (st != 0) return;
+  const int M = cheb_series<R>(k, a, bl, br, e.tau, e.jtab + (size_t)o * TDFE_JTAB_STRIDE, yr, yi, &amax);
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int j = R * t + r;
+    if (j < k) {
+      e.S.y[((size_t)o * e.k_max + j) * 2 + 0] = yr[r];
+      e.S.y[((size_t)o * e.k_max + j) * 2 + 1] = yi[r];
+    }
   }
   if (t == 0) {
     e.S.ext[2 * o + 0] = amax;
@@ -184,18 +206,18 @@ __device__ void small_exp_block(const SmallExp& e) {
 // seeded with -q_{j-1}, so that on entry Hq = (Hbar q_j - beta_{j-1} q_{j-1}) / m_j
 // with m_j = beta_{j-1} (m_0 = 1).  Then
 //   w_{j+1} = m_j Hq - alpha_j s_j w_j,   Hq <- -q_j = -s_j w_j,   partial ||w_{j+1}||^2.
-template <typename T>
+template <typename T, int SR>
 __global__ void __launch_bounds__(RED_THREADS)
     update_kernel(T* __restrict__ hq, const T* __restrict__ wa, T* __restrict__ wn, int C, int64_t nrows,
                   const double* alpha_j, const double* s_j, const double* m_j, const int* status,
                   double* __restrict__ partial, const int* done, SmallExp se) {
   __shared__ double sred[RED_THREADS];
-  if (*done) return;
-  if (blockIdx.x == 0 && threadIdx.x == 0) post_progress(se.progress, se.gen, se.k - 1);
   if ((int)blockIdx.x < se.nblk) {
-    small_exp_block(se);
+    small_exp_block<SR>(se, done);
     return;
   }
+  if (*done) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) post_progress(se.progress, se.gen, se.k - 1);
   const int bid = (int)blockIdx.x - se.nblk;  // streaming block index, 0..RED_BLOCKS-1
   if constexpr (sizeof(T) == 4) {
     // FP32: a lane moves one orbital's (re, im) pair as one 8-byte access
@@ -273,7 +295,7 @@ __global__ void __launch_bounds__(RED_THREADS)
 // bytes of a row (one FP64 or two FP32 orbitals).  Reads the cell results once (n^3 / p^3 vectors), w_j and
 // w_{j-1}, writes w_{j+1}; no operator output vector is kept, seeded or cleared.
 constexpr int CELL_BLOCKS = 2048;
-template <typename T, int W>
+template <typename T, int W, int SR>
 __global__ void __launch_bounds__(RED_THREADS)
     update_cells_kernel(const T* __restrict__ e, const T* __restrict__ wa, const T* __restrict__ wp,
                         T* __restrict__ wn, int C, CellMap M, const double* alpha_j, const double* s_j,
@@ -283,12 +305,12 @@ __global__ void __launch_bounds__(RED_THREADS)
   constexpr int NO = W / 2;  // orbitals per lane
   __shared__ double sred[RED_THREADS];
   __shared__ double sorb[2 * RED_THREADS / 4];
-  if (*done) return;
-  if (blockIdx.x == 0 && threadIdx.x == 0) post_progress(se.progress, se.gen, se.k - 1);
   if ((int)blockIdx.x < se.nblk) {
-    small_exp_block(se);
+    small_exp_block<SR>(se, done);
     return;
   }
+  if (*done) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) post_progress(se.progress, se.gen, se.k - 1);
   const int bid = (int)blockIdx.x - se.nblk;
   const int C2 = C / W;
   const int Op = C2 <= 4 ? 4 : (C2 <= 8 ? 8 : (C2 <= 16 ? 16 : 32));
@@ -404,14 +426,14 @@ __global__ void __launch_bounds__(RED_THREADS)
 // ---------------------------------------------------------------------------------------------
 // small exponential and adaptive stop, one wavefront per orbital
 // ---------------------------------------------------------------------------------------------
-// stop decision of orbital o after the small exponential (one wavefront, or
-// the whole block for the LDS path): error estimate, y at convergence, status
+// stop decision of orbital o after the small exponential: error estimate, y at
+// convergence (from Lyr / Lyi, or already in its result slot if these are
+// null), status; called by nthreads lanes
 __device__ void stop_test(Scal S, int o, int Nc, int k, int k_max, int kcap, double tau, double tol, double tol_rel,
                           int M,
                           double amax,
-                          double bk, double ylr, double yli, double yr, double yi, const double* Lyr,
-                          const double* Lyi, int nthreads, int* err_flag, int* host_flag, int gen,
-                          bool y_in_place = false) {
+                          double bk, double ylr, double yli, const double* Lyr, const double* Lyi, int nthreads,
+                          int* err_flag, int* host_flag, int gen) {
   const int t = threadIdx.x;
   int fin = 0;
   if (M < 0) {
@@ -435,17 +457,10 @@ __device__ void stop_test(Scal S, int o, int Nc, int k, int k_max, int kcap, dou
     const bool nonfinite = !isfinite(eps);
     // kcap: the chunk's Krylov dimension limit (k_max, or a soft cap)
     const bool stop = conv || nonfinite || k >= kcap;
-    if (stop && !y_in_place) {
-      if (Lyr == nullptr) {
-        if (t < k) {
-          S.y[((size_t)o * k_max + t) * 2 + 0] = yr;
-          S.y[((size_t)o * k_max + t) * 2 + 1] = yi;
-        }
-      } else {
-        for (int j = t; j < k; j += nthreads) {
-          S.y[((size_t)o * k_max + j) * 2 + 0] = Lyr[j];
-          S.y[((size_t)o * k_max + j) * 2 + 1] = Lyi[j];
-        }
+    if (stop && Lyr) {
+      for (int j = t; j < k; j += nthreads) {
+        S.y[((size_t)o * k_max + j) * 2 + 0] = Lyr[j];
+        S.y[((size_t)o * k_max + j) * 2 + 1] = Lyi[j];
       }
     }
     if (t == 0) {
@@ -487,23 +502,14 @@ __global__ void __launch_bounds__(CHK_THREADS)
   }
   __syncthreads();
   double amax = 0.0;
-  if (k <= CHK_THREADS) {
-    double yr = 0.0, yi = 0.0;
-    const int M = cheb_expm_e1_wave(k, sa, sb, tau, jtab + (size_t)o * TDFE_JTAB_STRIDE, &L.M, &L.inv, yr, yi, &amax);
-    const double ylr = __shfl(yr, k - 1), yli = __shfl(yi, k - 1);
-    stop_test(S, o, Nc, k, k_max, kcap, tau, tol, tol_rel, M, amax, sb[k - 1], ylr, yli, yr, yi, nullptr, nullptr,
-              CHK_THREADS, err_flag, host_flag, gen);
-  } else {
-    const int M = cheb_expm_e1(k, sa, sb, tau, L, jtab + (size_t)o * TDFE_JTAB_STRIDE, &amax);
-    stop_test(S, o, Nc, k, k_max, kcap, tau, tol, tol_rel, M, amax, sb[k - 1], L.yr[k - 1], L.yi[k - 1], 0.0, 0.0,
-              L.yr, L.yi, CHK_THREADS, err_flag, host_flag, gen);
-  }
+  const int M = cheb_expm_e1(k, sa, sb, tau, L, jtab + (size_t)o * TDFE_JTAB_STRIDE, &amax);
+  stop_test(S, o, Nc, k, k_max, kcap, tau, tol, tol_rel, M, amax, sb[k - 1], L.yr[k - 1], L.yi[k - 1], L.yr, L.yi,
+            CHK_THREADS, err_flag, host_flag, gen);
 }
 
 // beta_k = ||w_k|| from the update partials, the scale 1/beta_k of the next
-// basis vector, and -- for k <= one wavefront -- the stop test of the same
-// orbital, on the small exponential the update kernel has left in its result
-// slot and ext
+// basis vector, and the stop test of the same orbital, on the small
+// exponential the update kernel has left in its result slot and ext
 __global__ void __launch_bounds__(RED_THREADS)
     beta_check_kernel(const double* __restrict__ partial, int64_t nblocks, int C, Scal S, int Nc, int k, int k_max,
                       int kcap, double tau, double tol, double tol_rel, int* err_flag, int* host_flag, int gen) {
@@ -530,8 +536,8 @@ __global__ void __launch_bounds__(RED_THREADS)
   const int M = (int)S.ext[2 * o + 1];
   const double ylr = S.y[((size_t)o * k_max + k - 1) * 2 + 0];
   const double yli = S.y[((size_t)o * k_max + k - 1) * 2 + 1];
-  stop_test(S, o, Nc, k, k_max, kcap, tau, tol, tol_rel, M, amax, bk, ylr, yli, 0.0, 0.0, nullptr, nullptr, 1,
-            err_flag, host_flag, gen, true);
+  stop_test(S, o, Nc, k, k_max, kcap, tau, tol, tol_rel, M, amax, bk, ylr, yli, nullptr, nullptr, 1, err_flag,
+            host_flag, gen);
 }
 
 // z = ||psi|| sum_j y_j s_j w_j, written into the complex128 output chunk.
@@ -734,9 +740,19 @@ tdfe_status run_chunk(tdfe_ctx* c, const void* vw, const double* in, double* out
       hipLaunchKernelGGL(finalize_pairs_kernel, dim3(Nc), dim3(RED_THREADS), 0, c->stream, c->partial, groups, C,
                          S.alpha + (size_t)(k - 1) * Nc, 0, (double*)nullptr, (double*)nullptr, m, (const int*)S.done);
     }
-    SmallExp se{S, Nc, k, K, k <= CHK_THREADS ? Nc : 0, tau, c->jtab, dprog, gen};
-    if (cells) {
-      auto update = [&](auto kernel) {
+    const bool ride = k <= SMALL_ROWS * CHK_THREADS;  // small exponential on the update's leading blocks
+    SmallExp se{S, Nc, k, K, ride ? Nc : 0, tau, c->jtab, dprog, gen};
+    auto update = [&](auto rows) {
+      constexpr int R = decltype(rows)::value;
+      if (!cells) {
+        hipLaunchKernelGGL((update_kernel<T, R>), dim3(RED_BLOCKS + se.nblk), dim3(RED_THREADS), 0, c->stream, Hq,
+                           (const T*)wk, W + (int64_t)k * vstride, C, nd,
+                           (const double*)(S.alpha + (size_t)(k - 1) * Nc),
+                           (const double*)(S.scale + (size_t)(k - 1) * Nc), m, (const int*)S.status, c->partial,
+                           (const int*)S.done, se);
+        return;
+      }
+      auto run = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(CELL_BLOCKS + se.nblk), dim3(RED_THREADS), 0, c->stream, (const T*)c->eloc,
                            (const T*)wk, k >= 2 ? (const T*)(wk - vstride) : (const T*)nullptr,
                            W + (int64_t)k * vstride, C, map, (const double*)(S.alpha + (size_t)(k - 1) * Nc),
@@ -747,17 +763,18 @@ tdfe_status run_chunk(tdfe_ctx* c, const void* vw, const double* in, double* out
       // 16 bytes per lane where the columns allow it
       constexpr int WIDE = sizeof(T) == 4 ? 4 : 2;
       if (C % WIDE == 0)
-        update(update_cells_kernel<T, WIDE>);
+        run(update_cells_kernel<T, WIDE, R>);
       else
-        update(update_cells_kernel<T, 2>);
-    } else {
-        hipLaunchKernelGGL((update_kernel<T>), dim3(RED_BLOCKS + se.nblk), dim3(RED_THREADS), 0, c->stream, Hq,
-                       (const T*)wk, W + (int64_t)k * vstride, C, nd, (const double*)(S.alpha + (size_t)(k - 1) * Nc),
-                       (const double*)(S.scale + (size_t)(k - 1) * Nc), m, (const int*)S.status, c->partial,
-                       (const int*)S.done, se);
-    }
+        run(update_cells_kernel<T, 2, R>);
+    };
+    if (k <= CHK_THREADS || !ride)
+      update(std::integral_constant<int, 1>{});
+    else if (k <= 2 * CHK_THREADS)
+      update(std::integral_constant<int, 2>{});
+    else
+      update(std::integral_constant<int, SMALL_ROWS>{});
     // beta_k, the scale 1/beta_k of the next basis vector and the stop test
-    if (k <= CHK_THREADS) {
+    if (ride) {
       hipLaunchKernelGGL(beta_check_kernel, dim3(Nc), dim3(RED_THREADS), 0, c->stream, (const double*)c->partial,
                          (int64_t)red_blocks, C, S, Nc, k, K, Kc, tau, tol, tol_rel, err_flag, dflag, gen);
     } else {
@@ -957,11 +974,11 @@ __global__ void __launch_bounds__(CHK_THREADS)
   double amax = 0.0;
   int M;
   if (k <= CHK_THREADS) {
-    double yr = 0.0, yi = 0.0;
-    M = cheb_expm_e1_wave(k, sa, sb, tau, jtab, &L.M, &L.inv, yr, yi, &amax);
+    double yr[1], yi[1];
+    M = cheb_expm_e1_rows<1>(k, sa, sb, tau, jtab, yr, yi, &amax);
     if (M >= 0 && t < k) {
-      y[2 * t] = yr;
-      y[2 * t + 1] = yi;
+      y[2 * t] = yr[0];
+      y[2 * t + 1] = yi[0];
     }
   } else {
     M = cheb_expm_e1(k, sa, sb, tau, L, jtab, &amax);
