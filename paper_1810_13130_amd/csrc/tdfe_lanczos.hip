@@ -103,6 +103,33 @@ __device__ void block_col_sum(double v, int C, double* sred, double* out) {
   if (t < C) out[t] = sred[t];
 }
 
+// sum of v over the block of RED_THREADS lanes, in thread 0: DPP adds within
+// each wavefront (no LDS round trip, no barrier), one exchange of the four
+// wavefronts' sums; fixed order.  The reductions between two operator passes
+// are pure latency: with a tree of eight barriers and their scalars loaded
+// after it they took 3.5 and 4.8 us of a 27 us iteration on a small box (a
+// step of ten of these 336 -> 319 us with the reductions, the update's
+// coefficients and its grid as they are here).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double lane_add(double v) {
+  return v + __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false),
+                              __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false));
+}
+__device__ __forceinline__ double block_sum(double v, double* swave) {
+  v = lane_add<0xB1, 0xf>(v);   // quad_perm [1,0,3,2]
+  v = lane_add<0x4E, 0xf>(v);   // quad_perm [2,3,0,1]
+  v = lane_add<0x141, 0xf>(v);  // row_half_mirror
+  v = lane_add<0x140, 0xf>(v);  // row_mirror: each row of 16 holds its sum
+  v = lane_add<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+  v = lane_add<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3: lane 63 holds the sum
+  if ((threadIdx.x & 63) == 63) swave[threadIdx.x >> 6] = v;
+  __syncthreads();
+  double s = swave[0];
+#pragma unroll
+  for (int w = 1; w < RED_THREADS / 64; ++w) s += swave[w];
+  return s;
+}
+
 // copy one orbital chunk of the complex128 input into basis slot 0 (type T)
 // and per-column sum of squares partials
 template <typename T>
@@ -201,6 +228,21 @@ __device__ void small_exp_block(const SmallExp& e, const int* done) {
   }
 }
 
+// Coefficients of the three-term step of one orbital (zero once it has
+// stopped): every value is loaded before any is used, and before the kernel
+// looks at its done flag, so that a short step waits for memory once.
+struct Coef {
+  double s, ca, cm;
+  __device__ __forceinline__ Coef(const int* status, const double* alpha_j, const double* s_j, const double* m_j,
+                                  int o) {
+    const int st = status[o];
+    const double sj = s_j[o], aj = alpha_j[o], mj = m_j ? m_j[o] : 1.0;
+    s = st == 0 ? sj : 0.0;
+    ca = st == 0 ? aj * sj : 0.0;
+    cm = st == 0 ? mj : 0.0;
+  }
+};
+
 // Three-term step in two reads.  The operator pass of vector j accumulates
 // s_j^2 Hbar w_j (s_0 Hbar w_0 for j = 0) onto a buffer that this kernel
 // seeded with -q_{j-1}, so that on entry Hq = (Hbar q_j - beta_{j-1} q_{j-1}) / m_j
@@ -216,8 +258,8 @@ __global__ void __launch_bounds__(RED_THREADS)
     small_exp_block<SR>(se, done);
     return;
   }
-  if (*done) return;
-  if (blockIdx.x == 0 && threadIdx.x == 0) post_progress(se.progress, se.gen, se.k - 1);
+  const int dn = *done;
+  if (blockIdx.x == 0 && threadIdx.x == 0 && !dn) post_progress(se.progress, se.gen, se.k - 1);
   const int bid = (int)blockIdx.x - se.nblk;  // streaming block index, 0..RED_BLOCKS-1
   if constexpr (sizeof(T) == 4) {
     // FP32: a lane moves one orbital's (re, im) pair as one 8-byte access
@@ -231,10 +273,9 @@ __global__ void __launch_bounds__(RED_THREADS)
     const int rstride = (RED_THREADS / Op) * (gridDim.x - se.nblk);
     double acc = 0.0;
     if (o < Nc2) {
-      const bool live = status[o] == 0;
-      const double sd = live ? s_j[o] : 0.0;
-      const double ca = live ? alpha_j[o] * sd : 0.0;
-      const double cm = live ? (m_j ? m_j[o] : 1.0) : 0.0;
+      const Coef cf(status, alpha_j, s_j, m_j, o);
+      if (dn) return;
+      const double sd = cf.s, ca = cf.ca, cm = cf.cm;
       typedef float f2 __attribute__((ext_vector_type(2)));
       f2* __restrict__ h2 = (f2*)hq;
       const f2* __restrict__ a2 = (const f2*)wa;
@@ -253,6 +294,7 @@ __global__ void __launch_bounds__(RED_THREADS)
         acc += (double)v.x * (double)v.x + (double)v.y * (double)v.y;
       }
     }
+    if (dn) return;
     block_col_sum(acc, Op, sred, sred);
     __syncthreads();
     if (threadIdx.x < C) partial[(int64_t)bid * C + threadIdx.x] = (threadIdx.x & 1) ? 0.0 : sred[threadIdx.x >> 1];
@@ -265,10 +307,9 @@ __global__ void __launch_bounds__(RED_THREADS)
   double acc = 0.0;
   if (col < C) {
     const int o = col >> 1;
-    const bool live = status[o] == 0;
-    const double s = live ? s_j[o] : 0.0;
-    const double ca = live ? alpha_j[o] * s : 0.0;
-    const double cm = live ? (m_j ? m_j[o] : 1.0) : 0.0;
+    const Coef cf(status, alpha_j, s_j, m_j, o);
+    if (dn) return;
+    const double s = cf.s, ca = cf.ca, cm = cf.cm;
     for (int64_t r = (int64_t)bid * (RED_THREADS / Cp) + rlane; r < nrows; r += rstride) {
       const int64_t i = r * C + col;
       // non-temporal: each element is touched once here, and the vectors
@@ -282,6 +323,7 @@ __global__ void __launch_bounds__(RED_THREADS)
       acc += (double)vt * (double)vt;
     }
   }
+  if (dn) return;
   block_col_sum(acc, Cp, sred, sred);
   __syncthreads();
   if (threadIdx.x < C) partial[(int64_t)bid * C + threadIdx.x] = sred[threadIdx.x];
@@ -294,7 +336,7 @@ __global__ void __launch_bounds__(RED_THREADS)
 // Blocks work row by row of DoFs (see tdfe_cells.h), a lane moves 16
 // bytes of a row (one FP64 or two FP32 orbitals).  Reads the cell results once (n^3 / p^3 vectors), w_j and
 // w_{j-1}, writes w_{j+1}; no operator output vector is kept, seeded or cleared.
-constexpr int CELL_BLOCKS = 2048;
+constexpr int CELL_BLOCKS = 2048;  // at most: one block per row of DoFs up to this
 template <typename T, int W, int SR>
 __global__ void __launch_bounds__(RED_THREADS)
     update_cells_kernel(const T* __restrict__ e, const T* __restrict__ wa, const T* __restrict__ wp,
@@ -309,8 +351,8 @@ __global__ void __launch_bounds__(RED_THREADS)
     small_exp_block<SR>(se, done);
     return;
   }
-  if (*done) return;
-  if (blockIdx.x == 0 && threadIdx.x == 0) post_progress(se.progress, se.gen, se.k - 1);
+  const int dn = *done;
+  if (blockIdx.x == 0 && threadIdx.x == 0 && !dn) post_progress(se.progress, se.gen, se.k - 1);
   const int bid = (int)blockIdx.x - se.nblk;
   const int C2 = C / W;
   const int Op = C2 <= 4 ? 4 : (C2 <= 8 ? 8 : (C2 <= 16 ? 16 : 32));
@@ -325,13 +367,15 @@ __global__ void __launch_bounds__(RED_THREADS)
 #pragma unroll
     for (int q = 0; q < NO; ++q) {
       const int oo = o * NO + q;
-      const bool live = status[oo] == 0;
-      ca[q] = live ? alpha_j[oo] * s_j[oo] : 0.0;
-      cm[q] = live ? (m_j ? m_j[oo] : 1.0) : 0.0;
-      cb[q] = live && wp ? m_j[oo] * s_p[oo] : 0.0;
+      const Coef cf(status, alpha_j, s_j, m_j, oo);
+      const double sp = s_p[oo];
+      ca[q] = cf.ca;
+      cm[q] = cf.cm;
+      cb[q] = wp ? cf.cm * sp : 0.0;
     }
+    if (dn) return;
     const int nrows = M.NyI * M.NzI;
-    for (int r = bid; r < nrows; r += CELL_BLOCKS) {
+    for (int r = bid; r < nrows; r += (int)gridDim.x - se.nblk) {
       const CellRow R = cell_row(M, 1 + r % M.NyI, 1 + r / M.NyI);
       for (int I = xl; I < M.NxI; I += XL) {
         CellLane<T, W> L;
@@ -352,6 +396,7 @@ __global__ void __launch_bounds__(RED_THREADS)
       }
     }
   }
+  if (dn) return;
 #pragma unroll
   for (int q = 0; q < NO; ++q) {
     block_col_sum(acc[q], Op, sred, sred);
@@ -370,21 +415,18 @@ __global__ void __launch_bounds__(RED_THREADS)
 __global__ void __launch_bounds__(RED_THREADS)
     finalize_pairs_kernel(const double* __restrict__ partial, int64_t nblocks, int C, double* out, int mode,
                           double* scale0, double* cs0, const double* mult, const int* done) {
-  __shared__ double sred[RED_THREADS];
-  if (done && *done) return;
+  __shared__ double swave[RED_THREADS / 64];
   const int o = blockIdx.x;
+  const int dn = done ? *done : 0;
+  const double mo = mult ? mult[o] : 1.0;
   double acc = 0.0;
-  for (int64_t b = threadIdx.x; b < nblocks; b += RED_THREADS)
-    acc += partial[b * C + 2 * o] + partial[b * C + 2 * o + 1];
-  sred[threadIdx.x] = acc;
-  __syncthreads();
-  for (int s = RED_THREADS / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) sred[threadIdx.x] += sred[threadIdx.x + s];
-    __syncthreads();
+  for (int64_t b = threadIdx.x; b < nblocks; b += RED_THREADS) {
+    const double2 p2 = *(const double2*)(partial + b * C + 2 * o);
+    acc += p2.x + p2.y;
   }
-  if (threadIdx.x == 0) {
-    double v = sred[0];
-    if (mode == 0 && mult) v *= mult[o] * mult[o];
+  double v = block_sum(acc, swave);
+  if (threadIdx.x == 0 && !dn) {
+    if (mode == 0 && mult) v *= mo * mo;
     if (mode >= 1) v = sqrt(v);
     out[o] = v;
     if (mode >= 2) {
@@ -430,10 +472,8 @@ __global__ void __launch_bounds__(RED_THREADS)
 // convergence (from Lyr / Lyi, or already in its result slot if these are
 // null), status; called by nthreads lanes
 __device__ void stop_test(Scal S, int o, int Nc, int k, int k_max, int kcap, double tau, double tol, double tol_rel,
-                          int M,
-                          double amax,
-                          double bk, double ylr, double yli, const double* Lyr, const double* Lyi, int nthreads,
-                          int* err_flag, int* host_flag, int gen) {
+                          int M, double amax, double nrm, double bk, double ylr, double yli, const double* Lyr,
+                          const double* Lyi, int nthreads, int* err_flag, int* host_flag, int gen) {
   const int t = threadIdx.x;
   int fin = 0;
   if (M < 0) {
@@ -448,10 +488,10 @@ __device__ void stop_test(Scal S, int o, int Nc, int k, int k_max, int kcap, dou
       }
     }
   } else {
-    const double eps = fabs(tau) * bk * S.nrm[o] * sqrt(ylr * ylr + yli * yli);
+    const double eps = fabs(tau) * bk * nrm * sqrt(ylr * ylr + yli * yli);
     const bool happy = bk <= 1e-14 * amax;
     // mixed precision: no tighter than the storage precision of the basis allows
-    const bool conv = (eps <= fmax(tol, tol_rel * S.nrm[o])) || happy;
+    const bool conv = (eps <= fmax(tol, tol_rel * nrm)) || happy;
     // a NaN or Inf in beta_k or in the small exponential ends the orbital at
     // once (status 4, reported as TDFE_ENONFINITE) instead of running to k_max
     const bool nonfinite = !isfinite(eps);
@@ -503,7 +543,7 @@ __global__ void __launch_bounds__(CHK_THREADS)
   __syncthreads();
   double amax = 0.0;
   const int M = cheb_expm_e1(k, sa, sb, tau, L, jtab + (size_t)o * TDFE_JTAB_STRIDE, &amax);
-  stop_test(S, o, Nc, k, k_max, kcap, tau, tol, tol_rel, M, amax, sb[k - 1], L.yr[k - 1], L.yi[k - 1], L.yr, L.yi,
+  stop_test(S, o, Nc, k, k_max, kcap, tau, tol, tol_rel, M, amax, S.nrm[o], sb[k - 1], L.yr[k - 1], L.yi[k - 1], L.yr, L.yi,
             CHK_THREADS, err_flag, host_flag, gen);
 }
 
@@ -513,31 +553,25 @@ __global__ void __launch_bounds__(CHK_THREADS)
 __global__ void __launch_bounds__(RED_THREADS)
     beta_check_kernel(const double* __restrict__ partial, int64_t nblocks, int C, Scal S, int Nc, int k, int k_max,
                       int kcap, double tau, double tol, double tol_rel, int* err_flag, int* host_flag, int gen) {
-  __shared__ double sred[RED_THREADS];
-  if (*S.done) return;
+  __shared__ double swave[RED_THREADS / 64];
   const int o = blockIdx.x;
-  const int t = threadIdx.x;
+  const int dn = *S.done, st = S.status[o];
+  const double amax = S.ext[2 * o + 0], terms = S.ext[2 * o + 1], nrm = S.nrm[o];
+  const double2 yl = *(const double2*)(S.y + ((size_t)o * k_max + k - 1) * 2);
   double acc = 0.0;
-  for (int64_t b = t; b < nblocks; b += RED_THREADS) acc += partial[b * C + 2 * o] + partial[b * C + 2 * o + 1];
-  sred[t] = acc;
-  __syncthreads();
-  for (int s = RED_THREADS / 2; s > 0; s >>= 1) {
-    if (t < s) sred[t] += sred[t + s];
-    __syncthreads();
+  for (int64_t b = threadIdx.x; b < nblocks; b += RED_THREADS) {
+    const double2 p2 = *(const double2*)(partial + b * C + 2 * o);
+    acc += p2.x + p2.y;
   }
-  if (t != 0) return;
-  const double bk = sqrt(sred[0]);
+  const double bk = sqrt(block_sum(acc, swave));
+  if (threadIdx.x != 0 || dn) return;
   const double sc = bk > 0.0 ? 1.0 / bk : 0.0;
   S.beta[(size_t)(k - 1) * Nc + o] = bk;
   S.scale[(size_t)k * Nc + o] = sc;
   S.cs[(size_t)k * Nc + o] = sc * sc;
-  if (S.status[o] != 0) return;
-  const double amax = S.ext[2 * o + 0];
-  const int M = (int)S.ext[2 * o + 1];
-  const double ylr = S.y[((size_t)o * k_max + k - 1) * 2 + 0];
-  const double yli = S.y[((size_t)o * k_max + k - 1) * 2 + 1];
-  stop_test(S, o, Nc, k, k_max, kcap, tau, tol, tol_rel, M, amax, bk, ylr, yli, nullptr, nullptr, 1, err_flag,
-            host_flag, gen);
+  if (st != 0) return;
+  stop_test(S, o, Nc, k, k_max, kcap, tau, tol, tol_rel, (int)terms, amax, nrm, bk, yl.x, yl.y, nullptr, nullptr, 1,
+            err_flag, host_flag, gen);
 }
 
 // z = ||psi|| sum_j y_j s_j w_j, written into the complex128 output chunk.
@@ -676,8 +710,9 @@ tdfe_status run_chunk(tdfe_ctx* c, const void* vw, const double* in, double* out
   // per-cell operator output summed by the update itself (the nonlocal term
   // adds to an assembled vector)
   const bool cells = c->n_proj == 0 && tdfe_cells_ok(c, C, sizeof(T) == 4);
-  const int red_blocks = cells ? CELL_BLOCKS : RED_BLOCKS;  // rows of the update's norm partials
   const CellMap map{c->ncx, c->ncy, c->ncz, c->p, c->Nx - 2, c->Ny - 2, c->Nz - 2};
+  // streaming blocks of the update, and rows of its norm partials
+  const int red_blocks = cells ? std::min(CELL_BLOCKS, map.NyI * map.NzI) : RED_BLOCKS;
   hipLaunchKernelGGL(init_scal_kernel, dim3(1), dim3(64), 0, c->stream, S, Nc);
   if (!cells) TDFE_TRY(tdfe_zero(c, Hq, (size_t)vstride * sizeof(T)));
   TDFE_TRY(tdfe_zero(c, err_flag, sizeof(int)));
@@ -745,7 +780,7 @@ tdfe_status run_chunk(tdfe_ctx* c, const void* vw, const double* in, double* out
     auto update = [&](auto rows) {
       constexpr int R = decltype(rows)::value;
       if (!cells) {
-        hipLaunchKernelGGL((update_kernel<T, R>), dim3(RED_BLOCKS + se.nblk), dim3(RED_THREADS), 0, c->stream, Hq,
+        hipLaunchKernelGGL((update_kernel<T, R>), dim3(red_blocks + se.nblk), dim3(RED_THREADS), 0, c->stream, Hq,
                            (const T*)wk, W + (int64_t)k * vstride, C, nd,
                            (const double*)(S.alpha + (size_t)(k - 1) * Nc),
                            (const double*)(S.scale + (size_t)(k - 1) * Nc), m, (const int*)S.status, c->partial,
@@ -753,7 +788,7 @@ tdfe_status run_chunk(tdfe_ctx* c, const void* vw, const double* in, double* out
         return;
       }
       auto run = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(CELL_BLOCKS + se.nblk), dim3(RED_THREADS), 0, c->stream, (const T*)c->eloc,
+        hipLaunchKernelGGL(kernel, dim3(red_blocks + se.nblk), dim3(RED_THREADS), 0, c->stream, (const T*)c->eloc,
                            (const T*)wk, k >= 2 ? (const T*)(wk - vstride) : (const T*)nullptr,
                            W + (int64_t)k * vstride, C, map, (const double*)(S.alpha + (size_t)(k - 1) * Nc),
                            (const double*)(S.scale + (size_t)(k - 1) * Nc), m,
