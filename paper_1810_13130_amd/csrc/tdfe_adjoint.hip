@@ -153,29 +153,46 @@ __global__ void __launch_bounds__(N* N* CB) basis_quad_kernel(BasisParams P) {
 
 // -------------------------------------------------------------------------------------------
 // Vb_q (+)= tau varpi_q detJ_q Im[ sum_o sum_{j<kz} conj(A_qj) sum_{l<kx} C_jl B_ql ]
-// Cm rows are padded with zeros to a multiple of KT
+// Cm: [o][l][j], ks of each, C_jl at l ks + j
+//
+// A wavefront takes 64 Gauss points and one tile of KT values of j of one
+// orbital after the other; the block's wavefronts share the points and take
+// every BW-th tile, so that even a small mesh fills the chip, and their sums
+// meet in LDS.  The tile's rows of C are wavefront-uniform and contiguous
+// (scalar loads); the basis values, 32 bytes per (point, j) pair and twice
+// k Nc of them, are what has to come from memory.
+// 110,592 points, 4 orbitals, some 20 of each kind: 358 us with a thread per
+// point that took all tiles (1.7 wavefronts a SIMD), 141 us so.
 // -------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(EW)
+constexpr int BW = 4;
+__global__ void __launch_bounds__(64 * BW)
     bilinear_kernel(const double2* __restrict__ A, const double2* __restrict__ B, const double2* __restrict__ Cm,
                     const int* __restrict__ kz, const int* __restrict__ kx, int Nc, int ks, int64_t n_quad, double tau,
                     const double* __restrict__ wdet, double* __restrict__ out) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= n_quad) return;
-  double ar = 0.0, ai = 0.0;
+  __shared__ double sum[BW][64];
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t q = (int64_t)blockIdx.x * 64 + lane;
+  const int64_t qr = q < n_quad ? q : n_quad - 1;
+  double ai = 0.0;
+  int skip = w;  // tiles until this wavefront's next
   for (int o = 0; o < Nc; ++o) {
     const int kzo = kz[o], kxo = kx[o];
-    const double2* Ao = A + (int64_t)o * ks * n_quad + q;
-    const double2* Bo = B + (int64_t)o * ks * n_quad + q;
+    const double2* Ao = A + (int64_t)o * ks * n_quad + qr;
+    const double2* Bo = B + (int64_t)o * ks * n_quad + qr;
     const double2* Co = Cm + (int64_t)o * ks * ks;
-    for (int jt = 0; jt < kzo; jt += KT) {
+    const int tiles = (kzo + KT - 1) / KT;
+    for (; skip < tiles; skip += BW) {
+      const int jt = skip * KT;
       double tr[KT], ti[KT];
 #pragma unroll
       for (int u = 0; u < KT; ++u) tr[u] = ti[u] = 0.0;
+#pragma unroll 4
       for (int l = 0; l < kxo; ++l) {
         const double2 b = Bo[(int64_t)l * n_quad];
 #pragma unroll
         for (int u = 0; u < KT; ++u) {
-          const double2 cc = Co[(jt + u) * ks + l];
+          const double2 cc = Co[(int64_t)l * ks + jt + u];
           tr[u] += cc.x * b.x - cc.y * b.y;
           ti[u] += cc.x * b.y + cc.y * b.x;
         }
@@ -183,15 +200,21 @@ __global__ void __launch_bounds__(EW)
 #pragma unroll
       for (int u = 0; u < KT; ++u) {
         if (jt + u < kzo) {
+          // imaginary part of conj(a) t
           const double2 a = Ao[(int64_t)(jt + u) * n_quad];
-          // conj(a) * t
-          ar += a.x * tr[u] + a.y * ti[u];
           ai += a.x * ti[u] - a.y * tr[u];
         }
       }
     }
+    skip -= tiles;
   }
-  out[q] = tau * ai * wdet[q];
+  sum[w][lane] = ai;
+  __syncthreads();
+  if (w == 0 && q < n_quad) {
+#pragma unroll
+    for (int v = 1; v < BW; ++v) ai += sum[v][lane];
+    out[q] = tau * ai * wdet[q];
+  }
 }
 
 // -------------------------------------------------------------------------------------------
@@ -306,7 +329,7 @@ GradLayout layout(const tdfe_ctx* c, int n_orb, int n_steps, int ckpt, int ks) {
   g.o_qx_p = take(g.qbasis);
   g.o_qx_c = take(g.qbasis);
   g.o_qz = take(g.qbasis);
-  g.o_cm = take((size_t)n_orb * ks * ks * 2 * sizeof(double));
+  g.o_cm = take((size_t)n_orb * ks * ks * 2 * sizeof(double));  // read up to KT - 1 entries past its end, into o_k
   g.o_k = take((size_t)2 * n_orb * sizeof(int));
   g.o_de = take((size_t)n_steps * sizeof(double));
   g.o_part = take((size_t)RED_BLOCKS * sizeof(double));
@@ -458,8 +481,8 @@ bool small_matrix_impl(const KrylovRecord& X, const KrylovRecord& Z, int Nc, int
           sr += Tr[(size_t)j * kx + b] * u;
           si += Ti[(size_t)j * kx + b] * u;
         }
-        Co[((size_t)j * ks + l) * 2 + 0] = nn * sr;
-        Co[((size_t)j * ks + l) * 2 + 1] = nn * si;
+        Co[((size_t)l * ks + j) * 2 + 0] = nn * sr;
+        Co[((size_t)l * ks + j) * 2 + 1] = nn * si;
       }
   };
   const int nt = std::max(1, std::min({Nc, 8, (int)std::thread::hardware_concurrency()}));
@@ -583,7 +606,7 @@ struct Grad {
     int* kk = (int*)(base + g.o_k);
     TDFE_HIP(c, hipMemcpyAsync(Cm, Cm_host.data(), Cm_host.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
     TDFE_HIP(c, hipMemcpyAsync(kk, kk_host.data(), kk_host.size() * sizeof(int), hipMemcpyHostToDevice, c->stream));
-    hipLaunchKernelGGL(bilinear_kernel, dim3(nblk(c->n_quad)), dim3(EW), 0, c->stream, (const double2*)Zr.quad,
+    hipLaunchKernelGGL(bilinear_kernel, dim3((unsigned)((c->n_quad + 63) / 64)), dim3(64 * BW), 0, c->stream, (const double2*)Zr.quad,
                        (const double2*)X.quad, (const double2*)Cm, (const int*)kk, (const int*)(kk + n_orb), n_orb,
                        g.ks, c->n_quad, tau, c->wdet, Vb);
     TDFE_HIP(c, hipGetLastError());
