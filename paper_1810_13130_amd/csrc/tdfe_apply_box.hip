@@ -66,7 +66,7 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
   constexpr int VOL = N * N * N;
   constexpr int THREADS = CPB * N * CB;
   // 1D tables of order N, folded, as compile-time constants
-  constexpr BoxFoldSet<N> FS = make_box_foldset<N>();
+  constexpr BoxFoldSet<N> FS = make_box_foldset<N, sizeof(T) == 4>();
   auto wprod = [&](int b, int c) { return (T)(FS.wq[b] * FS.wq[c]); };
   __shared__ T sX[CPB * VOL * CB];
   __shared__ T sV[CPB * VOL];  // weighted potential of the block's cells
@@ -187,7 +187,8 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
       T line[N], o1[N], o2[N];
 #pragma unroll
       for (int i = 0; i < N; ++i) line[i] = u[i][c];
-      eo2<T, N, 1, 1>(FS.B, FS.SB, line, o1, o2);
+      eo<T, N, 1>(FS.B, line, o1);
+      eo0<T, N>(FS.SB, line, o2);
 #pragma unroll
       for (int a = 0; a < N; ++a) {
         sX[sidx(pl, a, c)] = o1[a];
@@ -248,7 +249,7 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
 #pragma unroll
   for (int b = 0; b < N; ++b) {
     T d[N];
-    eo<T, N, 1>(FS.S, uq[b], d);
+    eo0<T, N>(FS.S, uq[b], d);
     const T g = gz * (T)FS.wq[b];
 #pragma unroll
     for (int c = 0; c < N; ++c) acc[b][c] += g * d[c];
@@ -260,7 +261,7 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
     T l[N], d[N];
 #pragma unroll
     for (int b = 0; b < N; ++b) l[b] = uq[b][c];
-    eo<T, N, 1>(FS.S, l, d);
+    eo0<T, N>(FS.S, l, d);
     const T g = gy * (T)FS.wq[c];
     T le = 0;
 #pragma unroll

@@ -81,7 +81,7 @@ constexpr void split_tab(const double* A, int N, bool transpose, SplitT<double>&
     }
 }
 
-template <int N>
+template <int N, bool F32>
 constexpr PairSet make_pairset() {
   const tdfe1d::Rule R = tdfe1d::make_rule(N - 1);
   const GaussStiff K = make_gauss_stiff(R);
@@ -93,26 +93,48 @@ constexpr PairSet make_pairset() {
   split_tab(R.B, N, false, F.zB);
   split_tab(R.B, N, true, F.zBt);
   split_tab(K.S, N, false, F.zS);
+  if (F32) {
+    fit_stiffness(F.fS.E, F.fS.O, PH, N, nullptr, R.eta);
+    fit_stiffness(F.fSB.E, F.fSB.O, PH, N, nullptr, R.xi);
+    // the split S: rows that sum to zero
+    for (int a = 0; a < N / 2; ++a) {
+      double row[TDFE_MAXN]{}, one[TDFE_MAXN]{};
+      for (int i = 0; i < N / 2; ++i) {
+        row[i] = F.zS.own[a * PH + i];
+        row[N / 2 + i] = F.zS.oth[a * PH + i];
+        one[i] = one[N / 2 + i] = 1.0;
+      }
+      fit_f32(row, N, one, 0.0);
+      for (int i = 0; i < N / 2; ++i) {
+        F.zS.own[a * PH + i] = row[i];
+        F.zS.oth[a * PH + i] = row[N / 2 + i];
+      }
+    }
+  }
   for (int i = 0; i < TDFE_MAXN; ++i) F.wq[i] = R.wq[i];
   return F;
 }
 
 // out[a] = sum_i A[a][i] in[i], A folded with A[n-1-a][n-1-i] = A[a][i] (even N)
-template <typename T, int N>
+// ZERO: A sends a constant to zero (as eo0)
+template <typename T, int N, bool ZERO = false>
 __device__ __forceinline__ void eoe(const FoldE<double>& F, const T* in, T* out) {
-  constexpr int H = N / 2;
+  constexpr int H = N / 2, HE = ZERO ? H - 1 : H;
   T e[H], o[H];
 #pragma unroll
   for (int i = 0; i < H; ++i) {
     e[i] = in[i] + in[N - 1 - i];
     o[i] = in[i] - in[N - 1 - i];
   }
+  if constexpr (ZERO)
+#pragma unroll
+    for (int i = 0; i < HE; ++i) e[i] -= e[H - 1];
 #pragma unroll
   for (int a = 0; a < H; ++a) {
     T Pv = 0, Qv = 0;
 #pragma unroll
     for (int i = 0; i < H; ++i) {
-      Pv += (T)F.E[a * PH + i] * e[i];
+      if (i < HE) Pv += (T)F.E[a * PH + i] * e[i];
       Qv += (T)F.O[a * PH + i] * o[i];
     }
     out[a] = Pv + Qv;
@@ -165,7 +187,7 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
   constexpr int H = N / 2;
   constexpr int VOL = N * N * N;
   constexpr int THREADS = 2 * CPB * N * CB;
-  constexpr PairSet FS = make_pairset<N>();
+  constexpr PairSet FS = make_pairset<N, sizeof(T) == 4>();
   __shared__ T sX[CPB * VOL * CB];
   __shared__ T sV[CPB * VOL];
   __shared__ double sRed[THREADS];
@@ -293,7 +315,7 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
 #pragma unroll
       for (int i = 0; i < N; ++i) line[i] = u[i][c];
       eoe<T, N>(FS.fB, line, o1);
-      eoe<T, N>(FS.fSB, line, o2);
+      eoe<T, N, true>(FS.fSB, line, o2);
 #pragma unroll
       for (int a = 0; a < N; ++a) {
         sX[sidx(pl, a, zg(c))] = o1[a];
@@ -368,7 +390,7 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
     T l[N], d[N];
 #pragma unroll
     for (int b = 0; b < N; ++b) l[b] = uq[b][c];
-    eoe<T, N>(FS.fS, l, d);
+    eoe<T, N, true>(FS.fS, l, d);
     const T g = gy * wc[c];
     T le = 0;
 #pragma unroll

@@ -73,7 +73,7 @@ constexpr QHalf quad_half(const double* A, int N, int S, bool transpose, double 
 // trilinear cells: B (folded -> parts), Dg (parts -> parts), Dg^T (folded ->
 // folded), B^T (folded -> parts); box cells: B, S B (folded -> parts), S
 // (parts -> folded), B^T
-template <int N, bool BOX>
+template <int N, bool BOX, bool F32>
 constexpr QuadTables make_quad_tables() {
   const tdfe1d::Rule R = tdfe1d::make_rule(N - 1);
   QuadTables Q{};
@@ -82,6 +82,11 @@ constexpr QuadTables make_quad_tables() {
     const GaussStiff K = make_gauss_stiff(R);
     Q.t[1] = quad_half(K.SB, N, 1, false, 1.0);
     Q.t[2] = quad_half(K.S, N, 1, false, 4.0);
+    static_assert(!F32 || N % 2 == 0);
+    if (F32) {
+      fit_stiffness(Q.t[1].E, Q.t[1].O, 4, N, nullptr, R.xi);
+      fit_stiffness(Q.t[2].E, Q.t[2].O, 4, N, nullptr, R.eta);
+    }
   } else {
     Q.t[1] = quad_half(R.Dg, N, -1, false, 2.0);
     Q.t[2] = quad_half(R.Dg, N, -1, true, 2.0);
@@ -90,8 +95,8 @@ constexpr QuadTables make_quad_tables() {
   return Q;
 }
 
-template <int N, bool BOX>
-__device__ const QuadTables quad_tables = make_quad_tables<N, BOX>();
+template <int N, bool BOX, bool F32>
+__device__ const QuadTables quad_tables = make_quad_tables<N, BOX, F32>();
 
 template <typename T>
 struct QuadParams {
@@ -184,6 +189,13 @@ __device__ __forceinline__ void qmul0(const QTab<double>& t, double e, double o,
   qmul(t, e, o, 0.0, 0.0, p, q);
 }
 
+// what a table whose rows sum to zero (S, S B) is applied to: FP32 less the
+// value of the quad's last lane (see eo0), FP64 as it is
+__device__ __forceinline__ double off_quad(double v) { return v; }
+__device__ __forceinline__ float off_quad(float v) {
+  return v - __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xFF, 0xf, 0xf, false));
+}
+
 template <typename T, int N, bool BOX>
 constexpr int quad_wpe() {
   return sizeof(T) == 8 && !BOX && N == 6 ? 3 : 4;
@@ -256,7 +268,7 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(qua
   constexpr int PAD = ODD ? 0 : QC;
   constexpr int LX = N * QC + PAD, LY = N * LX + PAD;
   constexpr FoldSet<N> FS = make_foldset<N>();
-  constexpr BoxFoldSet<N> FB = make_box_foldset<N>();
+  constexpr BoxFoldSet<N> FB = make_box_foldset<N, sizeof(T) == 4>();
   // FP64 on trilinear cells at n = 7: two blocks per CU (14 waves) need 128
   // registers per lane, and the flux phase holds 158 (26 spilled values of it
   // made scratch traffic of 2.8 GB per launch): half of its arrays wait in LDS
@@ -303,7 +315,7 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(qua
     }
   }
   T tr = 0;
-  if (t < 128) tr = (T)((const double*)&quad_tables<N, BOX>)[t];
+  if (t < 128) tr = (T)((const double*)&quad_tables<N, BOX, sizeof(T) == 4>)[t];
   double cr = 0.0;
   if constexpr (!BOX)
     if (t < 24) cr = P.corners[(int64_t)cell * 24 + t];
@@ -446,7 +458,7 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(qua
 #pragma unroll
         for (int c = 0; c < N; ++c) {
           T p1, q1;
-          qmul0(td, r1[c], r2[c], p1, q1);
+          qmul0(td, off_quad(r1[c]), r2[c], p1, q1);
           t1[c] = p1 + q1;
           t2[c] = p1 - q1;
           qmul0(tb, r1[c], r2[c], p1, q1);
@@ -539,10 +551,10 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(qua
       }
       // z and y stiffness terms, the quadratic form
       T d[N];
-      eo<T, N, 1>(FB.S, ue, d);
+      eo0<T, N>(FB.S, ue, d);
 #pragma unroll
       for (int c = 0; c < N; ++c) se[c] += gz * d[c];
-      eo<T, N, 1>(FB.S, uo, d);
+      eo0<T, N>(FB.S, uo, d);
 #pragma unroll
       for (int c = 0; c < N; ++c) so[c] += gz * d[c];
       T le = 0;
@@ -550,7 +562,7 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(qua
       for (int c = 0; c < N; ++c) {
         const T g = gy * (T)FB.wq[c];
         T p1, q1;
-        qmul0(ts, ue[c], uo[c], p1, q1);
+        qmul0(ts, off_quad(ue[c]), uo[c], p1, q1);
         se[c] += g * p1;
         so[c] += g * q1;
         acc_energy<T>(energy, le, ue[c] * se[c] + uo[c] * so[c]);

@@ -58,6 +58,60 @@ constexpr GaussStiff make_gauss_stiff(const tdfe1d::Rule& R) {
   return G;
 }
 
+// FP32 entries of S and S B.  Rounded one by one they err by half a unit in
+// the last place of entries up to 42, the same on every cell, and what a smooth
+// orbital sees of it (on a cell little more than 1 and x) adds up over the
+// terms of an exponential; derivatives, whose square S is, send that to zero
+// by themselves.  So the entries are rounded together: the even half such that
+// its columns sum to zero (a constant has no stiffness; the rows do by eo0),
+// the odd half such that x keeps its image.  fit_f32: n entries rounded, then
+// one after the other moved by a few units where it brings sum_i w_i a_i
+// nearest to the target.
+constexpr void fit_f32(double* a, int n, const double* w, double target) {
+  for (int i = 0; i < n; ++i) a[i] = (double)(float)a[i];
+  for (int pass = 0; pass < 8; ++pass) {
+    double r = -target;
+    for (int i = 0; i < n; ++i) r += w[i] * a[i];
+    int best = -1;
+    double left = r < 0.0 ? -r : r, moved = 0.0;
+    for (int i = 0; i < n; ++i) {
+      if (w[i] == 0.0) continue;
+      const double v = (double)(float)(a[i] - r / w[i]);
+      const double rest = r + w[i] * (v - a[i]), ar = rest < 0.0 ? -rest : rest;
+      if (ar < left) {
+        left = ar;
+        best = i;
+        moved = v;
+      }
+    }
+    if (best < 0) return;
+    a[best] = moved;
+  }
+}
+// E, O: the halves, rows of ld; mr: the middle row (odd N); x: the input points
+constexpr void fit_stiffness(double* E, double* O, int ld, int N, double* mr, const double* x) {
+  const int H = N / 2, HE = (N & 1) ? H : H - 1;
+  for (int a = 0; a < H; ++a) {
+    double target = 0.0;
+    for (int i = 0; i < H; ++i) target += x[i] * O[a * ld + i];
+    fit_f32(O + a * ld, H, x, target);
+  }
+  for (int i = 0; i < HE; ++i) {
+    double col[TDFE_MAXN]{}, w[TDFE_MAXN]{};
+    for (int a = 0; a < H; ++a) {
+      col[a] = E[a * ld + i];
+      w[a] = 2.0;
+    }
+    if (N & 1) {
+      col[H] = mr[i];
+      w[H] = 1.0;
+    }
+    fit_f32(col, H + (N & 1), w, 0.0);
+    for (int a = 0; a < H; ++a) E[a * ld + i] = col[a];
+    if (N & 1) mr[i] = col[H];
+  }
+}
+
 constexpr void fold_c(const double* A, int N, int S, bool transpose, Folded<double>& F) {
   const int H = N / 2;
   for (int a = 0; a < H; ++a)
@@ -94,7 +148,7 @@ struct BoxFoldSet {
   Folded<double> B, Bt, S, SB;
   double wq[TDFE_MAXN];
 };
-template <int N>
+template <int N, bool F32>
 constexpr BoxFoldSet<N> make_box_foldset() {
   const tdfe1d::Rule R = tdfe1d::make_rule(N - 1);
   const GaussStiff K = make_gauss_stiff(R);
@@ -103,6 +157,10 @@ constexpr BoxFoldSet<N> make_box_foldset() {
   fold_c(R.B, N, 1, true, F.Bt);
   fold_c(K.S, N, 1, false, F.S);
   fold_c(K.SB, N, 1, false, F.SB);
+  if (F32) {
+    fit_stiffness(F.S.E, F.S.O, EO_MAX_H, N, F.S.mr, R.eta);
+    fit_stiffness(F.SB.E, F.SB.O, EO_MAX_H, N, F.SB.mr, R.xi);
+  }
   for (int i = 0; i < TDFE_MAXN; ++i) F.wq[i] = R.wq[i];
   return F;
 }
@@ -279,6 +337,42 @@ template <typename T, int N, int S1, int S2, typename FT>
 __device__ __forceinline__ void eo2(const Folded<FT>& F1, const Folded<FT>& F2, const T* in, T* out1, T* out2) {
   eo<T, N, S1>(F1, in, out1);
   eo<T, N, S2>(F2, in, out2);
+}
+
+// eo for a matrix that sends a constant to zero (S, S B): the middle value, or
+// the middle pair's sum, is taken off the folded sums first, and its column is
+// left out.  As many operations, and the rounding of the entries acts on the
+// differences along the line, not on the values.  With eo and entries rounded
+// one by one an FP32 exponential of smooth orbitals on box cells was off by
+// 4.5e-7 at p = 6 and 2.8e-7 or more at p = 7; with eo0 and fit_stiffness by
+// 1.7e-7 and 2.0e-7, which is what derivatives give.
+template <typename T, int N, typename FT>
+__device__ __forceinline__ void eo0(const Folded<FT>& F, const T* in, T* out) {
+  constexpr int H = N / 2, HE = (N & 1) ? H : H - 1;
+  const T mid = (N & 1) ? 2 * in[H] : in[H - 1] + in[H];
+  T e[HE > 0 ? HE : 1], o[H];
+#pragma unroll
+  for (int i = 0; i < H; ++i) {
+    if (i < HE) e[i] = in[i] + in[N - 1 - i] - mid;
+    o[i] = in[i] - in[N - 1 - i];
+  }
+#pragma unroll
+  for (int a = 0; a < H; ++a) {
+    T Pv = 0, Qv = 0;
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+      if (i < HE) Pv += (T)F.E[a * EO_MAX_H + i] * e[i];
+      Qv += (T)F.O[a * EO_MAX_H + i] * o[i];
+    }
+    out[a] = Pv + Qv;
+    out[N - 1 - a] = Pv - Qv;
+  }
+  if constexpr (N & 1) {
+    T m = 0;
+#pragma unroll
+    for (int i = 0; i < H; ++i) m += (T)F.mr[i] * e[i];
+    out[H] = m;
+  }
 }
 
 // host: fold an N x N table (row-major, stride TDFE_MAXN) with symmetry S

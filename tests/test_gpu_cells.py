@@ -35,7 +35,8 @@ def _cap(monkeypatch, cfg, cap):
 
 @pytest.mark.parametrize("cap", [None, "scatter", "slices"])
 @pytest.mark.parametrize("mesh,p,n_orb", [("box", 6, 5), ("box", 7, 8), ("graded", 6, 8), ("graded", 6, 9),
-                                          ("graded", 7, 17), ("box", 5, 19), ("graded", 4, 3), ("box", 1, 1)])
+                                          ("graded", 7, 17), ("box", 5, 19), ("graded", 4, 3), ("box", 1, 1),
+                                          ("box", 2, 1), ("box", 4, 1), ("box", 4, 2), ("box", 6, 2)])
 def test_operator_output_forms(mesh, p, n_orb, cap, monkeypatch):
     cfg = _cfg(mesh, p, n_orb)
     _cap(monkeypatch, cfg, cap)
@@ -53,7 +54,8 @@ def test_operator_output_forms(mesh, p, n_orb, cap, monkeypatch):
 
 
 @pytest.mark.parametrize("cap", [None, "scatter"])
-@pytest.mark.parametrize("mesh,p,n_orb", [("box", 7, 7), ("graded", 7, 9), ("graded", 6, 6), ("box", 5, 3)])
+@pytest.mark.parametrize("mesh,p,n_orb", [("box", 7, 7), ("graded", 7, 9), ("graded", 6, 6), ("box", 5, 3),
+                                          ("box", 3, 1), ("box", 5, 2)])
 def test_fp32_operator_output_forms(mesh, p, n_orb, cap, monkeypatch):
     cfg = _cfg(mesh, p, n_orb)
     _cap(monkeypatch, cfg, cap)
@@ -98,4 +100,23 @@ def test_one_column_stiffness_on_curved_cells(p):
     phi, _ = ctx.scf_fields(torch.from_numpy(x).cuda(), w=False)
     ref, _ = scf.Hartree(m, Z, R, tol=1e-13).solve(scf.density(m, x))
     assert rel(phi.cpu().numpy(), ref) < 1e-10
+    ctx.close()
+
+
+@pytest.mark.parametrize("p,n_orb", [(2, 1), (3, 2), (4, 3), (5, 2), (6, 1), (6, 5), (7, 3), (7, 5)])
+def test_fp32_exponential_of_smooth_orbitals(p, n_orb):
+    """The rounding of the FP32 stiffness entries is the same on every cell, so
+    a smooth orbital sums it up over the series; rounded together they must
+    not add to the storage rounding: 2^-24 sqrt(k) of some 12 iterations, 2.1e-7
+    in the 2-norm, with half as much again."""
+    cfg = W.scaled(W.CONFIGS[2], ncell=(8, 8, 8), p=p, n_orb=n_orb)
+    ctx = gpu_context(cfg, n_orb=n_orb, k_max=64, precision=1)
+    m, vq = oracle_mesh(cfg)
+    x = W.initial_psibar(cfg, m.dof_xyz, m.M)[:, :n_orb]
+    psi = torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    ctx.lanczos_expm(psi, 0.05, 1e-12)
+    ref = lanczos.lanczos_expm(lambda z: op.apply_Hbar(m, vq, z), x, 0.05, 1e-12, 64)[0]
+    err = np.linalg.norm(psi.cpu().numpy() - ref) / np.linalg.norm(ref)
+    print(f"[fp32 exponential] p={p} n_orb={n_orb} {err:.2e}", flush=True)
+    assert err < 3.2e-7
     ctx.close()
