@@ -347,3 +347,20 @@ tdfe_status tdfe_octree_bind(tdfe_ctx* c);
 
 // workspace carving (tdfe_setup.hip)
 int64_t tdfe_blocks_apply(const tdfe_ctx* c, int cols);
+
+// sum of v over the wavefront, in lane 63, by DPP adds (no LDS round trip);
+// fixed order
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double lane_add(double v) {
+  return v + __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false),
+                              __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false));
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  v = lane_add<0xB1, 0xf>(v);     // quad_perm [1,0,3,2]
+  v = lane_add<0x4E, 0xf>(v);     // quad_perm [2,3,0,1]
+  v = lane_add<0x141, 0xf>(v);    // row_half_mirror
+  v = lane_add<0x140, 0xf>(v);    // row_mirror: each row of 16 holds its sum
+  v = lane_add<0x142, 0xa>(v);    // row_bcast:15 into rows 1 and 3
+  return lane_add<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
+}
+

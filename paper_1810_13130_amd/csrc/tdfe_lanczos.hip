@@ -110,18 +110,8 @@ __device__ void block_col_sum(double v, int C, double* sred, double* out) {
 // after it they took 3.5 and 4.8 us of a 27 us iteration on a small box (a
 // step of ten of these 336 -> 319 us with the reductions, the update's
 // coefficients and its grid as they are here).
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double lane_add(double v) {
-  return v + __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false),
-                              __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false));
-}
 __device__ __forceinline__ double block_sum(double v, double* swave) {
-  v = lane_add<0xB1, 0xf>(v);   // quad_perm [1,0,3,2]
-  v = lane_add<0x4E, 0xf>(v);   // quad_perm [2,3,0,1]
-  v = lane_add<0x141, 0xf>(v);  // row_half_mirror
-  v = lane_add<0x140, 0xf>(v);  // row_mirror: each row of 16 holds its sum
-  v = lane_add<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
-  v = lane_add<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3: lane 63 holds the sum
+  v = wave_sum(v);
   if ((threadIdx.x & 63) == 63) swave[threadIdx.x >> 6] = v;
   __syncthreads();
   double s = swave[0];

@@ -620,6 +620,34 @@ __global__ void fdm_scale_kernel(double* v, int n1x, int n1y, int n1z, const dou
   v[d] /= lx[i] + ly[j] + lz[k];
 }
 
+// The same with the preconditioner's r.z: the transforms are products with S^T
+// and S, so r.z = r.S L^-1 S^T r is the sum of (S^T r)^2 / lambda here, where
+// both are at hand.  Row by row of x, partials in the first of three slots per
+// block.
+__global__ void __launch_bounds__(EW) fdm_scale_rz_kernel(double* v, int n1x, int n1y, int n1z, const double* lx,
+                                                          const double* ly, const double* lz, double* partial) {
+  __shared__ double sw[EW / 64];
+  const int t = threadIdx.x;
+  double rz = 0.0;
+  const int64_t rows = (int64_t)n1y * n1z;
+  for (int64_t row = (int64_t)blockIdx.x * (EW / 64) + (t >> 6); row < rows; row += (int64_t)gridDim.x * (EW / 64)) {
+    const int k = (int)(row / n1y), j = (int)(row - (int64_t)k * n1y);
+    const double lyz = ly[j] + lz[k];
+    for (int i = t & 63; i < n1x; i += 64) {
+      const double a = v[row * n1x + i], z = a / (lx[i] + lyz);
+      v[row * n1x + i] = z;
+      rz += a * z;
+    }
+  }
+  rz = wave_sum(rz);
+  if ((t & 63) == 63) sw[t >> 6] = rz;
+  __syncthreads();
+  if (t == 0) {
+    for (int w = 1; w < EW / 64; ++w) rz = (w == 1 ? sw[0] : rz) + sw[w];
+    partial[(int64_t)blockIdx.x * 3] = rz;
+  }
+}
+
 tdfe_status blas_ready(tdfe_ctx* c) {
   if (c->blas) return TDFE_OK;
   rocblas_handle h = nullptr;
@@ -860,8 +888,10 @@ void fdm_axis(const tdfe_ctx* c, const std::vector<double>& ax, std::vector<doub
 
 // t0 <- K_box^-1 t0 (interior vectors; t1 is scratch): the six 1D transforms
 // and the diagonal scaling of the fast diagonalisation of the rectilinear
-// stiffness built from the axes of tdfe_fdm_setup
-tdfe_status fdm_passes(tdfe_ctx* c) {
+// stiffness built from the axes of tdfe_fdm_setup.  rz (may be null): where the
+// scaling is a pass of its own it leaves t0 . K_box^-1 t0 in the r.z slots of
+// rz's blocks, and sets *rz_done
+tdfe_status fdm_passes(tdfe_ctx* c, double* rz = nullptr, int rz_blocks = 0, bool* rz_done = nullptr) {
   const int n1x = c->Nx - 2, n1y = c->Ny - 2, n1z = c->Nz - 2;
   const int64_t nd = c->n_dof;
   const double* Sx = c->fdmS;
@@ -912,7 +942,11 @@ tdfe_status fdm_passes(tdfe_ctx* c) {
 #undef TDFE_FDM_TILE
     else {
       TDFE_TRY(fdm_blas_pass(c, in, out, S, axis, trans));
-      if (sl) {
+      if (sl && rz) {
+        hipLaunchKernelGGL(fdm_scale_rz_kernel, dim3(rz_blocks), dim3(EW), 0, c->stream, out, n1x, n1y, n1z, sl, ly,
+                           lz, rz);
+        *rz_done = true;
+      } else if (sl) {
         hipLaunchKernelGGL(fdm_scale_kernel, dim3(nblk(nd)), dim3(EW), 0, c->stream, out, n1x, n1y, n1z, sl, ly, lz);
       }
     }
@@ -938,19 +972,6 @@ tdfe_status fdm_solve(tdfe_ctx* c, bool with_lift, double* phi_full) {
                      c->Nz);
   TDFE_HIP(c, hipGetLastError());
   c->last_poisson_iters = 0;
-  return TDFE_OK;
-}
-
-// curved meshes: the PCG preconditioner z = K_box^-1 r on full-grid vectors
-// (interior entries; the boundary entries of z are left as they are, zero)
-tdfe_status fdm_precondition(tdfe_ctx* c, const double* r_full, double* z_full) {
-  const int64_t nd = c->n_dof;
-  hipLaunchKernelGGL(gather_interior_kernel, dim3(nblk(nd)), dim3(EW), 0, c->stream, r_full, (const double*)nullptr,
-                     1.0, c->t0, c->Nx, c->Ny, c->Nz);
-  TDFE_TRY(fdm_passes(c));
-  hipLaunchKernelGGL(scatter_interior_kernel, dim3(nblk(nd)), dim3(EW), 0, c->stream, c->t0, z_full, c->Nx, c->Ny,
-                     c->Nz);
-  TDFE_HIP(c, hipGetLastError());
   return TDFE_OK;
 }
 
@@ -1128,43 +1149,74 @@ __global__ void pcg_rhs_kernel(double* b, const double* lift, const double* phi,
   }
 }
 
-__device__ void block_sum3(double v0, double v1, double v2, double* out) {
-  __shared__ double sred[3][EW];
+// sums over the block of EW lanes, the first nv of three, fixed order
+__device__ __forceinline__ void block_sum3(double v0, double v1, double v2, double* out, int nv = 3) {
+  __shared__ double sw[3][EW / 64];
   const int t = threadIdx.x;
-  sred[0][t] = v0;
-  sred[1][t] = v1;
-  sred[2][t] = v2;
-  __syncthreads();
-  for (int s = EW / 2; s > 0; s >>= 1) {
-    if (t < s) {
-      sred[0][t] += sred[0][t + s];
-      sred[1][t] += sred[1][t + s];
-      sred[2][t] += sred[2][t + s];
-    }
-    __syncthreads();
+  v0 = wave_sum(v0);
+  v1 = wave_sum(v1);
+  v2 = wave_sum(v2);
+  if ((t & 63) == 63) {
+    sw[0][t >> 6] = v0;
+    sw[1][t >> 6] = v1;
+    sw[2][t >> 6] = v2;
   }
-  if (t == 0) {
-    out[0] = sred[0][0];
-    out[1] = sred[1][0];
-    out[2] = sred[2][0];
+  __syncthreads();
+  if (t < nv) {
+    double s = sw[t][0];
+    for (int w = 1; w < EW / 64; ++w) s += sw[t][w];
+    out[t] = s;
   }
 }
 
-// r = b - Ap (interior), Ap = 0; Jacobi (jacobi != 0): z = D^-1 r, p = z;
+// node of a full-grid index: whether it is interior, and its DoF (32-bit
+// divisions where the grid allows: 64-bit ones take longer than the vectors)
+struct NodeOf {
+  int Nx, Ny, Nz;
+  int64_t dof;
+  bool in;
+  template <typename U>
+  __device__ __forceinline__ void split(U i) {
+    const U q = i / (U)Nx;
+    const int I = (int)(i - q * (U)Nx), K = (int)(q / (U)Ny), J = (int)(q - (U)K * (U)Ny);
+    in = I > 0 && I < Nx - 1 && J > 0 && J < Ny - 1 && K > 0 && K < Nz - 1;
+    dof = (I - 1) + (int64_t)(Nx - 2) * ((J - 1) + (int64_t)(Ny - 2) * (K - 1));
+  }
+  __device__ __forceinline__ NodeOf(int64_t i, int64_t n, int nx, int ny, int nz) : Nx(nx), Ny(ny), Nz(nz) {
+    if (n <= 0xffffffffll)
+      split((uint32_t)i);
+    else
+      split((uint64_t)i);
+  }
+};
+
+// CG vectors on the full grid (x, r, p, Ap; zero on the boundary).  With the
+// fast-diagonalisation preconditioner (jacobi = 0) the kernels that write r
+// leave its interior in rc, in DoF order, where the preconditioner turns it
+// into z, and the direction update reads z there.  These passes are bound by
+// memory (3.0M nodes: update 30 us, each further pass of one vector 4-5):
+// gathering r, scattering z, a pass for r.z and one for D cost 43 us of an
+// iteration's 353.
+//
+// r = b - Ap (interior), Ap = 0; Jacobi: z = D^-1 r, p = z; else rc;
 // partials of r.z (0 without Jacobi: the preconditioner pass fills it), r.r, b.b
 __global__ void __launch_bounds__(EW) pcg_start_kernel(const double* b, double* r, double* z, double* pv, double* Ap,
-                                                       const double* dinv, int jacobi, int64_t n, double* partial) {
+                                                       const double* dinv, int jacobi, int Nx, int Ny, int Nz,
+                                                       double* rc, double* partial) {
+  const int64_t n = (int64_t)Nx * Ny * Nz;
   double rz = 0, rr = 0, bb = 0;
   for (int64_t i = (int64_t)blockIdx.x * EW + threadIdx.x; i < n; i += (int64_t)gridDim.x * EW) {
-    const double di = dinv[i];
-    const double ri = di != 0.0 ? b[i] - Ap[i] : 0.0;  // dinv is 0 exactly on the boundary
+    const NodeOf nd(i, n, Nx, Ny, Nz);
+    const double ri = nd.in ? b[i] - Ap[i] : 0.0;
     r[i] = ri;
     Ap[i] = 0.0;
     if (jacobi) {
-      const double zi = di * ri;
+      const double zi = dinv[i] * ri;
       z[i] = zi;
       pv[i] = zi;
       rz += ri * zi;
+    } else if (nd.in) {
+      rc[nd.dof] = ri;
     }
     rr += ri * ri;
     bb += b[i] * b[i];
@@ -1172,54 +1224,65 @@ __global__ void __launch_bounds__(EW) pcg_start_kernel(const double* b, double* 
   block_sum3(rz, rr, bb, partial + blockIdx.x * 3);
 }
 
-// x += alpha p, r -= alpha Ap (interior), Ap = 0; Jacobi: z = D^-1 r;
+// x += alpha p, r -= alpha Ap (interior), Ap = 0; Jacobi: z = D^-1 r, else rc;
 // partials of r.z (0 without Jacobi), r.r
 __global__ void __launch_bounds__(EW) pcg_update_kernel(double* x, double* r, double* z, const double* pv, double* Ap,
-                                                        const double* dinv, int jacobi, const double* S, int64_t n,
-                                                        double* partial, const int* done) {
+                                                        const double* dinv, int jacobi, int Nx, int Ny, int Nz,
+                                                        double* rc, const double* S, double* partial,
+                                                        const int* done) {
   if (*done) return;
+  const int64_t n = (int64_t)Nx * Ny * Nz;
   const double alpha = S[3];
   double rz = 0, rr = 0;
   for (int64_t i = (int64_t)blockIdx.x * EW + threadIdx.x; i < n; i += (int64_t)gridDim.x * EW) {
-    const double di = dinv[i];
+    const NodeOf nd(i, n, Nx, Ny, Nz);
     const double pi = pv[i];
     x[i] += alpha * pi;
-    const double ri = di != 0.0 ? r[i] - alpha * Ap[i] : 0.0;
+    const double ri = nd.in ? r[i] - alpha * Ap[i] : 0.0;
     r[i] = ri;
     Ap[i] = 0.0;
     if (jacobi) {
-      const double zi = di * ri;
+      const double zi = dinv[i] * ri;
       z[i] = zi;
       rz += ri * zi;
+    } else if (nd.in) {
+      rc[nd.dof] = ri;
     }
     rr += ri * ri;
   }
   block_sum3(rz, rr, 0.0, partial + blockIdx.x * 3);
 }
 
-// the r.z slot of the update partials, after the preconditioner pass wrote z
-// (same grid and stride as pcg_update_kernel, so the fixed-order sums match)
-__global__ void __launch_bounds__(EW) pcg_rz_kernel(const double* r, const double* z, int64_t n, double* partial,
-                                                    const int* done) {
+// the r.z slot of the update partials, after the preconditioner wrote z (DoF
+// order) with transforms that scale as they go
+__global__ void __launch_bounds__(EW) pcg_rz_kernel(const double* r, const double* zc, int Nx, int Ny, int Nz,
+                                                    double* partial, const int* done) {
   if (done && *done) return;
+  const int64_t n = (int64_t)Nx * Ny * Nz;
   double rz = 0;
-  for (int64_t i = (int64_t)blockIdx.x * EW + threadIdx.x; i < n; i += (int64_t)gridDim.x * EW) rz += r[i] * z[i];
-  __shared__ double sred[EW];
-  sred[threadIdx.x] = rz;
-  __syncthreads();
-  for (int s = EW / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) sred[threadIdx.x] += sred[threadIdx.x + s];
-    __syncthreads();
+  for (int64_t i = (int64_t)blockIdx.x * EW + threadIdx.x; i < n; i += (int64_t)gridDim.x * EW) {
+    const NodeOf nd(i, n, Nx, Ny, Nz);
+    if (nd.in) rz += r[i] * zc[nd.dof];
   }
-  if (threadIdx.x == 0) partial[blockIdx.x * 3] = sred[0];
+  block_sum3(rz, 0.0, 0.0, partial + blockIdx.x * 3, 1);
 }
 
-// p = z + beta p
-__global__ void pcg_direction_kernel(const double* z, double* pv, const double* S, int64_t n, const int* done) {
-  if (*done) return;
+// p = z + beta p; at the start (S null) p = z.  z on the full grid (Jacobi) or
+// in DoF order (zc)
+__global__ void pcg_direction_kernel(const double* z, const double* zc, double* pv, const double* S, int Nx, int Ny,
+                                     int Nz, const int* done) {
+  if (done && *done) return;
+  const int64_t n = (int64_t)Nx * Ny * Nz;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  pv[i] = z[i] + S[4] * pv[i];
+  double zi;
+  if (zc) {
+    const NodeOf nd(i, n, Nx, Ny, Nz);
+    zi = nd.in ? zc[nd.dof] : 0.0;
+  } else {
+    zi = z[i];
+  }
+  pv[i] = S ? zi + S[4] * pv[i] : zi;
 }
 
 // mode 0 (start): S[0]=rz, S[1]=rr, S[2]=bb, done if converged
@@ -1257,24 +1320,20 @@ __device__ void pcg_scalars(int mode, double v0, double v1, double v2, double* S
   }
 }
 
-__global__ void __launch_bounds__(EW) pcg_scalar_kernel(const double* partial, int64_t nb, int stride, int mode,
-                                                        double* S, int* flags, double tol, int maxit,
-                                                        int* host_flag) {
-  if (mode != 0 && flags[0]) return;
-  __shared__ double sred[3][EW];
+template <int STRIDE>
+__global__ void __launch_bounds__(EW) pcg_scalar_kernel(const double* partial, int64_t nb, int mode, double* S,
+                                                        int* flags, double tol, int maxit, int* host_flag) {
+  __shared__ double sum[3];
   const int t = threadIdx.x;
+  const int dn = mode != 0 ? flags[0] : 0;
   double v[3] = {0, 0, 0};
   for (int64_t b = t; b < nb; b += EW)
-    for (int u = 0; u < stride; ++u) v[u] += partial[b * stride + u];
-  for (int u = 0; u < 3; ++u) sred[u][t] = v[u];
+#pragma unroll
+    for (int u = 0; u < STRIDE; ++u) v[u] += partial[b * STRIDE + u];
+  block_sum3(v[0], v[1], v[2], sum);
   __syncthreads();
-  for (int s = EW / 2; s > 0; s >>= 1) {
-    if (t < s)
-      for (int u = 0; u < 3; ++u) sred[u][t] += sred[u][t + s];
-    __syncthreads();
-  }
-  if (t != 0) return;
-  pcg_scalars(mode, sred[0][0], sred[1][0], sred[2][0], S, flags, tol, maxit);
+  if (t != 0 || dn) return;
+  pcg_scalars(mode, sum[0], sum[1], sum[2], S, flags, tol, maxit);
   if (flags[0]) {
     *host_flag = 1;  // pinned memory the host polls; cleared by the host before the solve
     __threadfence_system();
@@ -1344,48 +1403,57 @@ tdfe_status pcg_solve(tdfe_ctx* c) {
     return tdfe_launch_apply(c, a);
   };
   // preconditioner: Jacobi (z = D^-1 r inside the update kernels) or the fast
-  // diagonalisation of the rectilinear stand-in mesh (a pass of its own)
+  // diagonalisation of the rectilinear stand-in mesh (z = K_box^-1 r in c->t0)
   const int jacobi = c->pcg_precond == TDFE_PCG_JACOBI ? 1 : 0;
   auto precondition = [&](const int* done) -> tdfe_status {
     if (jacobi) return TDFE_OK;
-    TDFE_TRY(fdm_precondition(c, r, z));
-    hipLaunchKernelGGL(pcg_rz_kernel, dim3(PCG_BLOCKS), dim3(EW), 0, c->stream, (const double*)r, (const double*)z, nn,
-                       part, done);
+    bool rz_done = false;
+    TDFE_TRY(fdm_passes(c, part, PCG_BLOCKS, &rz_done));
+    if (!rz_done)
+      hipLaunchKernelGGL(pcg_rz_kernel, dim3(PCG_BLOCKS), dim3(EW), 0, c->stream, (const double*)r,
+                         (const double*)c->t0, c->Nx, c->Ny, c->Nz, part, done);
     TDFE_HIP(c, hipGetLastError());
     return TDFE_OK;
   };
   hipLaunchKernelGGL(pcg_rhs_kernel, dim3(nblk(nn)), dim3(EW), 0, c->stream, c->cload, (const double*)c->lift,
                      (const double*)c->phi, x, c->Nx, c->Ny, c->Nz);
   TDFE_TRY(tdfe_zero(c, Ap, nn * sizeof(double)));
-  if (!jacobi) TDFE_TRY(tdfe_zero(c, z, nn * sizeof(double)));  // boundary entries stay zero
   TDFE_TRY(apply_K(x, false, nullptr));
   hipLaunchKernelGGL(pcg_start_kernel, dim3(PCG_BLOCKS), dim3(EW), 0, c->stream, (const double*)c->cload, r, z, pv, Ap,
-                     (const double*)c->dinvK, jacobi, nn, part);
+                     (const double*)c->dinvK, jacobi, c->Nx, c->Ny, c->Nz, c->t0, part);
   TDFE_TRY(precondition(nullptr));
-  if (!jacobi) TDFE_HIP(c, hipMemcpyAsync(pv, z, nn * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
+  const double* zc = jacobi ? nullptr : c->t0;
+  if (!jacobi)
+    hipLaunchKernelGGL(pcg_direction_kernel, dim3(nblk(nn)), dim3(EW), 0, c->stream, (const double*)nullptr, zc, pv,
+                       (const double*)nullptr, c->Nx, c->Ny, c->Nz, (const int*)nullptr);
   volatile int* hflag = c->poll + 40;  // nothing on the stream writes it now
   *hflag = 0;
   int* dflag = nullptr;
   TDFE_HIP(c, hipHostGetDevicePointer((void**)&dflag, (void*)(c->poll + 40), 0));
-  hipLaunchKernelGGL(pcg_scalar_kernel, dim3(1), dim3(EW), 0, c->stream, (const double*)part, (int64_t)PCG_BLOCKS, 3,
+  hipLaunchKernelGGL((pcg_scalar_kernel<3>), dim3(1), dim3(EW), 0, c->stream, (const double*)part, (int64_t)PCG_BLOCKS,
                      0, S, flags, c->pcg_tol, c->pcg_maxit, dflag);
   TDFE_HIP(c, hipGetLastError());
-  const int LOOK = 4, RING = TDFE_N_EVENTS;
+  // iterations the host is ahead of the stop test it has seen: enqueuing one
+  // takes less than running one at every size, and each past the last still
+  // runs its transforms (4 ahead 3.88 ms at 31^3 DoFs, 23.2 at 143^3 for two
+  // solves; 1 ahead 3.63 and 22.1)
+  const int LOOK = 1, RING = TDFE_N_EVENTS;
   TDFE_TRY(tdfe_poll_events(c));
   TDFE_HIP(c, hipStreamSynchronize(c->stream));
   if (!*hflag) {
     for (int it = 1; it <= c->pcg_maxit; ++it) {
       int64_t groups = 0;
       TDFE_TRY(apply_K(pv, true, &groups));
-      hipLaunchKernelGGL(pcg_scalar_kernel, dim3(1), dim3(EW), 0, c->stream, (const double*)part, groups, 1, 1, S,
+      hipLaunchKernelGGL((pcg_scalar_kernel<1>), dim3(1), dim3(EW), 0, c->stream, (const double*)part, groups, 1, S,
                          flags, c->pcg_tol, c->pcg_maxit, dflag);
       hipLaunchKernelGGL(pcg_update_kernel, dim3(PCG_BLOCKS), dim3(EW), 0, c->stream, x, r, z, (const double*)pv, Ap,
-                         (const double*)c->dinvK, jacobi, (const double*)S, nn, part, (const int*)flags);
+                         (const double*)c->dinvK, jacobi, c->Nx, c->Ny, c->Nz, c->t0, (const double*)S, part,
+                         (const int*)flags);
       TDFE_TRY(precondition(flags));
-      hipLaunchKernelGGL(pcg_scalar_kernel, dim3(1), dim3(EW), 0, c->stream, (const double*)part, (int64_t)PCG_BLOCKS,
-                         3, 2, S, flags, c->pcg_tol, c->pcg_maxit, dflag);
-      hipLaunchKernelGGL(pcg_direction_kernel, dim3(nblk(nn)), dim3(EW), 0, c->stream, (const double*)z, pv,
-                         (const double*)S, nn, (const int*)flags);
+      hipLaunchKernelGGL((pcg_scalar_kernel<3>), dim3(1), dim3(EW), 0, c->stream, (const double*)part,
+                         (int64_t)PCG_BLOCKS, 2, S, flags, c->pcg_tol, c->pcg_maxit, dflag);
+      hipLaunchKernelGGL(pcg_direction_kernel, dim3(nblk(nn)), dim3(EW), 0, c->stream, (const double*)z, zc, pv,
+                         (const double*)S, c->Nx, c->Ny, c->Nz, (const int*)flags);
       TDFE_HIP(c, hipGetLastError());
       TDFE_HIP(c, hipEventRecord(c->evs[it % RING], c->stream));
       if (it > LOOK) {
