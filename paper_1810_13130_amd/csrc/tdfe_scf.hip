@@ -476,130 +476,160 @@ __global__ void scatter_interior_kernel(const double* in, double* full, int Nx, 
   full[node] = in[d];
 }
 
-// Register-tiled form of the same transform: a block stages FDM_TB lines and
-// the whole 1D matrix R (R = S for the transposed product, S^T otherwise) in
-// LDS; the FDM_G groups of FDM_TB lanes each own output modes
-// [g MPT, g MPT + MPT) of every line and sweep the input modes once (a row
-// of R is read at one address per group: LDS broadcasts in distinct banks).
-// lam scaling is supported along z only.
-constexpr int FDM_TB = 16, FDM_G = 16;
-// rows of R are padded with zeros to FDM_G * MPT entries, so the inner loop needs no bounds test
-inline size_t fdm_tile_lds(int nax, int mpt) {
-  return ((size_t)nax * FDM_G * mpt + (size_t)nax * FDM_TB) * sizeof(double);
-}
-template <int MPT>
-__global__ void __launch_bounds__(FDM_TB* FDM_G) fdm_tile_kernel(const double* __restrict__ in, double* __restrict__ out,
-                                                                 const double* __restrict__ R, int n1x, int n1y,
-                                                                 int n1z, int axis, const double* lx, const double* ly,
-                                                                 const double* lz) {
-  extern __shared__ double lds[];
-  const int nax = axis == 0 ? n1x : (axis == 1 ? n1y : n1z);
-  constexpr int RP = FDM_G * MPT;
-  double* sR = lds;                        // [nax][RP], zero beyond column nax
-  double* tile = lds + (size_t)nax * RP;   // [nax][FDM_TB]; reused as [FDM_TB][nax] for x-line output
-  const int64_t nlines = (int64_t)n1x * n1y * n1z / nax;
-  const int64_t l0 = (int64_t)blockIdx.x * FDM_TB;
-  const int t = threadIdx.x;
-  auto base_stride = [&](int64_t line, int64_t& base, int64_t& stride) {
-    if (axis == 0) {
-      base = line * n1x;
-      stride = 1;
-    } else if (axis == 1) {
-      const int64_t i = line % n1x, k = line / n1x;
-      base = i + k * (int64_t)n1x * n1y;
-      stride = n1x;
-    } else {
-      base = line;
-      stride = (int64_t)n1x * n1y;
-    }
+constexpr int FDM_LT = 16;  // lines per block
+
+// One 1D transform of every grid line along an axis, out[mp] = sum_m R[m][mp]
+// in[m] (R = S for the transposed product, S^T otherwise), on the FP64 matrix
+// instruction (16 x 16 results, 4 terms).  A block stages FDM_LT lines of the
+// axis in LDS and holds one wavefront per 16 output modes; a wavefront reads
+// its columns of R from global memory (the whole table is read by every block
+// and stays in L2), 16 terms ahead.  Along x the lines are the instruction's
+// rows and the modes its columns, along y and z the other way round, so that
+// the 16 lanes of a result row store to consecutive addresses.
+//
+// SOLVE (z only): both products along the axis and the scaling between them,
+// out = S ((S^T in) / (lx + ly + lz)), with the first product's result kept in
+// registers and put back into the staged lines; rz (may be null) receives the
+// block's part of in . out, which is the sum of (S^T in)^2 / lambda.
+//
+// What bounds it: up to some 60 nodes latency (a pass of 4 to 6 us), above
+// that R's way from L2 (at 124 nodes 20 us, the matrix unit at a third).  A pass
+// with the table and 16 lines in LDS, one block of four wavefronts a CU, took
+// 11.9 us at 63 nodes, 16.6 at 79, 70 at 101 and 112 at 124; this one 5.6, 9,
+// 15 and 19, and SOLVE 8.5, 14, 26 and 33 for two passes and the scaling.  The
+// line to the library's product lies where that is the faster one: at 143 nodes
+// it takes 24 us, this kernel 28, at 185 52 and 66; 32 lines a block, which
+// halves R's traffic but leaves fewer blocks, is within 5% everywhere.
+template <int AXIS, bool SOLVE>
+__global__ void __launch_bounds__(512)
+    fdm_line_kernel(const double* in, double* out, const double* __restrict__ R, const double* __restrict__ R2,
+                    int n1x, int n1y, int n1z, const double* lx, const double* ly, const double* lz, double* rz) {
+  typedef double V4 __attribute__((ext_vector_type(4)));
+  constexpr int LT = FDM_LT, SP = LT + 1;
+  extern __shared__ double tile[];  // [16 * wavefronts][SP], zero past the axis and the last line
+  __shared__ double swave[8];
+  const int nax = AXIS == 0 ? n1x : (AXIS == 1 ? n1y : n1z);
+  const int64_t nlines = AXIS == 0 ? (int64_t)n1y * n1z : (AXIS == 1 ? (int64_t)n1x * n1z : (int64_t)n1x * n1y);
+  const int64_t stride = AXIS == 0 ? 1 : (AXIS == 1 ? n1x : (int64_t)n1x * n1y);
+  const int64_t l0 = (int64_t)blockIdx.x * LT;
+  const int t = threadIdx.x, nt = blockDim.x, kp = nt >> 2;  // 16 modes per wavefront
+  const int lane = t & 63, c = lane & 15, g = lane >> 4;
+  const int mt = __builtin_amdgcn_readfirstlane(t >> 6);
+  auto base = [&](int64_t line) -> int64_t {
+    if (AXIS == 0) return line * n1x;
+    if (AXIS == 1) return line % n1x + (line / n1x) * n1x * n1y;
+    return line;
   };
-  // staging: eight loads in flight per thread before their LDS stores
-  constexpr int NT = FDM_TB * FDM_G, UNR = 8;
-  for (int i0 = t; i0 < nax * RP; i0 += NT * UNR) {
-    double v[UNR];
+  if (AXIS == 0) {
+    // a wavefront per line, lanes along it
+    for (int l = mt; l < LT; l += nt >> 6)
+      for (int m = lane; m < kp; m += 64)
+        tile[m * SP + l] = (m < nax && l0 + l < nlines) ? in[(l0 + l) * n1x + m] : 0.0;
+  } else {
+    const int l = t % LT;
+    const bool ok = l0 + l < nlines;
+    const int64_t b = base(ok ? l0 + l : 0);
+    const int step = nt / LT;
+    int m = t / LT;
+    for (; m + 3 * step < nax; m += 4 * step) {
+      double v[4];
 #pragma unroll
-    for (int u = 0; u < UNR; ++u) {
-      const int idx = i0 + u * NT;
-      const int m = idx / RP, mp = idx % RP;
-      v[u] = (idx < nax * RP && mp < nax) ? R[m * nax + mp] : 0.0;
-    }
+      for (int u = 0; u < 4; ++u) v[u] = in[b + (m + u * step) * stride];
 #pragma unroll
-    for (int u = 0; u < UNR; ++u) {
-      const int idx = i0 + u * NT;
-      if (idx < nax * RP) sR[idx] = v[u];
+      for (int u = 0; u < 4; ++u) tile[(m + u * step) * SP + l] = ok ? v[u] : 0.0;
     }
-  }
-  for (int i0 = t; i0 < nax * FDM_TB; i0 += NT * UNR) {
-    double v[UNR];
-#pragma unroll
-    for (int u = 0; u < UNR; ++u) {
-      const int idx = i0 + u * NT;
-      v[u] = 0.0;
-      if (idx < nax * FDM_TB) {
-        int m, l;
-        if (axis == 0) {
-          l = idx / nax;
-          m = idx % nax;
-        } else {
-          m = idx / FDM_TB;
-          l = idx % FDM_TB;
-        }
-        const int64_t line = l0 + l;
-        if (line < nlines) {
-          int64_t b, st;
-          base_stride(line, b, st);
-          v[u] = in[b + m * st];
-        }
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < UNR; ++u) {
-      const int idx = i0 + u * NT;
-      if (idx < nax * FDM_TB) {
-        const int m = axis == 0 ? idx % nax : idx / FDM_TB;
-        const int l = axis == 0 ? idx / nax : idx % FDM_TB;
-        tile[m * FDM_TB + l] = v[u];
-      }
-    }
+    for (; m < kp; m += step) tile[m * SP + l] = (ok && m < nax) ? in[b + m * stride] : 0.0;
   }
   __syncthreads();
-  const int l = t % FDM_TB;
-  const int g = t / FDM_TB;
-  const int mp0 = g * MPT;
-  double acc[MPT];
+  // rows past the axis are zero in the tile and, past the table's end, in R;
+  // columns past it are not stored
+  const uint32_t row4 = 32u * (uint32_t)nax;  // bytes of four rows of R
+  auto product = [&](const double* Rm) {
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc((void*)Rm, 0, (int)(8u * (uint32_t)nax * (uint32_t)nax), 0x00020000);
+    uint32_t o = 8u * (uint32_t)(g * nax + mt * 16 + c);
+    V4 acc = (V4)0.0;
+    double a0[4], a1[4];
+    auto fetch = [&](double(&a)[4]) {
 #pragma unroll
-  for (int q = 0; q < MPT; ++q) acc[q] = 0.0;
-  if (mp0 < nax) {
-    for (int m = 0; m < nax; ++m) {
-      const double v = tile[m * FDM_TB + l];
-      const double* Rm = sR + m * RP + mp0;
+      for (int s = 0; s < 4; ++s) {
+        a[s] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)o, 0, 0));
+        o += row4;
+      }
+    };
+    auto steps = [&](const double(&a)[4], int k) {
 #pragma unroll
-      for (int q = 0; q < MPT; ++q) acc[q] += Rm[q] * v;
+      for (int s = 0; s < 4; ++s) {
+        const double b = tile[(k + 4 * s + g) * SP + c];
+        acc = AXIS == 0 ? __builtin_amdgcn_mfma_f64_16x16x4f64(b, a[s], acc, 0, 0, 0)
+                        : __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b, acc, 0, 0, 0);
+      }
+    };
+    fetch(a0);
+    for (int k = 0; k < kp; k += 32) {
+      fetch(a1);
+      steps(a0, k);
+      if (k + 16 >= kp) break;
+      fetch(a0);
+      steps(a1, k + 16);
     }
-  }
-  const int64_t line = l0 + l;
-  if (axis == 0) {
+    return acc;
+  };
+  V4 acc = product(R);
+  const int64_t line = l0 + c;
+  if constexpr (SOLVE) {
+    double part = 0.0;
+    const int64_t lr = min(line, nlines - 1);
+    const double lxy = lx[lr % n1x] + ly[lr / n1x];
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < MPT; ++q)
-      if (mp0 + q < nax) tile[l * nax + mp0 + q] = acc[q];
-    __syncthreads();
-    for (int idx = t; idx < nax * FDM_TB; idx += FDM_TB * FDM_G) {
-      const int ll = idx / nax, mp = idx % nax;
-      if (l0 + ll < nlines) out[(l0 + ll) * n1x + mp] = tile[ll * nax + mp];
+    for (int r = 0; r < 4; ++r) {
+      const int m = mt * 16 + g + 4 * r;
+      const double z = m < nax ? acc[r] / (lxy + lz[min(m, nax - 1)]) : 0.0;
+      part += acc[r] * z;  // (lines past the last are zero)
+      tile[m * SP + c] = z;
     }
-    return;
+    if (rz) {
+      part = wave_sum(part);
+      if (lane == 63) swave[mt] = part;
+    }
+    __syncthreads();
+    if (rz && t == 0) {
+      double sum = swave[0];
+      for (int w = 1; w < nt >> 6; ++w) sum += swave[w];
+      rz[blockIdx.x] = sum;
+    }
+    acc = product(R2);
   }
-  if (line >= nlines) return;
-  int64_t b, st;
-  base_stride(line, b, st);
-  double lxy = 0.0;
-  if (lx) lxy = lx[line % n1x] + ly[line / n1x];  // axis 2: line = i + n1x j
+  if (AXIS == 0) {
+    const int m = mt * 16 + c;
 #pragma unroll
-  for (int q = 0; q < MPT; ++q) {
-    const int mp = mp0 + q;
-    if (mp < nax) out[b + (int64_t)mp * st] = lx ? acc[q] / (lxy + lz[mp]) : acc[q];
+    for (int r = 0; r < 4; ++r) {
+      const int64_t ln = l0 + g + 4 * r;
+      if (m < nax && ln < nlines) out[ln * n1x + m] = acc[r];
+    }
+  } else {
+    const int64_t b = base(line);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = mt * 16 + g + 4 * r;
+      if (m < nax && line < nlines) out[b + m * stride] = acc[r];
+    }
   }
+}
+
+// longest axis of fdm_line_kernel (eight wavefronts, one per 16 modes)
+constexpr int FDM_LINE_MAX = 128;
+template <int AXIS, bool SOLVE>
+tdfe_status launch_fdm_line(tdfe_ctx* c, const double* in, double* out, const double* R, const double* R2, int nax,
+                            int64_t nlines, const double* lx, const double* ly, const double* lz, double* rz) {
+  const int waves = (nax + 15) / 16;
+  const size_t shm = (size_t)waves * 16 * (FDM_LT + 1) * sizeof(double);  // at most 17 KB
+  hipLaunchKernelGGL((fdm_line_kernel<AXIS, SOLVE>), dim3((unsigned)((nlines + FDM_LT - 1) / FDM_LT)),
+                     dim3(64 * waves), shm, c->stream, in, out, R, R2, c->Nx - 2, c->Ny - 2, c->Nz - 2, lx, ly, lz,
+                     rz);
+  TDFE_HIP(c, hipGetLastError());
+  return TDFE_OK;
 }
 
 // Axes of more than 128 interior nodes: the 1D transform is a plain dense
@@ -622,8 +652,8 @@ __global__ void fdm_scale_kernel(double* v, int n1x, int n1y, int n1z, const dou
 
 // The same with the preconditioner's r.z: the transforms are products with S^T
 // and S, so r.z = r.S L^-1 S^T r is the sum of (S^T r)^2 / lambda here, where
-// both are at hand.  Row by row of x, partials in the first of three slots per
-// block.
+// both are at hand.  Row by row of x, one partial per block.
+constexpr int FDM_RZ_BLOCKS = 512;
 __global__ void __launch_bounds__(EW) fdm_scale_rz_kernel(double* v, int n1x, int n1y, int n1z, const double* lx,
                                                           const double* ly, const double* lz, double* partial) {
   __shared__ double sw[EW / 64];
@@ -644,7 +674,7 @@ __global__ void __launch_bounds__(EW) fdm_scale_rz_kernel(double* v, int n1x, in
   __syncthreads();
   if (t == 0) {
     for (int w = 1; w < EW / 64; ++w) rz = (w == 1 ? sw[0] : rz) + sw[w];
-    partial[(int64_t)blockIdx.x * 3] = rz;
+    partial[blockIdx.x] = rz;
   }
 }
 
@@ -888,78 +918,46 @@ void fdm_axis(const tdfe_ctx* c, const std::vector<double>& ax, std::vector<doub
 
 // t0 <- K_box^-1 t0 (interior vectors; t1 is scratch): the six 1D transforms
 // and the diagonal scaling of the fast diagonalisation of the rectilinear
-// stiffness built from the axes of tdfe_fdm_setup.  rz (may be null): where the
-// scaling is a pass of its own it leaves t0 . K_box^-1 t0 in the r.z slots of
-// rz's blocks, and sets *rz_done
-tdfe_status fdm_passes(tdfe_ctx* c, double* rz = nullptr, int rz_blocks = 0, bool* rz_done = nullptr) {
-  const int n1x = c->Nx - 2, n1y = c->Ny - 2, n1z = c->Nz - 2;
+// stiffness built from the axes of tdfe_fdm_setup.  rz (may be null): receives
+// *rz_blocks partial sums of t0 . K_box^-1 t0
+tdfe_status fdm_passes(tdfe_ctx* c, double* rz = nullptr, int64_t* rz_blocks = nullptr) {
+  const int n1[3] = {c->Nx - 2, c->Ny - 2, c->Nz - 2};
   const int64_t nd = c->n_dof;
-  const double* Sx = c->fdmS;
-  const double* Sy = Sx + (size_t)n1x * n1x;
-  const double* Sz = Sy + (size_t)n1y * n1y;
+  const double* S[3] = {c->fdmS, c->fdmS + (size_t)n1[0] * n1[0],
+                        c->fdmS + (size_t)n1[0] * n1[0] + (size_t)n1[1] * n1[1]};
+  const size_t nS = (size_t)n1[0] * n1[0] + (size_t)n1[1] * n1[1] + (size_t)n1[2] * n1[2];  // transposed copies follow
   const double* lx = c->fdmL;
-  const double* ly = lx + n1x;
-  const double* lz = ly + n1y;
-  const size_t nS = (size_t)n1x * n1x + (size_t)n1y * n1y + (size_t)n1z * n1z;
-  auto pass = [&](const double* in, double* out, int axis, int trans, bool scale) -> tdfe_status {
-    const int nax = axis == 0 ? n1x : (axis == 1 ? n1y : n1z);
-    const int64_t nlines = nd / nax;
-    const double* S = axis == 0 ? Sx : (axis == 1 ? Sy : Sz);
-    const double* St = S + nS;  // transposed copy
-    const double* sl = scale ? lx : nullptr;
-    int mpt = (nax + FDM_G - 1) / FDM_G;
-    for (int cand : {1, 2, 3, 4, 5, 6, 8})
-      if (mpt <= cand) {
-        mpt = cand;
-        break;
-      }
-    const size_t shm_t = fdm_tile_lds(nax, mpt);
-    const unsigned gt = (unsigned)((nlines + FDM_TB - 1) / FDM_TB);
-    const double* Rm = trans ? S : St;
-#define TDFE_FDM_TILE(M)                                                                                       \
-  do {                                                                                                          \
-    TDFE_HIP(c, hipFuncSetAttribute((const void*)fdm_tile_kernel<M>, hipFuncAttributeMaxDynamicSharedMemorySize, \
-                                    (int)shm_t));                                                              \
-    hipLaunchKernelGGL((fdm_tile_kernel<M>), dim3(gt), dim3(FDM_TB * FDM_G), shm_t, c->stream, in, out, Rm, n1x, \
-                       n1y, n1z, axis, sl, ly, lz);                                                            \
-  } while (0)
-    if (shm_t > 160 * 1024 || mpt > 8)
-      mpt = 1 << 30;  // matrix does not fit LDS: rocBLAS below
-    if (mpt <= 1)
-      TDFE_FDM_TILE(1);
-    else if (mpt <= 2)
-      TDFE_FDM_TILE(2);
-    else if (mpt <= 3)
-      TDFE_FDM_TILE(3);
-    else if (mpt <= 4)
-      TDFE_FDM_TILE(4);
-    else if (mpt <= 5)
-      TDFE_FDM_TILE(5);
-    else if (mpt <= 6)
-      TDFE_FDM_TILE(6);
-    else if (mpt <= 8)
-      TDFE_FDM_TILE(8);
-#undef TDFE_FDM_TILE
-    else {
-      TDFE_TRY(fdm_blas_pass(c, in, out, S, axis, trans));
-      if (sl && rz) {
-        hipLaunchKernelGGL(fdm_scale_rz_kernel, dim3(rz_blocks), dim3(EW), 0, c->stream, out, n1x, n1y, n1z, sl, ly,
-                           lz, rz);
-        *rz_done = true;
-      } else if (sl) {
-        hipLaunchKernelGGL(fdm_scale_kernel, dim3(nblk(nd)), dim3(EW), 0, c->stream, out, n1x, n1y, n1z, sl, ly, lz);
-      }
+  const double* ly = lx + n1[0];
+  const double* lz = ly + n1[1];
+  auto pass = [&](const double* in, double* out, int axis, int trans) -> tdfe_status {
+    const int nax = n1[axis];
+    if (nax > FDM_LINE_MAX) return fdm_blas_pass(c, in, out, S[axis], axis, trans);
+    const double* R = trans ? S[axis] : S[axis] + nS;
+    auto run = [&](auto kernel) { return kernel(c, in, out, R, nullptr, nax, nd / nax, lx, ly, lz, nullptr); };
+    return axis == 0 ? run(launch_fdm_line<0, false>) : run(launch_fdm_line<1, false>);
+  };
+  TDFE_TRY(pass(c->t0, c->t1, 0, 1));
+  TDFE_TRY(pass(c->t1, c->t0, 1, 1));
+  if (n1[2] <= FDM_LINE_MAX) {
+    const int64_t lines = nd / n1[2];
+    if (rz_blocks) *rz_blocks = (lines + FDM_LT - 1) / FDM_LT;
+    // in place: a block's lines are its own
+    TDFE_TRY((launch_fdm_line<2, true>(c, c->t0, c->t0, S[2], S[2] + nS, n1[2], lines, lx, ly, lz, rz)));
+  } else {
+    TDFE_TRY(fdm_blas_pass(c, c->t0, c->t1, S[2], 2, 1));
+    if (rz) {
+      *rz_blocks = FDM_RZ_BLOCKS;
+      hipLaunchKernelGGL(fdm_scale_rz_kernel, dim3(FDM_RZ_BLOCKS), dim3(EW), 0, c->stream, c->t1, n1[0], n1[1], n1[2],
+                         lx, ly, lz, rz);
+    } else {
+      hipLaunchKernelGGL(fdm_scale_kernel, dim3(nblk(nd)), dim3(EW), 0, c->stream, c->t1, n1[0], n1[1], n1[2], lx, ly,
+                         lz);
     }
     TDFE_HIP(c, hipGetLastError());
-    return TDFE_OK;
-  };
-  TDFE_TRY(pass(c->t0, c->t1, 0, 1, false));
-  TDFE_TRY(pass(c->t1, c->t0, 1, 1, false));
-  TDFE_TRY(pass(c->t0, c->t1, 2, 1, true));
-  TDFE_TRY(pass(c->t1, c->t0, 2, 0, false));
-  TDFE_TRY(pass(c->t0, c->t1, 1, 0, false));
-  TDFE_TRY(pass(c->t1, c->t0, 0, 0, false));
-  return TDFE_OK;
+    TDFE_TRY(fdm_blas_pass(c, c->t1, c->t0, S[2], 2, 0));
+  }
+  TDFE_TRY(pass(c->t0, c->t1, 1, 0));
+  return pass(c->t1, c->t0, 0, 0);
 }
 
 // box meshes: the exact Hartree solve, phi_interior = K^-1 (4 pi c - (K f))_interior
@@ -1199,7 +1197,7 @@ struct NodeOf {
 // iteration's 353.
 //
 // r = b - Ap (interior), Ap = 0; Jacobi: z = D^-1 r, p = z; else rc;
-// partials of r.z (0 without Jacobi: the preconditioner pass fills it), r.r, b.b
+// partials of r.z (0 without Jacobi: the preconditioner has its own), r.r, b.b
 __global__ void __launch_bounds__(EW) pcg_start_kernel(const double* b, double* r, double* z, double* pv, double* Ap,
                                                        const double* dinv, int jacobi, int Nx, int Ny, int Nz,
                                                        double* rc, double* partial) {
@@ -1251,20 +1249,6 @@ __global__ void __launch_bounds__(EW) pcg_update_kernel(double* x, double* r, do
     rr += ri * ri;
   }
   block_sum3(rz, rr, 0.0, partial + blockIdx.x * 3);
-}
-
-// the r.z slot of the update partials, after the preconditioner wrote z (DoF
-// order) with transforms that scale as they go
-__global__ void __launch_bounds__(EW) pcg_rz_kernel(const double* r, const double* zc, int Nx, int Ny, int Nz,
-                                                    double* partial, const int* done) {
-  if (done && *done) return;
-  const int64_t n = (int64_t)Nx * Ny * Nz;
-  double rz = 0;
-  for (int64_t i = (int64_t)blockIdx.x * EW + threadIdx.x; i < n; i += (int64_t)gridDim.x * EW) {
-    const NodeOf nd(i, n, Nx, Ny, Nz);
-    if (nd.in) rz += r[i] * zc[nd.dof];
-  }
-  block_sum3(rz, 0.0, 0.0, partial + blockIdx.x * 3, 1);
 }
 
 // p = z + beta p; at the start (S null) p = z.  z on the full grid (Jacobi) or
@@ -1320,9 +1304,11 @@ __device__ void pcg_scalars(int mode, double v0, double v1, double v2, double* S
   }
 }
 
+// rzp: nrz further partials of the first value (r.z of the preconditioner)
 template <int STRIDE>
-__global__ void __launch_bounds__(EW) pcg_scalar_kernel(const double* partial, int64_t nb, int mode, double* S,
-                                                        int* flags, double tol, int maxit, int* host_flag) {
+__global__ void __launch_bounds__(EW) pcg_scalar_kernel(const double* partial, int64_t nb, const double* rzp,
+                                                        int64_t nrz, int mode, double* S, int* flags, double tol,
+                                                        int maxit, int* host_flag) {
   __shared__ double sum[3];
   const int t = threadIdx.x;
   const int dn = mode != 0 ? flags[0] : 0;
@@ -1330,6 +1316,7 @@ __global__ void __launch_bounds__(EW) pcg_scalar_kernel(const double* partial, i
   for (int64_t b = t; b < nb; b += EW)
 #pragma unroll
     for (int u = 0; u < STRIDE; ++u) v[u] += partial[b * STRIDE + u];
+  for (int64_t b = t; b < nrz; b += EW) v[0] += rzp[b];
   block_sum3(v[0], v[1], v[2], sum);
   __syncthreads();
   if (t != 0 || dn) return;
@@ -1405,23 +1392,15 @@ tdfe_status pcg_solve(tdfe_ctx* c) {
   // preconditioner: Jacobi (z = D^-1 r inside the update kernels) or the fast
   // diagonalisation of the rectilinear stand-in mesh (z = K_box^-1 r in c->t0)
   const int jacobi = c->pcg_precond == TDFE_PCG_JACOBI ? 1 : 0;
-  auto precondition = [&](const int* done) -> tdfe_status {
-    if (jacobi) return TDFE_OK;
-    bool rz_done = false;
-    TDFE_TRY(fdm_passes(c, part, PCG_BLOCKS, &rz_done));
-    if (!rz_done)
-      hipLaunchKernelGGL(pcg_rz_kernel, dim3(PCG_BLOCKS), dim3(EW), 0, c->stream, (const double*)r,
-                         (const double*)c->t0, c->Nx, c->Ny, c->Nz, part, done);
-    TDFE_HIP(c, hipGetLastError());
-    return TDFE_OK;
-  };
+  int64_t nrz = 0;  // its partials of r.z, in z's place (z itself is in c->t0)
+  auto precondition = [&]() -> tdfe_status { return jacobi ? TDFE_OK : fdm_passes(c, z, &nrz); };
   hipLaunchKernelGGL(pcg_rhs_kernel, dim3(nblk(nn)), dim3(EW), 0, c->stream, c->cload, (const double*)c->lift,
                      (const double*)c->phi, x, c->Nx, c->Ny, c->Nz);
   TDFE_TRY(tdfe_zero(c, Ap, nn * sizeof(double)));
   TDFE_TRY(apply_K(x, false, nullptr));
   hipLaunchKernelGGL(pcg_start_kernel, dim3(PCG_BLOCKS), dim3(EW), 0, c->stream, (const double*)c->cload, r, z, pv, Ap,
                      (const double*)c->dinvK, jacobi, c->Nx, c->Ny, c->Nz, c->t0, part);
-  TDFE_TRY(precondition(nullptr));
+  TDFE_TRY(precondition());
   const double* zc = jacobi ? nullptr : c->t0;
   if (!jacobi)
     hipLaunchKernelGGL(pcg_direction_kernel, dim3(nblk(nn)), dim3(EW), 0, c->stream, (const double*)nullptr, zc, pv,
@@ -1431,7 +1410,7 @@ tdfe_status pcg_solve(tdfe_ctx* c) {
   int* dflag = nullptr;
   TDFE_HIP(c, hipHostGetDevicePointer((void**)&dflag, (void*)(c->poll + 40), 0));
   hipLaunchKernelGGL((pcg_scalar_kernel<3>), dim3(1), dim3(EW), 0, c->stream, (const double*)part, (int64_t)PCG_BLOCKS,
-                     0, S, flags, c->pcg_tol, c->pcg_maxit, dflag);
+                     (const double*)z, nrz, 0, S, flags, c->pcg_tol, c->pcg_maxit, dflag);
   TDFE_HIP(c, hipGetLastError());
   // iterations the host is ahead of the stop test it has seen: enqueuing one
   // takes less than running one at every size, and each past the last still
@@ -1444,14 +1423,15 @@ tdfe_status pcg_solve(tdfe_ctx* c) {
     for (int it = 1; it <= c->pcg_maxit; ++it) {
       int64_t groups = 0;
       TDFE_TRY(apply_K(pv, true, &groups));
-      hipLaunchKernelGGL((pcg_scalar_kernel<1>), dim3(1), dim3(EW), 0, c->stream, (const double*)part, groups, 1, S,
+      hipLaunchKernelGGL((pcg_scalar_kernel<1>), dim3(1), dim3(EW), 0, c->stream, (const double*)part, groups,
+                         (const double*)nullptr, (int64_t)0, 1, S,
                          flags, c->pcg_tol, c->pcg_maxit, dflag);
       hipLaunchKernelGGL(pcg_update_kernel, dim3(PCG_BLOCKS), dim3(EW), 0, c->stream, x, r, z, (const double*)pv, Ap,
                          (const double*)c->dinvK, jacobi, c->Nx, c->Ny, c->Nz, c->t0, (const double*)S, part,
                          (const int*)flags);
-      TDFE_TRY(precondition(flags));
+      TDFE_TRY(precondition());
       hipLaunchKernelGGL((pcg_scalar_kernel<3>), dim3(1), dim3(EW), 0, c->stream, (const double*)part,
-                         (int64_t)PCG_BLOCKS, 2, S, flags, c->pcg_tol, c->pcg_maxit, dflag);
+                         (int64_t)PCG_BLOCKS, (const double*)z, nrz, 2, S, flags, c->pcg_tol, c->pcg_maxit, dflag);
       hipLaunchKernelGGL(pcg_direction_kernel, dim3(nblk(nn)), dim3(EW), 0, c->stream, (const double*)z, zc, pv,
                          (const double*)S, c->Nx, c->Ny, c->Nz, (const int*)flags);
       TDFE_HIP(c, hipGetLastError());
