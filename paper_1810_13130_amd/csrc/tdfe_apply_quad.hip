@@ -1,4 +1,4 @@
-// Operator kernel for blocks of more than 8 real columns, n = 5..8: four lanes
+// Operator kernel for blocks of more than 8 real columns, n = 8 and FP64 n = 7: four lanes
 // per plane line, one wavefront per plane (Eq. DiscreteHamiltonian in the
 // Loewdin form, Eq. TDKSMatVecStandard), for box and trilinear cells.
 //
@@ -196,11 +196,6 @@ __device__ __forceinline__ float off_quad(float v) {
   return v - __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xFF, 0xf, 0xf, false));
 }
 
-template <typename T, int N, bool BOX>
-constexpr int quad_wpe() {
-  return sizeof(T) == 8 && !BOX && N == 6 ? 3 : 4;
-}
-
 // The Jacobian of a trilinear cell: its column along one reference axis is
 // bilinear in the other two coordinates, so the 3 n^2 columns of a cell are
 // formed once (entry [axis][u + n v], u and v the Gauss points of the other
@@ -255,10 +250,10 @@ __device__ __forceinline__ void quad_metric(T* g, const double* sJ, const double
 }
 
 template <typename T, int N, bool BOX, bool CELLS>
-__global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(quad_wpe<T, N, BOX>())))
+__global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(4)))
     quad_kernel(QuadParams<T> P) {
   constexpr int H = N / 2;
-  constexpr int HZ = (N + 1) / 2;  // positions of q in use
+  static_assert(N == 7 || N == 8);  // every lane of a quad holds entries
   constexpr bool ODD = (N & 1) != 0;
   constexpr int VOL = N * N * N;
   constexpr int THREADS = 64 * N;
@@ -290,8 +285,6 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(qua
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int q = F32 ? lane & 3 : lane >> 4;
   const int col = F32 ? lane >> 2 : lane & 15;
-  const bool live = HZ == 4 || q < HZ;
-  const int qc = live ? q : 0;  // idle lanes take lane 0's data; their table columns are 0
   const int L = remap_block(blockIdx.x, gridDim.x);
   const int ch = L % P.nchunks;
   const int cell = L / P.nchunks;
@@ -332,8 +325,8 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(qua
 
   // lane masks along x: node q and node n-1-q are DoFs (cell faces on the
   // domain boundary hold Dirichlet nodes)
-  const bool x1ok = live && !(q == 0 && cx == 0);
-  const bool x2ok = live && !(q == 0 && cx == P.ncx - 1);
+  const bool x1ok = !(q == 0 && cx == 0);
+  const bool x2ok = !(q == 0 && cx == P.ncx - 1);
   const bool jok = !(w == 0 && cy == 0) && !(w == N - 1 && cy == P.ncy - 1);
   auto kok = [&](int k) { return !(k == 0 && cz == 0) && !(k == N - 1 && cz == P.ncz - 1); };
   // row of node (0, w, k) among the DoFs (-1 relative to the first DoF of the
@@ -355,18 +348,17 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(qua
     int ln = lane;
     asm volatile("" : "+v"(ln));
     const int qq = F32 ? ln & 3 : ln >> 4, cc = F32 ? ln >> 2 : ln & 15;
-    const int qv = HZ == 4 || qq < HZ ? qq : 0, qm = N - 1 - qv;
-    return Pos{w * LY + qv * LX + cc, w * LY + qm * LX + cc, qv * LY + w * LX + cc, qm * LY + w * LX + cc,
-               w + N * qv,            w + N * qm,            qv + N * w,            qm + N * w};
+    const int qm = N - 1 - qq;
+    return Pos{w * LY + qq * LX + cc, w * LY + qm * LX + cc, qq * LY + w * LX + cc, qm * LY + w * LX + cc,
+               w + N * qq,            w + N * qm,            qq + N * w,            qm + N * w};
   };
 
-  // the quadratic form of a lane's points; the middle entry is held twice, idle
-  // lanes hold lane 0's
+  // the quadratic form of a lane's points; the middle entry is held twice
   auto park_energy = [&](double e) {
     int ln = lane;
     asm volatile("" : "+v"(ln));
     const int qq = F32 ? ln & 3 : ln >> 4, cc = F32 ? ln >> 2 : ln & 15;
-    const double ew = (HZ < 4 && qq >= HZ) ? 0.0 : (ODD && qq == H ? 0.5 : 1.0);
+    const double ew = ODD && qq == H ? 0.5 : 1.0;
     sRed[w * 64 + ln] = ch * QC + cc < P.cols ? e * ew : 0.0;
   };
   {
@@ -402,8 +394,8 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(qua
     // box cells: M^-1/2 factors of the lane's two x entries and of the z rows
     T mx1 = 0, mx2 = 0, my = 0, mz[N];
     if constexpr (BOX) {
-      mx1 = (T)P.m1x[cx * P.p + qc];
-      mx2 = (T)P.m1x[cx * P.p + N - 1 - qc];
+      mx1 = (T)P.m1x[cx * P.p + q];
+      mx2 = (T)P.m1x[cx * P.p + N - 1 - q];
       my = (T)P.m1y[cy * P.p + w];
 #pragma unroll
       for (int k = 0; k < N; ++k) mz[k] = (T)P.m1z[cz * P.p + k];
@@ -488,12 +480,10 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(qua
     }
     // ---------------- transposes (y = w; x lanes) -> (x = w; y lanes) ----------------------
     auto put = [&](int i1, int i2, const T* v1, const T* v2) {
-      if (live) {
 #pragma unroll
-        for (int c = 0; c < N; ++c) {
-          sX[i1 + c * QC] = v1[c];
-          sX[i2 + c * QC] = v2[c];
-        }
+      for (int c = 0; c < N; ++c) {
+        sX[i1 + c * QC] = v1[c];
+        sX[i2 + c * QC] = v2[c];
       }
     };
     // reads an array folded: sums in v1, differences in v2
@@ -531,7 +521,7 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(qua
 #pragma unroll
       for (int i = 1; i < N; ++i) {
         wa = w == i ? (T)FB.wq[i] : wa;
-        wb = qc == i ? (T)FB.wq[i] : wb;
+        wb = q == i ? (T)FB.wq[i] : wb;
       }
       // twice: the sums below are folded values
       const T gx = (T)(2.0 * P.kin * P.cellgeo[(int64_t)cell * 4 + 0]) * wb;
@@ -739,7 +729,7 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(qua
       int ln = lane;
       asm volatile("" : "+v"(ln));
       const int qq = F32 ? ln & 3 : ln >> 4, cc = ch * QC + (F32 ? ln >> 2 : ln & 15);
-      if (cc < P.cols && (HZ == 4 || qq < HZ)) {
+      if (cc < P.cols) {
         if constexpr (CELLS) {
           T* const E = P.y + ((int64_t)cell * VOL + N * w) * P.cols;
           const uint32_t o1 = (uint32_t)(qq * P.cols + cc), o2 = (uint32_t)((N - 1 - qq) * P.cols + cc);
