@@ -363,4 +363,16 @@ __device__ __forceinline__ double wave_sum(double v) {
   v = lane_add<0x142, 0xa>(v);    // row_bcast:15 into rows 1 and 3
   return lane_add<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
 }
-
+// acc += row(r) for r = first, first + step, .. below n, in that order, eight
+// loads in flight: the sums of block partials wait for memory once per eight
+// rows instead of once per row
+template <typename F>
+__device__ __forceinline__ void sum_rows(int64_t n, int first, int step, const F& row, double& acc) {
+  for (int64_t b = first; b < n; b += 8 * (int64_t)step) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = row(min(b + u * (int64_t)step, n - 1));
+#pragma unroll
+    for (int u = 0; u < 8; ++u) acc += b + u * (int64_t)step < n ? v[u] : 0.0;
+  }
+}

@@ -410,10 +410,10 @@ __global__ void __launch_bounds__(RED_THREADS)
   const int dn = done ? *done : 0;
   const double mo = mult ? mult[o] : 1.0;
   double acc = 0.0;
-  for (int64_t b = threadIdx.x; b < nblocks; b += RED_THREADS) {
+  sum_rows(nblocks, (int)threadIdx.x, RED_THREADS, [&](int64_t b) {
     const double2 p2 = *(const double2*)(partial + b * C + 2 * o);
-    acc += p2.x + p2.y;
-  }
+    return p2.x + p2.y;
+  }, acc);
   double v = block_sum(acc, swave);
   if (threadIdx.x == 0 && !dn) {
     if (mode == 0 && mult) v *= mo * mo;
@@ -445,7 +445,7 @@ __global__ void __launch_bounds__(RED_THREADS)
   const int64_t r1 = r0 + per < nrows ? r0 + per : nrows;
   double acc = 0.0;
   if (col < C)
-    for (int64_t r = r0 + rl; r < r1; r += nl) acc += partial[r * C + col];
+    sum_rows(r1 - r0, rl, nl, [&](int64_t r) { return partial[(r0 + r) * C + col]; }, acc);
   sred[threadIdx.x] = acc;
   __syncthreads();
   if (rl == 0 && col < C) {
@@ -549,10 +549,10 @@ __global__ void __launch_bounds__(RED_THREADS)
   const double amax = S.ext[2 * o + 0], terms = S.ext[2 * o + 1], nrm = S.nrm[o];
   const double2 yl = *(const double2*)(S.y + ((size_t)o * k_max + k - 1) * 2);
   double acc = 0.0;
-  for (int64_t b = threadIdx.x; b < nblocks; b += RED_THREADS) {
+  sum_rows(nblocks, (int)threadIdx.x, RED_THREADS, [&](int64_t b) {
     const double2 p2 = *(const double2*)(partial + b * C + 2 * o);
-    acc += p2.x + p2.y;
-  }
+    return p2.x + p2.y;
+  }, acc);
   const double bk = sqrt(block_sum(acc, swave));
   if (threadIdx.x != 0 || dn) return;
   const double sc = bk > 0.0 ? 1.0 / bk : 0.0;

@@ -183,7 +183,7 @@ __global__ void finalize4_kernel(const double* partial, int64_t nblocks, double*
   __shared__ double sred[256];
   const int v = blockIdx.x;
   double acc = 0.0;
-  for (int64_t b = threadIdx.x; b < nblocks; b += 256) acc += partial[b * 4 + v];
+  sum_rows(nblocks, (int)threadIdx.x, 256, [&](int64_t b) { return partial[b * 4 + v]; }, acc);
   sred[threadIdx.x] = acc;
   __syncthreads();
   for (int s = 128; s > 0; s >>= 1) {
@@ -1313,10 +1313,10 @@ __global__ void __launch_bounds__(EW) pcg_scalar_kernel(const double* partial, i
   const int t = threadIdx.x;
   const int dn = mode != 0 ? flags[0] : 0;
   double v[3] = {0, 0, 0};
-  for (int64_t b = t; b < nb; b += EW)
 #pragma unroll
-    for (int u = 0; u < STRIDE; ++u) v[u] += partial[b * STRIDE + u];
-  for (int64_t b = t; b < nrz; b += EW) v[0] += rzp[b];
+  for (int u = 0; u < STRIDE; ++u)
+    sum_rows(nb, t, EW, [&](int64_t b) { return partial[b * STRIDE + u]; }, v[u]);
+  sum_rows(nrz, t, EW, [&](int64_t b) { return rzp[b]; }, v[0]);
   block_sum3(v[0], v[1], v[2], sum);
   __syncthreads();
   if (t != 0 || dn) return;
