@@ -565,23 +565,37 @@ __global__ void __launch_bounds__(RED_THREADS)
 }
 
 // z = ||psi|| sum_j y_j s_j w_j, written into the complex128 output chunk.
-// One thread per (row, orbital); the coefficients y_j s_j of the block's
-// orbitals are staged in LDS in tiles of COMB_JT iterations (kcap: an upper
-// bound of every orbital's k, the iterations enqueued), and four basis
-// vectors are loaded per round so that several loads are in flight per lane.
+// A lane keeps one orbital and takes RPT rows; the coefficients y_j s_j of the
+// block's orbitals are staged in LDS in tiles of COMB_JT iterations (kcap: an
+// upper bound of every orbital's k, the iterations enqueued), and 8 values
+// are loaded per round so that several loads are in flight per lane.  Reads
+// the whole basis once, so memory bounds it; four rows per lane (from 2^18
+// values on) spread a block's start, two dependent reads and the staging,
+// over four times the data
+// (one row each: 209 us for 18 FP64 vectors of 63 MB, 89 us for 12 FP32 ones,
+// 7.6 ms for 115 of 374 MB; so 189 us, 80 us and 7.3 ms, 6.0 TB/s).
 constexpr int COMB_JT = 32;
-template <typename T>
+template <typename T, int RPT>
 __global__ void __launch_bounds__(256)
     combine_kernel(const T* __restrict__ W, int64_t stride_vec, int C, int64_t nrows, Scal S, int Nc, int k_max,
                    int kcap, double* __restrict__ out, int ld_out, int col0) {
+  typedef T V2 __attribute__((ext_vector_type(2)));
+  constexpr int JU = 8 / RPT;  // iterations per round
   __shared__ double2 sa[COMB_JT * (TDFE_MAX_COLS / 2)];
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int o = (int)(idx % Nc);
-  const int64_t r = idx / Nc;
-  const bool live = r < nrows;
-  const int kc = live ? S.kconv[o] : 0;
-  const T* __restrict__ w = W + (live ? r : 0) * C + 2 * o;
-  double zr = 0.0, zi = 0.0;
+  const int rpb = 256 / Nc;  // rows side by side in a block
+  const int o = (int)threadIdx.x % Nc, rl = (int)threadIdx.x / Nc;
+  const int64_t r0 = (int64_t)blockIdx.x * RPT * rpb + rl;
+  const int kc = rl < rpb && r0 < nrows ? S.kconv[o] : 0;
+  const V2* __restrict__ w[RPT];
+#pragma unroll
+  for (int u = 0; u < RPT; ++u) {
+    const int64_t r = r0 + u * rpb;
+    w[u] = (const V2*)W + (r < nrows ? r : 0) * Nc + o;
+  }
+  const int64_t sv = stride_vec >> 1;
+  double zr[RPT], zi[RPT];
+#pragma unroll
+  for (int u = 0; u < RPT; ++u) zr[u] = zi[u] = 0.0;
   for (int j0 = 0; j0 < kcap; j0 += COMB_JT) {
     const int jt = min(COMB_JT, kcap - j0);
     __syncthreads();
@@ -592,34 +606,38 @@ __global__ void __launch_bounds__(256)
     }
     __syncthreads();
     const int je = min(kc - j0, jt);  // this orbital's iterations in the tile (none if <= 0)
+    auto round = [&](int jj, auto count) {
+      constexpr int J = decltype(count)::value;
+      V2 q[J][RPT];
+#pragma unroll
+      for (int v = 0; v < J; ++v)
+#pragma unroll
+        for (int u = 0; u < RPT; ++u) q[v][u] = __builtin_nontemporal_load(w[u] + (j0 + jj + v) * sv);
+#pragma unroll
+      for (int v = 0; v < J; ++v) {
+        const double2 a = sa[(jj + v) * Nc + o];
+#pragma unroll
+        for (int u = 0; u < RPT; ++u) {
+          const double qr = (double)q[v][u].x, qi = (double)q[v][u].y;
+          zr[u] += a.x * qr - a.y * qi;
+          zi[u] += a.x * qi + a.y * qr;
+        }
+      }
+    };
     int jj = 0;
-    for (; jj + 4 <= je; jj += 4) {
-      double qr[4], qi[4];
+    for (; jj + JU <= je; jj += JU) round(jj, std::integral_constant<int, JU>{});
+    for (; jj < je; ++jj) round(jj, std::integral_constant<int, 1>{});
+  }
+  if (rl >= rpb) return;
+  const double nr = S.nrm[o];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const T* q = w + (int64_t)(j0 + jj + u) * stride_vec;
-        qr[u] = (double)q[0];
-        qi[u] = (double)q[1];
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const double2 a = sa[(jj + u) * Nc + o];
-        zr += a.x * qr[u] - a.y * qi[u];
-        zi += a.x * qi[u] + a.y * qr[u];
-      }
-    }
-    for (; jj < je; ++jj) {
-      const T* q = w + (int64_t)(j0 + jj) * stride_vec;
-      const double qr = (double)q[0], qi = (double)q[1];
-      const double2 a = sa[jj * Nc + o];
-      zr += a.x * qr - a.y * qi;
-      zi += a.x * qi + a.y * qr;
+  for (int u = 0; u < RPT; ++u) {
+    const int64_t r = r0 + u * rpb;
+    if (r < nrows) {
+      out[r * ld_out + col0 + 2 * o] = nr * zr[u];
+      out[r * ld_out + col0 + 2 * o + 1] = nr * zi[u];
     }
   }
-  if (!live) return;
-  const double nr = S.nrm[o];
-  out[r * ld_out + col0 + 2 * o] = nr * zr;
-  out[r * ld_out + col0 + 2 * o + 1] = nr * zi;
 }
 
 __global__ void init_scal_kernel(Scal S, int Nc) {
@@ -850,9 +868,14 @@ tdfe_status run_chunk(tdfe_ctx* c, const void* vw, const double* in, double* out
   }
   // combination
   {
-    const int64_t n = nd * Nc;
-    hipLaunchKernelGGL((combine_kernel<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, (const T*)W,
-                       vstride, C, nd, S, Nc, K, std::min(k_enq, K), out, ld, 2 * o0);
+    auto combine = [&](auto kernel, int rows) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)((nd + rows - 1) / rows)), dim3(256), 0, c->stream, (const T*)W, vstride,
+                         C, nd, S, Nc, K, std::min(k_enq, K), out, ld, 2 * o0);
+    };
+    if (nd * C >= 1 << 18)
+      combine(combine_kernel<T, 4>, 4 * (256 / Nc));
+    else
+      combine(combine_kernel<T, 1>, 256 / Nc);
     TDFE_HIP(c, hipGetLastError());
   }
   if (defer_slot) {
