@@ -759,18 +759,21 @@ def matrix_core_engines(steps=100, warmup=5, reps=100):
 
 def curved_kernel_name(p, cols, fp32):
     """Name of the trilinear-cell operator kernel a launch of `cols` real
-    columns runs (the library's default choice: lane pairs for FP64 and for
-    FP32 at p = 7, plane ownership for FP32 below; columns per block the next
-    power of two up to 16, at least 2 for lane pairs, or 32 for FP32 plane
-    launches of more than 16)."""
+    columns runs (the library's default choice: four lanes per line for more
+    than 8 columns at p = 7 and FP64 p = 6, else lane pairs for FP64 p >= 5 and
+    for FP32 at p = 7, else plane ownership; columns per block the next power
+    of two up to 16, at least 2 for lane pairs, or 32 for FP32 plane launches of
+    more than 16)."""
     n = p + 1
     pw = 1
     while pw < cols:
         pw *= 2
-    if not fp32 or n == 8:
-        t = "float" if fp32 else "double"
+    t = "float" if fp32 else "double"
+    if cols > 8 and (n == 8 or (n == 7 and not fp32)):
+        return f"quad_kernel<{t},{n},false,CELLS> (trilinear cells, four lanes per line)"
+    if (not fp32 and n > 5) or n == 8:
         return f"cpair_kernel<{t},{n},{max(2, min(pw, 16))},CPB> (trilinear cells, lane pairs)"
-    return f"cplane_kernel<float,{n},{32 if cols > 16 else pw},CPB> (trilinear cells)"
+    return f"cplane_kernel<{t},{n},{(32 if fp32 else 16) if cols > 16 else pw},CPB> (trilinear cells)"
 
 
 def workload_legs(cfg, steps, warmup, apply_reps, curved, matched=True, jacobi_count=False):
@@ -784,7 +787,7 @@ def workload_legs(cfg, steps, warmup, apply_reps, curved, matched=True, jacobi_c
     r64 = run_steps(ctx, psi, cfg, cfg.tol, steps, warmup)
     t_chunk = time_apply(ctx, chunk64, False, apply_reps)
     t_full = time_apply(ctx, cfg.n_orb, False, max(3, apply_reps // 4))
-    kname = curved_kernel_name(cfg.p, 2 * chunk64, False) if curved else "pair_kernel<double,6,16,1> (box cells)"
+    kname = curved_kernel_name(cfg.p, 2 * chunk64, False) if curved else "pair_kernel<double,6,16,1> + assemble_kernel (box cells)"
     res["f64"] = {**{k: v for k, v in r64.items() if k != "mu"}, "chunk_orbitals": chunk64,
                   "roofline": roofline(ctx, cfg, chunk64, t_chunk, False, kname, curved),
                   "apply_H_gdof_orb_per_s": ctx.n_dof * cfg.n_orb / t_full / 1e9, "apply_full_ms": t_full * 1e3}
@@ -810,7 +813,7 @@ def workload_legs(cfg, steps, warmup, apply_reps, curved, matched=True, jacobi_c
                     "dipole_rel_err": e, "dipole_err_rel_induced": e_ind, "steps_compared": n,
                     "speedup_vs_f64_same_tol": r32["steps_per_s"] / r64["steps_per_s"],
                     "roofline": roofline(ctx, cfg, chunk32, t_chunk32, True,
-                                         kname32 if curved else "plane_kernel<float,6,16,2> (box cells)", curved),
+                                         kname32 if curved else "plane_kernel<float,6,16,2> + assemble_kernel (box cells)", curved),
                     "apply_H_gdof_orb_per_s": ctx.n_dof * cfg.n_orb / t_full32 / 1e9, "apply_full_ms": t_full32 * 1e3}
     close(ctx)
     if matched:
