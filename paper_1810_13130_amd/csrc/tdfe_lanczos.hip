@@ -173,7 +173,25 @@ struct SmallExp {
   double* jtab;  // [Nc][TDFE_JTAB_STRIDE] Bessel tables
   unsigned* progress;  // pinned progress word (may be null)
   int gen;
+  // alpha_k still as the operator's block partials [groups][2 Nc] (0: it is in
+  // S.alpha), to be multiplied by mult^2 (may be null)
+  const double* apart;
+  int groups;
+  const double* mult;
 };
+
+// alpha_k of orbital o from the operator's block partials, on one wavefront;
+// every wavefront that asks forms the same sum in the same order
+__device__ __forceinline__ double alpha_of(const SmallExp& e, int o) {
+  const int C = 2 * e.Nc;
+  const double m = e.mult ? e.mult[o] : 1.0;
+  double acc = 0.0;
+  sum_rows(e.groups, (int)threadIdx.x & 63, 64, [&](int64_t b) {
+    const double2 p2 = *(const double2*)(e.apart + b * C + 2 * o);
+    return p2.x + p2.y;
+  }, acc);
+  return lane_read(wave_sum(acc), 63) * (m * m);
+}
 
 //
 // Up to SMALL_ROWS rows of T_k per lane, that is k <= 256 (chosen per launch
@@ -184,7 +202,7 @@ struct SmallExp {
 // its 115 iterations.
 constexpr int SMALL_ROWS = 4;
 // R rows of T_k per lane; every load is issued before the first is waited for
-template <int R>
+template <int R, bool OWN>
 __device__ void small_exp_block(const SmallExp& e, const int* done) {
   const int o = blockIdx.x;
   const int t = threadIdx.x;
@@ -200,8 +218,15 @@ __device__ void small_exp_block(const SmallExp& e, const int* done) {
     bl[r] = (row && j > 0) ? e.S.beta[(size_t)(j - 1) * Nc + o] : 0.0;
     br[r] = (row && j < k - 1) ? e.S.beta[(size_t)j * Nc + o] : 0.0;
   }
+  double ak = 0.0;
+  if constexpr (OWN) {
+    ak = alpha_of(e, o);
+#pragma unroll
+    for (int r = 0; r < R; ++r) a[r] = R * t + r == k - 1 ? ak : a[r];
+  }
   if (dn) return;
   if (o == 0 && t == 0) post_progress(e.progress, e.gen, k - 1);
+  if (OWN && t == 0) e.S.alpha[(size_t)(k - 1) * Nc + o] = ak;
   if (st != 0) return;
   const int M = cheb_series<R>(k, a, bl, br, e.tau, e.jtab + (size_t)o * TDFE_JTAB_STRIDE, yr, yi, &amax);
 #pragma unroll
@@ -245,7 +270,7 @@ __global__ void __launch_bounds__(RED_THREADS)
                   double* __restrict__ partial, const int* done, SmallExp se) {
   __shared__ double sred[RED_THREADS];
   if ((int)blockIdx.x < se.nblk) {
-    small_exp_block<SR>(se, done);
+    small_exp_block<SR, false>(se, done);
     return;
   }
   const int dn = *done;
@@ -327,7 +352,7 @@ __global__ void __launch_bounds__(RED_THREADS)
 // bytes of a row (one FP64 or two FP32 orbitals).  Reads the cell results once (n^3 / p^3 vectors), w_j and
 // w_{j-1}, writes w_{j+1}; no operator output vector is kept, seeded or cleared.
 constexpr int CELL_BLOCKS = 2048;  // at most: one block per row of DoFs up to this
-template <typename T, int W, int SR>
+template <typename T, int W, int SR, bool OWN>
 __global__ void __launch_bounds__(RED_THREADS)
     update_cells_kernel(const T* __restrict__ e, const T* __restrict__ wa, const T* __restrict__ wp,
                         T* __restrict__ wn, int C, CellMap M, const double* alpha_j, const double* s_j,
@@ -337,8 +362,9 @@ __global__ void __launch_bounds__(RED_THREADS)
   constexpr int NO = W / 2;  // orbitals per lane
   __shared__ double sred[RED_THREADS];
   __shared__ double sorb[2 * RED_THREADS / 4];
+  __shared__ double salpha[TDFE_MAX_COLS / 2];
   if ((int)blockIdx.x < se.nblk) {
-    small_exp_block<SR>(se, done);
+    small_exp_block<SR, OWN>(se, done);
     return;
   }
   const int dn = *done;
@@ -349,20 +375,28 @@ __global__ void __launch_bounds__(RED_THREADS)
   const int XL = RED_THREADS / Op;
   const int o = (int)threadIdx.x % Op;
   const int xl = (int)threadIdx.x / Op;
-  double acc[NO];
+  double acc[NO], ca[NO], cm[NO], cb[NO];
 #pragma unroll
-  for (int q = 0; q < NO; ++q) acc[q] = 0.0;
-  if (o < C2) {
-    double ca[NO], cm[NO], cb[NO];
-#pragma unroll
-    for (int q = 0; q < NO; ++q) {
-      const int oo = o * NO + q;
-      const Coef cf(status, alpha_j, s_j, m_j, oo);
-      const double sp = s_p[oo];
-      ca[q] = cf.ca;
-      cm[q] = cf.cm;
-      cb[q] = wp ? cf.cm * sp : 0.0;
+  for (int q = 0; q < NO; ++q) {
+    const int oo = min(o, C2 - 1) * NO + q;
+    const Coef cf(status, alpha_j, s_j, m_j, oo);
+    const double sp = s_p[oo];
+    ca[q] = OWN ? cf.s : cf.ca;
+    cm[q] = cf.cm;
+    cb[q] = wp ? cf.cm * sp : 0.0;
+    acc[q] = 0.0;
+  }
+  if constexpr (OWN) {
+    // few operator blocks: every block sums their partials itself (see run_chunk)
+    for (int oo = (int)threadIdx.x >> 6; oo < se.Nc; oo += RED_THREADS / 64) {
+      const double al = alpha_of(se, oo);
+      if ((threadIdx.x & 63) == 0) salpha[oo] = al;
     }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NO; ++q) ca[q] = ca[q] != 0.0 ? ca[q] * salpha[min(o, C2 - 1) * NO + q] : 0.0;
+  }
+  if (o < C2) {
     if (dn) return;
     const int nrows = M.NyI * M.NzI;
     for (int r = bid; r < nrows; r += (int)gridDim.x - se.nblk) {
@@ -431,6 +465,8 @@ __global__ void __launch_bounds__(RED_THREADS)
 // sums its contiguous share of rows for every column into out[b][C] (the
 // second level is finalize_pairs_kernel over the ALPHA_SLICES rows of out)
 constexpr int ALPHA_SLICES = 128;
+// up to this many partials every block of the update sums them itself
+constexpr int ALPHA_OWN = 2048;
 __global__ void __launch_bounds__(RED_THREADS)
     slice_sums_kernel(const double* __restrict__ partial, int64_t nrows, int C, double* __restrict__ out,
                       const int* done) {
@@ -770,7 +806,18 @@ tdfe_status run_chunk(tdfe_ctx* c, const void* vw, const double* in, double* out
     TDFE_TRY(cells ? tdfe_launch_apply_cells(c, a) : tdfe_launch_apply(c, a));
     // m = beta_{k-2} for k >= 2 (the operator input was scaled by s^2, not s), 1 for k = 1
     const double* m = k >= 2 ? S.beta + (size_t)(k - 2) * Nc : (const double*)nullptr;
-    if (groups > 64 * ALPHA_SLICES) {
+    const bool ride = k <= SMALL_ROWS * CHK_THREADS;  // small exponential on the update's leading blocks
+    // Few operator blocks: alpha is summed by the update's own blocks, each for
+    // itself, and left in S.alpha by the blocks of the small exponential; the
+    // update's norm partials then lie behind the operator's.  A launch of 2 to 3
+    // us less in iterations of 19 (one orbital on 4^3 cells, 11 blocks: a step
+    // of ten 290 -> 264 us) to 27 us (4 orbitals on 8^3 cells, 256 blocks: 28.6
+    // -> 27.7 ms in 680); beyond, every block's reads of all partials grow past
+    // what the launch costs.  Up to k = 64 only: its registers (80 instead of
+    // 44) are not worth having in the kernels of long iterations.
+    const bool own_alpha = cells && k <= CHK_THREADS && groups * C <= ALPHA_OWN;
+    double* const norms = own_alpha ? c->partial + ALPHA_OWN : c->partial;
+    if (!own_alpha && groups > 64 * ALPHA_SLICES) {
       // many operator blocks: a first level over slices of rows (all columns
       // at once), then the per-orbital sums over the slices (29,791 blocks:
       // 13 us against 45 us in one level; 4,096 blocks: 9.5 us against 6.8 us)
@@ -779,12 +826,11 @@ tdfe_status run_chunk(tdfe_ctx* c, const void* vw, const double* in, double* out
       hipLaunchKernelGGL(finalize_pairs_kernel, dim3(Nc), dim3(RED_THREADS), 0, c->stream, (const double*)c->partial2,
                          (int64_t)ALPHA_SLICES, C, S.alpha + (size_t)(k - 1) * Nc, 0, (double*)nullptr, (double*)nullptr,
                          m, (const int*)S.done);
-    } else {
+    } else if (!own_alpha) {
       hipLaunchKernelGGL(finalize_pairs_kernel, dim3(Nc), dim3(RED_THREADS), 0, c->stream, c->partial, groups, C,
                          S.alpha + (size_t)(k - 1) * Nc, 0, (double*)nullptr, (double*)nullptr, m, (const int*)S.done);
     }
-    const bool ride = k <= SMALL_ROWS * CHK_THREADS;  // small exponential on the update's leading blocks
-    SmallExp se{S, Nc, k, K, ride ? Nc : 0, tau, c->jtab, dprog, gen};
+    SmallExp se{S, Nc, k, K, ride ? Nc : 0, tau, c->jtab, dprog, gen, c->partial, own_alpha ? (int)groups : 0, m};
     auto update = [&](auto rows) {
       constexpr int R = decltype(rows)::value;
       if (!cells) {
@@ -801,14 +847,15 @@ tdfe_status run_chunk(tdfe_ctx* c, const void* vw, const double* in, double* out
                            W + (int64_t)k * vstride, C, map, (const double*)(S.alpha + (size_t)(k - 1) * Nc),
                            (const double*)(S.scale + (size_t)(k - 1) * Nc), m,
                            (const double*)(S.scale + (size_t)(k >= 2 ? k - 2 : 0) * Nc), (const int*)S.status,
-                           c->partial, (const int*)S.done, se);
+                           norms, (const int*)S.done, se);
       };
       // 16 bytes per lane where the columns allow it
       constexpr int WIDE = sizeof(T) == 4 ? 4 : 2;
-      if (C % WIDE == 0)
-        run(update_cells_kernel<T, WIDE, R>);
+      constexpr bool CAN_OWN = R == 1;
+      if (CAN_OWN && own_alpha)
+        C % WIDE == 0 ? run(update_cells_kernel<T, WIDE, R, CAN_OWN>) : run(update_cells_kernel<T, 2, R, CAN_OWN>);
       else
-        run(update_cells_kernel<T, 2, R>);
+        C % WIDE == 0 ? run(update_cells_kernel<T, WIDE, R, false>) : run(update_cells_kernel<T, 2, R, false>);
     };
     if (k <= CHK_THREADS || !ride)
       update(std::integral_constant<int, 1>{});
@@ -818,7 +865,7 @@ tdfe_status run_chunk(tdfe_ctx* c, const void* vw, const double* in, double* out
       update(std::integral_constant<int, SMALL_ROWS>{});
     // beta_k, the scale 1/beta_k of the next basis vector and the stop test
     if (ride) {
-      hipLaunchKernelGGL(beta_check_kernel, dim3(Nc), dim3(RED_THREADS), 0, c->stream, (const double*)c->partial,
+      hipLaunchKernelGGL(beta_check_kernel, dim3(Nc), dim3(RED_THREADS), 0, c->stream, (const double*)norms,
                          (int64_t)red_blocks, C, S, Nc, k, K, Kc, tau, tol, tol_rel, err_flag, dflag, gen);
     } else {
       hipLaunchKernelGGL(finalize_pairs_kernel, dim3(Nc), dim3(RED_THREADS), 0, c->stream, c->partial,
