@@ -234,10 +234,10 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
     // first node row: nodes outside the array (the Dirichlet planes at the
     // domain faces) have negative offsets or offsets past the end and read
     // 0; Dirichlet nodes inside its range (I = 0 or Nx-1, which alias a
-    // neighbouring row's DoF) read a value that the zero in sM cancels.  No
-    // address is selected and no value is masked.  The range is kept below
-    // 2^31 bytes, so every negative 32-bit offset is out of range; a block
-    // spans at most (n-1)(1 + row + plane) rows, far below that.
+    // neighbouring row's DoF) read a value that the zero in sM cancels, and
+    // lanes without a column or cell start past its end (gather_offset).  The
+    // range is kept below 2^31 bytes, so every negative 32-bit offset is out
+    // of range.
     T u[N][N];  // [i][k]: gathered values, all loads in flight together
     {
       // the resource is built from the block's first cell (the lowest rows
@@ -256,7 +256,7 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
           (void*)(uintptr_t)(((uint64_t)ahi << 32) | alo), 0, nrec, 0x00020000);
       const int ldb = P.ld * (int)sizeof(T);
       const int64_t kst = nk * ldb;
-      const int64_t off0 = ((n0 - base) * P.ld + colg) * (int64_t)sizeof(T);
+      const int64_t off0 = tdfe_span::gather_offset(act, n0 - base, P.ld, colg, (int)sizeof(T));
 #pragma unroll
       for (int k = 0; k < N; ++k) {
         const int ok = (int)(off0 + k * kst);
@@ -820,7 +820,7 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
           (void*)(uintptr_t)(((uint64_t)ahi << 32) | alo), 0, nrec, 0x00020000);
       const int ldb = P.ld * (int)sizeof(T);
       const int64_t kst = nk * ldb;
-      const int64_t off0 = ((n0 - base) * P.ld + colg) * (int64_t)sizeof(T);
+      const int64_t off0 = tdfe_span::gather_offset(act, n0 - base, P.ld, colg, (int)sizeof(T));
 #pragma unroll
       for (int k = 0; k < HZ; ++k) {
         const int ok = (int)(off0 + zg(k) * kst);

@@ -6,6 +6,7 @@
 #pragma once
 #include "tdfe_internal.h"
 #include "tdfe_rule1d.h"
+#include "tdfe_span.h"
 
 namespace {
 
@@ -270,7 +271,7 @@ struct CellOut {
 // block's first row on, byte offsets per lane; entries that are not read (the
 // Dirichlet planes, columns past the last) carry offsets past its end and
 // give 0
-constexpr uint32_t CELL_NO_READ = 0x80000000u;
+constexpr uint32_t CELL_NO_READ = tdfe_span::NO_READ;
 template <typename T, typename Params>
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t cell_rsrc(const Params& P, const CellPos& B) {
   const int64_t first = B.row(P), rows = (int64_t)(P.Nx - 2) * (P.Ny - 2) * (P.Nz - 2);
