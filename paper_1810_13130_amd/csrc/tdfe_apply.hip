@@ -625,20 +625,6 @@ int64_t tdfe_blocks_apply(const tdfe_ctx* c, int cols) {
   return c->n_cell;
 }
 
-// Launches of the plane, lane-pair and four-lane kernels: Loewdin DoF vectors,
-// p <= 7; two or more columns on trilinear cells (one column leaves n threads
-// per cell with the metric staged for the whole cell: the line kernel is
-// faster there, 0.64 ms against 2.2 ms for the Hartree solve's one-column
-// products on the graded mesh)
-static bool block_kernels_ok(const tdfe_ctx* c, const ApplyArgs& a) {
-  // 32-bit byte offsets within a block's cells, which may wrap to the next row
-  // or layer of cells (the line kernel has no such limit)
-  const int64_t plane = (int64_t)c->Nx * c->Ny, row = (int64_t)a.ld * (a.fp32 ? 4 : 8);
-  if (3 * c->n * plane * row >= (int64_t)1 << 31 || c->n_cell >= (int64_t)1 << 30) return false;
-  return c->variant != TDFE_VARIANT_LINE && a.lowdin && !a.fullgrid &&
-         (c->box ? tdfe_box_kernel_ok(c) : tdfe_curved_kernel_ok(c, a.cols, a.fp32));
-}
-
 static tdfe_status launch_blocks(tdfe_ctx* c, const ApplyArgs& a) {
   // default policy, from measurements on the benchmark and graded workloads:
   // the four-lane kernel where tdfe_quad_kernel_ok says; box cells: the
@@ -651,6 +637,34 @@ static tdfe_status launch_blocks(tdfe_ctx* c, const ApplyArgs& a) {
   return tdfe_launch_apply_box(c, a);
 }
 
+// Whether 32-bit byte offsets reach every node of a block's cells: always in
+// the four-lane kernel (a 64-bit address per row of nodes, and its own check),
+// else a matter of the cells per block of the kernel that would run.
+static bool offsets_near(const tdfe_ctx* c, const ApplyArgs& a) {
+  if (tdfe_quad_kernel_ok(c, a)) return true;
+  const int64_t row = (int64_t)a.ld * (a.fp32 ? 4 : 8), layer = (int64_t)c->Nx * c->Ny + c->Nx;
+  if (130 * c->p * layer * row < (int64_t)1 << 31) return true;  // for any block (at most 128 cells)
+  int64_t cells = 0;
+  ApplyArgs q = a;
+  q.query = true;
+  q.n_blocks_out = &cells;
+  return launch_blocks(const_cast<tdfe_ctx*>(c), q) == TDFE_OK &&
+         tdfe_span::near(c->p, c->ncx, c->ncy, c->ncz, cells, row);
+}
+
+// Launches of the plane, lane-pair and four-lane kernels: Loewdin DoF vectors,
+// p <= 7; two or more columns on trilinear cells (one column leaves n threads
+// per cell with the metric staged for the whole cell: the line kernel is
+// faster there, 0.64 ms against 2.2 ms for the Hartree solve's one-column
+// products on the graded mesh).  Box cells have kernels with 64-bit offsets
+// for rows so long or layers so large that 32 bits do not reach over a block;
+// trilinear cells go to the line kernel there.
+static bool block_kernels_ok(const tdfe_ctx* c, const ApplyArgs& a) {
+  if (c->variant == TDFE_VARIANT_LINE || !a.lowdin || a.fullgrid || c->n_cell >= (int64_t)1 << 30) return false;
+  if (c->box) return tdfe_box_kernel_ok(c);
+  return tdfe_curved_kernel_ok(c, a.cols, a.fp32) && offsets_near(c, a);
+}
+
 // Columns of a launch whose per-cell results fit the cell buffer (0: none).
 // Per-cell results take plain stores where the scatter takes atomics (1.3 TB/s
 // of values), and leave n^3 / p^3 vectors for the consumer to read where the
@@ -660,10 +674,17 @@ static tdfe_status launch_blocks(tdfe_ctx* c, const ApplyArgs& a) {
 // 38 + 28; 24^3 trilinear cells, p = 6 (607 MB) 545 + 228 us scattered, 537 +
 // 314 us per cell.
 static int cells_fit(const tdfe_ctx* c, const ApplyArgs& a) {
-  if (!c->eloc || c->mfma || a.cols % 2 || !block_kernels_ok(c, a)) return 0;
+  if (!c->eloc_bytes || c->mfma || a.cols % 2 || !block_kernels_ok(c, a)) return 0;
   const size_t col = (size_t)c->n_cell * c->n * c->n * c->n * (a.fp32 ? 4 : 8);
   const int cap = (int)std::min<size_t>(c->eloc_bytes / col, 1 << 20);
-  return a.cols <= cap ? a.cols : cap / 16 * 16;
+  const int step = a.cols <= cap ? a.cols : cap / 16 * 16;
+  // (64-bit offsets come with the scatter only)
+  for (int cols : {step, step ? a.cols % step : 0}) {
+    ApplyArgs s = a;
+    s.cols = cols;
+    if (cols && !offsets_near(c, s)) return 0;
+  }
+  return step;
 }
 
 bool tdfe_cells_ok(const tdfe_ctx* c, int cols, bool fp32) {
@@ -730,10 +751,11 @@ static tdfe_status launch_local(tdfe_ctx* c, const ApplyArgs& a) {
   if (block_kernels_ok(c, a)) {
     ApplyArgs b = a;
     b.eld = a.cols;
+    b.far = !offsets_near(c, a);
     return launch_blocks(c, b);
   }
-  // full-grid and one-column curved launches, p = 8: the line kernel, which
-  // scatters by atomics
+  // full-grid and one-column curved launches, p = 8, trilinear cells beyond
+  // 32-bit offsets: the line kernel, which scatters by atomics
   KParams P{};
   P.x = a.x;
   P.y = a.y;
@@ -762,6 +784,19 @@ static tdfe_status launch_local(tdfe_ctx* c, const ApplyArgs& a) {
   const bool geom = !c->box;
   if (a.fp32) return launch_p<float>(c, P, geom);
   return launch_p<double>(c, P, geom);
+}
+
+int tdfe_operator_route(const tdfe_ctx* c, int cols, int fp32) {
+  ApplyArgs a{};
+  a.cols = a.ld = cols;
+  a.lowdin = true;
+  a.fp32 = fp32 != 0;
+  if (c->octree || (c->mfma && tdfe_mfma_kernel_ok(c, a)) || !block_kernels_ok(c, a)) return 0;
+  const int kernel = tdfe_quad_kernel_ok(c, a) ? 4
+                     : !c->box                 ? 2
+                     : (c->variant == TDFE_VARIANT_PAIR || (c->variant == 0 && !a.fp32)) && tdfe_pair_kernel_ok(c) ? 3
+                                                                                                                 : 1;
+  return kernel + (offsets_near(c, a) ? 0 : 8) + (cells_fit(c, a) ? 16 : 0);
 }
 
 tdfe_status tdfe_launch_apply(tdfe_ctx* c, const ApplyArgs& a) {

@@ -50,6 +50,8 @@ struct PlaneParams {
   int ncx, ncy, ncz, p, Nx, Ny, Nz;
   int64_t n_cell;
   bool cells;
+  bool far;    // offsets of 64 bits (host)
+  bool query;  // report the cells per block only (host)
   double wq[TDFE_MAXN];  // Gauss weights (indexed by the thread's plane)
 };
 
@@ -60,7 +62,7 @@ constexpr int plane_wpe() {
   return sizeof(T) == 4 ? (N == 5 || N == 6 ? 3 : 2) : (N >= 6 ? 1 : 2);
 }
 
-template <typename T, int N, int CB, int CPB, bool CELLS>
+template <typename T, int N, int CB, int CPB, bool CELLS, bool FAR>
 __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_eu(plane_wpe<T, N>())))
     plane_kernel(PlaneParams<T> P) {
   constexpr int VOL = N * N * N;
@@ -134,21 +136,23 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
   T u[N][N];  // [i][k] gathered, then [i][c], then S B u at [x point][z point]
   {
     const int j = pl;
-    const __amdgpu_buffer_rsrc_t rx = cell_rsrc<T>(P, B0);
-    const uint32_t ldb = (uint32_t)P.ld * (uint32_t)sizeof(T), kst = (uint32_t)(NxI * NyI) * ldb;
-    uint32_t o0 = (uint32_t)(cp.row(P) - B0.row(P) + NxI * j) * ldb + (uint32_t)colg * (uint32_t)sizeof(T);
-    if (!act || (j == 0 && cp.y == 0) || (j == N - 1 && cp.y == P.ncy - 1)) o0 = CELL_NO_READ;
+    typedef CellIn<T, FAR> In;
+    typedef typename In::Off Off;
+    const In X(P, B0);
+    const Off ldb = (Off)P.ld * (Off)sizeof(T), kst = (Off)(NxI * NyI) * ldb;
+    Off o0 = (Off)(cp.row(P) - X.first + NxI * j) * ldb + (Off)colg * (Off)sizeof(T);
+    if (!act || (j == 0 && cp.y == 0) || (j == N - 1 && cp.y == P.ncy - 1)) o0 = In::NONE;
 #pragma unroll
     for (int k = 0; k < N; ++k) {
-      uint32_t ok = o0 + k * kst;
-      if (k == 0 && cp.z == 0) ok = CELL_NO_READ;
-      if (k == N - 1 && cp.z == P.ncz - 1) ok = CELL_NO_READ;
+      Off ok = o0 + k * kst;
+      if (k == 0 && cp.z == 0) ok = In::NONE;
+      if (k == N - 1 && cp.z == P.ncz - 1) ok = In::NONE;
 #pragma unroll
       for (int i = 0; i < N; ++i) {
-        uint32_t o = ok + i * ldb;
-        if (i == 0 && cp.x == 0) o = CELL_NO_READ;
-        if (i == N - 1 && cp.x == P.ncx - 1) o = CELL_NO_READ;
-        u[i][k] = cell_load<T>(rx, o);
+        Off o = ok + i * ldb;
+        if (i == 0 && cp.x == 0) o = In::NONE;
+        if (i == N - 1 && cp.x == P.ncx - 1) o = In::NONE;
+        u[i][k] = X.load(o);
       }
     }
 #pragma unroll
@@ -300,7 +304,7 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
       fx[q] = (T)sFc[q];
       fz[q] = (T)sFc[2 * N + q];
     }
-    const CellOut<T, N, CELLS> E(Y, P, B0, cp, c0, slot, j, colg, act);
+    const CellOut<T, N, CELLS, FAR> E(Y, P, B0, cp, c0, slot, j, colg, act);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       T o[N];
@@ -355,14 +359,20 @@ constexpr int plane_cpb() {
 template <typename T, int N, int CB>
 tdfe_status launch_plane(tdfe_ctx* c, PlaneParams<T>& P, int64_t* groups_out) {
   constexpr int CPB = plane_cpb<T, N, CB>();
+  if (P.query) {
+    *groups_out = CPB;
+    return TDFE_OK;
+  }
   const int64_t groups = (c->n_cell + CPB - 1) / CPB;
   P.nchunks = (P.cols + CB - 1) / CB;
   if (groups_out) *groups_out = groups;
   const dim3 grid((unsigned)(groups * P.nchunks)), block(CPB * N * CB);
   if (P.cells)
-    hipLaunchKernelGGL((plane_kernel<T, N, CB, CPB, true>), grid, block, 0, c->stream, P);
+    hipLaunchKernelGGL((plane_kernel<T, N, CB, CPB, true, false>), grid, block, 0, c->stream, P);
+  else if (P.far)
+    hipLaunchKernelGGL((plane_kernel<T, N, CB, CPB, false, true>), grid, block, 0, c->stream, P);
   else
-    hipLaunchKernelGGL((plane_kernel<T, N, CB, CPB, false>), grid, block, 0, c->stream, P);
+    hipLaunchKernelGGL((plane_kernel<T, N, CB, CPB, false, false>), grid, block, 0, c->stream, P);
   TDFE_HIP(c, hipGetLastError());
   return TDFE_OK;
 }
@@ -419,6 +429,8 @@ tdfe_status launch_box(tdfe_ctx* c, const ApplyArgs& a) {
   P.n_cell = c->n_cell;
   P.eld = a.eld;
   P.cells = a.cells;
+  P.far = a.far;
+  P.query = a.query;
   const int N = c->n;
   for (int i = 0; i < N; ++i) P.wq[i] = c->wq[i];
   return launch_plane_p<T>(c, P, a.n_blocks_out);

@@ -34,6 +34,7 @@ struct CurvedParams {
   int ncx, ncy, ncz, p, Nx, Ny, Nz;
   int64_t n_cell;
   bool cells;
+  bool query;  // report the cells per block only (host)
   double eta[TDFE_MAXN];  // Gauss points on [-1, 1]
   double wq[TDFE_MAXN];   // Gauss weights
 };
@@ -506,6 +507,10 @@ template <typename T, int N, int CB>
 tdfe_status launch_cplane(tdfe_ctx* c, CurvedParams<T>& P, int64_t* groups_out) {
   constexpr int CPB = cplane_cpb<T, N, CB>();
   static_assert(cplane_lds<T, N, CB>(CPB) <= 160 * 1024, "LDS");
+  if (P.query) {
+    *groups_out = CPB;
+    return TDFE_OK;
+  }
   const int64_t groups = (c->n_cell + CPB - 1) / CPB;
   P.nchunks = (P.cols + CB - 1) / CB;
   if (groups_out) *groups_out = groups;
@@ -1065,6 +1070,10 @@ template <typename T, int N, int CB>
 tdfe_status launch_cpair(tdfe_ctx* c, CurvedParams<T>& P, int64_t* groups_out) {
   constexpr int CPB = cpair_cpb<T, N, CB>();
   static_assert(cpair_lds<T, N, CB>(CPB) <= 160 * 1024, "LDS");
+  if (P.query) {
+    *groups_out = CPB;
+    return TDFE_OK;
+  }
   const int64_t groups = (c->n_cell + CPB - 1) / CPB;
   P.nchunks = (P.cols + CB - 1) / CB;
   if (groups_out) *groups_out = groups;
@@ -1112,6 +1121,7 @@ tdfe_status launch_curved(tdfe_ctx* c, const ApplyArgs& a) {
   P.n_cell = c->n_cell;
   P.eld = a.eld;
   P.cells = a.cells;
+  P.query = a.query;
   const int N = c->n;
   for (int i = 0; i < N; ++i) {
     P.eta[i] = c->eta[i];

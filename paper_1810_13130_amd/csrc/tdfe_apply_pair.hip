@@ -51,6 +51,8 @@ struct PairParams {
   int ncx, ncy, ncz, p, Nx, Ny, Nz;
   int64_t n_cell;
   bool cells;
+  bool far;    // offsets of 64 bits (host)
+  bool query;  // report the cells per block only (host)
   double wq[TDFE_MAXN];
 };
 
@@ -180,7 +182,7 @@ constexpr int pair_wpe() {
   return sizeof(T) == 8 ? 2 : 3;
 }
 
-template <typename T, int N, int CB, int CPB, bool CELLS>
+template <typename T, int N, int CB, int CPB, bool CELLS, bool FAR>
 __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_per_eu(pair_wpe<T, N>())))
     pair_kernel(PairParams<T> P) {
   static_assert(N % 2 == 0 && N / 2 <= PH, "even n <= 8");
@@ -267,20 +269,22 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
   // ---------------- A: plane j = pl, values (i, local k) ---------------------------------
   T u[N][H];  // [i][local k] gathered, then [i][c], then S B u at [x point][local z point]
   {
-    const __amdgpu_buffer_rsrc_t rx = cell_rsrc<T>(P, B0);
-    const uint32_t ldb = (uint32_t)P.ld * (uint32_t)sizeof(T), kst = (uint32_t)(NxI * NyI) * ldb;
-    uint32_t o0 = (uint32_t)(cp.row(P) - B0.row(P) + NxI * pl) * ldb + (uint32_t)colg * (uint32_t)sizeof(T);
-    if (!act || (pl == 0 && cp.y == 0) || (pl == N - 1 && cp.y == P.ncy - 1)) o0 = CELL_NO_READ;
+    typedef CellIn<T, FAR> In;
+    typedef typename In::Off Off;
+    const In X(P, B0);
+    const Off ldb = (Off)P.ld * (Off)sizeof(T), kst = (Off)(NxI * NyI) * ldb;
+    Off o0 = (Off)(cp.row(P) - X.first + NxI * pl) * ldb + (Off)colg * (Off)sizeof(T);
+    if (!act || (pl == 0 && cp.y == 0) || (pl == N - 1 && cp.y == P.ncy - 1)) o0 = In::NONE;
 #pragma unroll
     for (int k = 0; k < H; ++k) {
-      uint32_t ok = o0 + (uint32_t)zg(k) * kst;
-      if (k == 0 && (h ? cp.z == P.ncz - 1 : cp.z == 0)) ok = CELL_NO_READ;
+      Off ok = o0 + (Off)zg(k) * kst;
+      if (k == 0 && (h ? cp.z == P.ncz - 1 : cp.z == 0)) ok = In::NONE;
 #pragma unroll
       for (int i = 0; i < N; ++i) {
-        uint32_t o = ok + i * ldb;
-        if (i == 0 && cp.x == 0) o = CELL_NO_READ;
-        if (i == N - 1 && cp.x == P.ncx - 1) o = CELL_NO_READ;
-        u[i][k] = cell_load<T>(rx, o);
+        Off o = ok + i * ldb;
+        if (i == 0 && cp.x == 0) o = In::NONE;
+        if (i == N - 1 && cp.x == P.ncx - 1) o = In::NONE;
+        u[i][k] = X.load(o);
       }
     }
 #pragma unroll
@@ -420,10 +424,11 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
     }
     PlaneFactors Q;
     plane_factors(Q);
-    const CellOut<T, N, CELLS> E(Y, P, B0, cp, c0, slot, pl, colg, act);
-    uint32_t oz[H];  // this lane's z entries
+    const CellOut<T, N, CELLS, FAR> E(Y, P, B0, cp, c0, slot, pl, colg, act);
+    typedef typename CellOut<T, N, CELLS, FAR>::Off Off;
+    Off oz[H];  // this lane's z entries
 #pragma unroll
-    for (int k = 0; k < H; ++k) oz[k] = E.off + (uint32_t)zg(k) * (uint32_t)E.sz;
+    for (int k = 0; k < H; ++k) oz[k] = E.off + (Off)zg(k) * (Off)E.sz;
     const bool z0 = h ? E.hiz : E.loz;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
@@ -471,14 +476,20 @@ template <typename T, int N, int CB>
 tdfe_status launch_pair(tdfe_ctx* c, PairParams<T>& P, int64_t* groups_out) {
   constexpr int CPB = pair_cpb<T, N, CB>();
   static_assert(pair_lds<T, N, CB>(CPB) <= 160 * 1024, "LDS");
+  if (P.query) {
+    *groups_out = CPB;
+    return TDFE_OK;
+  }
   const int64_t groups = (c->n_cell + CPB - 1) / CPB;
   P.nchunks = (P.cols + CB - 1) / CB;
   if (groups_out) *groups_out = groups;
   const dim3 grid((unsigned)(groups * P.nchunks)), block(2 * CPB * N * CB);
   if (P.cells)
-    hipLaunchKernelGGL((pair_kernel<T, N, CB, CPB, true>), grid, block, 0, c->stream, P);
+    hipLaunchKernelGGL((pair_kernel<T, N, CB, CPB, true, false>), grid, block, 0, c->stream, P);
+  else if (P.far)
+    hipLaunchKernelGGL((pair_kernel<T, N, CB, CPB, false, true>), grid, block, 0, c->stream, P);
   else
-    hipLaunchKernelGGL((pair_kernel<T, N, CB, CPB, false>), grid, block, 0, c->stream, P);
+    hipLaunchKernelGGL((pair_kernel<T, N, CB, CPB, false, false>), grid, block, 0, c->stream, P);
   TDFE_HIP(c, hipGetLastError());
   return TDFE_OK;
 }
@@ -519,6 +530,8 @@ tdfe_status launch_pair_box(tdfe_ctx* c, const ApplyArgs& a) {
   P.n_cell = c->n_cell;
   P.eld = a.eld;
   P.cells = a.cells;
+  P.far = a.far;
+  P.query = a.query;
   const int N = c->n;
   for (int i = 0; i < N; ++i) P.wq[i] = c->wq[i];
   switch (N) {

@@ -4,6 +4,8 @@
 // Dg are antisymmetric: a 1D contraction splits into an even and an odd half
 // of size n/2 each.
 #pragma once
+#include <type_traits>
+
 #include "tdfe_internal.h"
 #include "tdfe_rule1d.h"
 #include "tdfe_span.h"
@@ -226,11 +228,14 @@ __device__ __forceinline__ CellPos cell_next(const Params& P, CellPos c, int slo
 // stores run at 5.5; see cells_fit for when the cell rows pay.
 //
 // Addresses are a block-uniform 64-bit base per node row (scalar arithmetic)
-// plus a 32-bit byte offset per lane (block_offsets_ok).
-template <typename T, int N, bool CELLS>
+// plus a byte offset per lane, of 32 bits where that reaches every node of the
+// block's cells (tdfe_span::near) and of 64 (FAR) where rows are so long, or
+// layers of nodes so large, that it does not.
+template <typename T, int N, bool CELLS, bool FAR = false>
 struct CellOut {
+  typedef std::conditional_t<FAR, int64_t, uint32_t> Off;
   char* base;        // the block's first cell, node (0, 0, 0)
-  uint32_t off;      // this lane's cell, node (0, j, 0) and column from there
+  Off off;           // this lane's cell, node (0, j, 0) and column from there
   int64_t sx, sz;    // bytes
   bool lox, hix, loz, hiz, jok;
   template <typename Params>
@@ -245,20 +250,20 @@ struct CellOut {
       sx = (int64_t)P.cols * (int)sizeof(T);
       sz = N * N * sx;
       base = (char*)Y + c0 * N * sz;
-      off = (uint32_t)((slot * (N * N * N) + N * j) * P.cols + colg) * (uint32_t)sizeof(T);
+      off = (Off)((slot * (N * N * N) + N * j) * P.cols + colg) * (Off)sizeof(T);
     } else {
       const int64_t NxI = P.Nx - 2, NyI = P.Ny - 2;
       sx = (int64_t)P.ld * (int)sizeof(T);
       sz = NxI * NyI * sx;
       base = (char*)Y + B.row(P) * sx;
-      off = (uint32_t)(c.row(P) - B.row(P) + NxI * j) * (uint32_t)sx + (uint32_t)colg * (uint32_t)sizeof(T);
+      off = (Off)(c.row(P) - B.row(P) + NxI * j) * (Off)sx + (Off)colg * (Off)sizeof(T);
     }
   }
   // x node i, z node k are written (i, k compile-time constants after unrolling)
   __device__ __forceinline__ bool xok(int i) const { return (i > 0 || lox) && (i < N - 1 || hix); }
   __device__ __forceinline__ bool zok(int k) const { return (k > 0 || loz) && (k < N - 1 || hiz); }
   // node (i, j, k) with k uniform, or i uniform and the z offset part of o
-  __device__ __forceinline__ void put(int i, int k, uint32_t o, T v) const {
+  __device__ __forceinline__ void put(int i, int k, Off o, T v) const {
     T* const d = (T*)(base + (i * sx + k * sz) + o);
     if constexpr (CELLS)
       *d = v;
@@ -267,28 +272,47 @@ struct CellOut {
   }
 };
 
-// the gather of a cell's plane: a buffer resource over the DoF vector from the
-// block's first row on, byte offsets per lane; entries that are not read (the
-// Dirichlet planes, columns past the last) carry offsets past its end and
-// give 0
-constexpr uint32_t CELL_NO_READ = tdfe_span::NO_READ;
-template <typename T, typename Params>
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t cell_rsrc(const Params& P, const CellPos& B) {
-  const int64_t first = B.row(P), rows = (int64_t)(P.Nx - 2) * (P.Ny - 2) * (P.Nz - 2);
-  const int64_t bytes = (rows - first) * P.ld * (int)sizeof(T);
-  const uint64_t ad = (uint64_t)(uintptr_t)P.x + (uint64_t)(first * P.ld * (int)sizeof(T));
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)ad);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(ad >> 32));
-  const int nrec = __builtin_amdgcn_readfirstlane((int)(bytes < 0x7fffffff ? bytes : 0x7fffffff));
-  return __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)(((uint64_t)hi << 32) | lo), 0, nrec, 0x00020000);
-}
+// The gather of a box cell's plane, by byte offsets per lane from the block's
+// first row (FAR: from the vector's).  Entries that are not read (the Dirichlet
+// planes, columns past the last) carry NONE, to which the offsets of a cell's
+// nodes may be added, and give 0.
+template <typename T, bool FAR>
+struct CellIn {
+  typedef uint32_t Off;
+  static constexpr Off NONE = tdfe_span::NO_READ;
+  __amdgpu_buffer_rsrc_t r;  // from the block's first row to the vector's end
+  int64_t first;
+  template <typename Params>
+  __device__ __forceinline__ CellIn(const Params& P, const CellPos& B) : first(B.row(P)) {
+    const int64_t rows = (int64_t)(P.Nx - 2) * (P.Ny - 2) * (P.Nz - 2);
+    const int64_t bytes = (rows - first) * P.ld * (int)sizeof(T);
+    const uint64_t ad = (uint64_t)(uintptr_t)P.x + (uint64_t)(first * P.ld * (int)sizeof(T));
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)ad);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(ad >> 32));
+    const int nrec = __builtin_amdgcn_readfirstlane((int)(bytes < 0x7fffffff ? bytes : 0x7fffffff));
+    r = __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)(((uint64_t)hi << 32) | lo), 0, nrec, 0x00020000);
+  }
+  __device__ __forceinline__ T load(Off o) const {
+    if constexpr (sizeof(T) == 8)
+      return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)o, 0, 0));
+    else
+      return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)o, 0, 0));
+  }
+};
 template <typename T>
-__device__ __forceinline__ T cell_load(__amdgpu_buffer_rsrc_t r, uint32_t o) {
-  if constexpr (sizeof(T) == 8)
-    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)o, 0, 0));
-  else
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)o, 0, 0));
-}
+struct CellIn<T, true> {
+  typedef int64_t Off;
+  static constexpr Off NONE = INT64_MIN;
+  const char* x;
+  static constexpr int64_t first = 0;
+  template <typename Params>
+  __device__ __forceinline__ CellIn(const Params& P, const CellPos&) : x((const char*)P.x) {}
+  // one load from a selected (always valid) address: no branches
+  __device__ __forceinline__ T load(Off o) const {
+    const T v = *(const T*)(x + (o < 0 ? 0 : o));
+    return o < 0 ? (T)0 : v;
+  }
+};
 
 // out[a] = sum_i A[a][i] in[i] by even/odd folding; A given folded (in any
 // precision, converted to T), symmetry S

@@ -224,6 +224,8 @@ struct ApplyArgs {
   bool overwrite;       // y = result instead of y += result (where tdfe_can_overwrite)
   int eld;              // columns of a row of `energy` (set by the launchers)
   bool cells;           // y holds per-cell results (set by the launchers)
+  bool far;             // box kernels: offsets of 64 bits (set by the launchers)
+  bool query;           // launch nothing, report the cells per block in *n_blocks_out (set by the launchers)
   bool nonlocal;        // Hbar launches: add the Kleinman-Bylander term when projectors are set
 };
 tdfe_status tdfe_launch_apply(tdfe_ctx* c, const ApplyArgs& a);
@@ -245,6 +247,10 @@ tdfe_status tdfe_launch_apply_quad(tdfe_ctx* c, const ApplyArgs& a);
 bool tdfe_cells_ok(const tdfe_ctx* c, int cols, bool fp32);
 tdfe_status tdfe_launch_apply_cells(tdfe_ctx* c, const ApplyArgs& a);
 bool tdfe_can_overwrite(const tdfe_ctx* c, const ApplyArgs& a);
+// host only: the kernel of an operator launch on the DoF vectors, 0 the line
+// kernel (or another mesh's or engine's), 1 plane, 2 trilinear, 3 lane pairs, 4
+// four lanes; + 8 with 64-bit offsets, + 16 through the cell buffer
+extern "C" int tdfe_operator_route(const tdfe_ctx* c, int cols, int fp32);
 // trilinear-cell variant in the same layout (tdfe_apply_curved.hip)
 bool tdfe_curved_kernel_ok(const tdfe_ctx* c, int cols, bool fp32);
 #define TDFE_VARIANT_LINE 1

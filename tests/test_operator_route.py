@@ -1,0 +1,80 @@
+"""Which operator kernel a launch runs on wide meshes and long rows (host only),
+and the span of a block's cells that the choice rests on, against a walk over
+every position of the block."""
+import ctypes
+import itertools
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+import workloads as W
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LINE, PLANE, TRILINEAR, PAIR, QUAD, FAR, CELLS = 0, 1, 2, 3, 4, 8, 16
+
+
+@pytest.fixture(scope="module")
+def lib():
+    from paper_1810_13130_amd import tdfe
+    if not os.path.exists(tdfe.LIB_PATH):
+        pytest.skip("libtdfe.so not built")
+    return tdfe.load()
+
+
+def _route(lib, mesh, p, nc, n_orb, fp32, variant=None, monkeypatch=None):
+    from paper_1810_13130_amd import tdfe
+    d = tdfe.MeshDesc()
+    d.p, d.nq, d.n_orb_max, d.k_max, d.precision = p, p + 1, n_orb, 4, 1 if fp32 else 0
+    d.ncell[0], d.ncell[1], d.ncell[2] = nc
+    v = np.ascontiguousarray(W.box_vertices(-1.0, 1.0, nc))
+    if mesh == "trilinear":
+        v[1, 1, 1] += 0.1 / max(nc)
+    d.vertices = v.ctypes.data_as(tdfe._DP)
+    h = ctypes.c_void_p()
+    assert lib.tdfe_fe_mesh_setup(ctypes.byref(d), None, ctypes.byref(h)) == 0
+    r = lib.tdfe_operator_route(h, 2 * n_orb, int(fp32))
+    lib.tdfe_destroy(h)
+    return r
+
+
+@pytest.mark.parametrize("mesh,p,nc,n_orb,fp32,want", [
+    ("box", 5, (16, 16, 16), 8, False, PAIR + CELLS),
+    # 32 columns of 20,000 rows and more across a block's z planes
+    ("box", 5, (96, 96, 2), 32, False, PAIR), ("box", 5, (120, 120, 2), 32, False, PAIR),
+    ("box", 5, (190, 190, 2), 32, False, PAIR + FAR), ("box", 4, (240, 240, 2), 32, True, PLANE),
+    ("box", 4, (400, 400, 2), 32, True, PLANE + FAR),
+    # rows of hundreds of orbitals
+    ("box", 5, (24, 24, 24), 512, False, PAIR), ("box", 5, (48, 48, 4), 512, False, PAIR + FAR),
+    ("box", 4, (24, 24, 2), 4096, False, PLANE + FAR), ("box", 6, (8, 8, 2), 4096, False, QUAD + CELLS),
+    # the four-lane kernel has an address per row of nodes
+    ("box", 6, (160, 160, 2), 32, False, QUAD), ("trilinear", 6, (160, 160, 2), 32, False, QUAD),
+    ("trilinear", 7, (120, 120, 2), 32, True, QUAD),
+    ("trilinear", 5, (100, 100, 2), 32, False, TRILINEAR), ("trilinear", 5, (190, 190, 2), 32, False, LINE),
+    ("trilinear", 6, (160, 160, 2), 32, True, TRILINEAR), ("box", 8, (4, 4, 4), 8, False, LINE)])
+def test_route(lib, mesh, p, nc, n_orb, fp32, want):
+    assert _route(lib, mesh, p, nc, n_orb, fp32) == want
+
+
+def test_block_span(tmp_path):
+    if shutil.which("g++") is None:
+        pytest.skip("no host compiler")
+    src = tmp_path / "span.cpp"
+    src.write_text('#include "tdfe_span.h"\n'
+                   'extern "C" long long rows(int p, int x, int y, int z, int cells) {\n'
+                   '  return tdfe_span::block_rows(p, x, y, z, cells);\n}\n')
+    out = tmp_path / "span.so"
+    subprocess.check_call(["g++", "-std=c++17", "-shared", "-fPIC", "-I",
+                           os.path.join(ROOT, "paper_1810_13130_amd", "csrc"), str(src), "-o", str(out)])
+    f = ctypes.CDLL(str(out)).rows
+    f.restype = ctypes.c_longlong
+    for p, (ncx, ncy, ncz) in itertools.product((1, 2, 5), itertools.product((1, 2, 3, 5), (1, 2, 4), (1, 2, 3, 7))):
+        nx, ny = ncx * p - 1, ncy * p - 1
+        c = np.arange(ncx * ncy * ncz)
+        row = p * ((c % ncx) + nx * ((c // ncx) % ncy) + nx * ny * (c // (ncx * ncy)))
+        for cells in (1, 2, 3, 7, 16, 32):
+            most = max(int(row[i:i + cells].max() - row[i]) for i in c)
+            got = f(p, ncx, ncy, ncz, cells)
+            assert got == most + p * (nx * ny + nx + 1), (p, ncx, ncy, ncz, cells)
