@@ -70,6 +70,20 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
   // 1D tables of order N, folded, as compile-time constants
   constexpr BoxFoldSet<N> FS = make_box_foldset<N, sizeof(T) == 4>();
   auto wprod = [&](int b, int c) { return (T)(FS.wq[b] * FS.wq[c]); };
+  // FP32 at n = 2, 4, 6 and 7: phase A takes x first, on the nodes (one contraction
+  // more), and at n = 4 interpolates by eo1: S multiplies the rounding of what it
+  // is applied to, and an exponential of smooth orbitals shows it.  In a model of
+  // this arithmetic (p = 3, 5, 6; 12 to 20 iterations) errors of 9.7e-8, 1.46e-7
+  // and 1.78e-7 become 7.0e-8, 1.26e-7 and 1.70e-7, where derivatives on either
+  // side of the flux give 8.0e-8, 1.30e-7 and 1.78e-7.
+  constexpr bool F32 = sizeof(T) == 4;
+  constexpr bool XFIRST = F32 && (N == 2 || N == 4 || N == 6 || N == 7), MID = F32 && N == 4;
+  auto interp = [&](const T* in, T* out) {
+    if constexpr (MID)
+      eo1<T, N>(FS.B, FS.b, in, out);
+    else
+      eo<T, N, 1>(FS.B, in, out);
+  };
   __shared__ T sX[CPB * VOL * CB];
   __shared__ T sV[CPB * VOL];  // weighted potential of the block's cells
   __shared__ double sRed[THREADS];
@@ -91,8 +105,8 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
   const CellPos B0 = cell_pos(P, (int)c0);
   const CellPos cp = CPB == 1 ? B0 : cell_next(P, B0, cell_ok ? slot : 0);
   T* __restrict__ Y = (T*)P.y;
-  T cs = (T)1;
-  if (P.colscale && act) cs = (T)P.colscale[colg >> 1];
+  double cs = 1.0;
+  if (P.colscale && act) cs = P.colscale[colg >> 1];
 
   // block staging: the weighted potential of the block's cells, their M^-1/2
   // factors along x, y and z and their metric go to LDS.  The loads are issued
@@ -166,37 +180,69 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
       if (f < CPB * NFC) sF[f] = fr[k];
     }
     __syncthreads();
-    const T my = (T)sFc[N + j] * cs;
+    // (the y factor goes into the z factors in FP64: two roundings fewer per
+    // value in FP32)
+    const double my = sFc[N + j] * (cs * FS.in);
     T fx[N], fz[N];
 #pragma unroll
     for (int q = 0; q < N; ++q) {
       fx[q] = (T)sFc[q];
-      fz[q] = (T)sFc[2 * N + q];
+      fz[q] = (T)(sFc[2 * N + q] * my);
     }
 #pragma unroll
     for (int k = 0; k < N; ++k)
 #pragma unroll
-      for (int i = 0; i < N; ++i) u[i][k] *= fx[i] * fz[k] * my;
-    // z: interpolation, per x node
+      for (int i = 0; i < N; ++i) u[i][k] *= fx[i] * fz[k];
+    if constexpr (XFIRST) {
+      // x, per z node: interpolation and S B; z of both, per x point: the first
+      // into the transpose buffer
+      T v[N][N];
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      T o[N];
-      eo<T, N, 1>(FS.B, u[i], o);
+      for (int k = 0; k < N; ++k) {
+        T line[N], o1[N], o2[N];
 #pragma unroll
-      for (int c = 0; c < N; ++c) u[i][c] = o[c];
-    }
-    // x, per z point: interpolation into the transpose buffer, S B kept
+        for (int i = 0; i < N; ++i) line[i] = u[i][k];
+        interp(line, o1);
+        eo0<T, N>(FS.SB, line, o2);
 #pragma unroll
-    for (int c = 0; c < N; ++c) {
-      T line[N], o1[N], o2[N];
-#pragma unroll
-      for (int i = 0; i < N; ++i) line[i] = u[i][c];
-      eo<T, N, 1>(FS.B, line, o1);
-      eo0<T, N>(FS.SB, line, o2);
+        for (int a = 0; a < N; ++a) {
+          v[a][k] = o1[a];
+          u[a][k] = o2[a];
+        }
+      }
 #pragma unroll
       for (int a = 0; a < N; ++a) {
-        sX[sidx(pl, a, c)] = o1[a];
-        u[a][c] = o2[a];
+        T o1[N], o2[N];
+        interp(v[a], o1);
+        eo<T, N, 1>(FS.B, u[a], o2);
+#pragma unroll
+        for (int c = 0; c < N; ++c) {
+          sX[sidx(pl, a, c)] = o1[c];
+          u[a][c] = o2[c];
+        }
+      }
+    } else {
+      // z: interpolation, per x node
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        T o[N];
+        interp(u[i], o);
+#pragma unroll
+        for (int c = 0; c < N; ++c) u[i][c] = o[c];
+      }
+      // x, per z point: interpolation into the transpose buffer, S B kept
+#pragma unroll
+      for (int c = 0; c < N; ++c) {
+        T line[N], o1[N], o2[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) line[i] = u[i][c];
+        interp(line, o1);
+        eo0<T, N>(FS.SB, line, o2);
+#pragma unroll
+        for (int a = 0; a < N; ++a) {
+          sX[sidx(pl, a, c)] = o1[a];
+          u[a][c] = o2[a];
+        }
       }
     }
   }
@@ -208,7 +254,7 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
     T l[N], o[N];
 #pragma unroll
     for (int j = 0; j < N; ++j) l[j] = sX[sidx(j, pl, c)];
-    eo<T, N, 1>(FS.B, l, o);
+    interp(l, o);
 #pragma unroll
     for (int b = 0; b < N; ++b) uq[b][c] = o[b];
   }
@@ -225,12 +271,12 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
   if (cell_ok) {
     // Gauss weight of this thread's x point, selected from the constants (an
     // array indexed per lane would be a memory load and a wait)
-    T wa = (T)FS.wq[0];
+    double wa = FS.wq[0];
 #pragma unroll
-    for (int q = 1; q < N; ++q) wa = pl == q ? (T)FS.wq[q] : wa;
-    gx = (T)(P.kin * sFc[3 * N + 0]);  // S B carries the x weights
-    gy = (T)(P.kin * sFc[3 * N + 1]) * wa;
-    gz = (T)(P.kin * sFc[3 * N + 2]) * wa;
+    for (int q = 1; q < N; ++q) wa = pl == q ? FS.wq[q] : wa;
+    gx = (T)(P.kin * FS.gx * sFc[3 * N + 0]);  // S B carries the x weights
+    gy = (T)(P.kin * FS.gs * sFc[3 * N + 1] * wa);
+    gz = (T)(P.kin * FS.gs * sFc[3 * N + 2] * wa);
   }
   // x stiffness term and the potential, per z point
   T acc[N][N];
@@ -298,11 +344,11 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
       for (int i = 0; i < N; ++i) h[i][c] = o[i];
     }
     T fx[N], fz[N];
-    const T my = (T)sFc[N + j];
+    const double my = sFc[N + j] * FS.out;
 #pragma unroll
     for (int q = 0; q < N; ++q) {
       fx[q] = (T)sFc[q];
-      fz[q] = (T)sFc[2 * N + q];
+      fz[q] = (T)(sFc[2 * N + q] * my);
     }
     const CellOut<T, N, CELLS, FAR> E(Y, P, B0, cp, c0, slot, j, colg, act);
 #pragma unroll
@@ -312,7 +358,7 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
       if (E.jok && E.xok(i)) {
 #pragma unroll
         for (int k = 0; k < N; ++k)
-          if (E.zok(k)) E.put(i, k, E.off, o[k] * fx[i] * fz[k] * my);
+          if (E.zok(k)) E.put(i, k, E.off, o[k] * (fx[i] * fz[k]));
       }
     }
   }

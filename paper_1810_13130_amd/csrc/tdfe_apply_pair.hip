@@ -61,6 +61,7 @@ struct PairSet {
   FoldE<double> fB, fBt, fS, fSB;  // B, B^T, S, S B (x and y directions)
   SplitT<double> zB, zBt, zS;      // B, B^T, S along z
   double wq[TDFE_MAXN];
+  double in = 1.0, out = 1.0, gx = 1.0, gy = 1.0, gz = 1.0;  // as in BoxFoldSet
 };
 
 constexpr void fold_even(const double* A, int N, bool transpose, FoldE<double>& F) {
@@ -96,22 +97,28 @@ constexpr PairSet make_pairset() {
   split_tab(R.B, N, true, F.zBt);
   split_tab(K.S, N, false, F.zS);
   if (F32) {
-    fit_stiffness(F.fS.E, F.fS.O, PH, N, nullptr, R.eta);
-    fit_stiffness(F.fSB.E, F.fSB.O, PH, N, nullptr, R.xi);
-    // the split S: rows that sum to zero
-    for (int a = 0; a < N / 2; ++a) {
-      double row[TDFE_MAXN]{}, one[TDFE_MAXN]{};
-      for (int i = 0; i < N / 2; ++i) {
-        row[i] = F.zS.own[a * PH + i];
-        row[N / 2 + i] = F.zS.oth[a * PH + i];
-        one[i] = one[N / 2 + i] = 1.0;
-      }
-      fit_f32(row, N, one, 0.0);
-      for (int i = 0; i < N / 2; ++i) {
-        F.zS.own[a * PH + i] = row[i];
-        F.zS.oth[a * PH + i] = row[N / 2 + i];
-      }
+    constexpr F32Factors f = f32_factors(N);
+    for (int i = 0; i < PH * PH; ++i) {
+      F.fB.E[i] *= f.B;
+      F.fB.O[i] *= f.B;
+      F.fBt.E[i] *= f.Bt;
+      F.fBt.O[i] *= f.Bt;
+      F.fS.E[i] *= f.S;
+      F.fS.O[i] *= f.S;
+      F.fSB.E[i] *= f.SB;
+      F.fSB.O[i] *= f.SB;
+      F.zB.own[i] *= f.zB;
+      F.zB.oth[i] *= f.zB;
+      F.zBt.own[i] *= f.zB;
+      F.zBt.oth[i] *= f.zB;
+      F.zS.own[i] *= f.zS;
+      F.zS.oth[i] *= f.zS;
     }
+    F.in = 1.0 / (f.B * f.B * f.zB);
+    F.out = 1.0 / (f.Bt * f.Bt * f.zB);
+    F.gx = f.B / f.SB;
+    F.gy = 1.0 / f.S;
+    F.gz = 1.0 / f.zS;
   }
   for (int i = 0; i < TDFE_MAXN; ++i) F.wq[i] = R.wq[i];
   return F;
@@ -215,8 +222,8 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
   const CellPos B0 = cell_pos(P, (int)c0);
   const CellPos cp = CPB == 1 ? B0 : cell_next(P, B0, cell_ok ? slot : 0);
   T* __restrict__ Y = (T*)P.y;
-  T cs = (T)1;
-  if (P.colscale && act) cs = (T)P.colscale[colg >> 1];
+  double cs = 1.0;
+  if (P.colscale && act) cs = P.colscale[colg >> 1];
 
   // block staging (as in the plane kernel): potential, M^-1/2 factors along
   // x, y, z and the metric of the block's cells; loads issued before the
@@ -256,14 +263,14 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
   // Loewdin factors of node plane j = pl (phases A and C; read again in C
   // rather than held through B)
   struct PlaneFactors {
-    T fx[N], fz[H], my;
+    T fx[N], fz[H];
   };
-  auto plane_factors = [&](PlaneFactors& Q) {
-    Q.my = (T)sFc[N + pl];
+  auto plane_factors = [&](PlaneFactors& Q, double s) {
+    const double my = sFc[N + pl] * s;
 #pragma unroll
     for (int q = 0; q < N; ++q) Q.fx[q] = (T)sFc[q];
 #pragma unroll
-    for (int q = 0; q < H; ++q) Q.fz[q] = (T)sFc[2 * N + zg(q)];
+    for (int q = 0; q < H; ++q) Q.fz[q] = (T)(sFc[2 * N + zg(q)] * my);
   };
 
   // ---------------- A: plane j = pl, values (i, local k) ---------------------------------
@@ -299,31 +306,60 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
     }
     __syncthreads();
     PlaneFactors Q;
-    plane_factors(Q);
+    plane_factors(Q, cs * FS.in);
 #pragma unroll
     for (int k = 0; k < H; ++k)
 #pragma unroll
-      for (int i = 0; i < N; ++i) u[i][k] *= Q.fx[i] * Q.fz[k] * (Q.my * cs);
-    // z: interpolation (paired), per x node
+      for (int i = 0; i < N; ++i) u[i][k] *= Q.fx[i] * Q.fz[k];
+    if constexpr (sizeof(T) == 4) {
+      // FP32: x first, on the nodes (see the plane kernel)
+      T v[N][H];
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      T o[H];
-      zsplit<T, N>(FS.zB, u[i], o);
+      for (int k = 0; k < H; ++k) {
+        T line[N], o1[N], o2[N];
 #pragma unroll
-      for (int c = 0; c < H; ++c) u[i][c] = o[c];
-    }
-    // x, per local z point: interpolation into the transpose buffer, S B kept
+        for (int i = 0; i < N; ++i) line[i] = u[i][k];
+        eoe<T, N>(FS.fB, line, o1);
+        eoe<T, N, true>(FS.fSB, line, o2);
 #pragma unroll
-    for (int c = 0; c < H; ++c) {
-      T line[N], o1[N], o2[N];
-#pragma unroll
-      for (int i = 0; i < N; ++i) line[i] = u[i][c];
-      eoe<T, N>(FS.fB, line, o1);
-      eoe<T, N, true>(FS.fSB, line, o2);
+        for (int a = 0; a < N; ++a) {
+          v[a][k] = o1[a];
+          u[a][k] = o2[a];
+        }
+      }
 #pragma unroll
       for (int a = 0; a < N; ++a) {
-        sX[sidx(pl, a, zg(c))] = o1[a];
-        u[a][c] = o2[a];
+        T o1[H], o2[H];
+        zsplit<T, N>(FS.zB, v[a], o1);
+        zsplit<T, N>(FS.zB, u[a], o2);
+#pragma unroll
+        for (int c = 0; c < H; ++c) {
+          sX[sidx(pl, a, zg(c))] = o1[c];
+          u[a][c] = o2[c];
+        }
+      }
+    } else {
+      // z: interpolation (paired), per x node
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        T o[H];
+        zsplit<T, N>(FS.zB, u[i], o);
+#pragma unroll
+        for (int c = 0; c < H; ++c) u[i][c] = o[c];
+      }
+      // x, per local z point: interpolation into the transpose buffer, S B kept
+#pragma unroll
+      for (int c = 0; c < H; ++c) {
+        T line[N], o1[N], o2[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) line[i] = u[i][c];
+        eoe<T, N>(FS.fB, line, o1);
+        eoe<T, N, true>(FS.fSB, line, o2);
+#pragma unroll
+        for (int a = 0; a < N; ++a) {
+          sX[sidx(pl, a, zg(c))] = o1[a];
+          u[a][c] = o2[a];
+        }
       }
     }
   }
@@ -350,12 +386,12 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
   double energy = 0.0;
   T gx = 0, gy = 0, gz = 0;
   if (cell_ok) {
-    T wa = (T)FS.wq[0];  // selected from the constants: no per-lane memory load
+    double wa = FS.wq[0];  // selected from the constants: no per-lane memory load
 #pragma unroll
-    for (int q = 1; q < N; ++q) wa = pl == q ? (T)FS.wq[q] : wa;
-    gx = (T)(P.kin * sFc[3 * N + 0]);  // S B carries the x weights
-    gy = (T)(P.kin * sFc[3 * N + 1]) * wa;
-    gz = (T)(P.kin * sFc[3 * N + 2]) * wa;
+    for (int q = 1; q < N; ++q) wa = pl == q ? FS.wq[q] : wa;
+    gx = (T)(P.kin * FS.gx * sFc[3 * N + 0]);  // S B carries the x weights
+    gy = (T)(P.kin * FS.gy * sFc[3 * N + 1] * wa);
+    gz = (T)(P.kin * FS.gz * sFc[3 * N + 2] * wa);
   }
   // z Gauss weights of this lane's points: the rule's weights are symmetric
   // (bitwise, for every order), so the mirror point's weight is wq[c] itself
@@ -423,7 +459,7 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
       for (int i = 0; i < N; ++i) hh[i][c] = o[i];
     }
     PlaneFactors Q;
-    plane_factors(Q);
+    plane_factors(Q, FS.out);
     const CellOut<T, N, CELLS, FAR> E(Y, P, B0, cp, c0, slot, pl, colg, act);
     typedef typename CellOut<T, N, CELLS, FAR>::Off Off;
     Off oz[H];  // this lane's z entries
@@ -437,7 +473,7 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
       if (E.jok && E.xok(i)) {
 #pragma unroll
         for (int k = 0; k < H; ++k)
-          if (k > 0 || z0) E.put(i, 0, oz[k], o[k] * (Q.fx[i] * Q.fz[k] * Q.my));
+          if (k > 0 || z0) E.put(i, 0, oz[k], o[k] * (Q.fx[i] * Q.fz[k]));
       }
     }
   }

@@ -76,22 +76,18 @@ constexpr QHalf quad_half(const double* A, int N, int S, bool transpose, double 
 template <int N, bool BOX, bool F32>
 constexpr QuadTables make_quad_tables() {
   const tdfe1d::Rule R = tdfe1d::make_rule(N - 1);
+  const F32Factors f = BOX && F32 ? f32_factors(N) : F32Factors{};
   QuadTables Q{};
-  Q.t[0] = quad_half(R.B, N, 1, false, 1.0);
+  Q.t[0] = quad_half(R.B, N, 1, false, f.B);
   if (BOX) {
     const GaussStiff K = make_gauss_stiff(R);
-    Q.t[1] = quad_half(K.SB, N, 1, false, 1.0);
-    Q.t[2] = quad_half(K.S, N, 1, false, 4.0);
-    static_assert(!F32 || N % 2 == 0);
-    if (F32) {
-      fit_stiffness(Q.t[1].E, Q.t[1].O, 4, N, nullptr, R.xi);
-      fit_stiffness(Q.t[2].E, Q.t[2].O, 4, N, nullptr, R.eta);
-    }
+    Q.t[1] = quad_half(K.SB, N, 1, false, f.SB);
+    Q.t[2] = quad_half(K.S, N, 1, false, 4.0 * f.S);
   } else {
     Q.t[1] = quad_half(R.Dg, N, -1, false, 2.0);
     Q.t[2] = quad_half(R.Dg, N, -1, true, 2.0);
   }
-  Q.t[3] = quad_half(R.B, N, 1, true, 1.0);
+  Q.t[3] = quad_half(R.B, N, 1, true, f.Bt);  // (Bt = B at n = 8: one scale for gather and results)
   return Q;
 }
 
@@ -263,7 +259,7 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(4))
   constexpr int PAD = ODD ? 0 : QC;
   constexpr int LX = N * QC + PAD, LY = N * LX + PAD;
   constexpr FoldSet<N> FS = make_foldset<N>();
-  constexpr BoxFoldSet<N> FB = make_box_foldset<N, sizeof(T) == 4>();
+  constexpr BoxFoldSet<N> FB = make_box_foldset<N, BOX && sizeof(T) == 4>();
   // FP64 on trilinear cells at n = 7: two blocks per CU (14 waves) need 128
   // registers per lane, and the flux phase holds 158 (26 spilled values of it
   // made scratch traffic of 2.8 GB per launch): half of its arrays wait in LDS
@@ -364,8 +360,8 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(4))
   {
     const int colg = ch * QC + col;
     const bool cok = colg < P.cols;
-    T cs = cok ? (T)1 : (T)0;
-    if (P.colscale && cok) cs = (T)P.colscale[colg >> 1];
+    double cs = cok ? 1.0 : 0.0;
+    if (P.colscale && cok) cs = P.colscale[colg >> 1];
 
     // ---------------- A: node plane y = w ----------------------------------------------
     T r1[N], r2[N];
@@ -391,14 +387,18 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(4))
         }
       }
     }
-    // box cells: M^-1/2 factors of the lane's two x entries and of the z rows
-    T mx1 = 0, mx2 = 0, my = 0, mz[N];
+    // box cells: M^-1/2 factors of the lane's two x entries and of the z rows,
+    // the y factor in the latter
+    T mx1 = 0, mx2 = 0, mi1 = 0, mi2 = 0, mz[N];
     if constexpr (BOX) {
-      mx1 = (T)P.m1x[cx * P.p + q];
-      mx2 = (T)P.m1x[cx * P.p + N - 1 - q];
-      my = (T)P.m1y[cy * P.p + w];
+      const double x1 = P.m1x[cx * P.p + q], x2 = P.m1x[cx * P.p + N - 1 - q];
+      const double my = P.m1y[cy * P.p + w] * FB.in;
+      mx1 = (T)x1;
+      mx2 = (T)x2;
+      mi1 = (T)(x1 * cs);
+      mi2 = (T)(x2 * cs);
 #pragma unroll
-      for (int k = 0; k < N; ++k) mz[k] = (T)P.m1z[cz * P.p + k];
+      for (int k = 0; k < N; ++k) mz[k] = (T)(P.m1z[cz * P.p + k] * my);
     }
     __builtin_amdgcn_sched_barrier(0);
     {
@@ -428,11 +428,11 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(4))
       for (int k = 0; k < N; ++k) {
         T m1, m2;
         if constexpr (BOX) {
-          m1 = mx1 * mz[k] * (my * cs);
-          m2 = mx2 * mz[k] * (my * cs);
+          m1 = mi1 * mz[k];
+          m2 = mi2 * mz[k];
         } else {
-          m1 = sM[PA.n1 + N * N * k] * cs;
-          m2 = sM[PA.n2 + N * N * k] * cs;
+          m1 = sM[PA.n1 + N * N * k] * (T)cs;
+          m2 = sM[PA.n2 + N * N * k] * (T)cs;
         }
         const T u1 = r1[k] * m1, u2 = r2[k] * m2;
         r1[k] = u1 + u2;
@@ -441,10 +441,10 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(4))
       const QTab<T> tb = qtab(sT, 0, lane), td = qtab(sT, 1, lane);
       T o[N];
       if constexpr (BOX) {
-        eo<T, N, 1>(FS.B, r1, o);
+        eo<T, N, 1>(FB.B, r1, o);
 #pragma unroll
         for (int c = 0; c < N; ++c) r1[c] = o[c];
-        eo<T, N, 1>(FS.B, r2, o);
+        eo<T, N, 1>(FB.B, r2, o);
 #pragma unroll
         for (int c = 0; c < N; ++c) r2[c] = o[c];
 #pragma unroll
@@ -460,10 +460,10 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(4))
       } else {
 #pragma unroll
         for (int k = 0; k < N; ++k) qmul0(tb, r1[k], r2[k], r1[k], r2[k]);
-        eo<T, N, 1>(FS.B, r1, o);
+        eo<T, N, 1>(FB.B, r1, o);
 #pragma unroll
         for (int c = 0; c < N; ++c) r1[c] = o[c];
-        eo<T, N, 1>(FS.B, r2, o);
+        eo<T, N, 1>(FB.B, r2, o);
 #pragma unroll
         for (int c = 0; c < N; ++c) r2[c] = o[c];
 #pragma unroll
@@ -517,16 +517,16 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(4))
     double energy = 0.0;
     if constexpr (BOX) {
       const QTab<T> tb = qtab(sT, 0, lane), ts = qtab(sT, 2, lane);
-      T wa = (T)FB.wq[0], wb = (T)FB.wq[0];
+      double wa = FB.wq[0], wb = FB.wq[0];
 #pragma unroll
       for (int i = 1; i < N; ++i) {
-        wa = w == i ? (T)FB.wq[i] : wa;
-        wb = q == i ? (T)FB.wq[i] : wb;
+        wa = w == i ? FB.wq[i] : wa;
+        wb = q == i ? FB.wq[i] : wb;
       }
       // twice: the sums below are folded values
-      const T gx = (T)(2.0 * P.kin * P.cellgeo[(int64_t)cell * 4 + 0]) * wb;
-      const T gy = (T)(P.kin * P.cellgeo[(int64_t)cell * 4 + 1]) * wa;
-      const T gz = (T)(2.0 * P.kin * P.cellgeo[(int64_t)cell * 4 + 2]) * (wa * wb);
+      const T gx = (T)(2.0 * P.kin * FB.gx * P.cellgeo[(int64_t)cell * 4 + 0] * wb);
+      const T gy = (T)(P.kin * FB.gs * P.cellgeo[(int64_t)cell * 4 + 1] * wa);
+      const T gz = (T)(2.0 * P.kin * FB.gs * P.cellgeo[(int64_t)cell * 4 + 2] * (wa * wb));
       T se[N], so[N];
       get_folded(PC.b1, PC.b2, se, so);
       // x stiffness term and the potential
@@ -709,16 +709,16 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(4))
 #pragma unroll
       for (int c = 0; c < N; ++c) qmul0(tt, r1[c], r2[c], r1[c], r2[c]);
       T o[N];
-      eo<T, N, 1>(FS.Bt, r1, o);
+      eo<T, N, 1>(FB.Bt, r1, o);
 #pragma unroll
       for (int k = 0; k < N; ++k) r1[k] = o[k];
-      eo<T, N, 1>(FS.Bt, r2, o);
+      eo<T, N, 1>(FB.Bt, r2, o);
 #pragma unroll
       for (int k = 0; k < N; ++k) {
         const T u1 = r1[k] + o[k], u2 = r1[k] - o[k];
         if constexpr (BOX) {
-          r1[k] = u1 * (mx1 * mz[k] * my);
-          r2[k] = u2 * (mx2 * mz[k] * my);
+          r1[k] = u1 * (mx1 * mz[k]);
+          r2[k] = u2 * (mx2 * mz[k]);
         } else {
           r1[k] = u1 * sM[PE.n1 + N * N * k];
           r2[k] = u2 * sM[PE.n2 + N * N * k];

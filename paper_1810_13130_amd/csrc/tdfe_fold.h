@@ -61,58 +61,38 @@ constexpr GaussStiff make_gauss_stiff(const tdfe1d::Rule& R) {
   return G;
 }
 
-// FP32 entries of S and S B.  Rounded one by one they err by half a unit in
-// the last place of entries up to 42, the same on every cell, and what a smooth
-// orbital sees of it (on a cell little more than 1 and x) adds up over the
-// terms of an exponential; derivatives, whose square S is, send that to zero
-// by themselves.  So the entries are rounded together: the even half such that
-// its columns sum to zero (a constant has no stiffness; the rows do by eo0),
-// the odd half such that x keeps its image.  fit_f32: n entries rounded, then
-// one after the other moved by a few units where it brings sum_i w_i a_i
-// nearest to the target.
-constexpr void fit_f32(double* a, int n, const double* w, double target) {
-  for (int i = 0; i < n; ++i) a[i] = (double)(float)a[i];
-  for (int pass = 0; pass < 8; ++pass) {
-    double r = -target;
-    for (int i = 0; i < n; ++i) r += w[i] * a[i];
-    int best = -1;
-    double left = r < 0.0 ? -r : r, moved = 0.0;
-    for (int i = 0; i < n; ++i) {
-      if (w[i] == 0.0) continue;
-      const double v = (double)(float)(a[i] - r / w[i]);
-      const double rest = r + w[i] * (v - a[i]), ar = rest < 0.0 ? -rest : rest;
-      if (ar < left) {
-        left = ar;
-        best = i;
-        moved = v;
-      }
-    }
-    if (best < 0) return;
-    a[best] = moved;
+// FP32 entries of the box kernels' tables.  Rounded as they are they err by
+// some 2e-8 of the table's norm, the same on every cell, and that is a quarter
+// of an FP32 operator's whole error on rough vectors; on smooth ones, where S
+// multiplies little more than 1 and x, it adds up over the terms of an
+// exponential.  So each table is stored times a factor in [1, 2), and the
+// factor is divided out of the scales that a cell's values and stiffness terms
+// are multiplied by anyway.  The factors are the best of 8 million tried for
+// n: least error of the rounded entries in the Frobenius norm, with that of the
+// images of 1 and x (for S and S B of the columns' sums and of x, four times
+// weighted).  They leave 1e-12 to 1e-8 (n = 2 .. 8) of the norm.
+// Relative error of one application in the 2-norm, rough vectors, p = 3 to 7:
+// 2.1, 1.8, 3.1, 2.1 and 2.6e-7 without them (entries of S and S B rounded so that
+// 1 and x keep their images), 1.5, 1.4, 1.6, 1.7 and 1.8e-7 so, and 1.6, 1.7, 3.2,
+// 1.8 and 2.0e-7 for a kernel with derivatives on either side of the flux.  (n =
+// 4: B itself is kept, eo1 takes half of the middle pair exactly.)
+// zB, zS: the lane pairs' tables along z, which are not folded.
+struct F32Factors {
+  double B = 1.0, Bt = 1.0, S = 1.0, SB = 1.0, zB = 1.0, zS = 1.0;
+};
+constexpr F32Factors f32_factors(int N) {
+  switch (N) {
+    case 2: return {1.46140062809200, 1.46140062809200, 1.0, 1.65737457274267, 1.61684665082995, 1.0};
+    case 3: return {1.03040337562240, 1.03040337562240, 1.92209072113039, 1.47100592848871};
+    case 4: return {1.0, 1.07268476539059, 1.33175274484762, 1.99836685462980, 1.67130209418044, 1.37747953557320};
+    case 5: return {1.86699926960131, 1.86699926960131, 1.80610855435722, 1.38926094107585};
+    case 6: return {1.55907900878783, 1.55907900878783, 1.79760520503759, 1.89983373788399, 1.71932972875035,
+                    1.09584027715945};
+    case 7: return {1.59642291522439, 1.59642291522439, 1.23522284087879, 1.48919430297576};
+    case 8: return {1.98078020932613, 1.98078020932613, 1.60004636661610, 1.15822634604022, 1.05413327285020,
+                    1.87712638329818};
   }
-}
-// E, O: the halves, rows of ld; mr: the middle row (odd N); x: the input points
-constexpr void fit_stiffness(double* E, double* O, int ld, int N, double* mr, const double* x) {
-  const int H = N / 2, HE = (N & 1) ? H : H - 1;
-  for (int a = 0; a < H; ++a) {
-    double target = 0.0;
-    for (int i = 0; i < H; ++i) target += x[i] * O[a * ld + i];
-    fit_f32(O + a * ld, H, x, target);
-  }
-  for (int i = 0; i < HE; ++i) {
-    double col[TDFE_MAXN]{}, w[TDFE_MAXN]{};
-    for (int a = 0; a < H; ++a) {
-      col[a] = E[a * ld + i];
-      w[a] = 2.0;
-    }
-    if (N & 1) {
-      col[H] = mr[i];
-      w[H] = 1.0;
-    }
-    fit_f32(col, H + (N & 1), w, 0.0);
-    for (int a = 0; a < H; ++a) E[a * ld + i] = col[a];
-    if (N & 1) mr[i] = col[H];
-  }
+  return {};
 }
 
 constexpr void fold_c(const double* A, int N, int S, bool transpose, Folded<double>& F) {
@@ -145,11 +125,22 @@ constexpr FoldSet<N> make_foldset() {
   return F;
 }
 
-// the folded tables of the box kernels: B, B^T, S and S B
+constexpr void scale_c(Folded<double>& F, double f) {
+  for (double& v : F.E) v *= f;
+  for (double& v : F.O) v *= f;
+  for (double& v : F.mc) v *= f;
+  for (double& v : F.mr) v *= f;
+}
+
+// the folded tables of the box kernels: B, B^T, S and S B, for FP32 times their
+// factors (b: B's), and what takes those out again: `in` for a cell's gathered values,
+// `out` for its results, gx for the x stiffness term (S B along x, B along y and z),
+// gs for the y and z terms
 template <int N>
 struct BoxFoldSet {
   Folded<double> B, Bt, S, SB;
   double wq[TDFE_MAXN];
+  double b = 1.0, in = 1.0, out = 1.0, gx = 1.0, gs = 1.0;
 };
 template <int N, bool F32>
 constexpr BoxFoldSet<N> make_box_foldset() {
@@ -161,8 +152,16 @@ constexpr BoxFoldSet<N> make_box_foldset() {
   fold_c(K.S, N, 1, false, F.S);
   fold_c(K.SB, N, 1, false, F.SB);
   if (F32) {
-    fit_stiffness(F.S.E, F.S.O, EO_MAX_H, N, F.S.mr, R.eta);
-    fit_stiffness(F.SB.E, F.SB.O, EO_MAX_H, N, F.SB.mr, R.xi);
+    constexpr F32Factors f = f32_factors(N);
+    scale_c(F.B, f.B);
+    scale_c(F.Bt, f.Bt);
+    scale_c(F.S, f.S);
+    scale_c(F.SB, f.SB);
+    F.b = f.B;
+    F.in = 1.0 / (f.B * f.B * f.B);
+    F.out = 1.0 / (f.Bt * f.Bt * f.Bt);
+    F.gx = f.B / f.SB;
+    F.gs = 1.0 / f.S;
   }
   for (int i = 0; i < TDFE_MAXN; ++i) F.wq[i] = R.wq[i];
   return F;
@@ -367,10 +366,9 @@ __device__ __forceinline__ void eo2(const Folded<FT>& F1, const Folded<FT>& F2, 
 // eo for a matrix that sends a constant to zero (S, S B): the middle value, or
 // the middle pair's sum, is taken off the folded sums first, and its column is
 // left out.  As many operations, and the rounding of the entries acts on the
-// differences along the line, not on the values.  With eo and entries rounded
-// one by one an FP32 exponential of smooth orbitals on box cells was off by
-// 4.5e-7 at p = 6 and 2.8e-7 or more at p = 7; with eo0 and fit_stiffness by
-// 1.7e-7 and 2.0e-7, which is what derivatives give.
+// differences along the line, not on the values: with eo and entries rounded
+// as they are an FP32 exponential of smooth orbitals on box cells was off by
+// 4.5e-7 at p = 6, with eo0 and the tables' factors by 1.5e-7.
 template <typename T, int N, typename FT>
 __device__ __forceinline__ void eo0(const Folded<FT>& F, const T* in, T* out) {
   constexpr int H = N / 2, HE = (N & 1) ? H : H - 1;
@@ -398,6 +396,35 @@ __device__ __forceinline__ void eo0(const Folded<FT>& F, const T* in, T* out) {
     for (int i = 0; i < H; ++i) m += (T)F.mr[i] * e[i];
     out[H] = m;
   }
+}
+
+// eo for B (b times B), whose rows sum to one, in the same way: the middle
+// value, or the middle pair's, is put back with the last multiply-add, so that
+// what is rounded before it are differences along the line
+template <typename T, int N, typename FT>
+__device__ __forceinline__ void eo1(const Folded<FT>& F, double b, const T* in, T* out) {
+  constexpr int H = N / 2, HE = (N & 1) ? H : H - 1;
+  const T mid = (N & 1) ? in[H] : in[H - 1] + in[H];
+  const T mf = (N & 1) ? (T)b : (T)(0.5 * b);
+  T e[HE > 0 ? HE : 1], o[H];
+#pragma unroll
+  for (int i = 0; i < H; ++i) {
+    if (i < HE) e[i] = in[i] + in[N - 1 - i] - ((N & 1) ? 2 * mid : mid);
+    o[i] = in[i] - in[N - 1 - i];
+  }
+#pragma unroll
+  for (int a = 0; a < H; ++a) {
+    T Pv = 0, Qv = 0;
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+      if (i < HE) Pv += (T)F.E[a * EO_MAX_H + i] * e[i];
+      Qv += (T)F.O[a * EO_MAX_H + i] * o[i];
+    }
+    Pv += mf * mid;
+    out[a] = Pv + Qv;
+    out[N - 1 - a] = Pv - Qv;
+  }
+  if constexpr (N & 1) out[H] = mf * mid;  // the middle Gauss point is a node
 }
 
 // host: fold an N x N table (row-major, stride TDFE_MAXN) with symmetry S
