@@ -7,13 +7,15 @@
 // 4 positions q of the axis the phase contracts most (x in A and C, y in B), a
 // lane holding that axis's entries q and n-1-q, and the n z entries in its
 // registers:
-//   A  gather; x: B, z: B, x: Dg (box: z: B, x: B and S B)
+//   A  gather; x: B, z: B, x: Dg (FP32: x: B and D, z: B on both; box: z: B, x: B
+//      and S B)
 //   -- LDS transpose of the two arrays -->
 //   B  y: B on both; y and z derivatives, the six-entry metric, the potential,
 //      transposed derivatives (box: the stiffness S along y and z, weights,
 //      potential); y: B^T
 //   -- LDS transpose (box: of the one array) -->
-//   C  x: Dg^T (box: none) and B^T, z: B^T; results x M^-1/2 (as CellOut).
+//   C  x: Dg^T and B^T (FP32: B^T and D^T; box: B^T), z: B^T; results x M^-1/2 (as
+//      CellOut).
 // A lane's two entries are folded into their even and odd parts, and every 1D
 // table into a 4 x 4 even and a 4 x 4 odd half, so a contraction across the
 // four lanes is two 4 x 4 products: FP64 by v_mfma_f64_4x4x4 (lane = 16 q +
@@ -26,8 +28,9 @@
 // and they share it (8 MFMA and 16 FMA take the sum of their times), so what
 // this layout buys is not rate but registers and addresses: 2 n values per
 // array and lane instead of 4 n (lane pairs) or n^2 (planes), so four waves
-// per SIMD hide each other's gathers, transposes and barriers, and cell, plane
-// and z row are uniform per wave, so masks and 64-bit addresses are scalar.
+// per SIMD (FP64 at n = 8 two: its cell takes 117 KB of LDS) hide each other's
+// gathers, transposes and barriers, and cell, plane and z row are uniform per
+// wave, so masks and 64-bit addresses are scalar.
 // What bounds it: FP64 at n = 7, 31^3 trilinear cells of 16 columns: vector and
 // matrix units are busy half of the 1.20 ms (45k cycles of them per cell, 0.63
 // ms at full use); waits at the ten barriers and the transposes' latency take
@@ -35,6 +38,11 @@
 // FP64 815 -> 588 us, FP32 406 -> 389 us (FP32's DPP steps issue at half the
 // rate of plain FP32, so at n = 7 the plane kernel stays ahead: 370 against
 // 430 us).
+// FP32 takes the x derivative from the nodes and every table with a factor
+// (F32Factors): one application on rough vectors is off by 1.55e-7 (lane pairs
+// 1.67e-7; with Dg on the interpolated values and plain tables 2.02e-7), an
+// exponential of 40 iterations by 1.05e-7 (1.15e-7; 1.40e-7), for 3% of the
+// launch (13 x 14 x 15 cells, 32 columns 220 -> 227 us).
 #include "tdfe_fold.h"
 
 namespace {
@@ -50,7 +58,7 @@ struct QHalf {
 };
 // tables in the order a kernel stages them
 struct QuadTables {
-  QHalf t[4];
+  QHalf t[6];
 };
 
 constexpr QHalf quad_half(const double* A, int N, int S, bool transpose, double f) {
@@ -71,12 +79,12 @@ constexpr QHalf quad_half(const double* A, int N, int S, bool transpose, double 
 }
 
 // trilinear cells: B (folded -> parts), Dg (parts -> parts), Dg^T (folded ->
-// folded), B^T (folded -> parts); box cells: B, S B (folded -> parts), S
-// (parts -> folded), B^T
+// folded), B^T (folded -> parts), FP32 also D, D^T (folded -> parts); box
+// cells: B, S B (folded -> parts), S (parts -> folded), B^T
 template <int N, bool BOX, bool F32>
 constexpr QuadTables make_quad_tables() {
   const tdfe1d::Rule R = tdfe1d::make_rule(N - 1);
-  const F32Factors f = BOX && F32 ? f32_factors(N) : F32Factors{};
+  const F32Factors f = F32 ? f32_factors(N) : F32Factors{};
   QuadTables Q{};
   Q.t[0] = quad_half(R.B, N, 1, false, f.B);
   if (BOX) {
@@ -84,8 +92,10 @@ constexpr QuadTables make_quad_tables() {
     Q.t[1] = quad_half(K.SB, N, 1, false, f.SB);
     Q.t[2] = quad_half(K.S, N, 1, false, 4.0 * f.S);
   } else {
-    Q.t[1] = quad_half(R.Dg, N, -1, false, 2.0);
-    Q.t[2] = quad_half(R.Dg, N, -1, true, 2.0);
+    Q.t[1] = quad_half(R.Dg, N, -1, false, 2.0 * f.G);
+    Q.t[2] = quad_half(R.Dg, N, -1, true, 2.0 * f.G);
+    Q.t[4] = quad_half(R.D, N, -1, false, f.D);
+    Q.t[5] = quad_half(R.D, N, -1, true, f.D);
   }
   Q.t[3] = quad_half(R.B, N, 1, true, f.Bt);  // (Bt = B at n = 8: one scale for gather and results)
   return Q;
@@ -103,7 +113,7 @@ struct QuadParams {
   const double* colscale;
   double kin;
   const void* vw;
-  const T* minv;          // trilinear cells: M^-1/2 per DoF
+  const double* minv;     // trilinear cells: M^-1/2 per DoF
   const double* corners;  // trilinear cells: [n_cell][2][2][2][3]
   const double* m1x;      // box cells: separable M^-1/2 factors
   const double* m1y;
@@ -214,10 +224,11 @@ __device__ __forceinline__ void quad_jacobian_column(double* sJ, const double* C
   }
 }
 
-// kin w detJ J^-1 J^-T at Gauss point (a, b, c)
+// kin w detJ J^-1 J^-T at Gauss point (a, b, c), for derivatives that carry the
+// factors 1 / fx along x and 1 / fy along y and z
 template <typename T, int N>
 __device__ __forceinline__ void quad_metric(T* g, const double* sJ, const double* sEW, int a, int b, int c,
-                                            double kin) {
+                                            double kin, double fx, double fy) {
   double Jm[3][3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
@@ -237,12 +248,13 @@ __device__ __forceinline__ void quad_metric(T* g, const double* sJ, const double
   A[2][2] = Jm[0][0] * Jm[1][1] - Jm[0][1] * Jm[1][0];
   const double det = Jm[0][0] * A[0][0] + Jm[0][1] * A[1][0] + Jm[0][2] * A[2][0];
   const double s = kin * sEW[N + a] * sEW[N + b] * sEW[N + c] / det;
-  g[0] = (T)(s * (A[0][0] * A[0][0] + A[0][1] * A[0][1] + A[0][2] * A[0][2]));
-  g[1] = (T)(s * (A[0][0] * A[1][0] + A[0][1] * A[1][1] + A[0][2] * A[1][2]));
-  g[2] = (T)(s * (A[0][0] * A[2][0] + A[0][1] * A[2][1] + A[0][2] * A[2][2]));
-  g[3] = (T)(s * (A[1][0] * A[1][0] + A[1][1] * A[1][1] + A[1][2] * A[1][2]));
-  g[4] = (T)(s * (A[1][0] * A[2][0] + A[1][1] * A[2][1] + A[1][2] * A[2][2]));
-  g[5] = (T)(s * (A[2][0] * A[2][0] + A[2][1] * A[2][1] + A[2][2] * A[2][2]));
+  const double xx = s * (fx * fx), xy = s * (fx * fy), yy = s * (fy * fy);
+  g[0] = (T)(xx * (A[0][0] * A[0][0] + A[0][1] * A[0][1] + A[0][2] * A[0][2]));
+  g[1] = (T)(xy * (A[0][0] * A[1][0] + A[0][1] * A[1][1] + A[0][2] * A[1][2]));
+  g[2] = (T)(xy * (A[0][0] * A[2][0] + A[0][1] * A[2][1] + A[0][2] * A[2][2]));
+  g[3] = (T)(yy * (A[1][0] * A[1][0] + A[1][1] * A[1][1] + A[1][2] * A[1][2]));
+  g[4] = (T)(yy * (A[1][0] * A[2][0] + A[1][1] * A[2][1] + A[1][2] * A[2][2]));
+  g[5] = (T)(yy * (A[2][0] * A[2][0] + A[2][1] * A[2][1] + A[2][2] * A[2][2]));
 }
 
 template <typename T, int N, bool BOX, bool CELLS>
@@ -258,19 +270,22 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(4))
   // that the four positions q fall into different bank groups
   constexpr int PAD = ODD ? 0 : QC;
   constexpr int LX = N * QC + PAD, LY = N * LX + PAD;
-  constexpr FoldSet<N> FS = make_foldset<N>();
-  constexpr BoxFoldSet<N> FB = make_box_foldset<N, BOX && sizeof(T) == 4>();
+  constexpr FoldSet<N> FS = make_foldset<N>(F32 ? f32_factors(N).G : 1.0);
+  constexpr BoxFoldSet<N> FB = make_box_foldset<N, sizeof(T) == 4>();
   // FP64 on trilinear cells at n = 7: two blocks per CU (14 waves) need 128
   // registers per lane, and the flux phase holds 158 (26 spilled values of it
   // made scratch traffic of 2.8 GB per launch): half of its arrays wait in LDS
   constexpr bool PARK = !F32 && !BOX && N == 7;
+  // what takes the tables' factors out of the x and of the y and z derivatives
+  constexpr double GX = F32 ? f32_factors(N).B / f32_factors(N).D : 1.0, GY = F32 ? 1.0 / f32_factors(N).G : 1.0;
   constexpr int NX = PARK && 2 * N * THREADS > N * LY ? 2 * N * THREADS : N * LY;
   __shared__ T sX[NX];
   __shared__ T sV[VOL];
   __shared__ T sG[BOX ? 1 : VOL * 6];
   __shared__ T sM[BOX ? 1 : VOL];
   __shared__ double sRed[THREADS];
-  __shared__ T sT[128];
+  constexpr int NTAB = F32 && !BOX ? 192 : 128;
+  __shared__ T sT[NTAB];
   __shared__ double sC[BOX ? 1 : 24];
   __shared__ double sJ[BOX ? 1 : 9 * N * N];
   __shared__ double sEW[2 * N];
@@ -300,11 +315,11 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(4))
       // results are not scattered)
       const int I = cx * P.p + r % N, J = cy * P.p + (r / N) % N, K = cz * P.p + r / (N * N);
       const bool in = r < VOL && I > 0 && I < P.Nx - 1 && J > 0 && J < P.Ny - 1 && K > 0 && K < P.Nz - 1;
-      mr[k] = P.minv[in ? (int64_t)(I - 1) + (int64_t)NxI * ((int64_t)(J - 1) + (int64_t)NyI * (K - 1)) : 0];
+      mr[k] = (T)(FB.in * P.minv[in ? (int64_t)(I - 1) + (int64_t)NxI * ((int64_t)(J - 1) + (int64_t)NyI * (K - 1)) : 0]);
     }
   }
   T tr = 0;
-  if (t < 128) tr = (T)((const double*)&quad_tables<N, BOX, sizeof(T) == 4>)[t];
+  if (t < NTAB) tr = (T)((const double*)&quad_tables<N, BOX, sizeof(T) == 4>)[t];
   double cr = 0.0;
   if constexpr (!BOX)
     if (t < 24) cr = P.corners[(int64_t)cell * 24 + t];
@@ -410,7 +425,7 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(4))
           if constexpr (!BOX) sM[r] = mr[k];
         }
       }
-      if (t < 128) sT[t] = tr;
+      if (t < NTAB) sT[t] = tr;
       if constexpr (!BOX)
         if (t < 24) sC[t] = cr;
       __syncthreads();
@@ -418,7 +433,7 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(4))
         if (t < 3 * N * N) quad_jacobian_column<N>(sJ, sC, sEW, t);
         __syncthreads();
         for (int r = t; r < VOL; r += THREADS)
-          quad_metric<T, N>(sG + r * 6, sJ, sEW, r % N, (r / N) % N, r / (N * N), P.kin);
+          quad_metric<T, N>(sG + r * 6, sJ, sEW, r % N, (r / N) % N, r / (N * N), P.kin, GX, GY);
       }
     }
     const Pos PA = pos();
@@ -438,9 +453,34 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(4))
         r1[k] = u1 + u2;
         r2[k] = u1 - u2;
       }
-      const QTab<T> tb = qtab(sT, 0, lane), td = qtab(sT, 1, lane);
+      const QTab<T> tb = qtab(sT, 0, lane), td = qtab(sT, F32 && !BOX ? 4 : 1, lane);
       T o[N];
-      if constexpr (BOX) {
+      if constexpr (F32 && !BOX) {
+        // the x derivative from the nodes (D = Dg B)
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+          qmul0(td, r1[k], r2[k], t2[k], t1[k]);  // (antisymmetric: the odd part first)
+          qmul0(tb, r1[k], r2[k], r1[k], r2[k]);
+        }
+        auto along_z = [&](T* v) {
+          eo<T, N, 1>(FB.B, v, o);
+#pragma unroll
+          for (int c = 0; c < N; ++c) v[c] = o[c];
+        };
+        along_z(r1);
+        along_z(r2);
+        along_z(t1);
+        along_z(t2);
+#pragma unroll
+        for (int c = 0; c < N; ++c) {
+          const T u1 = r1[c] + r2[c], u2 = r1[c] - r2[c];
+          r1[c] = u1;
+          r2[c] = u2;
+          const T v1 = t1[c] + t2[c], v2 = t1[c] - t2[c];
+          t1[c] = v1;
+          t2[c] = v2;
+        }
+      } else if constexpr (BOX) {
         eo<T, N, 1>(FB.B, r1, o);
 #pragma unroll
         for (int c = 0; c < N; ++c) r1[c] = o[c];
@@ -694,7 +734,13 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(4))
       put(PD.b1, PD.b2, ue, uo);
       __syncthreads();
       get_folded(PD.a1, PD.a2, r1, r2);
-      const QTab<T> tg = qtab(sT, 2, lane);
+      const QTab<T> tg = qtab(sT, F32 ? 5 : 2, lane);
+      if constexpr (F32) {
+        // B^T s + D^T f_x
+        const QTab<T> tt = qtab(sT, 3, lane);
+#pragma unroll
+        for (int c = 0; c < N; ++c) qmul0(tt, r1[c], r2[c], r1[c], r2[c]);
+      }
 #pragma unroll
       for (int c = 0; c < N; ++c) {
         T p1, q1;
@@ -705,9 +751,11 @@ __global__ void __launch_bounds__(64 * N) __attribute__((amdgpu_waves_per_eu(4))
     }
     const Pos PE = pos();
     {
-      const QTab<T> tt = qtab(sT, 3, lane);
+      if constexpr (!F32 || BOX) {
+        const QTab<T> tt = qtab(sT, 3, lane);
 #pragma unroll
-      for (int c = 0; c < N; ++c) qmul0(tt, r1[c], r2[c], r1[c], r2[c]);
+        for (int c = 0; c < N; ++c) qmul0(tt, r1[c], r2[c], r1[c], r2[c]);
+      }
       T o[N];
       eo<T, N, 1>(FB.Bt, r1, o);
 #pragma unroll
@@ -791,7 +839,7 @@ tdfe_status launch_quad_t(tdfe_ctx* c, const ApplyArgs& a) {
   P.colscale = a.colscale;
   P.kin = a.kin;
   P.vw = a.fp32 ? (const void*)a.vw32 : (const void*)a.vw;
-  P.minv = sizeof(T) == 4 ? (const T*)(const void*)c->minv32 : (const T*)(const void*)c->minv;
+  P.minv = c->minv;
   P.corners = c->corners;
   P.m1x = c->m1x;
   P.m1y = c->m1y;

@@ -79,6 +79,7 @@ constexpr GaussStiff make_gauss_stiff(const tdfe1d::Rule& R) {
 // zB, zS: the lane pairs' tables along z, which are not folded.
 struct F32Factors {
   double B = 1.0, Bt = 1.0, S = 1.0, SB = 1.0, zB = 1.0, zS = 1.0;
+  double D = 1.0, G = 1.0;  // trilinear cells, four-lane kernel
 };
 constexpr F32Factors f32_factors(int N) {
   switch (N) {
@@ -90,7 +91,8 @@ constexpr F32Factors f32_factors(int N) {
                     1.09584027715945};
     case 7: return {1.59642291522439, 1.59642291522439, 1.23522284087879, 1.48919430297576};
     case 8: return {1.98078020932613, 1.98078020932613, 1.60004636661610, 1.15822634604022, 1.05413327285020,
-                    1.87712638329818};
+                    1.87712638329818,
+                    1.56014991319470, 1.03100566826716};
   }
   return {};
 }
@@ -111,8 +113,16 @@ constexpr void fold_c(const double* A, int N, int S, bool transpose, Folded<doub
   }
 }
 
+constexpr void scale_c(Folded<double>& F, double f) {
+  for (double& v : F.E) v *= f;
+  for (double& v : F.O) v *= f;
+  for (double& v : F.mc) v *= f;
+  for (double& v : F.mr) v *= f;
+}
+
+// g: factor of Dg and Dg^T
 template <int N>
-constexpr FoldSet<N> make_foldset() {
+constexpr FoldSet<N> make_foldset(double g = 1.0) {
   const tdfe1d::Rule R = tdfe1d::make_rule(N - 1);
   FoldSet<N> F{};
   fold_c(R.B, N, 1, false, F.B);
@@ -121,15 +131,10 @@ constexpr FoldSet<N> make_foldset() {
   fold_c(R.D, N, -1, true, F.Dt);
   fold_c(R.Dg, N, -1, false, F.G);
   fold_c(R.Dg, N, -1, true, F.Gt);
+  scale_c(F.G, g);
+  scale_c(F.Gt, g);
   for (int i = 0; i < TDFE_MAXN; ++i) F.wq[i] = R.wq[i];
   return F;
-}
-
-constexpr void scale_c(Folded<double>& F, double f) {
-  for (double& v : F.E) v *= f;
-  for (double& v : F.O) v *= f;
-  for (double& v : F.mc) v *= f;
-  for (double& v : F.mr) v *= f;
 }
 
 // the folded tables of the box kernels: B, B^T, S and S B, for FP32 times their
