@@ -330,6 +330,11 @@ __global__ void __launch_bounds__(CPB * N * N * CB)
         sU[lidx<N, CB>(slot, c, b, a, col)] = uq[a];
         sR[lidx<N, CB>(slot, c, b, a, col)] = pot[a] + r2[a];
       }
+      // The quadratic form is made final after each phase: left alone the compiler
+      // keeps the products of all phases for the reduction at the end (FP64 n =
+      // 9, 8 columns: 57 registers spilled; 16 orbitals on 12 x 11 x 13 cells 731
+      // us a launch, 570 so, and 705 with unfolded tables, 34 spilled)
+      asm volatile("" : "+v"(energy));
     } else {
 #pragma unroll
       for (int a = 0; a < N; ++a) {
@@ -356,6 +361,7 @@ __global__ void __launch_bounds__(CPB * N * N * CB)
         f[c] = (T)gz * sW3[a + N * (b + N * c)] * d[c];
         energy += (double)f[c] * (double)d[c];
       }
+      asm volatile("" : "+v"(energy));
       eo<T, N, -1>(FS.Gt, f, d);
 #pragma unroll
       for (int c = 0; c < N; ++c) sR[lidx<N, CB>(slot, c, b, a, col)] = r2[c] + d[c];
@@ -376,6 +382,7 @@ __global__ void __launch_bounds__(CPB * N * N * CB)
         f[b] = (T)gy * sW3[a + N * (b + N * c)] * d[b];
         energy += (double)f[b] * (double)d[b];
       }
+      asm volatile("" : "+v"(energy));
       eo<T, N, -1>(FS.Gt, f, d);
 #pragma unroll
       for (int b = 0; b < N; ++b) r1[b] = r2[b] + d[b];
@@ -434,6 +441,7 @@ __global__ void __launch_bounds__(CPB * N * N * CB)
         sGY[li] = ffy;
         sGZ[li] = ffz;
       }
+      asm volatile("" : "+v"(energy));
       eo<T, N, -1>(FS.Gt, fx, r1);
 #pragma unroll
       for (int a = 0; a < N; ++a) sU[lidx<N, CB>(slot, c, b, a, col)] = pot[a] + r1[a];
