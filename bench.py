@@ -760,10 +760,10 @@ def matrix_core_engines(steps=100, warmup=5, reps=100):
 def curved_kernel_name(p, cols, fp32):
     """Name of the trilinear-cell operator kernel a launch of `cols` real
     columns runs (the library's default choice: four lanes per line for more
-    than 8 columns at p = 7 and FP64 p = 6, else lane pairs for FP64 p >= 5 and
-    for FP32 at p = 7, else plane ownership; columns per block the next power
-    of two up to 16, at least 2 for lane pairs, or 32 for FP32 plane launches of
-    more than 16)."""
+    than 8 columns at p = 7 and FP64 p = 6, else lane pairs for FP64 p >= 5, for
+    FP32 at p = 7 and for FP64 launches of few columns below, else plane
+    ownership; columns per block the next power of two up to 16, at least 2 for
+    lane pairs, or 32 for FP32 plane launches of more than 16)."""
     n = p + 1
     pw = 1
     while pw < cols:
@@ -771,7 +771,7 @@ def curved_kernel_name(p, cols, fp32):
     t = "float" if fp32 else "double"
     if cols > 8 and (n == 8 or (n == 7 and not fp32)):
         return f"quad_kernel<{t},{n},false,CELLS> (trilinear cells, four lanes per line)"
-    if (not fp32 and n > 5) or n == 8:
+    if n == 8 if fp32 else n > 5 or cols <= {2: 2, 3: 8}.get(n, 4):
         return f"cpair_kernel<{t},{n},{max(2, min(pw, 16))},CPB> (trilinear cells, lane pairs)"
     return f"cplane_kernel<{t},{n},{(32 if fp32 else 16) if cols > 16 else pw},CPB> (trilinear cells)"
 

@@ -633,16 +633,18 @@ int64_t tdfe_blocks_apply(const tdfe_ctx* c, int cols) {
   return c->n_cell;
 }
 
+// box cells: lane pairs for FP64 at even n (two waves per SIMD), planes otherwise
+static bool box_pair(const tdfe_ctx* c, const ApplyArgs& a) {
+  return (c->variant == TDFE_VARIANT_PAIR || (c->variant == 0 && !a.fp32)) && tdfe_pair_kernel_ok(c);
+}
+
 static tdfe_status launch_blocks(tdfe_ctx* c, const ApplyArgs& a) {
   // default policy, from measurements on the benchmark and graded workloads:
-  // the four-lane kernel where tdfe_quad_kernel_ok says; box cells: the
-  // lane-pair kernel for FP64 at even n (two waves per SIMD), the plane kernel
-  // otherwise; trilinear cells: see tdfe_launch_apply_curved
+  // the four-lane kernel where tdfe_quad_kernel_ok says; box cells: see
+  // box_pair; trilinear cells: see tdfe_curved_pair
   if (tdfe_quad_kernel_ok(c, a)) return tdfe_launch_apply_quad(c, a);
   if (!c->box) return tdfe_launch_apply_curved(c, a);
-  const bool pair = c->variant == TDFE_VARIANT_PAIR || (c->variant == 0 && !a.fp32);
-  if (pair && tdfe_pair_kernel_ok(c)) return tdfe_launch_apply_pair(c, a);
-  return tdfe_launch_apply_box(c, a);
+  return box_pair(c, a) ? tdfe_launch_apply_pair(c, a) : tdfe_launch_apply_box(c, a);
 }
 
 // Whether 32-bit byte offsets reach every node of a block's cells: always in
@@ -800,11 +802,8 @@ int tdfe_operator_route(const tdfe_ctx* c, int cols, int fp32) {
   a.lowdin = true;
   a.fp32 = fp32 != 0;
   if (c->octree || (c->mfma && tdfe_mfma_kernel_ok(c, a)) || !block_kernels_ok(c, a)) return 0;
-  const int kernel = tdfe_quad_kernel_ok(c, a) ? 4
-                     : !c->box                 ? 2
-                     : (c->variant == TDFE_VARIANT_PAIR || (c->variant == 0 && !a.fp32)) && tdfe_pair_kernel_ok(c) ? 3
-                                                                                                                 : 1;
-  return kernel + (offsets_near(c, a) ? 0 : 8) + (cells_fit(c, a) ? 16 : 0);
+  const bool pair = c->box ? box_pair(c, a) : tdfe_curved_pair(c, a.cols, a.fp32);
+  return (tdfe_quad_kernel_ok(c, a) ? 4 : (pair ? 3 : 1)) + (offsets_near(c, a) ? 0 : 8) + (cells_fit(c, a) ? 16 : 0);
 }
 
 tdfe_status tdfe_launch_apply(tdfe_ctx* c, const ApplyArgs& a) {

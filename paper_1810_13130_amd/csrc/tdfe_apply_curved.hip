@@ -1127,13 +1127,7 @@ tdfe_status launch_curved(tdfe_ctx* c, const ApplyArgs& a) {
     P.eta[i] = c->eta[i];
     P.wq[i] = c->wq[i];
   }
-  // lane pairs for FP64 above n = 5 (two waves per SIMD instead of one; at n =
-  // 5 a plane fits: 295 against 385 us per 8-orbital launch on 24^3 cells) and
-  // for FP32 at n = 8 (162 VGPRs against the plane kernel's 256: 1.75 against
-  // 1.98 ms per 2-orbital launch of the all-electron workload); plane ownership
-  // for FP32 otherwise (at n = 7 both run two waves per SIMD and the pairs'
-  // duplicated z work loses: 2.24 against 1.50 ms per 16-orbital graded launch)
-  const bool pair = c->variant == TDFE_VARIANT_PAIR || (c->variant == 0 && (sizeof(T) == 8 ? N > 5 : N == 8));
+  const bool pair = tdfe_curved_pair(c, a.cols, sizeof(T) == 4);
   if (pair) {
     switch (N) {
       case 2: return launch_cpair_n<T, 2>(c, P, a.n_blocks_out);
@@ -1159,6 +1153,24 @@ tdfe_status launch_curved(tdfe_ctx* c, const ApplyArgs& a) {
 }
 
 }  // namespace
+
+// Lane pairs or planes, the better of the two per launch:
+//  * FP64 above n = 5: pairs (two waves per SIMD instead of one);
+//  * FP64 below, where a plane fits the registers: planes, except for launches
+//    of few columns, which leave planes too few lanes in flight.  One orbital
+//    on 900,000 DoFs, planes against pairs: n = 5 154 and 98 us, n = 4 145 and
+//    84, n = 3 112 and 141, n = 2 218 and 208; two: n = 5 111 and 106, n = 4 106
+//    and 81, n = 3 157 and 138, n = 2 260 and 273; four: n = 5 134 and 181, n = 4
+//    132 and 123, n = 3 247 and 218; eight: n = 5 228 and 332, n = 3 293 and 365;
+//  * FP32 at n = 8: pairs (162 VGPRs against the plane kernel's 256: 1.75 against
+//    1.98 ms per 2-orbital launch of the all-electron workload); below planes (at
+//    n = 7 both run two waves per SIMD and the pairs' duplicated z work loses:
+//    2.24 against 1.50 ms per 16-orbital graded launch).
+bool tdfe_curved_pair(const tdfe_ctx* c, int cols, bool fp32) {
+  if (c->variant != 0) return c->variant == TDFE_VARIANT_PAIR;
+  if (fp32) return c->n == 8;
+  return c->n > 5 || cols <= (c->n == 3 ? 8 : (c->n == 2 ? 2 : 4));
+}
 
 // true if the curved plane kernel handles this launch: trilinear cells, p <= 7,
 // two or more real columns (one column leaves n threads per cell with the

@@ -248,11 +248,12 @@ bool tdfe_cells_ok(const tdfe_ctx* c, int cols, bool fp32);
 tdfe_status tdfe_launch_apply_cells(tdfe_ctx* c, const ApplyArgs& a);
 bool tdfe_can_overwrite(const tdfe_ctx* c, const ApplyArgs& a);
 // host only: the kernel of an operator launch on the DoF vectors, 0 the line
-// kernel (or another mesh's or engine's), 1 plane, 2 trilinear, 3 lane pairs, 4
-// four lanes; + 8 with 64-bit offsets, + 16 through the cell buffer
+// kernel (or another mesh's or engine's), 1 plane, 3 lane pairs, 4 four lanes; + 8
+// with 64-bit offsets, + 16 through the cell buffer
 extern "C" int tdfe_operator_route(const tdfe_ctx* c, int cols, int fp32);
 // trilinear-cell variant in the same layout (tdfe_apply_curved.hip)
 bool tdfe_curved_kernel_ok(const tdfe_ctx* c, int cols, bool fp32);
+bool tdfe_curved_pair(const tdfe_ctx* c, int cols, bool fp32);
 #define TDFE_VARIANT_LINE 1
 #define TDFE_VARIANT_PAIR 2
 #define TDFE_VARIANT_PLANE 3

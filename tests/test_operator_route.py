@@ -13,7 +13,7 @@ import pytest
 import workloads as W
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-LINE, PLANE, TRILINEAR, PAIR, QUAD, FAR, CELLS = 0, 1, 2, 3, 4, 8, 16
+LINE, PLANE, PAIR, QUAD, FAR, CELLS = 0, 1, 3, 4, 8, 16
 
 
 @pytest.fixture(scope="module")
@@ -52,10 +52,19 @@ def _route(lib, mesh, p, nc, n_orb, fp32, variant=None, monkeypatch=None):
     # the four-lane kernel has an address per row of nodes
     ("box", 6, (160, 160, 2), 32, False, QUAD), ("trilinear", 6, (160, 160, 2), 32, False, QUAD),
     ("trilinear", 7, (120, 120, 2), 32, True, QUAD),
-    ("trilinear", 5, (100, 100, 2), 32, False, TRILINEAR), ("trilinear", 5, (190, 190, 2), 32, False, LINE),
-    ("trilinear", 6, (160, 160, 2), 32, True, TRILINEAR), ("box", 8, (4, 4, 4), 8, False, LINE)])
+    ("trilinear", 5, (100, 100, 2), 32, False, PAIR), ("trilinear", 5, (190, 190, 2), 32, False, LINE),
+    ("trilinear", 6, (160, 160, 2), 32, True, PLANE), ("box", 8, (4, 4, 4), 8, False, LINE)])
 def test_route(lib, mesh, p, nc, n_orb, fp32, want):
     assert _route(lib, mesh, p, nc, n_orb, fp32) == want
+
+
+@pytest.mark.parametrize("p,pairs", [(1, 1), (2, 4), (3, 2), (4, 2), (5, 16), (6, 4), (7, 4)])
+def test_trilinear_fp64_kernel_by_columns(lib, p, pairs):
+    """Lane pairs up to so many orbitals; from nine columns on the four-lane
+    kernel at p = 6 and 7, planes else."""
+    for n_orb in (1, 2, 3, 4, 5, 9, 16):
+        want = PAIR if n_orb <= pairs else QUAD if p > 5 else PLANE
+        assert _route(lib, "trilinear", p, (7, 6, 5), n_orb, False) & 7 == want, n_orb
 
 
 def test_block_span(tmp_path):
