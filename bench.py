@@ -787,7 +787,7 @@ def workload_legs(cfg, steps, warmup, apply_reps, curved, matched=True, jacobi_c
     r64 = run_steps(ctx, psi, cfg, cfg.tol, steps, warmup)
     t_chunk = time_apply(ctx, chunk64, False, apply_reps)
     t_full = time_apply(ctx, cfg.n_orb, False, max(3, apply_reps // 4))
-    kname = curved_kernel_name(cfg.p, 2 * chunk64, False) if curved else "pair_kernel<double,6,16,1> + assemble_kernel (box cells)"
+    kname = curved_kernel_name(cfg.p, 2 * chunk64, False) if curved else "pair_kernel<double,6,16,1> (box cells)"
     res["f64"] = {**{k: v for k, v in r64.items() if k != "mu"}, "chunk_orbitals": chunk64,
                   "roofline": roofline(ctx, cfg, chunk64, t_chunk, False, kname, curved),
                   "apply_H_gdof_orb_per_s": ctx.n_dof * cfg.n_orb / t_full / 1e9, "apply_full_ms": t_full * 1e3}

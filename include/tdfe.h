@@ -99,7 +99,8 @@ typedef struct {
  * TDFE_APPLY_VARIANT=line|pair|plane forces one operator kernel family
  * where it applies (the default picks per mesh, order and precision);
  * TDFE_CELL_BUFFER_BYTES=n caps the buffer of per-cell operator results (at
- * most 256 MB; launches that do not fit add to the output directly).
+ * most 256 MB; launches that do not fit add to the output directly) and has
+ * every launch that fits go through it (by default those where that pays).
  * hip_stream: hipStream_t (may be 0).  *out receives a new context. */
 tdfe_status tdfe_fe_mesh_setup(const tdfe_mesh_desc* d, void* hip_stream, tdfe_ctx** out);
 
@@ -230,9 +231,11 @@ tdfe_status tdfe_projector_info(const tdfe_ctx* ctx, int* n_groups, int64_t* sto
 tdfe_status tdfe_apply_H(tdfe_ctx* ctx, const void* dev_psibar, void* dev_out, int n_orb);
 
 /* apply_H_add: dev_out += Hbar dev_psibar (same operator as apply_H, no
- * zeroing of dev_out): exactly one launch of the operator kernel (followed by
- * the nonlocal kernels when projectors are set), for composite operators and
- * for timing that kernel alone. */
+ * zeroing of dev_out): the operator kernel, which adds to dev_out or, where
+ * that is faster, leaves per-cell results that a second kernel sums into it,
+ * followed by the nonlocal kernels when projectors are set; for composite
+ * operators and for timing.  dev_out is read and written: calls on several
+ * streams that add to one array must be ordered by the caller. */
 tdfe_status tdfe_apply_H_add(tdfe_ctx* ctx, const void* dev_psibar, void* dev_out, int n_orb);
 
 /* apply_H_add_f32: dev_out += Hbar dev_psibar in FP32 (the mixed-precision

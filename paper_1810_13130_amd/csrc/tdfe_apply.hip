@@ -647,6 +647,10 @@ static tdfe_status launch_blocks(tdfe_ctx* c, const ApplyArgs& a) {
   return box_pair(c, a) ? tdfe_launch_apply_pair(c, a) : tdfe_launch_apply_box(c, a);
 }
 
+static size_t cell_bytes(const tdfe_ctx* c, int cols, bool fp32) {
+  return (size_t)c->n_cell * c->n * c->n * c->n * cols * (fp32 ? 4 : 8);
+}
+
 // Whether 32-bit byte offsets reach every node of a block's cells: always in
 // the four-lane kernel (a 64-bit address per row of nodes, and its own check),
 // else a matter of the cells per block of the kernel that would run.
@@ -675,18 +679,11 @@ static bool block_kernels_ok(const tdfe_ctx* c, const ApplyArgs& a) {
   return tdfe_curved_kernel_ok(c, a.cols, a.fp32) && offsets_near(c, a);
 }
 
-// Columns of a launch whose per-cell results fit the cell buffer (0: none).
-// Per-cell results take plain stores where the scatter takes atomics (1.3 TB/s
-// of values), and leave n^3 / p^3 vectors for the consumer to read where the
-// scatter leaves one, so they pay while they stay in the memory-side cache.
-// Operator + update per Krylov step: 16^3 box cells, p = 5, 8 orbitals, FP64
-// (113 MB) 112 + 36 us scattered, 63 + 48 us per cell; FP32 (57 MB) 56 + 24 and
-// 38 + 28; 24^3 trilinear cells, p = 6 (607 MB) 545 + 228 us scattered, 537 +
-// 314 us per cell.
+// Columns of a launch whose per-cell results fit the cell buffer (0: none): all
+// of them, or a multiple of 16.
 static int cells_fit(const tdfe_ctx* c, const ApplyArgs& a) {
   if (!c->eloc_bytes || c->mfma || a.cols % 2 || !block_kernels_ok(c, a)) return 0;
-  const size_t col = (size_t)c->n_cell * c->n * c->n * c->n * (a.fp32 ? 4 : 8);
-  const int cap = (int)std::min<size_t>(c->eloc_bytes / col, 1 << 20);
+  const int cap = (int)std::min<size_t>(c->eloc_bytes / cell_bytes(c, 1, a.fp32), 1 << 20);
   const int step = a.cols <= cap ? a.cols : cap / 16 * 16;
   // (64-bit offsets come with the scatter only)
   for (int cols : {step, step ? a.cols % step : 0}) {
@@ -697,12 +694,62 @@ static int cells_fit(const tdfe_ctx* c, const ApplyArgs& a) {
   return step;
 }
 
+// Per-cell results take plain stores where the scatter takes atomics, and leave
+// n^3 / p^3 vectors to be summed.  Summed by the Krylov update, which then has no
+// operator output to read, seed and clear, they pay wherever they fit, except
+// with n^3 / p^3 = 8 (n = 2) and, on trilinear cells, 3.4 (n = 3) beyond what the
+// L2s hold.  Per iteration: 16^3 box cells, p = 5, 8 orbitals, FP64 (113 MB) 112 +
+// 36 us scattered, 63 + 48 us per cell; FP32 (57 MB) 56 + 24 and 38 + 28.  Beyond
+// the memory-side cache: 24^3 trilinear cells, p = 6, FP64 (607 MB) 545 + 228 us
+// scattered, 537 + 314 us per cell.  An exponential of one orbital at p = 1, box
+// cells, 900,000 DoFs: FP64 (115 MB) 782 us scattered, 902 per cell.
 bool tdfe_cells_ok(const tdfe_ctx* c, int cols, bool fp32) {
   ApplyArgs a{};
   a.cols = a.ld = cols;
   a.lowdin = true;
   a.fp32 = fp32;
-  return cells_fit(c, a) == cols;
+  return cells_fit(c, a) == cols &&
+         (c->cell_always || c->p >= (c->box ? 2 : 3) || cell_bytes(c, cols, fp32) <= (size_t)32 << 20);
+}
+
+// Whether a launch into a DoF vector goes through the cell buffer, `step` columns
+// at a time, with a pass of its own that sums the cells.  The pass costs 3 to 5
+// us and reading the buffer; what it saves are the atomics, which are performed
+// per 64-byte segment (a row of columns that is no whole number of segments costs
+// up to twice its size) and hide behind the arithmetic of the larger orders, and
+// where the result replaces y the pass that clears it.  So, from 1.2 million
+// values on:
+//  * box cells, result replaces y: always (16^3 cells, p = 5, 8 orbitals 90 us
+//    against 102, 64 orbitals in slices 642 and 714; 20 x 19 x 21 one orbital 42
+//    and 84), except for the four-lane kernel at n = 7 beyond 64 MB, which hides its
+//    atomics (16 x 15 x 17, 8 orbitals 161 and 148);
+//  * box cells, added to y: rows that split a segment, not the FP64 four-lane kernel
+//    (p = 5, one orbital 42 and 80, 5 orbitals 140 and 163; 8 orbitals 177 and 161;
+//    p = 6, 5 orbitals 136 and 113); FP32 also whole segments, from 250,000 DoFs and
+//    up to 128 MB (8 orbitals 97 us per cell and 101; 60,000 DoFs: 24 and 18);
+//  * trilinear cells, result replaces y: the four-lane kernel (n = 8: 14 x 13 x 15,
+//    8 orbitals 205 and 216; n = 7 up to 64 MB), and up to three orbitals from p = 3 on (p =
+//    5, one 89 and 118; 8 orbitals 253 and 230);
+//  * trilinear cells, added to y, from 250,000 DoFs and p = 3 on: FP64 up to three
+//    orbitals (p = 5, one 88 and 112; 8 orbitals 274 and 210), FP32 rows that split a
+//    segment (p = 4, 9 orbitals 226 and 278; 8 orbitals 116 and 99), in the four-lane
+//    kernel beyond 64 bytes.
+static bool sum_pays(const tdfe_ctx* c, const ApplyArgs& a, int step) {
+  if (c->cell_always) return true;
+  const bool quad = tdfe_quad_kernel_ok(c, a), sliced = step < a.cols;
+  const int row = a.cols * (a.fp32 ? 4 : 8);
+  const size_t bytes = cell_bytes(c, a.cols, a.fp32);
+  const bool split = row % 64 != 0;
+  if (c->p < 2 || c->n_dof * a.cols < 1200000) return false;
+  if (a.overwrite) {
+    if (sliced && a.cols % step != 0 && a.cols % step < 16) return false;
+    if (quad) return c->n == 8 || bytes <= (size_t)64 << 20;
+    return c->box || (c->p >= 3 && row < 64);
+  }
+  if (sliced) return false;
+  const bool large = c->n_dof >= 250000;
+  if (c->box) return split ? a.fp32 || !quad : a.fp32 && large && bytes <= (size_t)128 << 20;
+  return large && c->p >= 3 && (row < 64 ? !quad : a.fp32 && split);
 }
 
 tdfe_status tdfe_launch_apply_cells(tdfe_ctx* c, const ApplyArgs& a0) {
@@ -744,8 +791,12 @@ static tdfe_status launch_cells_sum(tdfe_ctx* c, const ApplyArgs& a0, int step) 
   return TDFE_OK;
 }
 
-bool tdfe_can_overwrite(const tdfe_ctx* c, const ApplyArgs& a) {
-  return !c->octree && !a.fp32 && !a.energy && cells_fit(c, a) > 0;
+bool tdfe_can_overwrite(const tdfe_ctx* c, const ApplyArgs& a0) {
+  if (c->octree || a0.fp32 || a0.energy) return false;
+  ApplyArgs a = a0;
+  a.overwrite = true;
+  const int step = cells_fit(c, a);
+  return step > 0 && sum_pays(c, a, step);
 }
 
 static tdfe_status launch_local(tdfe_ctx* c, const ApplyArgs& a) {
@@ -757,7 +808,8 @@ static tdfe_status launch_local(tdfe_ctx* c, const ApplyArgs& a) {
   if (a.lowdin && a.fullgrid) return tdfe_fail(c, TDFE_EINVAL, "apply: Loewdin scaling on the full node grid");
   if (c->mfma && tdfe_mfma_kernel_ok(c, a)) return tdfe_launch_apply_mfma(c, a);
   const int step = cells_fit(c, a);
-  if (step == a.cols || (step > 0 && !a.energy)) return launch_cells_sum(c, a, step);
+  if ((step == a.cols || (step > 0 && !a.energy)) && (a.overwrite || sum_pays(c, a, step)))
+    return launch_cells_sum(c, a, step);
   if (block_kernels_ok(c, a)) {
     ApplyArgs b = a;
     b.eld = a.cols;
@@ -803,7 +855,10 @@ int tdfe_operator_route(const tdfe_ctx* c, int cols, int fp32) {
   a.fp32 = fp32 != 0;
   if (c->octree || (c->mfma && tdfe_mfma_kernel_ok(c, a)) || !block_kernels_ok(c, a)) return 0;
   const bool pair = c->box ? box_pair(c, a) : tdfe_curved_pair(c, a.cols, a.fp32);
-  return (tdfe_quad_kernel_ok(c, a) ? 4 : (pair ? 3 : 1)) + (offsets_near(c, a) ? 0 : 8) + (cells_fit(c, a) ? 16 : 0);
+  const int step = cells_fit(c, a);
+  return (tdfe_quad_kernel_ok(c, a) ? 4 : (pair ? 3 : 1)) + (offsets_near(c, a) ? 0 : 8) +
+         (step && sum_pays(c, a, step) ? 16 : 0) + (tdfe_can_overwrite(c, a) ? 32 : 0) +
+         (tdfe_cells_ok(c, cols, a.fp32) ? 64 : 0);
 }
 
 tdfe_status tdfe_launch_apply(tdfe_ctx* c, const ApplyArgs& a) {

@@ -102,6 +102,7 @@ struct tdfe_ctx {
   // (at most TDFE_CELL_BYTES; 0: octree meshes and p = 8)
   void* eloc = nullptr;
   size_t eloc_bytes = 0, cell_cap = TDFE_CELL_BYTES;
+  bool cell_always = false;   // use it wherever a launch fits (TDFE_CELL_BUFFER_BYTES is set)
   void* half = nullptr;       // [n_dof][2 n_orb_max] predictor state (complex128)
   double* partial = nullptr;  // reduction partials
   double* partial2 = nullptr; // [128][TDFE_MAX_COLS] first level of the two-level alpha reduction
@@ -249,7 +250,8 @@ tdfe_status tdfe_launch_apply_cells(tdfe_ctx* c, const ApplyArgs& a);
 bool tdfe_can_overwrite(const tdfe_ctx* c, const ApplyArgs& a);
 // host only: the kernel of an operator launch on the DoF vectors, 0 the line
 // kernel (or another mesh's or engine's), 1 plane, 3 lane pairs, 4 four lanes; + 8
-// with 64-bit offsets, + 16 through the cell buffer
+// with 64-bit offsets, + 16 added to a vector through the cell buffer, + 32 its
+// result replacing the vector so, + 64 summed by the Krylov update
 extern "C" int tdfe_operator_route(const tdfe_ctx* c, int cols, int fp32);
 // trilinear-cell variant in the same layout (tdfe_apply_curved.hip)
 bool tdfe_curved_kernel_ok(const tdfe_ctx* c, int cols, bool fp32);

@@ -274,6 +274,7 @@ void init_variant(tdfe_ctx* c) {
   // a smaller cell buffer (tests: column slices, or 0 for the scatter)
   const char* b = std::getenv("TDFE_CELL_BUFFER_BYTES");
   if (b) c->cell_cap = (size_t)std::min<unsigned long long>(std::strtoull(b, nullptr, 10), TDFE_CELL_BYTES);
+  c->cell_always = b != nullptr;
 }
 
 // Krylov chunk: as many orbitals as fit in 60% of the device memory free at

@@ -13,7 +13,8 @@ import pytest
 import workloads as W
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-LINE, PLANE, PAIR, QUAD, FAR, CELLS = 0, 1, 3, 4, 8, 16
+LINE, PLANE, PAIR, QUAD, FAR = 0, 1, 3, 4, 8
+ADD, REPLACE, KRYLOV = 16, 32, 64  # through the cell buffer
 
 
 @pytest.fixture(scope="module")
@@ -41,14 +42,14 @@ def _route(lib, mesh, p, nc, n_orb, fp32, variant=None, monkeypatch=None):
 
 
 @pytest.mark.parametrize("mesh,p,nc,n_orb,fp32,want", [
-    ("box", 5, (16, 16, 16), 8, False, PAIR + CELLS),
+    ("box", 5, (16, 16, 16), 8, False, PAIR + REPLACE + KRYLOV),
     # 32 columns of 20,000 rows and more across a block's z planes
     ("box", 5, (96, 96, 2), 32, False, PAIR), ("box", 5, (120, 120, 2), 32, False, PAIR),
     ("box", 5, (190, 190, 2), 32, False, PAIR + FAR), ("box", 4, (240, 240, 2), 32, True, PLANE),
     ("box", 4, (400, 400, 2), 32, True, PLANE + FAR),
     # rows of hundreds of orbitals
     ("box", 5, (24, 24, 24), 512, False, PAIR), ("box", 5, (48, 48, 4), 512, False, PAIR + FAR),
-    ("box", 4, (24, 24, 2), 4096, False, PLANE + FAR), ("box", 6, (8, 8, 2), 4096, False, QUAD + CELLS),
+    ("box", 4, (24, 24, 2), 4096, False, PLANE + FAR), ("box", 6, (8, 8, 2), 4096, False, QUAD),
     # the four-lane kernel has an address per row of nodes
     ("box", 6, (160, 160, 2), 32, False, QUAD), ("trilinear", 6, (160, 160, 2), 32, False, QUAD),
     ("trilinear", 7, (120, 120, 2), 32, True, QUAD),
@@ -65,6 +66,25 @@ def test_trilinear_fp64_kernel_by_columns(lib, p, pairs):
     for n_orb in (1, 2, 3, 4, 5, 9, 16):
         want = PAIR if n_orb <= pairs else QUAD if p > 5 else PLANE
         assert _route(lib, "trilinear", p, (7, 6, 5), n_orb, False) & 7 == want, n_orb
+
+
+# where apply_H_add, apply_H and the Krylov update go through the cell buffer:
+# not in launches of microseconds, nor where the atomics hide
+@pytest.mark.parametrize("mesh,p,nc,n_orb,fp32,want", [
+    ("box", 3, (6, 5, 7), 8, False, KRYLOV), ("box", 1, (17, 16, 18), 8, False, KRYLOV),
+    ("box", 1, (98, 97, 99), 1, False, 0), ("box", 5, (20, 19, 21), 1, False, ADD + REPLACE + KRYLOV),
+    ("box", 5, (20, 19, 21), 5, False, ADD + REPLACE + KRYLOV), ("box", 5, (16, 16, 16), 32, False, REPLACE),
+    ("box", 6, (16, 15, 17), 8, False, KRYLOV), ("box", 6, (7, 6, 8), 16, False, REPLACE + KRYLOV),
+    ("box", 7, (14, 13, 15), 8, False, REPLACE + KRYLOV), ("box", 5, (8, 7, 9), 8, True, KRYLOV),
+    ("box", 4, (13, 17, 11), 5, True, ADD + KRYLOV), ("box", 5, (20, 19, 21), 8, True, ADD + KRYLOV),
+    ("box", 5, (20, 19, 21), 16, True, KRYLOV), ("trilinear", 3, (6, 5, 7), 1, False, KRYLOV),
+    ("trilinear", 5, (20, 19, 21), 1, False, ADD + REPLACE + KRYLOV), ("trilinear", 5, (20, 19, 21), 8, False, KRYLOV),
+    ("trilinear", 2, (49, 48, 50), 1, False, 0), ("trilinear", 7, (14, 13, 15), 8, False, REPLACE + KRYLOV),
+    ("trilinear", 4, (24, 23, 25), 9, True, ADD + KRYLOV), ("trilinear", 4, (24, 23, 25), 8, True, KRYLOV)])
+def test_cell_buffer(lib, mesh, p, nc, n_orb, fp32, want):
+    r = _route(lib, mesh, p, nc, n_orb, fp32)
+    assert r & (ADD if fp32 else ADD + REPLACE) == want & (ADD + REPLACE)
+    assert r & KRYLOV == want & KRYLOV
 
 
 def test_block_span(tmp_path):
