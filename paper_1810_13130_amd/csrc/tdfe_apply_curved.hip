@@ -64,7 +64,7 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
   const int group = L / P.nchunks;
   const int col = t % CB;
   const int pl = (t / CB) % N;
-  const int slot = CPB == 1 ? 0 : t / (CB * N);
+  const int slot = t / (CB * N);  // (not folded for one cell per block: see the pair kernel)
   const int64_t cell = (int64_t)group * CPB + slot;
   const bool cell_ok = cell < P.n_cell;
   const int colg = chunk * CB + col;
@@ -467,9 +467,15 @@ __global__ void __launch_bounds__(CPB * N * CB) __attribute__((amdgpu_waves_per_
       eo<T, N, 1>(FS.Bt, h[i], o);
       // (the node tests depend on the cell only: uniform whenever a wave holds one cell)
       if (E.jok && E.xok(i)) {
+        T* const row = Y + ((n0 + i) * P.ld + colg);
 #pragma unroll
         for (int k = 0; k < N; ++k)
-          if (E.zok(k)) E.put(i, k, E.off, o[k] * ml[k]);
+          if (E.zok(k)) {
+            if constexpr (CELLS)
+              E.put(i, k, E.off, o[k] * ml[k]);
+            else
+              unsafeAtomicAdd(row + (int64_t)k * nk * P.ld, o[k] * ml[k]);
+          }
       }
     }
   }
@@ -492,14 +498,16 @@ constexpr int cplane_lds(int cpb) {
   return cpb * VOL * CB * (int)sizeof(T) + cpb * VOL * (int)sizeof(T) * 8 + cpb * N * CB * 8 + cpb * 24 * 8;
 }
 
-// cells per block: at most 512 threads; the metric makes a cell's LDS about
-// 1.4x that of a box cell, so the budgets are larger than the box kernel's
-// (an FP64 block still runs alone on its CU at one wave per SIMD)
+// cells per block: at most 512 threads, and 128 up to n = 4, where larger blocks
+// set their atomics off together (FP32 n = 4, 16 orbitals on 33 x 32 x 34 cells
+// 257 us with 512 threads, 229 so; 24 orbitals 445 and 341); the metric makes a
+// cell's LDS about 1.4x that of a box cell, so the budgets are larger than the box
+// kernel's (an FP64 block still runs alone on its CU at one wave per SIMD)
 template <typename T, int N, int CB>
 constexpr int cplane_cpb() {
   constexpr int budget = sizeof(T) == 8 ? 96 * 1024 : 48 * 1024;
   int cpb = 1;
-  while (cpb * 2 * N * CB <= 512 && cplane_lds<T, N, CB>(cpb * 2) <= budget) cpb *= 2;
+  while (cpb * 2 * N * CB <= (N <= 4 ? 128 : 512) && cplane_lds<T, N, CB>(cpb * 2) <= budget) cpb *= 2;
   return cpb;
 }
 
@@ -722,7 +730,11 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
   const int group = L / P.nchunks;
   const int col = r % CB;
   const int pl = (r / CB) % N;
-  const int slot = CPB == 1 ? 0 : r / (CB * N);
+  // A lane's value also where a block holds one cell: with the constant 0 the
+  // compiler keeps more addresses in registers (FP32 n = 8, 16 columns: 208 and two
+  // waves per SIMD, 154 and three so: 16 orbitals on 14 x 13 x 15 cells 233 and 176
+  // us; FP64 n = 8 spills 20 registers instead of 78)
+  const int slot = r / (CB * N);
   const int64_t cell = (int64_t)group * CPB + slot;
   const bool cell_ok = cell < P.n_cell;
   const int colg = chunk * CB + col;
@@ -1032,9 +1044,19 @@ __global__ void __launch_bounds__(2 * CPB * N * CB) __attribute__((amdgpu_waves_
       T o[HZ];
       zpair<T, N>(ZS.Bt, hh[i], o, (T)1);
       if (E.jok && E.xok(i)) {
+        // (atomics from a 64-bit address per row of nodes: with the block's base and
+        // 32-bit offsets, as the cells' stores have, n = 2 loses a wave per SIMD
+        // for FP64: 16 orbitals on 49 x 48 x 50 cells at n = 2 1868 and 1440 us, at
+        // n = 7 394 and 360; FP32 n = 6, 8 orbitals 146 and 113)
+        T* const row = Y + ((n0 + i) * P.ld + colg);
 #pragma unroll
         for (int k = 0; k < HZ; ++k)
-          if ((k > 0 || z0) && !(ODD && k == H && h)) E.put(i, 0, oz[k], o[k] * ml[k]);
+          if ((k > 0 || z0) && !(ODD && k == H && h)) {
+            if constexpr (CELLS)
+              E.put(i, 0, oz[k], o[k] * ml[k]);
+            else
+              unsafeAtomicAdd(row + (int64_t)zg(k) * nk * P.ld, o[k] * ml[k]);
+          }
       }
     }
   }
