@@ -760,8 +760,8 @@ def matrix_core_engines(steps=100, warmup=5, reps=100):
 def curved_kernel_name(p, cols, fp32):
     """Name of the trilinear-cell operator kernel a launch of `cols` real
     columns runs (the library's default choice: four lanes per line for more
-    than 8 columns at p = 7 and FP64 p = 6, else lane pairs for FP64 p >= 5, for
-    FP32 at p = 7 and for FP64 launches of few columns below, else plane
+    than 8 columns at FP64 p >= 6, and less than 16 at FP32 p = 7, else lane
+    pairs for FP64 p >= 5, for FP32 at p = 7 and for FP64 launches of few columns below, else plane
     ownership; columns per block the next power of two up to 16, at least 2 for
     lane pairs, or 32 for FP32 plane launches of more than 16)."""
     n = p + 1
@@ -769,7 +769,7 @@ def curved_kernel_name(p, cols, fp32):
     while pw < cols:
         pw *= 2
     t = "float" if fp32 else "double"
-    if cols > 8 and (n == 8 or (n == 7 and not fp32)):
+    if 8 < cols and (n == 8 and cols < 16 if fp32 else n > 6):
         return f"quad_kernel<{t},{n},false,CELLS> (trilinear cells, four lanes per line)"
     if n == 8 if fp32 else n > 5 or cols <= {2: 2, 3: 8}.get(n, 4):
         return f"cpair_kernel<{t},{n},{max(2, min(pw, 16))},CPB> (trilinear cells, lane pairs)"

@@ -868,8 +868,15 @@ tdfe_status launch_quad_t(tdfe_ctx* c, const ApplyArgs& a) {
 // other kernels: FP64 n = 8 588 : 815 (trilinear) and 123 : 127 us (box),
 // n = 7 626 : 718 and 122 : 132; FP32 n = 8 389 : 406 and 59 : 64.  Below, a
 // quarter of the lanes idle or the FP32 planes win: FP64 n = 6 644 : 554 and
-// 121 : 106, n = 5 385 : 295, FP32 n = 7 530 : 470.
+// 121 : 106, n = 5 385 : 295, FP32 n = 7 530 : 470.  FP32 on trilinear cells: only
+// where a block of 16 columns is not full, and where 32-bit offsets do not reach
+// over a cell, which lane pairs need (14 x 13 x 15 cells, four lanes and pairs: 5
+// orbitals 92 and 104 us, 8 104 and 94, 16 226 and 167, 32 427 and 340; 9 x 10 x
+// 8: 5 32 and 40, 16 63 and 55).
 bool tdfe_quad_kernel_ok(const tdfe_ctx* c, const ApplyArgs& a) {
+  if (!c->box && a.fp32 && a.cols >= 16 &&
+      tdfe_span::near(c->p, c->ncx, c->ncy, c->ncz, 1, (int64_t)a.ld * (int)sizeof(float)))
+    return false;
   return c->variant == 0 && (c->n == 8 || (c->n == 7 && !a.fp32)) && a.cols > 8 &&
          c->n_cell * ((a.cols + QC - 1) / QC) < (int64_t)1 << 31 &&
          (int64_t)c->n * a.ld * (a.fp32 ? 4 : 8) < (int64_t)1 << 31;

@@ -52,7 +52,7 @@ def _route(lib, mesh, p, nc, n_orb, fp32, variant=None, monkeypatch=None):
     ("box", 4, (24, 24, 2), 4096, False, PLANE + FAR), ("box", 6, (8, 8, 2), 4096, False, QUAD),
     # the four-lane kernel has an address per row of nodes
     ("box", 6, (160, 160, 2), 32, False, QUAD), ("trilinear", 6, (160, 160, 2), 32, False, QUAD),
-    ("trilinear", 7, (120, 120, 2), 32, True, QUAD),
+    ("trilinear", 7, (120, 120, 2), 32, True, PAIR), ("trilinear", 7, (160, 160, 2), 32, True, QUAD),
     ("trilinear", 5, (100, 100, 2), 32, False, PAIR), ("trilinear", 5, (190, 190, 2), 32, False, LINE),
     ("trilinear", 6, (160, 160, 2), 32, True, PLANE), ("box", 8, (4, 4, 4), 8, False, LINE)])
 def test_route(lib, mesh, p, nc, n_orb, fp32, want):
@@ -85,6 +85,15 @@ def test_cell_buffer(lib, mesh, p, nc, n_orb, fp32, want):
     r = _route(lib, mesh, p, nc, n_orb, fp32)
     assert r & (ADD if fp32 else ADD + REPLACE) == want & (ADD + REPLACE)
     assert r & KRYLOV == want & KRYLOV
+
+
+def test_trilinear_fp32_kernel_by_columns(lib):
+    """p = 7: four lanes where a block of 16 columns is not full, else pairs;
+    below planes."""
+    for p in range(1, 8):
+        for n_orb in (1, 4, 5, 7, 8, 9, 16, 32):
+            want = PLANE if p < 7 else QUAD if 4 < n_orb < 8 else PAIR
+            assert _route(lib, "trilinear", p, (7, 6, 5), n_orb, True) & 7 == want, (p, n_orb)
 
 
 def test_block_span(tmp_path):
