@@ -682,7 +682,7 @@ static bool block_kernels_ok(const tdfe_ctx* c, const ApplyArgs& a) {
 // Columns of a launch whose per-cell results fit the cell buffer (0: none): all
 // of them, or a multiple of 16.
 static int cells_fit(const tdfe_ctx* c, const ApplyArgs& a) {
-  if (!c->eloc_bytes || c->mfma || a.cols % 2 || !block_kernels_ok(c, a)) return 0;
+  if (!c->eloc_bytes || a.cols % 2 || !block_kernels_ok(c, a)) return 0;
   const int cap = (int)std::min<size_t>(c->eloc_bytes / cell_bytes(c, 1, a.fp32), 1 << 20);
   const int step = a.cols <= cap ? a.cols : cap / 16 * 16;
   // (64-bit offsets come with the scatter only)

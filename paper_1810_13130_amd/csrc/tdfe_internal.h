@@ -99,7 +99,7 @@ struct tdfe_ctx {
   void* krylov = nullptr;     // (k_max+1) x [n_dof][2 chunk_orb]
   void* hq = nullptr;         // [n_dof][2 max(chunk_orb, wide_orb)] apply output
   // per-cell results of the operator, [n_cell][n^3][columns], and their size
-  // (at most TDFE_CELL_BYTES; 0: octree meshes and p = 8)
+  // (at most TDFE_CELL_BYTES; 0: octree meshes, p = 8, matrix-core contexts)
   void* eloc = nullptr;
   size_t eloc_bytes = 0, cell_cap = TDFE_CELL_BYTES;
   bool cell_always = false;   // use it wherever a launch fits (TDFE_CELL_BUFFER_BYTES is set)

@@ -213,7 +213,8 @@ void carve(tdfe_ctx* c, char* base) {
   c->krylov = k.take<char>((size_t)(c->k_max + 1) * nd * 2 * c->chunk_orb * elem_bytes(c));
   c->hq = k.take<char>((size_t)nd * cols * elem_bytes(c));
   const size_t evol = (size_t)ne * c->n * c->n * c->n;
-  c->eloc_bytes = c->octree || c->n > 8
+  // (none where no kernel writes per-cell results)
+  c->eloc_bytes = c->octree || c->n > 8 || c->mfma || c->variant == TDFE_VARIANT_LINE
                       ? 0
                       : std::min(evol * 2 * std::max(c->n_orb_max, c->wide_orb) * sizeof(double), c->cell_cap);
   c->eloc = c->eloc_bytes ? (void*)k.take<char>(c->eloc_bytes) : nullptr;
