@@ -11,7 +11,8 @@
 //      transposed derivatives; transposed y interpolation of (V u_q + ...) and of
 //      the x flux
 //   -- LDS transpose of the two arrays -->
-//   C  (plane at node y = j): x: B^T s + D^T s_x; z: B^T; results x M^-1/2 (CellOut).
+//   C  (plane at node y = j): x: B^T s + D^T s_x; z: B^T; results x M^-1/2 (to the cell's
+//      rows, CellOut, or added to the DoF vector by atomics).
 // The x derivative is taken on the nodes (D = Dg B along x) so that x never
 // crosses threads; only y does.  Contractions use the even/odd folded tables.
 #include "tdfe_fold.h"

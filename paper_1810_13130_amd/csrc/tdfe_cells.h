@@ -1,5 +1,6 @@
 // Sums of per-cell results at the DoFs (the assembly of Eq. DiscreteHamiltonian),
-// for kernels that read the four-lane operator's output [n_cell][n^3][cols].
+// for kernels that read the per-cell output [n_cell][n^3][cols] of the plane,
+// lane-pair and four-lane operators.
 //
 // A DoF on a cell face, edge or corner has 2, 4 or 8 contributions.  Along a row
 // of DoFs (fixed y and z node) the y and z sharing is the row's own, so a block

@@ -14,8 +14,9 @@
 //    which removes the normalisation pass;
 //  * alpha_k = Re<q_k, Hbar q_k> comes from the operator kernel's own
 //    quadrature-point quadratic form (no extra pass over the vectors);
-//  * the three-term update, the zeroing of the operator output and the norm
-//    partials are one streaming kernel;
+//  * the three-term update and the norm partials are one streaming kernel,
+//    which also sums the operator's per-cell results (update_cells_kernel) or,
+//    where they do not pay, clears the operator output (update_kernel);
 //  * all reductions are two-level with a fixed summation order
 //    (deterministic);
 //  * the small exponential is evaluated on the device by the Chebyshev
@@ -344,13 +345,14 @@ __global__ void __launch_bounds__(RED_THREADS)
   if (threadIdx.x < C) partial[(int64_t)bid * C + threadIdx.x] = sred[threadIdx.x];
 }
 
-// The three-term step after the four-lane operator, whose output is per cell:
-// one pass sums a DoF's contributions and takes the step,
+// The three-term step after an operator that leaves per-cell results: one pass
+// sums a DoF's contributions and takes the step,
 //   w_{j+1} = m_j (sum of the cells' s_j^2 Hbar w_j) - alpha_j s_j w_j
 //             - m_j s_{j-1} w_{j-1},      m_j = beta_{j-1} (1 and no last term for j = 0).
-// Blocks work row by row of DoFs (see tdfe_cells.h), a lane moves 16
-// bytes of a row (one FP64 or two FP32 orbitals).  Reads the cell results once (n^3 / p^3 vectors), w_j and
-// w_{j-1}, writes w_{j+1}; no operator output vector is kept, seeded or cleared.
+// Blocks work row by row of DoFs (see tdfe_cells.h), a lane moves 16 bytes of a
+// row (one FP64 or two FP32 orbitals).  Reads the cell results once (n^3 / p^3
+// vectors), w_j and w_{j-1}, writes w_{j+1}; no operator output vector is kept,
+// seeded or cleared.
 constexpr int CELL_BLOCKS = 2048;  // at most: one block per row of DoFs up to this
 template <typename T, int W, int SR, bool OWN>
 __global__ void __launch_bounds__(RED_THREADS)
@@ -705,12 +707,6 @@ __global__ void zero_norm_kernel(Scal S, int Nc, int* host_flag, int gen) {
       __threadfence_system();
     }
   }
-}
-
-int pad_cols(int C) {
-  int p = 1;
-  while (p < C) p <<= 1;
-  return p;
 }
 
 // per-orbital results of one chunk into a deferred-result slot:
