@@ -61,9 +61,10 @@ def apply_flops(n, n_cell, n_orb):
 
 
 # the operator sources of the kernels the committed counter summaries cover
-OPERATOR_SOURCES = {"curved": ("tdfe_apply_curved.hip", "tdfe_apply_quad.hip", "tdfe_fold.h", "tdfe_rule1d.h"),
+OPERATOR_SOURCES = {"curved": ("tdfe_apply_curved.hip", "tdfe_apply_quad.hip", "tdfe_fold.h", "tdfe_rule1d.h",
+                               "tdfe_span.h"),
                     "box": ("tdfe_apply_box.hip", "tdfe_apply_pair.hip", "tdfe_cells.h", "tdfe_fold.h",
-                            "tdfe_rule1d.h")}
+                            "tdfe_rule1d.h", "tdfe_span.h")}
 TRAFFIC_PROFILES = {"curved": "operator_graded_31x31x31_p6_hbm_bytes.md",
                     "box": "operator_16x16x16_p5_8orb_hbm_bytes.md"}
 
