@@ -499,37 +499,43 @@ constexpr int cplane_lds(int cpb) {
   return cpb * VOL * CB * (int)sizeof(T) + cpb * VOL * (int)sizeof(T) * 8 + cpb * N * CB * 8 + cpb * 24 * 8;
 }
 
-// cells per block: at most 512 threads, and 128 up to n = 4, where larger blocks
-// set their atomics off together (FP32 n = 4, 16 orbitals on 33 x 32 x 34 cells
-// 257 us with 512 threads, 229 so; 24 orbitals 445 and 341); the metric makes a
-// cell's LDS about 1.4x that of a box cell, so the budgets are larger than the box
-// kernel's (an FP64 block still runs alone on its CU at one wave per SIMD)
+// cells per block: at most 512 threads, and for the scatter 128 up to n = 4, where
+// larger blocks set their atomics off together (FP32 n = 4, 16 orbitals on 33 x 32 x
+// 34 cells 257 us with 512 threads, 229 so; 24 orbitals 445 and 341; per-cell
+// results are no faster so, and leave more partials of the quadratic form to
+// sum: an exponential of 13 orbitals on 60,000 DoFs at n = 3 240 us, and 210); the
+// metric makes a cell's LDS about 1.4x that of a box cell, so the budgets are
+// larger than the box kernel's (an FP64 block still runs alone on its CU at one
+// wave per SIMD)
 template <typename T, int N, int CB>
-constexpr int cplane_cpb() {
+constexpr int cplane_cpb(bool cells) {
   constexpr int budget = sizeof(T) == 8 ? 96 * 1024 : 48 * 1024;
   int cpb = 1;
-  while (cpb * 2 * N * CB <= (N <= 4 ? 128 : 512) && cplane_lds<T, N, CB>(cpb * 2) <= budget) cpb *= 2;
+  while (cpb * 2 * N * CB <= (N <= 4 && !cells ? 128 : 512) && cplane_lds<T, N, CB>(cpb * 2) <= budget) cpb *= 2;
   return cpb;
 }
 
-template <typename T, int N, int CB>
-tdfe_status launch_cplane(tdfe_ctx* c, CurvedParams<T>& P, int64_t* groups_out) {
-  constexpr int CPB = cplane_cpb<T, N, CB>();
+template <typename T, int N, int CB, bool CELLS>
+tdfe_status launch_cplane_as(tdfe_ctx* c, CurvedParams<T>& P, int64_t* groups_out) {
+  constexpr int CPB = cplane_cpb<T, N, CB>(CELLS);
   static_assert(cplane_lds<T, N, CB>(CPB) <= 160 * 1024, "LDS");
-  if (P.query) {
-    *groups_out = CPB;
-    return TDFE_OK;
-  }
   const int64_t groups = (c->n_cell + CPB - 1) / CPB;
   P.nchunks = (P.cols + CB - 1) / CB;
   if (groups_out) *groups_out = groups;
   const dim3 grid((unsigned)(groups * P.nchunks)), block(CPB * N * CB);
-  if (P.cells)
-    hipLaunchKernelGGL((cplane_kernel<T, N, CB, CPB, true>), grid, block, 0, c->stream, P);
-  else
-    hipLaunchKernelGGL((cplane_kernel<T, N, CB, CPB, false>), grid, block, 0, c->stream, P);
+  hipLaunchKernelGGL((cplane_kernel<T, N, CB, CPB, CELLS>), grid, block, 0, c->stream, P);
   TDFE_HIP(c, hipGetLastError());
   return TDFE_OK;
+}
+
+template <typename T, int N, int CB>
+tdfe_status launch_cplane(tdfe_ctx* c, CurvedParams<T>& P, int64_t* groups_out) {
+  if (P.query) {
+    *groups_out = cplane_cpb<T, N, CB>(true);  // of either form at most
+    return TDFE_OK;
+  }
+  return P.cells ? launch_cplane_as<T, N, CB, true>(c, P, groups_out)
+                 : launch_cplane_as<T, N, CB, false>(c, P, groups_out);
 }
 
 // columns per block: the next power of two up to 16; FP32 launches of more
