@@ -694,62 +694,79 @@ static int cells_fit(const tdfe_ctx* c, const ApplyArgs& a) {
   return step;
 }
 
+// Atomics are performed per 64-byte segment: a row of columns of more than one
+// segment that is no whole number of them costs up to twice its size.
+static bool split_row(int cols, bool fp32) {
+  const int row = cols * (fp32 ? 4 : 8);
+  return row > 64 && row % 64 != 0;
+}
+
 // Per-cell results take plain stores where the scatter takes atomics, and leave
 // n^3 / p^3 vectors to be summed.  Summed by the Krylov update, which then has no
-// operator output to read, seed and clear, they pay wherever they fit, except
-// with n^3 / p^3 = 8 (n = 2) and, on trilinear cells, 3.4 (n = 3) beyond what the
-// L2s hold.  Per iteration: 16^3 box cells, p = 5, 8 orbitals, FP64 (113 MB) 112 +
-// 36 us scattered, 63 + 48 us per cell; FP32 (57 MB) 56 + 24 and 38 + 28.  Beyond
-// the memory-side cache: 24^3 trilinear cells, p = 6, FP64 (607 MB) 545 + 228 us
-// scattered, 537 + 314 us per cell.  An exponential of one orbital at p = 1, box
-// cells, 900,000 DoFs: FP64 (115 MB) 782 us scattered, 902 per cell.
+// operator output to read, seed and clear, they pay wherever they fit from n^3 /
+// p^3 = 3.4 on (n = 3), on trilinear cells 2.4 (n = 4).  Per iteration: 16^3 box
+// cells, p = 5, 8 orbitals, FP64 (113 MB) 112 + 36 us scattered, 63 + 48 us per
+// cell; FP32 (57 MB) 56 + 24 and 38 + 28.  Beyond the memory-side cache: 24^3
+// trilinear cells, p = 6, FP64 (607 MB) 545 + 228 us scattered, 537 + 314 us per
+// cell.  Below n = 3 or 4 they pay while the L2s hold them, or against split rows
+// (p = 1, box, 13 orbitals, 250,000 DoFs FP32 1,546 us scattered, 1,138 per cell, 60,000
+// DoFs FP64 711 and 632), but not for one orbital (p = 1, 60,000 DoFs FP64 168 and 196;
+// trilinear p = 2, 900,000 DoFs FP32 334 and 434, 60,000 149 and 137).
 bool tdfe_cells_ok(const tdfe_ctx* c, int cols, bool fp32) {
   ApplyArgs a{};
   a.cols = a.ld = cols;
   a.lowdin = true;
   a.fp32 = fp32;
-  return cells_fit(c, a) == cols &&
-         (c->cell_always || c->p >= (c->box ? 2 : 3) || cell_bytes(c, cols, fp32) <= (size_t)32 << 20);
+  if (cells_fit(c, a) != cols) return false;
+  if (c->cell_always || c->p >= (c->box ? 2 : 3)) return true;
+  if (cols == 2) return c->p == 2 && c->n_dof < 200000;
+  return cell_bytes(c, cols, fp32) <= (size_t)32 << 20 || split_row(cols, fp32);
 }
 
 // Whether a launch into a DoF vector goes through the cell buffer, `step` columns
 // at a time, with a pass of its own that sums the cells.  The pass costs 3 to 5
-// us and reading the buffer; what it saves are the atomics, which are performed
-// per 64-byte segment (a row of columns that is no whole number of segments costs
-// up to twice its size) and hide behind the arithmetic of the larger orders, and
-// where the result replaces y the pass that clears it.  So, from 1.2 million
-// values on:
+// us and reading the buffer; what it saves are the atomics, which hide behind the
+// arithmetic of the larger orders, and where the result replaces y the pass that
+// clears it.  So, from 200,000 DoFs or a million values on:
+//  * p = 1, eight values per DoF: split rows only (250,000 DoFs, box, 9 orbitals FP64
+//    239 us per cell against 346, FP32 172 and 244);
 //  * box cells, result replaces y: always (16^3 cells, p = 5, 8 orbitals 90 us
 //    against 102, 64 orbitals in slices 642 and 714; 20 x 19 x 21 one orbital 42
 //    and 84), except for the four-lane kernel at n = 7 beyond 64 MB, which hides its
 //    atomics (16 x 15 x 17, 8 orbitals 161 and 148);
-//  * box cells, added to y: rows that split a segment, not the FP64 four-lane kernel
-//    (p = 5, one orbital 42 and 80, 5 orbitals 140 and 163; 8 orbitals 177 and 161;
-//    p = 6, 5 orbitals 136 and 113); FP32 also whole segments, from 250,000 DoFs and
-//    up to 128 MB (8 orbitals 97 us per cell and 101; 60,000 DoFs: 24 and 18);
+//  * box cells, added to y: less than a segment or split rows, not the FP64
+//    four-lane kernel (p = 5, one orbital 42 and 80, 5 orbitals 140 and 163; 8
+//    orbitals 177 and 161; p = 6, 5 orbitals 136 and 113); FP32 also whole segments,
+//    from 200,000 DoFs and up to 128 MB (8 orbitals 97 us per cell and 101; 60,000
+//    DoFs: 24 and 18), and split rows in slices (p = 2, 13 orbitals, 900,000 DoFs 314
+//    and 497);
 //  * trilinear cells, result replaces y: the four-lane kernel (n = 8: 14 x 13 x 15,
 //    8 orbitals 205 and 216; n = 7 up to 64 MB), and up to three orbitals from p = 3 on (p =
 //    5, one 89 and 118; 8 orbitals 253 and 230);
-//  * trilinear cells, added to y, from 250,000 DoFs and p = 3 on: FP64 up to three
-//    orbitals (p = 5, one 88 and 112; 8 orbitals 274 and 210), FP32 rows that split a
-//    segment (p = 4, 9 orbitals 226 and 278; 8 orbitals 116 and 99), in the four-lane
-//    kernel beyond 64 bytes.
+//  * trilinear cells, added to y, from 200,000 DoFs on, not the four-lane kernel:
+//    less than a segment from p = 3 on (FP64 p = 5, one orbital 88 and 112), FP32 from
+//    two orbitals also at p = 2 (3 orbitals 138 and 160, 5 183 and 231; one 86 and 75);
+//    FP32 split rows from p = 3 on (p = 4, 9 orbitals 226 and 278; 8 orbitals 116 and
+//    99), in the four-lane kernel too.
+// A last slice of less than 8 columns is not worth a launch and a sum (p > 1).
 static bool sum_pays(const tdfe_ctx* c, const ApplyArgs& a, int step) {
   if (c->cell_always) return true;
-  const bool quad = tdfe_quad_kernel_ok(c, a), sliced = step < a.cols;
+  const bool quad = tdfe_quad_kernel_ok(c, a), sliced = step < a.cols, large = c->n_dof >= 200000;
   const int row = a.cols * (a.fp32 ? 4 : 8);
   const size_t bytes = cell_bytes(c, a.cols, a.fp32);
-  const bool split = row % 64 != 0;
-  if (c->p < 2 || c->n_dof * a.cols < 1200000) return false;
+  const bool split = split_row(a.cols, a.fp32);
+  if (!large && c->n_dof * a.cols < 1000000) return false;
+  if (c->p == 1) return split && (c->box || !a.fp32);
+  if (sliced && a.cols % step != 0 && a.cols % step < 8) return false;
   if (a.overwrite) {
-    if (sliced && a.cols % step != 0 && a.cols % step < 16) return false;
     if (quad) return c->n == 8 || bytes <= (size_t)64 << 20;
     return c->box || (c->p >= 3 && row < 64);
   }
-  if (sliced) return false;
-  const bool large = c->n_dof >= 250000;
-  if (c->box) return split ? a.fp32 || !quad : a.fp32 && large && bytes <= (size_t)128 << 20;
-  return large && c->p >= 3 && (row < 64 ? !quad : a.fp32 && split);
+  if (sliced) return c->box && a.fp32 && split;
+  if (c->box) return row < 64 || split ? a.fp32 || !quad : a.fp32 && large && bytes <= (size_t)128 << 20;
+  if (!large) return false;
+  if (row < 64) return !quad && (c->p >= 3 || (a.fp32 && a.cols >= 4));
+  return a.fp32 && split && c->p >= 3;
 }
 
 tdfe_status tdfe_launch_apply_cells(tdfe_ctx* c, const ApplyArgs& a0) {

@@ -80,7 +80,11 @@ def test_trilinear_fp64_kernel_by_columns(lib, p, pairs):
     ("box", 5, (20, 19, 21), 16, True, KRYLOV), ("trilinear", 3, (6, 5, 7), 1, False, KRYLOV),
     ("trilinear", 5, (20, 19, 21), 1, False, ADD + REPLACE + KRYLOV), ("trilinear", 5, (20, 19, 21), 8, False, KRYLOV),
     ("trilinear", 2, (49, 48, 50), 1, False, 0), ("trilinear", 7, (14, 13, 15), 8, False, REPLACE + KRYLOV),
-    ("trilinear", 4, (24, 23, 25), 9, True, ADD + KRYLOV), ("trilinear", 4, (24, 23, 25), 8, True, KRYLOV)])
+    ("trilinear", 4, (24, 23, 25), 9, True, ADD + KRYLOV), ("trilinear", 4, (24, 23, 25), 8, True, KRYLOV),
+    ("box", 1, (40, 39, 41), 9, False, ADD + REPLACE + KRYLOV), ("box", 1, (40, 39, 41), 1, False, 0),
+    ("trilinear", 1, (40, 39, 41), 13, True, KRYLOV), ("trilinear", 2, (20, 19, 21), 1, True, KRYLOV),
+    ("trilinear", 2, (49, 48, 50), 1, True, 0), ("trilinear", 2, (49, 48, 50), 3, True, ADD),
+    ("box", 2, (49, 48, 50), 13, True, ADD), ("box", 3, (22, 21, 23), 2, False, ADD + REPLACE + KRYLOV)])
 def test_cell_buffer(lib, mesh, p, nc, n_orb, fp32, want):
     r = _route(lib, mesh, p, nc, n_orb, fp32)
     assert r & (ADD if fp32 else ADD + REPLACE) == want & (ADD + REPLACE)
