@@ -1191,7 +1191,7 @@ tdfe_status launch_curved(tdfe_ctx* c, const ApplyArgs& a) {
 //    84, n = 3 112 and 141, n = 2 218 and 208; two: n = 5 111 and 106, n = 4 106
 //    and 81, n = 3 157 and 138, n = 2 260 and 273; four: n = 5 134 and 181, n = 4
 //    132 and 123, n = 3 247 and 218; eight: n = 5 228 and 332, n = 3 293 and 365;
-//  * FP32 at n = 8: pairs (162 VGPRs against the plane kernel's 256: 1.75 against
+//  * FP32 at n = 8: pairs (154 VGPRs against the plane kernel's 256: 1.75 against
 //    1.98 ms per 2-orbital launch of the all-electron workload); below planes (at
 //    n = 7 both run two waves per SIMD and the pairs' duplicated z work loses:
 //    2.24 against 1.50 ms per 16-orbital graded launch).

@@ -229,7 +229,7 @@ __device__ __forceinline__ CellPos cell_next(const Params& P, CellPos c, int slo
 // (plain stores; the consumer sums the cells, tdfe_cells.h).  Otherwise added
 // to the DoF vector y by hardware atomics, DoF nodes only.  Atomics on this
 // chip are performed beyond the per-XCD L2s at about 1.3 TB/s of values, plain
-// stores run at 5.5; see cells_fit for when the cell rows pay.
+// stores run at 5.5; see sum_pays and tdfe_cells_ok for when the cell rows pay.
 //
 // Addresses are a block-uniform 64-bit base per node row (scalar arithmetic)
 // plus a byte offset per lane, of 32 bits where that reaches every node of the
